@@ -80,6 +80,7 @@ struct asynclm_ctx {
     DecodeBuffers b{};
     ChunkBuffers cb{};
     bool chunk_ok = false;              // the matrix-core append path supports this model
+    RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
     unsigned* bar = nullptr;            // its grid-barrier counters
@@ -573,15 +574,52 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     return hipSuccess;
 }
 
+// One forward pass over n = 2..ROWS_MAX rows of one sequence (models outside the matrix-core append path).
+hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
+    const int dt = c->cfg.dtype;
+    const Geom& g = c->g;
+    hipStream_t s = c->stream;
+    const RowsPass p{seq, c->len[seq], n};
+    RowsTokens tk{};
+    for (int r = 0; r < n; ++r) tk.t[r] = tokens[r];
+    // Key splits: one per 256 keys (one pass of the attention's inner loop), merged by the last workgroup of a (row, kv head).
+    int nsplit = 1;
+    if (c->opt_attn_split > 0) nsplit = std::min(c->opt_attn_split, ATTN_MAX_SPLIT);
+    else
+        while (nsplit < (p.pos0 + n + 255) / 256 && nsplit < ATTN_MAX_SPLIT) nsplit *= 2;
+    hipError_t e;
+    if ((e = run(c, KC_EMBED, [&] { return launch_rows_embed(dt, c->embed, tk, c->rb, c->b, p, g, s); }))) return e;
+    for (int l = 0; l < c->cfg.n_layers; ++l) {
+        void* kvl = kv_layer_ptr(c, l);
+        if ((e = run(c, KC_QKV, [&] { return launch_rows_qkv(dt, c->wqkv[l], c->attn_norm[l], kvl, c->rb, c->b, p, g, s); }))) return e;
+        if ((e = run(c, KC_ATTN, [&] { return launch_rows_attn(dt, kvl, nsplit, c->rb, p, g, s); }))) return e;
+        if ((e = run(c, KC_OPROJ, [&] { return launch_rows_oproj(dt, c->wo[l], c->rb, p, g, s); }))) return e;
+        if ((e = run(c, KC_GATEUP, [&] { return launch_rows_gateup(dt, c->wgate_up[l], c->ffn_norm[l], c->rb, p, g, s); }))) return e;
+        if ((e = run(c, KC_DOWN, [&] { return launch_rows_down(dt, c->wdown[l], c->rb, p, g, s); }))) return e;
+    }
+    if (with_head) {
+        DecodeBuffers b = c->b;
+        b.x = c->rb.x + (size_t)(n - 1) * g.d;
+        if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); }))) return e;
+        if ((e = run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, c->b, g, s); }))) return e;
+    }
+    c->len[seq] += n;
+    return hipSuccess;
+}
+
 // Append n >= 1 tokens to a sequence and leave logits for the token after them.
 int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
-    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, CHUNK_MAX) : 1;
+    // the one-kernel and the two-stream step are asked for by option: then every token takes such a step
+    const bool rows_path = !c->chunk_ok && !c->opt_fused && !c->opt_pipeline && rows_supported(c->cfg.dtype, c->g);
+    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, CHUNK_MAX) : rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
     int i = 0;
     while (i < n) {
         const int rows = std::min(chunk, n - i);
         const bool last = i + rows == n;
         if (rows == 1) {
             HIPCK(c, step_one_token(c, seq, tokens[i], last));
+        } else if (!c->chunk_ok) {
+            HIPCK(c, forward_rows(c, seq, tokens + i, rows, last));
         } else {
             PassBuilder& pb = c->pass;
             pb.clear();
@@ -645,7 +683,7 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
         g.kv_vt_offset = c->chunk_ok ? row_planes * plane : 0;
         g.kv_layer_stride = (row_planes + (c->chunk_ok ? 2 : 0)) * plane;
         g.kv_seq_stride = g.kv_layer_stride * cfg->n_layers;
-        if (c->chunk_ok) c->opt_chunk = CHUNK_MAX;
+        c->opt_chunk = c->chunk_ok ? CHUNK_MAX : ROWS_MAX;
     }
     c->len.assign(cfg->max_seqs, 0);
     c->nban.assign(cfg->max_seqs, 0);
@@ -709,6 +747,15 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
             hipMemset(cb.act_hi, 0, M * g.F * 2) || hipMemset(cb.act_lo, 0, M * g.F * 2) || hipMemset(cb.q_hi, 0, qn * 2) ||
             hipMemset(cb.q_lo, 0, qn * 2))
             return bail(ASYNCLM_E_DEVICE);
+    }
+    if (!c->chunk_ok) {
+        if ((e = rows_init(cfg->dtype)) != hipSuccess) { report_hip("rows_init", e); return bail(ASYNCLM_E_DEVICE); }
+        const size_t R = ROWS_MAX, qd = (size_t)g.Hq * g.dh;
+        ALLOC(c->rb.x, R * g.d); ALLOC(c->rb.q, R * qd); ALLOC(c->rb.o, R * qd); ALLOC(c->rb.a, R * g.F);
+        ALLOC(c->rb.part_acc, R * qd * ATTN_MAX_SPLIT);
+        ALLOC(c->rb.part_ml, R * g.Hq * ATTN_MAX_SPLIT * 2);
+        ALLOC(c->rb.counters, R * g.Hkv);
+        if (hipMemset(c->rb.counters, 0, sizeof(int32_t) * R * g.Hkv) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     }
     // cache rows that were never written are read (and masked) by the chunk attention: keep them finite
     if (hipMemset(c->kv, 0, g.kv_seq_stride * (size_t)cfg->max_seqs * elem_bytes(c)) != hipSuccess) return bail(ASYNCLM_E_DEVICE);

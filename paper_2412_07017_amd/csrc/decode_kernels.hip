@@ -161,13 +161,16 @@ struct AttnArgs {
     int32_t* counters;      // [Hkv], zero between launches
     int32_t nsplit;
     int32_t defer_merge;    // 1: leave the partials to the O projection (no merge here, even for one split)
+    int32_t pos0, seq;      // MODE 2: position of row 0 and sequence (the step descriptor is not read)
     PipeSync sync;
 };
 
-// PIPE: see k_gemv.  The query and the newest cache row come from the QKV kernel of the same step, which may still be
+// MODE 0: the default kernel; 2 (ROWS): blockIdx.z is one of several rows of a pass, with its own query, length and partial
+// results; 1 (PIPE): see k_gemv.  The query and the newest cache row come from the QKV kernel of the same step, which may still be
 // running when this kernel starts: neither the query nor any cache row is read before its hand-over.
-template <typename KVT, int DH, int G, bool PAIR, bool PIPE>
-__global__ __launch_bounds__(256, PIPE ? 2 : 1) void k_attn_decode(AttnArgs a, Geom g) {
+template <typename KVT, int DH, int G, bool PAIR, int MODE>
+__global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs a, Geom g) {
+    constexpr bool PIPE = MODE == 1, ROWS = MODE == 2;
     constexpr int EPL = Elem<KVT>::EPL;
     constexpr int PPW = 64 / (DH / EPL);        // positions per wave-wide load
     extern __shared__ float lds[];
@@ -176,7 +179,12 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 1) void k_attn_decode(AttnArgs a, G
 
     const int tid = threadIdx.x;
     const int kvh = blockIdx.x, split = blockIdx.y, nsplit = a.nsplit;
-    const int len = a.step->pos + 1;
+    const int len = ROWS ? a.pos0 + (int)blockIdx.z + 1 : a.step->pos + 1;
+    if (ROWS) {
+        const size_t r = blockIdx.z;
+        a.q += r * g.Hq * DH; a.o += r * g.Hq * DH; a.counters += r * g.Hkv;
+        a.part_acc += r * g.Hq * nsplit * DH; a.part_ml += r * g.Hq * nsplit * 2;
+    }
     if (PIPE) pipe_stamp(a.sync, 0);
     if (PIPE && !pipe_wait(a.sync, &s_go)) return;
     // split boundaries: equal shares rounded up to whole workgroup rounds
@@ -185,7 +193,7 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 1) void k_attn_decode(AttnArgs a, G
     per = (per + quantum - 1) / quantum * quantum;
     const int s0 = min(split * per, len), s1 = min(s0 + per, len);
 
-    const KVT* Kp = (const KVT*)a.kv_layer + (size_t)a.step->seq * g.kv_seq_stride + (size_t)kvh * g.kv_head_stride;
+    const KVT* Kp = (const KVT*)a.kv_layer + (size_t)(ROWS ? a.seq : a.step->seq) * g.kv_seq_stride + (size_t)kvh * g.kv_head_stride;
     const KVT* Vp = Kp + g.kv_v_offset;
     float mh[G], lh[G];
     attn_split<KVT, DH, G, PAIR>(a.q, Kp, Vp, g.kv_lo_offset, kvh, s0, s1, g.scale, lds, mh, lh);
@@ -517,20 +525,22 @@ hipError_t launch_lmhead(int dtype, const void* wout, const float* gain, float* 
 }
 
 template <typename KVT, int DH, bool PAIR>
-static hipError_t launch_attn_t(const AttnArgs& a, const Geom& g, hipStream_t s) {
-    const dim3 grid(g.Hkv, a.nsplit), block(256);
+static hipError_t launch_attn_t(const AttnArgs& a, const Geom& g, hipStream_t s, int rows = 0) {
+    const dim3 grid(g.Hkv, a.nsplit, rows > 0 ? rows : 1), block(256);
     const bool pipe = a.sync.go_wait || a.sync.go_signal;
 #define ATTN_CASE(GG)                                                                                                   \
     case GG: {                                                                                                          \
         const size_t lds = sizeof(float) * attn_lds_floats<KVT, DH, GG>();                                              \
         if (lds > 48 * 1024) {                                                                                          \
-            hipError_t e = hipFuncSetAttribute(pipe ? (const void*)(k_attn_decode<KVT, DH, GG, PAIR, true>)             \
-                                                    : (const void*)(k_attn_decode<KVT, DH, GG, PAIR, false>),           \
+            hipError_t e = hipFuncSetAttribute(rows ? (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 2>)                \
+                                               : pipe ? (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 1>)              \
+                                                      : (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 0>),             \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
             if (e) return e;                                                                                            \
         }                                                                                                               \
-        if (pipe) hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, true>), grid, block, lds, s, a, g);              \
-        else hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, false>), grid, block, lds, s, a, g);                  \
+        if (rows) hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 2>), grid, block, lds, s, a, g);                 \
+        else if (pipe) hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 1>), grid, block, lds, s, a, g);            \
+        else hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 0>), grid, block, lds, s, a, g);                      \
         break;                                                                                                          \
     }
     switch (g.Hq / g.Hkv) {
@@ -551,6 +561,16 @@ hipError_t launch_attn_decode(int dtype, const void* kv_layer, int nsplit, bool 
     if (dtype == 0) return g.dh == 64 ? launch_attn_t<float, 64, false>(a, g, s) : launch_attn_t<float, 128, false>(a, g, s);
     if (g.kv_lo_offset) return g.dh == 64 ? launch_attn_t<bf16_t, 64, true>(a, g, s) : launch_attn_t<bf16_t, 128, true>(a, g, s);
     return g.dh == 64 ? launch_attn_t<bf16_t, 64, false>(a, g, s) : launch_attn_t<bf16_t, 128, false>(a, g, s);
+}
+
+hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s) {
+    if (nsplit < 1 || nsplit > ATTN_MAX_SPLIT || p.n < 1 || p.n > ROWS_MAX) return hipErrorInvalidValue;
+    AttnArgs a{};
+    a.q = rb.q; a.kv_layer = kv_layer; a.o = rb.o; a.part_acc = rb.part_acc; a.part_ml = rb.part_ml; a.counters = rb.counters;
+    a.nsplit = nsplit; a.pos0 = p.pos0; a.seq = p.seq;
+    if (dtype == 0) return g.dh == 64 ? launch_attn_t<float, 64, false>(a, g, s, p.n) : launch_attn_t<float, 128, false>(a, g, s, p.n);
+    if (g.kv_lo_offset) return g.dh == 64 ? launch_attn_t<bf16_t, 64, true>(a, g, s, p.n) : launch_attn_t<bf16_t, 128, true>(a, g, s, p.n);
+    return g.dh == 64 ? launch_attn_t<bf16_t, 64, false>(a, g, s, p.n) : launch_attn_t<bf16_t, 128, false>(a, g, s, p.n);
 }
 
 hipError_t launch_argmax_flat(const float* logits, int n, const int32_t* ban, int nban, float* part_v, int32_t* part_i,
@@ -576,10 +596,10 @@ hipError_t launch_argmax(const float* logits_base, const DecodeBuffers& b, const
 template <typename KVT, int DH, bool PAIR>
 static const void* attn_func_pipe(int G, size_t* lds) {
     switch (G) {
-        case 1: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 1>(); return (const void*)(k_attn_decode<KVT, DH, 1, PAIR, true>);
-        case 2: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 2>(); return (const void*)(k_attn_decode<KVT, DH, 2, PAIR, true>);
-        case 4: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 4>(); return (const void*)(k_attn_decode<KVT, DH, 4, PAIR, true>);
-        case 8: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 8>(); return (const void*)(k_attn_decode<KVT, DH, 8, PAIR, true>);
+        case 1: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 1>(); return (const void*)(k_attn_decode<KVT, DH, 1, PAIR, 1>);
+        case 2: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 2>(); return (const void*)(k_attn_decode<KVT, DH, 2, PAIR, 1>);
+        case 4: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 4>(); return (const void*)(k_attn_decode<KVT, DH, 4, PAIR, 1>);
+        case 8: *lds = sizeof(float) * attn_lds_floats<KVT, DH, 8>(); return (const void*)(k_attn_decode<KVT, DH, 8, PAIR, 1>);
         default: return nullptr;
     }
 }

@@ -78,6 +78,33 @@ struct ChunkBuffers {
     float* attn_ml;           // [unit][2][32]
 };
 
+// Several rows of one sequence per pass through the vector-unit kernels (decode_rows.hip): models outside the matrix-core
+// append path.  Eight rows: the vectors of 4096 columns fill 128 of the 160 KiB of LDS, and the 2 x 8 products per weight
+// element take the vector units about two thirds of the time that the weight stream takes.
+constexpr int ROWS_MAX = 8;
+struct RowsTokens { int32_t t[ROWS_MAX]; };
+struct RowsPass { int32_t seq, pos0, n; };
+struct RowsBuffers {
+    float* x;               // [ROWS_MAX][d]
+    float* q;               // [ROWS_MAX][Hq*dh]
+    float* o;               // [ROWS_MAX][Hq*dh]
+    float* a;               // [ROWS_MAX][F]
+    float* part_acc;        // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][dh]
+    float* part_ml;         // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][2]
+    int32_t* counters;      // [ROWS_MAX][Hkv], zero between launches
+};
+// whether the vectors and the parked results of every product fit LDS with the present number of workgroups
+bool rows_supported(int dtype, const Geom& g);
+hipError_t rows_init(int dtype);
+hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
+                             const Geom& g, hipStream_t s);
+hipError_t launch_rows_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const RowsBuffers& rb, const DecodeBuffers& b,
+                           const RowsPass& p, const Geom& g, hipStream_t s);
+hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
+hipError_t launch_rows_oproj(int dtype, const void* wo, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
+hipError_t launch_rows_gateup(int dtype, const void* wgu, const float* gain, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
+hipError_t launch_rows_down(int dtype, const void* wd, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
+
 // Fused (persistent, single-kernel) decoding step.
 struct FusedPlan {
     bool supported;

@@ -1,0 +1,70 @@
+"""GPU: models outside the matrix-core append path take prompts and interrupts several rows per pass through the vector-unit
+kernels.  Each case is compared with the same stream taken token by token (option chunk = 1) and, for fp32, with the oracle in
+64 bits: one shape per kernel variant (one or two row pairs at a time, vectors that fit LDS at once or in segments), row counts
+around a full pass, contexts on both sides of one key split."""
+import numpy as np
+import pytest
+import torch
+
+import asynclm_inputs as ai
+from asynclm_inputs.configs import ModelConfig
+from oracle import asynclm_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+FP32, PAIR, BF16 = "fp32", "pair", "bf16"
+
+# Differences of two correct orders of summation, relative to the logits (2-norm).  fp32: two layers of sums of up to 4104 terms,
+# random signs: sqrt(4104) * 2^-24 = 4e-6 per product.  pair: values are stored with 2^-17, and a stored value may round the
+# other way: a few 2^-17.  bf16: the same with 2^-9.
+TOL = {FP32: 1e-5, PAIR: 5e-5, BF16: 4e-3}
+
+
+def _model(d, hq, hkv, dh, ffn, dtype):
+    return ModelConfig(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=dh, ffn=ffn, vocab=520, rms_eps=1e-5,
+                       rope_theta=10000.0, dtype=dtype)
+
+
+CASES = [
+    (FP32, _model(256, 4, 4, 64, 688, "fp32")),        # a wave per row pair, one segment, last rows of a tile
+    (FP32, _model(136, 4, 2, 128, 4104, "fp32")),      # 4104 gate rows: two pairs at a time, odd counts; down: 4104 columns, two segments
+    (FP32, _model(2056, 2, 1, 64, 4104, "fp32")),      # down: two pairs at a time and two segments
+    (PAIR, _model(520, 8, 2, 64, 1032, "bf16")),       # paired cache, head_dim 64
+    (BF16, _model(264, 8, 1, 128, 8200, "bf16")),      # single-plane cache, eight heads per kv head, three segments
+]
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a.astype(np.float64) - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("kind,model", CASES, ids=["%s-d%d-f%d" % (k, m.d_model, m.ffn) for k, m in CASES])
+def test_rows_of_a_pass_equal_token_by_token(kind, model):
+    import paper_2412_07017_amd as pkg
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    fmt = pkg.KV_BF16 if kind == BF16 else pkg.KV_AUTO
+    tk = lambda n, sub: [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 931, n, model.vocab, sub=sub)]
+    lms = [pkg.AsyncLM(model, w, max_positions=640, max_seqs=2, stream=torch.cuda.Stream(), kv_format=fmt) for _ in range(2)]
+    lms[1].set_option("chunk", 1)
+    dec = orc.CachedDecoder(orc.Shape.of(model), ai.weights_to_numpy(w), dtype=np.float64) if kind == FP32 else None
+    for lm in lms:
+        lm.prefill(1, tk(5, 99))                       # another sequence: rows of sequence 0 must not touch it
+    for step, n in enumerate([2, 3, 8, 9, 231, 17, 25, 1, 7]):       # 253 tokens, then past one key split of 256
+        toks = tk(n, step)
+        for lm in lms:
+            (lm.prefill if step == 0 else lm.inject_interrupt)(0, toks)
+        a, b = lms[0].logits(0), lms[1].logits(0)
+        assert np.isfinite(a).all()
+        assert _rel(a, b) <= TOL[kind], (n, _rel(a, b))
+        if dec is not None:
+            (dec.prefill if step == 0 else dec.inject)(toks)
+            assert _rel(a, dec.logits) <= TOL[kind], (n, _rel(a, dec.logits))
+        assert lms[0].seq_len(0) == lms[1].seq_len(0)
+    for lm in lms:
+        lm.inject_interrupt(1, tk(11, 100))
+    assert _rel(lms[0].logits(1), lms[1].logits(1)) <= TOL[kind]
+    assert lms[0].decode_step(0, forced_token=3) == lms[1].decode_step(0, forced_token=3) == 3
+    assert _rel(lms[0].logits(0), lms[1].logits(0)) <= TOL[kind]
+    for lm in lms:
+        lm.close()
