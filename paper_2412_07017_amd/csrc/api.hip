@@ -20,9 +20,9 @@ struct PassBuilder {
     int G = 1, Hkv = 1, max_keys = 0;
     void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = 0; max_keys = 0; }
     int tiles_of(int n) const { return (G * n + 31) / 32; }
-    // rows, attention tasks, and the attention's partial results (task x kv head x at least 4 key splits) all fit one pass
+    // batched steps: rows, attention tasks, and the attention's partial results (task x kv head x at least 4 key splits) all fit one pass
     bool fits(int n) const {
-        return t.rows + n <= CHUNK_MAX && t.ntasks + tiles_of(n) <= CHUNK_MAX_TASKS &&
+        return t.rows + n <= CHUNK_BATCH_ROWS && t.ntasks + tiles_of(n) <= CHUNK_BATCH_TASKS &&
                (long long)(t.ntasks + tiles_of(n)) * Hkv * 4 <= CHUNK_ATTN_MAX_UNITS;
     }
     // Appends a group of n rows to sequence `seq` (length before: pos0).  forced: see ChunkGroup; `rest` holds the
@@ -80,6 +80,7 @@ struct asynclm_ctx {
     DecodeBuffers b{};
     ChunkBuffers cb{};
     bool chunk_ok = false;              // the matrix-core append path supports this model
+    int pass_rows = CHUNK_BATCH_ROWS;   // rows that one of its passes can hold (CHUNK_BATCH_ROWS .. CHUNK_MAX)
     RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
@@ -96,7 +97,7 @@ struct asynclm_ctx {
     std::vector<int32_t> nban;          // host mirror of the number of banned token ids per sequence
     std::vector<char> choice_stale;     // the ban list changed after the sequence's greedy token was computed
     PassBuilder pass;                   // row table of the append-chunk pass being built
-    int32_t* chosen_host = nullptr;     // pinned, CHUNK_MAX ints
+    int32_t* chosen_host = nullptr;     // pinned, CHUNK_MAX_GROUPS ints
     // pinned staging of what the host uploads on the hot path (a pageable source would make the copy wait for the
     // stream): two copies of the row table and a small ring of ban-list rows, each reused once its event has passed
     ChunkTable* tab_host[2] = {nullptr, nullptr};
@@ -450,44 +451,62 @@ int check_tokens(const asynclm_ctx* c, const int32_t* t, int32_t n) {
     return ASYNCLM_OK;
 }
 
-// Split-K factors of the four products of a layer (workgroups = N/32 * S, each of 4 waves).
-struct ChunkSplits { int qkv, o, gu, down; };
+// Plans of the four products of a layer.
+struct ChunkPlans { GemmPlan qkv, o, gu, down; };
 
-// A product with N output rows and K columns over MT row tiles runs (N/128) * (row blocks) * S workgroups, one per
-// compute unit at a time: S = the split that comes closest to one workgroup per unit, with at least two
-// 128-column blocks per workgroup, within the capacity of the partial planes.
-int pick_gemm_split(const asynclm_ctx* c, int N, int K, int MT) {
-    const int row_blocks = MT <= 4 ? 1 : (MT + 7) / 8;          // as launch_chunk_gemm tiles the rows
-    const int tiles = N / 128 * row_blocks, nblk = K / 128;
+// A product with N output rows and K columns over MT row tiles.  Up to four row tiles: (N / 128) S workgroups, one per
+// compute unit at a time: S = the split that comes closest to one workgroup per unit, with at least two 128-column blocks
+// per workgroup.  More: workgroups of nt weight-row tiles x 256 rows run in rounds of one per compute unit; a k-block costs
+// nt, a workgroup's start and end about as much as 14 (0.6 us each), and a partial plane of 512 x 4096 floats, written and
+// read back, about 6.5.  All within the capacity of the partial planes.  `swiglu`: pairs of gate and up rows, no split.
+GemmPlan pick_gemm_plan(const asynclm_ctx* c, int N, int K, int MT, bool swiglu = false) {
+    const int nblk = K / 128;
     const int smax = std::min(CHUNK_GEMM_MAX_SPLIT, std::max(1, nblk / 2));
-    int s;
-    if (MT <= 3) {
-        s = std::max(1, std::min((c->n_cu + tiles / 2) / tiles, smax));
-    } else {
-        // wide passes are bound by the matrix cores: the workgroups run in rounds of one per compute unit, each taking
-        // its k-blocks plus about one and a half blocks' time of prologue and epilogue; every split also costs a
-        // partial plane to write and read back
-        // (a plane of 512 x 4096 floats, written and read back, costs about as much as one k-block of a workgroup)
-        s = 1;
-        double best = 0;
-        const double plane = 0.9 * ((double)MT * 32 * N) / (512.0 * 4096.0);
-        for (int k = 1; k <= smax; ++k) {
-            const int rounds = (tiles * k + c->n_cu - 1) / c->n_cu;
-            const double cost = rounds * ((double)nblk / k + 1.5) + plane * (k - 1);
-            if (k == 1 || cost < best) { best = cost; s = k; }
+    auto fits = [&](int s) { return s == 1 || (size_t)s * MT * 32 * N <= c->cb.part_capacity; };
+    if (MT <= 4) {
+        const int tiles = N / 128;
+        int s = std::max(1, std::min((c->n_cu + tiles / 2) / tiles, smax));
+        if (MT == 4) {          // bound by the matrix cores rather than the weight stream: whole rounds, few planes
+            s = 1;
+            double best = 0;
+            const double plane = 0.9 * ((double)MT * 32 * N) / (512.0 * 4096.0);
+            for (int k = 1; k <= smax; ++k) {
+                const int rounds = (tiles * k + c->n_cu - 1) / c->n_cu;
+                const double cost = rounds * ((double)nblk / k + 1.5) + plane * (k - 1);
+                if (k == 1 || cost < best) { best = cost; s = k; }
+            }
+        }
+        if (c->opt_chunk_split > 0) s = std::min(c->opt_chunk_split, std::max(1, nblk));
+        if (swiglu) s = 1;
+        while (!fits(s)) --s;
+        return {s, 4};
+    }
+    const int my = (MT + 7) / 8;
+    GemmPlan best{1, 4};
+    double best_cost = 0;
+    const double plane = 6.5 * ((double)MT * 32 * N) / (512.0 * 4096.0);
+    int s0 = 1, s1 = swiglu ? 1 : smax;
+    if (!swiglu && c->opt_chunk_split > 0) { s0 = s1 = std::min(c->opt_chunk_split, std::max(1, nblk)); while (!fits(s1)) --s1; s0 = s1; }
+    bool any = false;
+    for (int s = s0; s <= s1; ++s) {
+        if (!fits(s)) break;
+        for (int nt = 8; nt >= 4; --nt) {
+            const int tiles = (N / 32 + nt - 1) / nt * my * s;
+            const int rounds = (tiles + c->n_cu - 1) / c->n_cu;
+            const double cost = rounds * ((double)((nblk + s - 1) / s) * nt + 14.0) + (swiglu ? 0.0 : plane * s);
+            if (!any || cost < best_cost) { any = true; best_cost = cost; best = {s, nt}; }
         }
     }
-    if (c->opt_chunk_split > 0) s = std::min(c->opt_chunk_split, std::max(1, nblk));
-    while (s > 1 && (size_t)s * MT * 32 * N > c->cb.part_capacity) --s;
-    return s;
+    return best;
 }
 
-ChunkSplits chunk_splits(const asynclm_ctx* c, int MT) {
+ChunkPlans chunk_plans(const asynclm_ctx* c, int MT) {
     const Geom& g = c->g;
     // the gate/up product of a wide pass is never split (unless forced): split-K would lose its SwiGLU epilogue
-    const int gu = MT > 3 && c->opt_chunk_split == 0 ? 1 : pick_gemm_split(c, 2 * g.F, g.d, MT);
-    return {pick_gemm_split(c, (g.Hq + 2 * g.Hkv) * g.dh, g.d, MT), pick_gemm_split(c, g.d, g.Hq * g.dh, MT), gu,
-            pick_gemm_split(c, g.d, g.F, MT)};
+    GemmPlan gu = pick_gemm_plan(c, 2 * g.F, g.d, MT, MT > 3 && c->opt_chunk_split == 0);
+    if (MT > 4 && gu.s == 1) gu = pick_gemm_plan(c, 2 * g.F, g.d, MT, true);
+    return {pick_gemm_plan(c, (g.Hq + 2 * g.Hkv) * g.dh, g.d, MT), pick_gemm_plan(c, g.d, g.Hq * g.dh, MT), gu,
+            pick_gemm_plan(c, g.d, g.F, MT)};
 }
 
 // Key splits of the chunk attention: about two 32-key tiles per wave, a multiple of 4, no more than fill the
@@ -504,7 +523,7 @@ int pick_chunk_attn_split(const asynclm_ctx* c, int max_keys, int ntasks) {
     return n;
 }
 
-// One forward pass over the rows of `pb` (1..CHUNK_MAX rows in any number of groups).  Groups that want logits
+// One forward pass over the rows of `pb` (1..pass_rows rows in any number of groups).  Groups that want logits
 // get them from the single-row head kernels (one group) or from one more product on the matrix cores (several).
 hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     const Geom& g = c->g;
@@ -512,7 +531,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     hipStream_t s = c->stream;
     const ChunkTable& t = pb.t;
     const int rows = t.rows, MT = (rows + 31) / 32;
-    const ChunkSplits sp = chunk_splits(c, MT);
+    const ChunkPlans sp = chunk_plans(c, MT);
     const int nqkv = (g.Hq + 2 * g.Hkv) * g.dh, qd = g.Hq * g.dh;
     const int asplit = pick_chunk_attn_split(c, pb.max_keys, t.ntasks);
     // passes made of large groups (at least 16 tasks, three or more per block on average) share keys and values
@@ -540,32 +559,32 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_embed(c->embed, cb, rows, g, s); }))) return e;
     for (int l = 0; l < c->cfg.n_layers; ++l) {
         void* kvl = kv_layer_ptr(c, l);
-        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, l > 0, sp.down, MT, c->attn_norm[l], rows, g, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, l > 0, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.qkv, MT, s); }))) return e;
-        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, sp.qkv, kvl, c->b, rows, MT, g, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, sp.qkv.s, kvl, c->b, rows, MT, g, s); }))) return e;
         if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, wsplit, t.ntasks, t.nblocks, g, s); }))) return e; }
         else if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn(cb, kvl, asplit, t.ntasks, g, s); }))) return e;
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb, sp.o, MT, s); }))) return e;
-        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, true, sp.o, MT, c->ffn_norm[l], rows, g, s); }))) return e;
-        if (sp.gu == 1) {                 // no split-K: the SwiGLU is the product's epilogue
-            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, true, sp.o.s, MT, c->ffn_norm[l], rows, g, s); }))) return e;
+        if (sp.gu.s == 1) {                 // no split-K: the SwiGLU is the product's epilogue
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, MT, s); }))) return e;
         } else {
             if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wgate_up[l], 2 * g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, MT, s); }))) return e;
-            if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_swiglu(cb, sp.gu, MT, rows, g, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_swiglu(cb, sp.gu.s, MT, rows, g, s); }))) return e;
         }
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb, sp.down, MT, s); }))) return e;
     }
     const bool head_on_mfma = t.nhead > 1 && g.V % 128 == 0 && (size_t)((t.nhead + 31) / 32) * 32 * g.V <= cb.part_capacity;
     if (head_on_mfma) {
         const int MTh = (t.nhead + 31) / 32;
-        if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_head_rows(cb, sp.down, MT, c->final_norm, t.ngroups, g, s); }))) return e;
-        if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, 1, MTh, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_head_rows(cb, sp.down.s, MT, c->final_norm, t.ngroups, g, s); }))) return e;
+        if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, GemmPlan{1, 4}, MTh, s); }))) return e;
         if ((e = run(c, KC_ARGMAX, [&] { return launch_chunk_logits(cb, MTh, c->logits, c->b, t.ngroups, g, s); }))) return e;
     } else {
         for (int gi = 0; gi < t.ngroups; ++gi) {
             if (t.group[gi].head < 0) continue;
             const int seq = t.group[gi].seq;
-            if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_last_row(cb, sp.down, MT, gi, c->b, g, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_last_row(cb, sp.down.s, MT, gi, c->b, g, s); }))) return e;
             if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, c->b, g, s); }))) return e;
             if ((e = run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, c->b, g, s); }))) return e;
         }
@@ -611,7 +630,7 @@ hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, b
 int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
     // the one-kernel and the two-stream step are asked for by option: then every token takes such a step
     const bool rows_path = !c->chunk_ok && !c->opt_fused && !c->opt_pipeline && rows_supported(c->cfg.dtype, c->g);
-    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, CHUNK_MAX) : rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
+    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, c->pass_rows) : rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
     int i = 0;
     while (i < n) {
         const int rows = std::min(chunk, n - i);
@@ -633,11 +652,23 @@ int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
 
 }  // namespace
 
+static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows);
+
 extern "C" {
 
 int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream) {
     if (out) *out = nullptr;
     if (!out || !cfg || !w) return ASYNCLM_E_INVAL;
+    // where memory is too short for the buffers of large passes, the smallest ones do
+    const int r = create_ctx(out, cfg, w, hip_stream, CHUNK_MAX);
+    if (r != ASYNCLM_E_NOMEM) return r;
+    (void)hipGetLastError();
+    return create_ctx(out, cfg, w, hip_stream, CHUNK_BATCH_ROWS);
+}
+
+}  // extern "C"
+
+static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows) {
     if (!config_ok(cfg)) return ASYNCLM_E_INVAL;
     if (!w->embed || !w->final_norm || !w->lm_head || !w->attn_norm || !w->wqkv || !w->wo || !w->ffn_norm ||
         !w->wgate_up || !w->wdown)
@@ -721,18 +752,24 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
     ALLOC(c->stamp_done, (size_t)c->pipe_kernels_max * STAMP_DONE_SLOTS);
     if (c->chunk_ok) {
         ChunkBuffers& cb = c->cb;
-        const size_t M = CHUNK_MAX, qd = (size_t)g.Hq * g.dh;
+        // Rows per pass: longer prompts take passes of up to 2048 rows (fewer partial planes, whole rounds of workgroups; one
+        // 16384-token prompt of the 8B shape: see forward_chunk), as long as the context can be that long and the partial
+        // results of the attention fit.
+        c->pass_rows = std::max(CHUNK_BATCH_ROWS, std::min({max_rows, g.max_pos, CHUNK_ATTN_MAX_UNITS * 32 / g.Hq / 32 * 32,
+                                                            CHUNK_MAX_TASKS * 32 / (g.Hq / g.Hkv)}));
+        const size_t M = c->pass_rows, MB = CHUNK_BATCH_ROWS, qd = (size_t)g.Hq * g.dh;
         // split-K partial planes: every split of the widest product for passes of up to 96 rows (bound by the weight
         // stream: many splits), two for the largest pass (bound by the matrix cores: few), the output head for one
         // row per group
         const size_t wmax = std::max(std::max((size_t)2 * g.F, (size_t)(g.Hq + 2 * g.Hkv) * g.dh), (size_t)g.d);
-        cb.part_capacity = std::max(std::max((size_t)96 * CHUNK_GEMM_MAX_SPLIT * wmax, 2 * M * wmax), (size_t)CHUNK_MAX_TASKS * g.V);
+        const size_t wunsplit = std::max((size_t)(g.Hq + 2 * g.Hkv) * g.dh, (size_t)g.d);       // the widest product without SwiGLU
+        cb.part_capacity = std::max({(size_t)96 * CHUNK_GEMM_MAX_SPLIT * wmax, 2 * MB * wmax, M * wunsplit, (size_t)CHUNK_MAX_GROUPS * g.V});
         if ((e = chunk_init()) != hipSuccess) { report_hip("chunk_init", e); return bail(ASYNCLM_E_DEVICE); }
-        cb.q_cols = (g.Hq / g.Hkv) * CHUNK_MAX + 32;
+        cb.q_cols = (g.Hq / g.Hkv) * c->pass_rows + 32;
         const size_t qn = (size_t)g.Hkv * cb.q_cols * g.dh;
         c->pass.G = g.Hq / g.Hkv; c->pass.Hkv = g.Hkv;
         ALLOC(cb.tab, 1);
-        ALLOC(cb.chosen, M);
+        ALLOC(cb.chosen, (size_t)CHUNK_MAX_GROUPS);
         ALLOC(cb.x, M * g.d);
         ALLOC(cb.nrm_hi, M * g.d); ALLOC(cb.nrm_lo, M * g.d);
         ALLOC(cb.att_hi, M * qd); ALLOC(cb.att_lo, M * qd);
@@ -742,7 +779,7 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
         ALLOC(cb.attn_o, (size_t)CHUNK_ATTN_MAX_UNITS * g.dh * 32);
         ALLOC(cb.attn_ml, (size_t)CHUNK_ATTN_MAX_UNITS * 64);
         // rows beyond the current chunk are multiplied into discarded columns only, but must stay finite
-        if (hipMemset(cb.tab, 0, sizeof(ChunkTable)) || hipMemset(cb.chosen, 0, M * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
+        if (hipMemset(cb.tab, 0, sizeof(ChunkTable)) || hipMemset(cb.chosen, 0, CHUNK_MAX_GROUPS * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
             hipMemset(cb.nrm_lo, 0, M * g.d * 2) || hipMemset(cb.att_hi, 0, M * qd * 2) || hipMemset(cb.att_lo, 0, M * qd * 2) ||
             hipMemset(cb.act_hi, 0, M * g.F * 2) || hipMemset(cb.act_lo, 0, M * g.F * 2) || hipMemset(cb.q_hi, 0, qn * 2) ||
             hipMemset(cb.q_lo, 0, qn * 2))
@@ -800,7 +837,7 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
             hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess)
             return bail(ASYNCLM_E_DEVICE);
     }
-    if (hipHostMalloc((void**)&c->chosen_host, sizeof(int32_t) * CHUNK_MAX, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
+    if (hipHostMalloc((void**)&c->chosen_host, sizeof(int32_t) * CHUNK_MAX_GROUPS, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
     for (int i = 0; i < 2; ++i)
         if (hipHostMalloc((void**)&c->tab_host[i], sizeof(ChunkTable), hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&c->tab_ev[i], hipEventDisableTiming) != hipSuccess)
@@ -809,7 +846,7 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
     for (int i = 0; i < asynclm_ctx::BAN_RING; ++i)
         if (hipEventCreateWithFlags(&c->ban_ev[i], hipEventDisableTiming) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     c->batch_seen.assign(cfg->max_seqs, 0);
-    c->batch_owner.reserve(CHUNK_MAX_TASKS + 1);
+    c->batch_owner.reserve(CHUNK_MAX_GROUPS + 1);
     // fused decoding step: pointer table, barrier counters, launch plan
     {
         std::vector<const void*> tab;
@@ -841,6 +878,8 @@ int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_w
     *out = c;
     return ASYNCLM_OK;
 }
+
+extern "C" {
 
 int asynclm_destroy(asynclm_ctx* c) {
     if (!c) return ASYNCLM_OK;
@@ -955,7 +994,7 @@ int asynclm_step_batch(asynclm_ctx* c, int32_t nseq, const int32_t* seqs, const 
         return ASYNCLM_OK;
     }
 
-    // One weight pass per CHUNK_MAX rows: groups are packed in the order given; a group that does not fit is
+    // One weight pass per CHUNK_BATCH_ROWS rows: groups are packed in the order given; a group that does not fit is
     // continued in the next pass (its later rows see its earlier ones through the cache).
     for (int i = 0; i < nseq; ++i)
         if (forced_of(i) < 0) HIPCK(c, refresh_choice(c, seqs[i]));
@@ -984,8 +1023,8 @@ int asynclm_step_batch(asynclm_ctx* c, int32_t nseq, const int32_t* seqs, const 
         int done = 0;                       // rows of this sequence already placed (the chosen token is row 0)
         const int total = 1 + k;
         while (done < total) {
-            int space = CHUNK_MAX - pb.t.rows;
-            if (space == 0 || !pb.fits(1)) { const int r = flush(); if (r) return r; space = CHUNK_MAX; }
+            int space = CHUNK_BATCH_ROWS - pb.t.rows;
+            if (space == 0 || !pb.fits(1)) { const int r = flush(); if (r) return r; space = CHUNK_BATCH_ROWS; }
             int n = std::min(space, total - done);
             while (n > 1 && !pb.fits(n)) --n;
             const int pos0 = c->len[q];     // rows placed by earlier passes are already counted
@@ -1195,7 +1234,7 @@ int asynclm_synchronize(asynclm_ctx* c) {
 
 int asynclm_set_option(asynclm_ctx* c, const char* name, int32_t value) {
     if (!c || !name) return ASYNCLM_E_INVAL;
-    if (!std::strcmp(name, "chunk")) { if (value < 1 || value > CHUNK_MAX) return ASYNCLM_E_INVAL; c->opt_chunk = value; return ASYNCLM_OK; }
+    if (!std::strcmp(name, "chunk")) { if (value < 1 || value > CHUNK_BATCH_ROWS) return ASYNCLM_E_INVAL; c->opt_chunk = value; return ASYNCLM_OK; }
     if (!std::strcmp(name, "chunk_split")) { if (value < 0 || value > CHUNK_GEMM_MAX_SPLIT) return ASYNCLM_E_INVAL; c->opt_chunk_split = value; return ASYNCLM_OK; }
     // the options below change the launch geometry of a decoding step: its captured graphs are built again (this call allocates)
     auto regraph = [&]() -> int {

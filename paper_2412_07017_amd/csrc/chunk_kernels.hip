@@ -36,6 +36,21 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
     lo = f32_to_bf16(v - __uint_as_float((uint32_t)hi << 16));
 }
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// two fp32 -> two bf16 (round to nearest even) in one 32-bit word, first value in the low half (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16x2(float x, float y) {
+    const f32x2 v = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// hi = bf16(p), lo = bf16(p - hi) for a pair of values
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) {
+    hi = pack_bf16x2(x, y);
+    lo = pack_bf16x2(x - __uint_as_float(hi << 16), y - __uint_as_float(hi & 0xffff0000u));
+}
+
 // offset (elements) of (row m, column k) in a tiled plane with K columns
 __device__ __forceinline__ size_t tiled_off(int m, int k, int K) {
     const int kk = k & 127;
@@ -294,8 +309,8 @@ __global__ void k_chunk_rope_kv(const float* __restrict__ P, int S, size_t s_str
 // skinny GEMM on the matrix cores:  P[s][m][n] = sum_{k in slice s} X[m][k] W[n][k]
 // ---------------------------------------------------------------------------------------------
 // Which kernel takes a pass (launch_chunk_gemm): up to 32 rows this one (bound by the weight stream, a wave per 32
-// weight rows); 33-64 rows k_chunk_gemm_ks (the waves split the k-steps); 65-128 rows k_chunk_gemm_wide with a wave
-// per row tile; more rows k_chunk_gemm_wide with 256-row workgroups.  The template serves any MT <= 3; MT = 1 is used.
+// weight rows); 33-64 rows k_chunk_gemm_ks (the waves split the k-steps); 65-128 rows k_chunk_gemm_wide, a wave
+// per row tile; more rows k_chunk_gemm_big.  The template serves any MT <= 3; MT = 1 is used.
 // Workgroup = 4 waves on 128 weight rows (32 per wave) and one contiguous run of 128-element k-blocks
 // (the S workgroups of a row tile split K and write separate partial planes that the consumer adds in
 // a fixed order: no atomics, results are bit-reproducible).
@@ -514,12 +529,11 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
 }
 
 // ---------------------------------------------------------------------------------------------
-// wide GEMM on the matrix cores for passes of more than 96 rows (prefill, large batched steps)
+// wide GEMM on the matrix cores for passes of 65-128 rows
 // ---------------------------------------------------------------------------------------------
-// Workgroup = NW waves on a tile of 128 weight rows x (32 NW MW) token rows and one run of k-blocks.  Beyond 96
-// rows a pass is bound by the matrix cores, not by the weight stream, so the tile is shaped for operand reuse:
-//  * every wave multiplies ALL 128 weight rows of the tile with its own MW row tiles (32 token rows each):
-//    per 16-column k-step 4 weight operands and 2 MW activation operands (hi, lo) feed 8 MW products;
+// Workgroup = 4 waves on a tile of 128 weight rows x 128 token rows and one run of k-blocks:
+//  * every wave multiplies ALL 128 weight rows of the tile with its own row tile (32 token rows):
+//    per 16-column k-step 4 weight operands and 2 activation operands (hi, lo) feed 8 products;
 //  * the weight block (128 rows x 128 columns) is loaded once per workgroup (4 rows x 256 contiguous bytes
 //    per instruction), transposed into operand order through a double-buffered, XOR-swizzled LDS tile that
 //    the waves share: one barrier per k-block;
@@ -710,6 +724,247 @@ __global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __res
 #pragma unroll
             for (int b = 0; b < 4; ++b)
                 *(float4*)(prow + nt * 32 + 8 * b) = make_float4(acc[nt][j][4 * b], acc[nt][j][4 * b + 1], acc[nt][j][4 * b + 2], acc[nt][j][4 * b + 3]);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// large GEMM on the matrix cores for passes of more than 128 rows (prefill, long interrupts, large batched steps)
+// ---------------------------------------------------------------------------------------------
+// Workgroup = 4 waves, one per SIMD, on a tile of 32 NT weight rows (NT = 4..8) x 256 token rows and one run of k-blocks.
+// Every wave multiplies all NT weight-row tiles with its own two row tiles: per 16-column step NT weight and 4 activation
+// operands (hi, lo) feed 4 NT products.  Such a pass is bound by the matrix cores and, with operands that are not zero, by
+// the power they may take, so the loop is made for few bytes per product and no idle issue slots:
+//  * weights and activations of a block of 32 columns go from global memory straight to LDS (16 bytes per lane and load,
+//    no registers): three buffers, the block after next is requested while a block is multiplied.  The weights are
+//    row-major in memory; the transposition into operand order is the choice of the 16-byte piece a lane loads (LDS row r,
+//    piece p holds piece p ^ ((r / 2) & 3) of the row: eight consecutive rows then cover all banks once).
+//  * every load and every LDS read is issued between two products.  Issued together at the start of a block, the same
+//    loads kept the matrix cores idle for 40 % of the time (0.94-1.17 PFLOP/s); spread, the cores are busy 87-91 % of the
+//    cycles and the clock drops to the power limit instead (1.3-1.7 GHz with random operands, 2.4 with zeros).
+//  * one barrier per block, after the operands of its last step are in registers.
+// NT and the split of K come from pick_gemm_plan: the tiles should fill whole rounds of one workgroup per compute unit.
+// Measured stand-alone, random operands, counted with both planes: gate/up of the 8B shape (28672 x 4096) 512 rows 204 us =
+// 1.18 PFLOP/s, 2048 rows 736 us = 1.31; down of the 70B shape (8192 x 28672), 2048 rows 1.38.  The kernel before this one
+// (128 weight rows per workgroup, activations straight to registers): 225 us = 1.07 at 512 rows.  The same matrix
+// instruction in a loop without any loads sustains 1.82 PFLOP/s with random operands.
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef const __attribute__((address_space(1))) void* global_ptr;
+
+constexpr int BIG_M = 8;                                    // row tiles per workgroup
+template <int NT> struct BigShape {
+    static constexpr int W_BYTES = NT * 2048, BUF = W_BYTES + BIG_M * 4096;     // 32 columns: weights, then [row tile][plane][step] KiB
+    static constexpr int LW = (2 * NT + 3) / 4, L = LW + 8;                     // loads per wave and block: weights, all
+};
+template <int NT> struct BigPtrs {
+    const bf16_t* w[BigShape<NT>::LW];
+    int w_off[BigShape<NT>::LW];
+    const bf16_t* x[2][2];                                  // [row tile][plane]
+};
+struct BigLane { int a0, a1, b, wave; };                    // LDS offsets of the lane's operands: weights of step 0 / 1, activations
+
+// Load j of the wave's share of block `blk` (32 columns) into the buffer at `base`.
+template <int NT>
+__device__ __forceinline__ void big_load(unsigned char* base, const BigPtrs<NT>& p, int blk, int wave, int j) {
+    constexpr int LW = BigShape<NT>::LW;
+    if (j < LW) {
+        __builtin_amdgcn_global_load_lds((global_ptr)(p.w[j] + (size_t)blk * 32), (lds_ptr)(base + p.w_off[j]), 16, 0, 0);
+    } else {
+        const int q = j - LW, mt = q >> 2, pl = (q >> 1) & 1, st = q & 1;
+        __builtin_amdgcn_global_load_lds((global_ptr)(p.x[mt][pl] + ((size_t)blk * 2 + st) * 512),
+                                         (lds_ptr)(base + BigShape<NT>::W_BYTES + (((wave * 2 + mt) * 2 + pl) * 2 + st) * 1024), 16, 0, 0);
+    }
+}
+
+// The 4 NT products of one step; `between(m)` runs after product m.
+template <int NT, class F>
+__device__ __forceinline__ void big_mma(const u32x4 (&a)[NT], const u32x4 (&x)[2][2], f32x16 (&acc)[NT][2], F&& between) {
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                acc[nt][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[nt]), __builtin_bit_cast(bf16x8, x[j][pl]),
+                                                                     acc[nt][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                between((pl * NT + nt) * 2 + j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+}
+
+// One block.  On entry its data are in `rd` for every wave and nobody reads `wr` any more; a1 / x1 hold the operands of
+// the previous block's second step.  Requests block `blk` into `wr`, multiplies the previous second step and this block's
+// first one, leaves the operands of its second step in a1 / x1 and the next block complete in LDS for every wave.
+// The two pointers never meet (the buffers rotate), which the compiler has to know: it would otherwise wait for all
+// loads to LDS before every LDS read.  The empty asm statements keep the reads on their side of the barrier.
+template <int NT, bool FIRST>
+__device__ __forceinline__ void big_block(const unsigned char* __restrict__ rd, unsigned char* __restrict__ wr, const BigPtrs<NT>& p, int blk,
+                                          const BigLane& ln, f32x16 (&acc)[NT][2], u32x4 (&a1)[NT], u32x4 (&x1)[2][2]) {
+    constexpr int L = BigShape<NT>::L, LA = (L + 1) / 2, STEP = 4 * NT / LA;
+    static_assert(STEP >= 1 && NT + 4 <= 4 * NT, "every load and read of a block has a product to stand behind");
+    int oa0 = ln.a0, oa1 = ln.a1, ob = ln.b;
+    asm volatile("" : "+v"(oa0), "+v"(oa1), "+v"(ob));
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 a0[NT], x0[2][2];
+    auto read0 = [&](int m) {
+        if (m < NT) a0[m] = *(const u32x4*)(rd + m * 2048 + oa0);
+        else if (m < NT + 4) x0[(m - NT) >> 1][(m - NT) & 1] = *(const u32x4*)(rd + ob + (m - NT) * 2048);
+    };
+    if (FIRST) {
+#pragma unroll
+        for (int j = 0; j < LA; ++j) big_load<NT>(wr, p, blk, ln.wave, j);
+#pragma unroll
+        for (int m = 0; m < NT + 4; ++m) read0(m);
+    } else {
+        big_mma<NT>(a1, x1, acc, [&](int m) { read0(m); if (m % STEP == STEP - 1 && m / STEP < LA) big_load<NT>(wr, p, blk, ln.wave, m / STEP); });
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(a0[nt]));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { asm volatile("" : "+v"(x0[j][0])); asm volatile("" : "+v"(x0[j][1])); }
+    __builtin_amdgcn_sched_barrier(0);
+    big_mma<NT>(a0, x0, acc, [&](int m) {
+        if (m < NT) a1[m] = *(const u32x4*)(rd + m * 2048 + oa1);
+        else if (m < NT + 4) x1[(m - NT) >> 1][(m - NT) & 1] = *(const u32x4*)(rd + ob + (m - NT) * 2048 + 1024);
+        if (m % STEP == STEP - 1 && m / STEP < L - LA) big_load<NT>(wr, p, blk, ln.wave, LA + m / STEP);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(a1[nt]));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { asm volatile("" : "+v"(x1[j][0])); asm volatile("" : "+v"(x1[j][1])); }
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L) : "memory");       // this wave's share of the next block has landed ...
+    __builtin_amdgcn_s_barrier();                                   // ... and everybody's
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// SWIGLU (S = 1): W holds the gate rows [0, N/2) and the up rows [N/2, N); a weight-row tile is 16 gate rows and the 16 up
+// rows of the same columns, which end up in the same lane (registers 4b + r and 4(b + 2) + r), and the epilogue writes
+// silu(gate) * up as hi/lo planes in operand order.
+template <int NT, bool SWIGLU>
+__global__ __launch_bounds__(256) void k_chunk_gemm_big(const bf16_t* __restrict__ W, int N, int K, const bf16_t* __restrict__ Xhi,
+                                                        const bf16_t* __restrict__ Xlo, float* __restrict__ P, size_t s_stride, int n_stride,
+                                                        int S, int MT, int ntiles, bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo) {
+    extern __shared__ __align__(1024) unsigned char big_lds[];      // [3 buffers]
+    constexpr int BUF = BigShape<NT>::BUF, L = BigShape<NT>::L, LW = BigShape<NT>::LW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int MY = (MT + BIG_M - 1) / BIG_M;
+    int ntile, my, sp;
+    {
+        // Workgroups go round robin over the XCDs by linear id.  An XCD takes weight tiles of its own, each with two row
+        // blocks next to each other, and all of its tiles before the next pair of row blocks: what its 32 compute units
+        // read at a time (16 weight tiles, two row blocks) stays in its L2.
+        int q = blockIdx.x;
+        const int MG = MY & 1 ? 1 : 2;
+        if ((ntiles & 7) == 0) {
+            const int xcd = q & 7;
+            q >>= 3;
+            const int mi = q % MG; q /= MG;
+            ntile = (q % (ntiles >> 3)) * 8 + xcd; q /= ntiles >> 3;
+            my = (q % (MY / MG)) * MG + mi; sp = q / (MY / MG);
+        } else {
+            my = q % MY; q /= MY;
+            ntile = q % ntiles; sp = q / ntiles;
+        }
+    }
+    const int nblk = K >> 7;                                        // (K / 128) * S < 2^31
+    const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S) * 4, nb = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S) * 4 - b0;
+    const int NR = SWIGLU ? N >> 1 : N;                             // rows of the result
+    BigPtrs<NT> p;
+#pragma unroll
+    for (int j = 0; j < LW; ++j) {
+        // load q covers LDS rows 16 q .. 16 q + 15 of the tile, four lanes each; past the end the last one again
+        const int q = min(wave * LW + j, 2 * NT - 1);
+        const int r = 16 * q + (lane >> 2), c = (lane & 3) ^ ((r >> 1) & 3);
+        int row;
+        if (SWIGLU) {
+            const int f = min((ntile * NT + (r >> 5)) * 16 + (r & 15), NR - 1);
+            row = (r & 16) ? NR + f : f;
+        } else row = min(ntile * NT * 32 + r, NR - 1);
+        p.w[j] = W + (size_t)row * K + c * 8;
+        p.w_off[j] = q * 1024;
+    }
+    int mtile[2];                                                   // past the pass's end: the last tile again, not stored
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        mtile[j] = my * BIG_M + wave * 2 + j;
+        const size_t o = (size_t)min(mtile[j], MT - 1) * nblk * 4096 + lane * 8;
+        p.x[j][0] = Xhi + o; p.x[j][1] = Xlo + o;
+    }
+    BigLane ln;
+    {
+        const int i = lane & 31, gh = lane >> 5, z = (i >> 1) & 3;
+        ln.a0 = i * 64 + ((gh ^ z) << 4); ln.a1 = i * 64 + (((2 + gh) ^ z) << 4);
+        ln.b = BigShape<NT>::W_BYTES + wave * 8192 + lane * 16; ln.wave = wave;
+    }
+    f32x16 acc[NT][2];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nt][j][r] = 0.f;
+
+    if (nb > 0) {
+        const int last = b0 + nb - 1;                               // nb >= 4
+        u32x4 a1[NT], x1[2][2];
+#pragma unroll
+        for (int j = 0; j < L; ++j) big_load<NT>(big_lds, p, b0, wave, j);
+#pragma unroll
+        for (int j = 0; j < L; ++j) big_load<NT>(big_lds + BUF, p, b0 + 1, wave, j);
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L) : "memory");
+        __builtin_amdgcn_s_barrier();
+        big_block<NT, true>(big_lds, big_lds + 2 * BUF, p, b0 + 2, ln, acc, a1, x1);
+        int cur = 1;
+        for (int i = 1; i < nb; ++i) {
+            const int prev = cur == 0 ? 2 : cur - 1;                // the buffer of block i - 1 takes block i + 2
+            big_block<NT, false>(big_lds + cur * BUF, big_lds + prev * BUF, p, min(b0 + i + 2, last), ln, acc, a1, x1);
+            cur = cur == 2 ? 0 : cur + 1;
+        }
+        big_mma<NT>(a1, x1, acc, [](int) {});
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no load may still be on its way to LDS when the workgroup ends
+    }
+
+    // lane (j, g) holds D[8b + 4g + r][j] in register 4b + r: four consecutive weight rows of token row j
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (mtile[j] >= MT) continue;
+        const int m = mtile[j] * 32 + (lane & 31);
+        if (SWIGLU) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const int f = (ntile * NT + nt) * 16 + 8 * b + 4 * (lane >> 5);
+                    uint32_t hi[2], lo[2];
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        float v[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const float gt = acc[nt][j][4 * b + 2 * r + e], up = acc[nt][j][4 * (b + 2) + 2 * r + e];
+                            v[e] = gt / (1.f + expf(-gt)) * up;
+                        }
+                        split_pair(v[0], v[1], hi[r], lo[r]);
+                    }
+                    if (f < NR) {
+                        const size_t o = tiled_off(m, f, NR);       // four columns inside one 8-element group
+                        *reinterpret_cast<uint2*>(act_hi + o) = make_uint2(hi[0], hi[1]);
+                        *reinterpret_cast<uint2*>(act_lo + o) = make_uint2(lo[0], lo[1]);
+                    }
+                }
+        } else {
+            float* prow = P + sp * s_stride + (size_t)m * n_stride;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int n = (ntile * NT + nt) * 32 + 8 * b + 4 * (lane >> 5);
+                    if (n < NR) *(float4*)(prow + n) = make_float4(acc[nt][j][4 * b], acc[nt][j][4 * b + 1], acc[nt][j][4 * b + 2], acc[nt][j][4 * b + 3]);
+                }
+        }
     }
 }
 
@@ -913,21 +1168,6 @@ __device__ __forceinline__ void attn_stage_k(const uint4 (&kh)[8], const uint4 (
         kt[attn_k_slot(4 * q + r0, c)] = kh[q];
         kt[512 + attn_k_slot(4 * q + r0, c)] = kl[q];
     }
-}
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// two fp32 -> two bf16 (round to nearest even) in one 32-bit word, first value in the low half (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint32_t pack_bf16x2(float x, float y) {
-    const f32x2 v = {x, y};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// hi = bf16(p), lo = bf16(p - hi) for a pair of values
-__device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) {
-    hi = pack_bf16x2(x, y);
-    lo = pack_bf16x2(x - __uint_as_float(hi << 16), y - __uint_as_float(hi & 0xffff0000u));
 }
 
 // The per-tile arithmetic outside the matrix cores is what bounds this kernel (a wave is alone on its SIMD and every
@@ -1499,9 +1739,18 @@ constexpr int ATTN_LDS_BYTES = 4 * 1024 * 16;       // k_chunk_attn: per wave on
 
 static size_t gemm_lds_bytes(int MT) { return (size_t)(2048 + 2 * MT * 2 * 512) * 16; }
 constexpr int GEMM_WIDE_LDS_BYTES = 2 * 2048 * 16;  // k_chunk_gemm_wide: two buffers of one 128 x 128 weight block
-// 256-row workgroups of the wide product: four waves with two row tiles each (eight waves with one tile each, two
-// per SIMD, measure 2-4 % slower: the loop is bound by operand delivery and power, not by latency)
-constexpr int WIDE_NW = 4, WIDE_MW = 2;
+template <bool SWIGLU>
+static const void* big_func(int nt) {
+    switch (nt) {
+        case 4: return (const void*)(k_chunk_gemm_big<4, SWIGLU>);
+        case 5: return (const void*)(k_chunk_gemm_big<5, SWIGLU>);
+        case 6: return (const void*)(k_chunk_gemm_big<6, SWIGLU>);
+        case 7: return (const void*)(k_chunk_gemm_big<7, SWIGLU>);
+        case 8: return (const void*)(k_chunk_gemm_big<8, SWIGLU>);
+        default: return nullptr;
+    }
+}
+static int big_lds_bytes(int nt) { return 3 * (nt * 2048 + BIG_M * 4096); }
 
 hipError_t chunk_init() {
     hipError_t e;
@@ -1513,37 +1762,49 @@ hipError_t chunk_init() {
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<4, 1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<WIDE_NW, WIDE_MW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    for (int nt = 4; nt <= 8; ++nt) {
+        if ((e = hipFuncSetAttribute(big_func<false>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
+        if ((e = hipFuncSetAttribute(big_func<true>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
+    }
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<4, 1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<WIDE_NW, WIDE_MW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     return hipSuccess;
 }
 
+template <bool SWIGLU>
+static hipError_t launch_big(const bf16_t* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, float* part, int S, int nt, int MT,
+                             bf16_t* act_hi, bf16_t* act_lo, hipStream_t s) {
+    const void* f = big_func<SWIGLU>(nt);
+    if (!f || K % 128 || K / 128 < S) return hipErrorInvalidValue;
+    const int per = nt * (SWIGLU ? 16 : 32), rows = SWIGLU ? N / 2 : N, MY = (MT + BIG_M - 1) / BIG_M;
+    int ntiles = (rows + per - 1) / per, n_stride = N;
+    size_t ps = (size_t)MT * 32 * N;
+    void* params[] = {&W, &N, &K, &xhi, &xlo, &part, &ps, &n_stride, &S, &MT, &ntiles, &act_hi, &act_lo};
+    return hipLaunchKernel(f, dim3((unsigned)ntiles * MY * S), dim3(256), params, big_lds_bytes(nt), s);
+}
+
 hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                             int S, int MT, hipStream_t s) {
+                             GemmPlan pl, int MT, hipStream_t s) {
+    const int S = pl.s;
     const dim3 grid(N / 128, S), block(256);
     const size_t ps = (size_t)MT * 32 * N, lds = gemm_lds_bytes(MT);
     if (S < 1 || S > CHUNK_GEMM_MAX_SPLIT || S > K / 128 || N % 128 || K % 128 || ps * S > c.part_capacity) return hipErrorInvalidValue;
     if (MT < 1 || MT > CHUNK_MAX / 32) return hipErrorInvalidValue;
     // one row tile: weight-streaming kernel, a wave per 32 weight rows; two: the waves split the k-steps; three or four:
-    // a wave per row tile (128-row workgroups); more: 256-row workgroups
+    // a wave per row tile (128-row workgroups); more: 256-row workgroups with pl.nt weight-row tiles
     if (MT == 1) {
         hipLaunchKernelGGL((k_chunk_gemm<1, false>), grid, block, lds, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr, 0);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, false>), grid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr);
-    } else {
-        const int MY = MT <= 4 ? 1 : (MT + 7) / 8;
-        const dim3 wgrid((unsigned)(N / 128) * MY * S);
-        if (MT <= 4) hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, false>), wgrid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
-        else hipLaunchKernelGGL((k_chunk_gemm_wide<WIDE_NW, WIDE_MW, false>), wgrid, dim3(WIDE_NW * 64), GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
-    }
+    } else if (MT <= 4) {
+        hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, false>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
+    } else return launch_big<false>((const bf16_t*)W, N, K, xhi, xlo, c.part, S, pl.nt, MT, nullptr, nullptr, s);
     return hipGetLastError();
 }
 
 // Gate/up product with the SwiGLU in its epilogue (no split-K): W = [gate rows | up rows] (2F x K), result in
 // c.act_hi / c.act_lo.
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                                    int MT, hipStream_t s) {
+                                    GemmPlan pl, int MT, hipStream_t s) {
     if (MT < 1 || MT > CHUNK_MAX / 32 || F < 1 || K % 128 || (MT > 1 && F % 64)) return hipErrorInvalidValue;
     const bf16_t* Wb = (const bf16_t*)W;
     if (MT == 1) {
@@ -1559,12 +1820,9 @@ hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* x
         hipLaunchKernelGGL((k_chunk_gemm<1, true>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(1), s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, rp);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo);
-    } else {
-        const int MY = MT <= 4 ? 1 : (MT + 7) / 8;
-        const dim3 wgrid((unsigned)(F / 64) * MY);
-        if (MT <= 4) hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, true>), wgrid, dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
-        else hipLaunchKernelGGL((k_chunk_gemm_wide<WIDE_NW, WIDE_MW, true>), wgrid, dim3(WIDE_NW * 64), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
-    }
+    } else if (MT <= 4) {
+        hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, true>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
+    } else return launch_big<true>(Wb, 2 * F, K, xhi, xlo, nullptr, 1, pl.nt, MT, c.act_hi, c.act_lo, s);
     return hipGetLastError();
 }
 

@@ -31,8 +31,11 @@ struct DecodeBuffers {
     unsigned* pipe_abort;     // give-up word of the two-stream step (see PipeSync)
 };
 
-constexpr int CHUNK_MAX = 512;         // rows per forward pass of the append-chunk path
-constexpr int CHUNK_MAX_TASKS = 128;   // attention tiles (32 query columns of one group) per pass
+constexpr int CHUNK_MAX = 2048;        // rows per forward pass of the append-chunk path (one sequence; see asynclm_ctx::pass_rows)
+constexpr int CHUNK_MAX_TASKS = 512;   // attention tiles (32 query columns of one group) per pass
+constexpr int CHUNK_MAX_GROUPS = 128;
+// a batched step fills passes of at most this many rows and tiles
+constexpr int CHUNK_BATCH_ROWS = 512, CHUNK_BATCH_TASKS = 128;
 constexpr int CHUNK_ATTN_MAX_SPLIT = 128;
 constexpr int CHUNK_ATTN_MAX_UNITS = 4096;   // (task, kv head, key split) partial results per pass
 constexpr int CHUNK_GEMM_MAX_SPLIT = 8;
@@ -48,30 +51,30 @@ struct ChunkGroup {
     int32_t pad0, pad1;
 };
 struct ChunkTask { int32_t seq, row0, n, pos0, tile, pad0, pad1, pad2; };         // query columns 32 tile .. 32 tile + 31 of a group
-// Every group has at least one task, so a pass holds at most CHUNK_MAX_TASKS groups.  The rows come last: a
+// Every group has at least one task, so a batched pass holds at most CHUNK_MAX_GROUPS groups.  The rows come last: a
 // pass uploads the table up to its last used row.
 struct ChunkTaskBlock { int32_t task0, n; };   // up to four consecutive tasks of one group (they share keys and values)
 struct ChunkTable {
     int32_t rows, ngroups, ntasks, nhead;
     int32_t nblocks, pad0, pad1, pad2;
-    ChunkGroup group[CHUNK_MAX_TASKS];
+    ChunkGroup group[CHUNK_MAX_GROUPS];
     ChunkTask task[CHUNK_MAX_TASKS];
-    ChunkTaskBlock block[CHUNK_MAX_TASKS];
+    ChunkTaskBlock block[CHUNK_MAX_GROUPS];     // at most four tasks each: as many as groups in a batched pass, tasks / 4 for one group
     ChunkRow row[CHUNK_MAX];
 };
 
 // Device buffers of the append-chunk path (bf16 models).  "hi/lo" are the two bf16 planes of a value.
 struct ChunkBuffers {
     ChunkTable* tab;
-    int32_t* chosen;          // [CHUNK_MAX] token chosen for the first row of each group
-    float* x;                 // [CHUNK_MAX][d] residual stream
-    // inputs of the products, CHUNK_MAX rows each, stored in matrix-core operand order (tiled planes)
+    int32_t* chosen;          // [CHUNK_MAX_GROUPS] token chosen for the first row of each group
+    float* x;                 // [pass rows][d] residual stream
+    // inputs of the products, as many rows each, stored in matrix-core operand order (tiled planes)
     bf16_t *nrm_hi, *nrm_lo;  // d columns:     normalised input of the QKV, gate/up and output-head products
     bf16_t *att_hi, *att_lo;  // Hq*dh columns: attention output
     bf16_t *act_hi, *act_lo;  // F columns:     SwiGLU output
     // rotated, scaled queries [Hkv][q_cols][dh]: the columns of a group are [q head within the kv group][row]
     bf16_t *q_hi, *q_lo;
-    int q_cols;               // G * CHUNK_MAX + 32 (a tile may read up to 31 columns past its group)
+    int q_cols;               // G * pass rows + 32 (a tile may read up to 31 columns past its group)
     float* part;              // split-K partial planes of the current product
     size_t part_capacity;     // floats in `part`
     float* attn_o;            // [unit][dh][32]      unit = (task * Hkv + kv head) * nsplit + split
@@ -150,10 +153,13 @@ hipError_t launch_chunk_logits(const ChunkBuffers& c, int MT_head, float* logits
 hipError_t launch_chunk_swiglu(const ChunkBuffers& c, int S, int MT, int rows, const Geom& g, hipStream_t s);
 hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, const DecodeBuffers& b, int rows, int MT,
                                 const Geom& g, hipStream_t s);
+// How a product of the append path is cut: split of K into s parts with partial planes of their own, nt weight-row tiles of 32
+// per workgroup (passes of more than four row tiles only).
+struct GemmPlan { int s, nt; };
 hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                             int S, int MT, hipStream_t s);
+                             GemmPlan pl, int MT, hipStream_t s);
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                                    int MT, hipStream_t s);
+                                    GemmPlan pl, int MT, hipStream_t s);
 hipError_t launch_chunk_attn(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, const Geom& g, hipStream_t s);
 hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, int nblocks, const Geom& g,
                                   hipStream_t s);

@@ -1,0 +1,85 @@
+"""GPU: passes of more than 128 rows (large matrix-core product, up to 2048 rows per pass) against passes of 32 rows on the
+same model.  What is compared is the whole cache image of every row, not only the last row's logits: the second layer's
+keys and values depend on every product of the first."""
+
+import numpy as np
+import pytest
+import torch
+
+import asynclm_inputs as ai
+from asynclm_inputs.configs import ModelConfig
+
+pytestmark = pytest.mark.gpu
+
+HEADER = 56                 # bytes of the image's description
+# Both sides carry inputs of products as two bf16 (relative error 2^-17 each) and add in fp32; a second-layer key sees five
+# products in a row: 5 * 2^-16 = 7.6e-5 of its norm.
+TOL = 1e-4
+
+
+def _planes(lm, model, n):
+    """Keys [layer, head, position, channel] and values [layer, head, tile, ...] of sequence 0, hi + lo."""
+    size = lm.kv_bytes(0)
+    buf = torch.empty(size, dtype=torch.uint8, pin_memory=True)
+    lm.kv_swap_out(0, buf.data_ptr(), size)
+    L, H, dh = model.n_layers, model.n_kv_heads, model.head_dim
+    k, v = H * n * dh, H * ((n + 31) // 32 * 32) * dh
+    assert size == HEADER + L * 2 * (k + v) * 2 + model.vocab * 4
+    raw = torch.frombuffer(buf.numpy(), dtype=torch.uint8, offset=HEADER, count=L * 2 * (k + v) * 2).view(torch.bfloat16)
+    raw = raw.to(torch.float32).view(L, 2 * (k + v))
+    keys = (raw[:, :k] + raw[:, k:2 * k]).view(L, H, n, dh)
+    vals = (raw[:, 2 * k:2 * k + v] + raw[:, 2 * k + v:]).view(L, H, -1, 32 * dh)
+    return keys.numpy(), vals.numpy()
+
+
+def _worst(a, b):
+    d = np.linalg.norm(a.astype(np.float64) - b, axis=-1)
+    return float((d / np.linalg.norm(b, axis=-1)).max())
+
+
+# F / 16 gate-up tiles against 32 per weight-row tile of a workgroup at eight row blocks: 2176 and 2432 take 5 (the last
+# tile part empty), 2816 6, 3200 7 (both part empty), 3712 8; 1024 the smallest; rows: edges of row tiles, of
+# 256-row blocks and of a pass
+@pytest.mark.parametrize("n,ffn,heads,kv", [(129, 1024, 4, 4), (257, 1024, 4, 1), (1024, 1024, 8, 1), (1801, 2176, 4, 2), (2047, 2432, 4, 2),
+                                            (2048, 2816, 4, 4), (1999, 3200, 4, 2), (2100, 3712, 4, 2)])
+def test_large_passes_equal_passes_of_32_rows(n, ffn, heads, kv):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=512, n_q_heads=heads, n_kv_heads=kv, head_dim=128, ffn=ffn, vocab=1024, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 941, n, model.vocab)
+    got = []
+    for chunk in (None, 32):
+        lm = pkg.AsyncLM(model, w, max_positions=n + 8, stream=torch.cuda.Stream())
+        if chunk:
+            lm.set_option("chunk", chunk)
+        lm.prefill(0, toks)
+        got.append((*_planes(lm, model, n), lm.logits(0)))
+        lm.close()
+    (ka, va, la), (kb, vb, lb) = got
+    assert np.isfinite(ka).all() and np.isfinite(va).all() and np.isfinite(la).all()
+    assert _worst(ka, kb) <= TOL, _worst(ka, kb)
+    tail = n % 32                                        # a last tile of values that is part empty: compare as a whole
+    assert _worst(va, vb) <= TOL, (_worst(va, vb), tail)
+    assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
+
+
+def test_pass_size_option_still_bounds_a_pass():
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 942, 1100, model.vocab)
+    out = []
+    for chunk in (None, 512):
+        lm = pkg.AsyncLM(model, w, max_positions=1200, stream=torch.cuda.Stream())
+        if chunk:
+            lm.set_option("chunk", chunk)
+        with pytest.raises(pkg.AsyncLMError):
+            lm.set_option("chunk", 513)
+        lm.prefill(0, toks)
+        out.append(lm.logits(0))
+        lm.close()
+    assert np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1]) <= TOL
