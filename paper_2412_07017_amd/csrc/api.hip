@@ -32,8 +32,8 @@ struct PassBuilder {
         for (int r = 0; r < n; ++r) {
             ChunkRow& R = t.row[row0 + r];
             R = ChunkRow{};
-            R.token = forced == -2 ? rest[r] : (r == 0 ? 0 : rest[r - 1]);
-            R.seq = seq; R.pos = pos0 + r; R.row0 = row0; R.n = n;
+            R.token = forced == -2 ? rest[r] : (r == 0 ? forced : rest[r - 1]);      // -1: chosen on the device
+            R.seq = seq; R.pos = pos0 + r; R.row0 = row0; R.n = n; R.group = r == 0 && forced != -2 ? t.ngroups : -1;
         }
         ChunkGroup& Gp = t.group[t.ngroups++];
         Gp = ChunkGroup{};
@@ -100,7 +100,7 @@ struct asynclm_ctx {
     int32_t* chosen_host = nullptr;     // pinned, CHUNK_MAX_GROUPS ints
     // pinned staging of what the host uploads on the hot path (a pageable source would make the copy wait for the
     // stream): two copies of the row table and a small ring of ban-list rows, each reused once its event has passed
-    ChunkTable* tab_host[2] = {nullptr, nullptr};
+    unsigned char* tab_host[2] = {nullptr, nullptr};
     hipEvent_t tab_ev[2] = {nullptr, nullptr};
     int tab_next = 0;
     static constexpr int BAN_RING = 4;
@@ -523,11 +523,32 @@ int pick_chunk_attn_split(const asynclm_ctx* c, int max_keys, int ntasks) {
     return n;
 }
 
+// Layer `l` and the output head for one row of a pass, x its residual stream, whose position and sequence are in the step
+// descriptor: the kernels of a decoding step.
+hipError_t last_row_layer(asynclm_ctx* c, int l, float* x, int len_after) {
+    const int dt = c->cfg.dtype;
+    const Geom& g = c->g;
+    hipStream_t s = c->stream;
+    const SplitPlan sp = pick_nsplit(c, len_after);
+    void* kvl = kv_layer_ptr(c, l);
+    DecodeBuffers b = c->b;
+    b.x = x;
+    hipError_t e;
+    if ((e = run(c, KC_QKV, [&] { return launch_qkv(dt, c->wqkv[l], c->attn_norm[l], kvl, b, g, s); }))) return e;
+    if (sp.mfma) { if ((e = run(c, KC_ATTN, [&] { return launch_decode_attn_mfma(c->cb, kvl, sp.nsplit, b, g, s); }))) return e; }
+    else if ((e = run(c, KC_ATTN, [&] { return launch_attn_decode(dt, kvl, sp.nsplit, sp.merge_in_oproj, b, g, s); }))) return e;
+    if ((e = run(c, KC_OPROJ, [&] { return launch_oproj(dt, c->wo[l], sp.merge_in_oproj ? sp.nsplit : 0, b, g, s); }))) return e;
+    if ((e = run(c, KC_GATEUP, [&] { return launch_gateup(dt, c->wgate_up[l], c->ffn_norm[l], b, g, s); }))) return e;
+    if ((e = run(c, KC_DOWN, [&] { return launch_down(dt, c->wdown[l], b, g, s); }))) return e;
+    if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); }))) return e;
+    return run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, b, g, s); });
+}
+
 // One forward pass over the rows of `pb` (1..pass_rows rows in any number of groups).  Groups that want logits
 // get them from the single-row head kernels (one group) or from one more product on the matrix cores (several).
 hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     const Geom& g = c->g;
-    const ChunkBuffers& cb = c->cb;
+    ChunkBuffers& cb = c->cb;
     hipStream_t s = c->stream;
     const ChunkTable& t = pb.t;
     const int rows = t.rows, MT = (rows + 31) / 32;
@@ -548,18 +569,39 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     hipError_t e;
     {   // through pinned memory: the copy is asynchronous and the host goes on enqueuing the pass
         const int i = c->tab_next;
-        const size_t bytes = offsetof(ChunkTable, row) + sizeof(ChunkRow) * rows;
         if ((e = hipEventSynchronize(c->tab_ev[i]))) return e;         // the upload that last used this copy has finished
-        std::memcpy(c->tab_host[i], &t, bytes);
-        if ((e = hipMemcpyAsync(cb.tab, c->tab_host[i], bytes, hipMemcpyHostToDevice, s))) return e;
+        size_t bytes = 0;
+        auto put = [&](const void* src, size_t n) {
+            const size_t at = bytes;
+            std::memcpy(c->tab_host[i] + at, src, n);
+            bytes += (n + 31) / 32 * 32;
+            return cb.tab_mem + at;
+        };
+        cb.tab.group = (const ChunkGroup*)put(t.group, sizeof(ChunkGroup) * t.ngroups);
+        cb.tab.task = (const ChunkTask*)put(t.task, sizeof(ChunkTask) * t.ntasks);
+        cb.tab.block = (const ChunkTaskBlock*)put(t.block, sizeof(ChunkTaskBlock) * t.nblocks);
+        cb.tab.row = (const ChunkRow*)put(t.row, sizeof(ChunkRow) * t.rows);
+        if ((e = hipMemcpyAsync(cb.tab_mem, c->tab_host[i], bytes, hipMemcpyHostToDevice, s))) return e;
         if ((e = hipEventRecord(c->tab_ev[i], s))) return e;
         c->tab_next = i ^ 1;
     }
-    if ((e = run(c, KC_BEGIN, [&] { return launch_begin_chunk(cb, c->b, t.ngroups, s); }))) return e;
-    if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_embed(c->embed, cb, rows, g, s); }))) return e;
+    // A pass over one sequence: after the last layer's keys and values nothing but its last row is needed any more, so that
+    // row finishes the pass through the single-row kernels (fp32 activations; its own key and value are formed once more
+    // there), and a pass that wants no logits ends with the keys and values.  One layer of n: 3 % of a prompt's time at 32
+    // layers.  Several sequences (a batched step: few rows) stay together to the end.
+    const bool tail = t.ngroups == 1;
+    const GemmPlan kv_plan = pick_gemm_plan(c, 2 * g.Hkv * g.dh, g.d, MT);
     for (int l = 0; l < c->cfg.n_layers; ++l) {
         void* kvl = kv_layer_ptr(c, l);
-        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, l > 0, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
+        if (l == 0) { if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_embed_norm(c->embed, cb, c->attn_norm[0], rows, c->b, g, s); }))) return e; }
+        else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, true, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
+        if (tail && l == c->cfg.n_layers - 1) {
+            const char* wkv = (const char*)c->wqkv[l] + (size_t)qd * g.d * elem_bytes(c);
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(wkv, 2 * g.Hkv * g.dh, g.d, cb.nrm_hi, cb.nrm_lo, cb, kv_plan, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, kv_plan.s, kvl, c->b, rows, MT, g, s, true); }))) return e;
+            if (t.nhead > 0 && (e = last_row_layer(c, l, cb.x + (size_t)(rows - 1) * g.d, pb.max_keys))) return e;
+            break;
+        }
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.qkv, MT, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, sp.qkv.s, kvl, c->b, rows, MT, g, s); }))) return e;
         if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, wsplit, t.ntasks, t.nblocks, g, s); }))) return e; }
@@ -580,7 +622,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
         if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_head_rows(cb, sp.down.s, MT, c->final_norm, t.ngroups, g, s); }))) return e;
         if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, GemmPlan{1, 4}, MTh, s); }))) return e;
         if ((e = run(c, KC_ARGMAX, [&] { return launch_chunk_logits(cb, MTh, c->logits, c->b, t.ngroups, g, s); }))) return e;
-    } else {
+    } else if (!tail) {
         for (int gi = 0; gi < t.ngroups; ++gi) {
             if (t.group[gi].head < 0) continue;
             const int seq = t.group[gi].seq;
@@ -768,7 +810,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         cb.q_cols = (g.Hq / g.Hkv) * c->pass_rows + 32;
         const size_t qn = (size_t)g.Hkv * cb.q_cols * g.dh;
         c->pass.G = g.Hq / g.Hkv; c->pass.Hkv = g.Hkv;
-        ALLOC(cb.tab, 1);
+        ALLOC(cb.tab_mem, CHUNK_TAB_BYTES);
         ALLOC(cb.chosen, (size_t)CHUNK_MAX_GROUPS);
         ALLOC(cb.x, M * g.d);
         ALLOC(cb.nrm_hi, M * g.d); ALLOC(cb.nrm_lo, M * g.d);
@@ -779,7 +821,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         ALLOC(cb.attn_o, (size_t)CHUNK_ATTN_MAX_UNITS * g.dh * 32);
         ALLOC(cb.attn_ml, (size_t)CHUNK_ATTN_MAX_UNITS * 64);
         // rows beyond the current chunk are multiplied into discarded columns only, but must stay finite
-        if (hipMemset(cb.tab, 0, sizeof(ChunkTable)) || hipMemset(cb.chosen, 0, CHUNK_MAX_GROUPS * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
+        if (hipMemset(cb.chosen, 0, CHUNK_MAX_GROUPS * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
             hipMemset(cb.nrm_lo, 0, M * g.d * 2) || hipMemset(cb.att_hi, 0, M * qd * 2) || hipMemset(cb.att_lo, 0, M * qd * 2) ||
             hipMemset(cb.act_hi, 0, M * g.F * 2) || hipMemset(cb.act_lo, 0, M * g.F * 2) || hipMemset(cb.q_hi, 0, qn * 2) ||
             hipMemset(cb.q_lo, 0, qn * 2))
@@ -839,7 +881,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
     }
     if (hipHostMalloc((void**)&c->chosen_host, sizeof(int32_t) * CHUNK_MAX_GROUPS, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
     for (int i = 0; i < 2; ++i)
-        if (hipHostMalloc((void**)&c->tab_host[i], sizeof(ChunkTable), hipHostMallocDefault) != hipSuccess ||
+        if (hipHostMalloc((void**)&c->tab_host[i], CHUNK_TAB_BYTES, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&c->tab_ev[i], hipEventDisableTiming) != hipSuccess)
             return bail(ASYNCLM_E_NOMEM);
     if (hipHostMalloc((void**)&c->ban_host, sizeof(int32_t) * asynclm_ctx::BAN_RING * (1 + BAN_MAX), hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);

@@ -42,8 +42,10 @@ constexpr int CHUNK_GEMM_MAX_SPLIT = 8;
 
 // What one pass of the append-chunk path processes: rows, grouped by sequence.  A group is a run of
 // consecutive rows appended to one sequence: [chosen token] ++ [interrupt tokens], or plain tokens.
-// The host fills the table; k_begin_chunk resolves the tokens that are chosen on the device.
-struct ChunkRow { int32_t token, seq, pos, row0, n, pad0, pad1, pad2; };          // row0, n: its group
+// The host fills the table; k_chunk_embed_norm resolves the tokens that are chosen on the device.
+// row0, n: its group; token < 0 (first row of a group only): the greedy token of the sequence's current logits;
+// group: number of the group whose chosen token this row carries, -1 for the other rows
+struct ChunkRow { int32_t token, seq, pos, row0, n, group, pad1, pad2; };
 struct ChunkGroup {
     int32_t seq, row0, n, pos0;
     int32_t forced;     // first row: >= 0 this token, -1 greedy argmax of the sequence's logits, -2 already in the row table
@@ -51,21 +53,25 @@ struct ChunkGroup {
     int32_t pad0, pad1;
 };
 struct ChunkTask { int32_t seq, row0, n, pos0, tile, pad0, pad1, pad2; };         // query columns 32 tile .. 32 tile + 31 of a group
-// Every group has at least one task, so a batched pass holds at most CHUNK_MAX_GROUPS groups.  The rows come last: a
-// pass uploads the table up to its last used row.
+// Every group has at least one task, so a batched pass holds at most CHUNK_MAX_GROUPS groups.  A pass uploads the used
+// entries only, packed one after the other (ChunkTab): under 1 KB for an interrupt.
 struct ChunkTaskBlock { int32_t task0, n; };   // up to four consecutive tasks of one group (they share keys and values)
 struct ChunkTable {
-    int32_t rows, ngroups, ntasks, nhead;
-    int32_t nblocks, pad0, pad1, pad2;
+    int32_t rows, ngroups, ntasks, nhead, nblocks;
     ChunkGroup group[CHUNK_MAX_GROUPS];
     ChunkTask task[CHUNK_MAX_TASKS];
     ChunkTaskBlock block[CHUNK_MAX_GROUPS];     // at most four tasks each: as many as groups in a batched pass, tasks / 4 for one group
     ChunkRow row[CHUNK_MAX];
 };
 
+struct ChunkTab { const ChunkGroup* group; const ChunkTask* task; const ChunkTaskBlock* block; const ChunkRow* row; };
+constexpr size_t CHUNK_TAB_BYTES = sizeof(ChunkGroup) * CHUNK_MAX_GROUPS + sizeof(ChunkTask) * CHUNK_MAX_TASKS +
+                                   (sizeof(ChunkTaskBlock) * CHUNK_MAX_GROUPS + 31) / 32 * 32 + sizeof(ChunkRow) * CHUNK_MAX;
+
 // Device buffers of the append-chunk path (bf16 models).  "hi/lo" are the two bf16 planes of a value.
 struct ChunkBuffers {
-    ChunkTable* tab;
+    unsigned char* tab_mem;   // [CHUNK_TAB_BYTES]
+    ChunkTab tab;             // the running pass's entries in it
     int32_t* chosen;          // [CHUNK_MAX_GROUPS] token chosen for the first row of each group
     float* x;                 // [pass rows][d] residual stream
     // inputs of the products, as many rows each, stored in matrix-core operand order (tiled planes)
@@ -137,8 +143,8 @@ hipError_t decode_init(int dtype, int max_k);
 void decode_set_gemv_grid(int grid);
 int decode_gemv_grid();
 hipError_t chunk_init();
-hipError_t launch_begin_chunk(const ChunkBuffers& c, const DecodeBuffers& b, int ngroups, hipStream_t s);
-hipError_t launch_chunk_embed(const void* E, const ChunkBuffers& c, int rows, const Geom& g, hipStream_t s);
+hipError_t launch_chunk_embed_norm(const void* E, const ChunkBuffers& c, const float* gain, int rows, const DecodeBuffers& b, const Geom& g,
+                                   hipStream_t s);
 hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, bool add_partials, int S, int MT, const float* gain, int rows,
                                    const Geom& g, hipStream_t s);
 // residual stream of the last row of group `group` -> the single-row path's x (and its sequence -> the step descriptor)
@@ -151,8 +157,9 @@ hipError_t launch_chunk_head_rows(const ChunkBuffers& c, int S, int MT, const fl
 hipError_t launch_chunk_logits(const ChunkBuffers& c, int MT_head, float* logits_base, const DecodeBuffers& b, int ngroups,
                                const Geom& g, hipStream_t s);
 hipError_t launch_chunk_swiglu(const ChunkBuffers& c, int S, int MT, int rows, const Geom& g, hipStream_t s);
+// kv_only: the product held the key and value rows only
 hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, const DecodeBuffers& b, int rows, int MT,
-                                const Geom& g, hipStream_t s);
+                                const Geom& g, hipStream_t s, bool kv_only = false);
 // How a product of the append path is cut: split of K into s parts with partial planes of their own, nt weight-row tiles of 32
 // per workgroup (passes of more than four row tiles only).
 struct GemmPlan { int s, nt; };
