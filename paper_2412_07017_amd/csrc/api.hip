@@ -555,13 +555,18 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     const ChunkPlans sp = chunk_plans(c, MT);
     const int nqkv = (g.Hq + 2 * g.Hkv) * g.dh, qd = g.Hq * g.dh;
     const int asplit = pick_chunk_attn_split(c, pb.max_keys, t.ntasks);
-    // passes made of large groups (at least 16 tasks, three or more per block on average) share keys and values
-    // between the tasks of a block; their key splits: about two workgroups per compute unit, at least four tiles each
-    const bool wide_attn = t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks;
+    // Four waves on one tile of keys (k_chunk_attn_wide) or a wave of its own for every task and split (k_chunk_attn): the
+    // first loads a tile once for up to four tasks and issues its loads from four waves, the second starts sooner and runs
+    // more waves of small work.  8B shape, 4 layers, whole pass: 24 rows (3 tasks) into 1.1k 668 (wide) against 664 us, 2.1k
+    // 685 / 679, 4.2k 707 / 723, 16.4k 786 / 810; 48 rows (6 tasks) into 1.1k 748 / 753, 2.1k 746 / 767, 16.4k 890 / 940.
+    // Batched steps of mostly single rows: 4 sequences of up to 1k 795 / 784, 16 of up to 4.2k 1217 / 1243.
+    // Key splits of the first: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
+    // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).
+    const bool wide_attn = pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
     int wsplit = 1;
     if (wide_attn) {
         const long long wgs = (long long)t.nblocks * g.Hkv;
-        wsplit = (int)std::max(1LL, std::min<long long>((2LL * c->n_cu + wgs - 1) / wgs, ((pb.max_keys + 31) / 32 + 3) / 4));
+        wsplit = (int)std::max(1LL, std::min<long long>((2LL * c->n_cu + wgs - 1) / wgs, ((pb.max_keys + 31) / 32 + 1) / 2));
         wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
         while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
     }

@@ -1151,6 +1151,7 @@ struct ChunkAttnArgs {
     ChunkTab tab;
     float* part_o;      // [unit][128][32]
     float* part_ml;     // [unit][2][32]
+    bf16_t* out_hi; bf16_t* out_lo;             // tiled planes (one split: no merge)
     int32_t nsplit, q_cols;
 };
 
@@ -1495,42 +1496,127 @@ __global__ __launch_bounds__(256) void k_decode_attn_merge(DecodeAttnArgs a, Geo
 // the same attention for large groups (prefill, long interrupts): keys and values shared by four tasks
 // ---------------------------------------------------------------------------------------------
 // Workgroup = (block of up to four consecutive tasks of one group, kv head, key split); wave w works on task w of
-// the block (128 query columns per workgroup).  The K and V^T tiles of 32 keys (both planes, 32 KiB) are loaded once
-// per workgroup, 8 x 16 bytes per thread, into a double-buffered LDS tile while the previous tile is multiplied:
-// K in the swizzled row layout of attn_stage_k, V^T verbatim (it is stored in operand order), and all four waves
-// read their operands from there.  Against one wave per task this divides the traffic from L2 by four, which is
-// what bounds a 512-row pass over a long context.  Partial results go to the same units as k_chunk_attn writes, so
-// k_chunk_attn_combine serves both.
+// the block (128 query columns per workgroup).  The K and V^T tiles of 32 keys (both planes, 32 KiB) go from global memory
+// straight to a double-buffered LDS tile (16 bytes per lane and load, eight loads per wave, issued between the products of
+// the tile before): K in the swizzled row layout of attn_k_slot, V^T verbatim (it is stored in operand order).  All four
+// waves read their operands from there, a quarter of the traffic from L2 of one wave per task.
+// What bounds it: products and softmax alternate in a wave, so one wave per SIMD leaves the matrix cores idle during the
+// softmax and behind every LDS read.  The kernel is kept to 256 registers (values are read from LDS when they are used,
+// the next tile needs no registers), so that two workgroups share a compute unit and one multiplies while the other
+// does its softmax.  2048 rows over 8k keys on average (16k prompt of the 8B shape): 1190 -> 735 us a layer and pass =
+// 1.12 PFLOP/s counted with the three hi/lo products; 48 rows into 16.4k keys 66 -> 51 us against a wave per task.
 
-struct WideTileRegs { uint4 k[4], v[4]; };   // this thread's share of a tile: K hi, hi, lo, lo; V^T hi, hi, lo, lo
+// Where a wave's eight loads of a tile come from: four of the 16 KiB of K (4 rows each) and four of the 16 of V^T.  LDS in
+// 16-byte chunks: K hi [0, 512), K lo [512, 1024), V^T hi [1024, 1536), V^T lo [1536, 2048).
+struct WideSrc {
+    const bf16_t* k; const bf16_t* v;       // this wave's plane of K and V^T (waves 0, 1: hi, waves 2, 3: lo)
+    uint32_t koff[4], voff;                 // the lane's elements within a tile
+    int slot;                               // first LDS chunk of the wave's K loads
+};
+__device__ __forceinline__ void attn_wide_load(uint4* buf, const WideSrc& w, int tile, int j) {
+    const bf16_t* src = j < 4 ? w.k + (size_t)tile * 4096 + w.koff[j & 3] : w.v + (size_t)tile * 4096 + w.voff + (j & 3) * 512;
+    __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)(buf + w.slot + (j < 4 ? 0 : 1024) + (j & 3) * 64), 16, 0, 0);
+}
 
-__device__ __forceinline__ void attn_wide_load(WideTileRegs& r, const bf16_t* Kp, const bf16_t* Vt, size_t lo, int tile, int tid) {
-    // K: chunk c = tid + 256 h is row c / 16, 16-byte piece c % 16 of the tile; V^T: chunk c of the tile's contiguous 8 KiB
-    const bf16_t* kp = Kp + (size_t)tile * 32 * 128 + (size_t)tid * 8;
-    const bf16_t* vp = Vt + ((size_t)tile * 512 + tid) * 8;
+// One tile: multiplies the tile in `rd` (if `work`) and requests tile `next` into `wr`.  The buffers never meet, see big_block.
+__device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __restrict__ rd, uint4* __restrict__ wr, const WideSrc& w, int next,
+                                               const u32x4 (&qh)[8], const u32x4 (&ql)[8], int key0, int qpos, bool work, int lane) {
+    if (!work) {                                                    // uniform over the wave
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        r.k[h] = load16(kp + h * 2048); r.k[2 + h] = load16(kp + lo + h * 2048);
-        r.v[h] = load16(vp + h * 2048); r.v[2 + h] = load16(vp + lo + h * 2048);
+        for (int j = 0; j < 8; ++j) attn_wide_load(wr, w, next, j);
+        return;
+    }
+    const int i = lane & 31, gh = lane >> 5;
+    const int krow = (i >> 3) * 4 + (i & 3) + 16 * ((i >> 2) & 1);  // key (within the tile) held in A row i
+    int kbase = krow * 16, kx = attn_k_slot(krow, 0) & 15, vbase = 1024 + lane;
+    asm volatile("" : "+v"(kbase), "+v"(vbase));                    // the reads stay behind the barrier before this call
+    __builtin_amdgcn_sched_barrier(0);
+    const u32x4* kt = reinterpret_cast<const u32x4*>(rd);
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    auto kread = [&](int t, int pl) { return kt[pl * 512 + kbase + ((2 * t + gh) ^ kx)]; };
+    auto mma = [](const u32x4& a, const u32x4& b, const f32x16& c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    };
+    u32x4 kq[3][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { kq[j][0] = kread(j, 0); kq[j][1] = kread(j, 1); }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        if (t + 2 < 8) { kq[(t + 2) % 3][0] = kread(t + 2, 0); kq[(t + 2) % 3][1] = kread(t + 2, 1); }
+        __builtin_amdgcn_sched_barrier(0);
+        s = mma(kq[t % 3][0], qh[t], s);
+        attn_wide_load(wr, w, next, t);
+        __builtin_amdgcn_sched_barrier(0);
+        s = mma(kq[t % 3][1], qh[t], s);
+        s = mma(kq[t % 3][0], ql[t], s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    u32x4 v0[4];                                                    // the first values are on their way during the softmax
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) v0[dt] = kt[vbase + dt * 128];
+    __builtin_amdgcn_sched_barrier(0);
+    // register r of lane (j, g) is key key0 + 16 g + r for query column j
+    if (__builtin_amdgcn_ballot_w64(key0 + 31 > qpos) != 0) {       // the tile reaches past some column's position
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (key0 + 16 * gh + r > qpos) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mnew = fmaxf(st.mrun, mx);
+    const float msafe = mnew == -INFINITY ? 0.f : mnew;
+    constexpr float LOG2E = 1.44269504088896340736f;
+    const float corr = __builtin_amdgcn_exp2f((st.mrun - msafe) * LOG2E), mlog = -msafe * LOG2E;
+    float psum = 0.f;
+    uint32_t ph[8], pl[8];
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[r], LOG2E, mlog)), p1 = __builtin_amdgcn_exp2f(fmaf(s[r + 1], LOG2E, mlog));
+        psum += p0 + p1;
+        split_pair(p0, p1, ph[r >> 1], pl[r >> 1]);
+    }
+    st.lrun = st.lrun * corr + psum;
+    if (__builtin_amdgcn_ballot_w64(mnew != st.mrun) != 0) {        // some column's running maximum moved
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[dt][r] *= corr;
+    }
+    st.mrun = mnew;
+    __builtin_amdgcn_sched_barrier(0);
+    // V^T chunk (plane, dt, t) is KiB plane * 8 + dt * 2 + t of the values; the next group of four is read while one is multiplied
+    u32x4 v1[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const u32x4 pht = {ph[4 * t], ph[4 * t + 1], ph[4 * t + 2], ph[4 * t + 3]};
+        const u32x4 plt = {pl[4 * t], pl[4 * t + 1], pl[4 * t + 2], pl[4 * t + 3]};
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) v1[dt] = kt[vbase + 512 + dt * 128 + t * 64];        // lo plane
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) st.o[dt] = mma(v0[dt], pht, st.o[dt]);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) st.o[dt] = mma(v0[dt], plt, st.o[dt]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t == 0) {
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) v0[dt] = kt[vbase + dt * 128 + 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) st.o[dt] = mma(v1[dt], pht, st.o[dt]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// buffer layout (16-byte chunks): K hi [0, 512), K lo [512, 1024), V^T hi [1024, 1536), V^T lo [1536, 2048)
-__device__ __forceinline__ void attn_wide_store(const WideTileRegs& r, uint4* buf, int tid) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int row = (tid >> 4) + 16 * h, c = tid & 15;
-        buf[attn_k_slot(row, c)] = r.k[h];
-        buf[512 + attn_k_slot(row, c)] = r.k[2 + h];
-        buf[1024 + tid + 256 * h] = r.v[h];
-        buf[1536 + tid + 256 * h] = r.v[2 + h];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_chunk_attn_wide(ChunkAttnArgs a, Geom g) {
+__global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geom g) {
     constexpr int DH = 128;
     extern __shared__ uint4 attn_lds[];                    // [2 buffers][2048 chunks]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 31, gh = lane >> 5;
     const int G = g.Hq / g.Hkv;
     const int kvh = blockIdx.x % g.Hkv, split = blockIdx.y;
@@ -1548,9 +1634,17 @@ __global__ __launch_bounds__(256) void k_chunk_attn_wide(ChunkAttnArgs a, Geom g
     const int Lw = T.pos0 + min((32 * T.tile) % T.n + 32, T.n);
 
     const size_t seq_off = (size_t)T.seq * g.kv_seq_stride + (size_t)kvh * g.kv_head_stride;
-    const bf16_t* Kp = a.kv_layer + seq_off;
-    const bf16_t* Vt = a.kv_layer + g.kv_vt_offset + seq_off;
-    const size_t lo = g.kv_lo_offset;
+    WideSrc w;
+    {
+        const size_t lo = wave >= 2 ? g.kv_lo_offset : 0;
+        w.k = a.kv_layer + seq_off + lo; w.v = a.kv_layer + g.kv_vt_offset + seq_off + lo;
+        w.slot = wave * 256; w.voff = (wave & 1) * 2048 + lane * 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = ((wave & 1) * 4 + j) * 4 + (lane >> 4), c = (lane & 15) ^ (attn_k_slot(r, 0) & 15);
+            w.koff[j] = r * 128 + c * 8;
+        }
+    }
     const int col = 32 * T.tile + i;
     const int qpos = T.pos0 + col % T.n;
 
@@ -1562,35 +1656,47 @@ __global__ __launch_bounds__(256) void k_chunk_attn_wide(ChunkAttnArgs a, Geom g
     st.mrun = -INFINITY; st.lrun = 0.f;
 
     if (t0 < t1) {
-        uint4 qh[8], ql[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) attn_wide_load(attn_lds, w, t0, j);
+        u32x4 qh[8], ql[8];
         {
             const size_t qo = ((size_t)kvh * a.q_cols + (size_t)G * T.row0 + col) * DH + gh * 8;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) { qh[t] = load16(a.q_hi + qo + t * 16); ql[t] = load16(a.q_lo + qo + t * 16); }
-        }
-        WideTileRegs regs;
-        __builtin_amdgcn_sched_barrier(0);
-        attn_wide_load(regs, Kp, Vt, lo, t0, tid);
-        attn_wide_store(regs, attn_lds, tid);
-        __syncthreads();
-        for (int tile = t0; tile < t1; ++tile) {
-            uint4* buf = attn_lds + ((tile - t0) & 1) * 2048;
-            attn_wide_load(regs, Kp, Vt, lo, min(tile + 1, t1 - 1), tid);
-            __builtin_amdgcn_sched_barrier(0);
-            if (live && tile * 32 < Lw) {                   // uniform over the wave
-                uint4 vh[8], vl[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) { vh[k] = buf[1024 + k * 64 + lane]; vl[k] = buf[1536 + k * 64 + lane]; }
-                attn_tile(st, vh, vl, qh, ql, buf, tile * 32, qpos, lane);
+            for (int t = 0; t < 8; ++t) {
+                qh[t] = *(global_u32x4_ptr)(uintptr_t)(a.q_hi + qo + t * 16);
+                ql[t] = *(global_u32x4_ptr)(uintptr_t)(a.q_lo + qo + t * 16);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            attn_wide_store(regs, attn_lds + (((tile - t0) & 1) ^ 1) * 2048, tid);
-            __syncthreads();
         }
+        for (int tile = t0; tile < t1; ++tile) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's share of the tile has landed ...
+            __builtin_amdgcn_s_barrier();                           // ... and everybody's, and the other buffer has been read
+            __builtin_amdgcn_sched_barrier(0);
+            const int cur = (tile - t0) & 1;
+            attn_wide_tile(st, attn_lds + cur * 2048, attn_lds + (cur ^ 1) * 2048, w, min(tile + 1, t1 - 1), qh, ql, tile * 32, qpos,
+                           live && tile * 32 < Lw, lane);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // no load may still be on its way to LDS when the workgroup ends
     }
     st.lrun += __shfl_xor(st.lrun, 32, 64);
     if (!live) return;
 
+    if (a.nsplit == 1) {                                            // nothing to merge: the output goes straight to the tiled planes
+        if (col >= G * T.n) return;
+        const float inv = st.lrun > 0.f ? 1.f / st.lrun : 0.f;
+        const int gq = col / T.n, m = T.row0 + col - gq * T.n, hq = kvh * G + gq;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                uint32_t h0, l0, h1, l1;
+                split_pair(st.o[dt][4 * q4] * inv, st.o[dt][4 * q4 + 1] * inv, h0, l0);
+                split_pair(st.o[dt][4 * q4 + 2] * inv, st.o[dt][4 * q4 + 3] * inv, h1, l1);
+                const size_t o = tiled_off(m, hq * DH + dt * 32 + 8 * q4 + 4 * gh, g.Hq * DH);
+                *reinterpret_cast<uint2*>(a.out_hi + o) = make_uint2(h0, h1);
+                *reinterpret_cast<uint2*>(a.out_lo + o) = make_uint2(l0, l1);
+            }
+        return;
+    }
     const size_t unit = ((size_t)task * g.Hkv + kvh) * a.nsplit + split;
     float* po = a.part_o + unit * DH * 32;
 #pragma unroll
@@ -1869,9 +1975,10 @@ hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, i
     ChunkAttnArgs a{};
     a.q_hi = c.q_hi; a.q_lo = c.q_lo; a.kv_layer = (const bf16_t*)kv_layer; a.tab = c.tab;
     a.part_o = c.attn_o; a.part_ml = c.attn_ml; a.nsplit = nsplit; a.q_cols = c.q_cols;
+    a.out_hi = c.att_hi; a.out_lo = c.att_lo;
     hipLaunchKernelGGL(k_chunk_attn_wide, dim3(nblocks * g.Hkv, nsplit), dim3(256), ATTN_LDS_BYTES, s, a, g);
     hipError_t e = hipGetLastError();
-    if (e) return e;
+    if (e || nsplit == 1) return e;
     hipLaunchKernelGGL(k_chunk_attn_combine, dim3(ntasks * g.Hkv, 4), dim3(256), 0, s, c.attn_o, c.attn_ml, nsplit, g, c.tab,
                        c.att_hi, c.att_lo);
     return hipGetLastError();

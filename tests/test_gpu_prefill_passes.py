@@ -83,3 +83,28 @@ def test_pass_size_option_still_bounds_a_pass():
         out.append(lm.logits(0))
         lm.close()
     assert np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1]) <= TOL
+
+
+# k_chunk_attn_wide with every number of live waves in a block and of key splits: 1 to 9 query tiles over contexts below and
+# above 3072 keys (where it also takes single tiles), against one split per wave (a batched step of one sequence at a time has
+# the other kernel below 3072 keys)
+@pytest.mark.parametrize("ctx", [70, 3040, 3300])
+@pytest.mark.parametrize("rows", [2, 8, 9, 24, 31, 40, 72])
+def test_shared_key_attention_on_short_interrupts(ctx, rows):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=512, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 943, ctx + rows, model.vocab)
+    got = []
+    for chunk in (512, 1):                               # 1: the interrupt token by token through the single-row kernels
+        lm = pkg.AsyncLM(model, w, max_positions=ctx + rows + 8, stream=torch.cuda.Stream())
+        lm.prefill(0, toks[:ctx])
+        lm.set_option("chunk", chunk)
+        lm.inject_interrupt(0, toks[ctx:])
+        got.append((*_planes(lm, model, ctx + rows), lm.logits(0)))
+        lm.close()
+    (ka, va, la), (kb, vb, lb) = got
+    assert _worst(ka, kb) <= TOL, _worst(ka, kb)
+    assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
