@@ -825,6 +825,9 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         ALLOC(cb.part, cb.part_capacity);
         ALLOC(cb.attn_o, (size_t)CHUNK_ATTN_MAX_UNITS * g.dh * 32);
         ALLOC(cb.attn_ml, (size_t)CHUNK_ATTN_MAX_UNITS * 64);
+        ALLOC(cb.amax_v, (size_t)CHUNK_MAX_GROUPS * CHUNK_LOGIT_SLICES); ALLOC(cb.amax_i, (size_t)CHUNK_MAX_GROUPS * CHUNK_LOGIT_SLICES);
+        ALLOC(cb.amax_counters, (size_t)CHUNK_MAX_GROUPS);
+        if (hipMemset(cb.amax_counters, 0, sizeof(int32_t) * CHUNK_MAX_GROUPS) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
         // rows beyond the current chunk are multiplied into discarded columns only, but must stay finite
         if (hipMemset(cb.chosen, 0, CHUNK_MAX_GROUPS * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
             hipMemset(cb.nrm_lo, 0, M * g.d * 2) || hipMemset(cb.att_hi, 0, M * qd * 2) || hipMemset(cb.att_lo, 0, M * qd * 2) ||

@@ -220,40 +220,64 @@ __global__ __launch_bounds__(256) void k_chunk_head_rows(const float* __restrict
     row_emit(v, rsqrtf(ss / (float)d + eps), gn, d, tid, G.head, out_hi, out_lo);
 }
 
-// Workgroup = group that wants logits: row `head` of the output-head product -> logits of its sequence,
-// greedy argmax (lowest index on ties) -> next_token.
-__global__ __launch_bounds__(1024) void k_chunk_logits(const float* __restrict__ P, int V, ChunkTab tab,
-                                                       float* __restrict__ logits_base, SeqState* st,
-                                                       const int32_t* __restrict__ banned) {
-    __shared__ float sv[16];
-    __shared__ int si[16];
+// Row `head` of the output-head product of every group that wants logits -> logits of its sequence, greedy argmax (lowest
+// index on ties) -> next_token.  grid (groups, CHUNK_LOGIT_SLICES): a workgroup copies a slice of the row (16 bytes per lane)
+// and leaves its maximum; the last one of a group merges them.  Bound by the copy: one workgroup per row took 47 us for 16 rows
+// of 128256 logits, 24 slices take 13 us.  No fence: partial results are written through and read past the caches, as
+// in PipeSync.
+__global__ __launch_bounds__(256) void k_chunk_logits(const float* __restrict__ P, int V, ChunkTab tab, float* __restrict__ logits_base,
+                                                      SeqState* st, const int32_t* __restrict__ banned, float* part_v, int32_t* part_i,
+                                                      int32_t* counters) {
+    __shared__ float sv[4];
+    __shared__ int si[4];
+    __shared__ int s_last;
     const ChunkGroup G = tab.group[blockIdx.x];
     if (G.head < 0) return;
     const float* src = P + (size_t)G.head * V;
     float* dst = logits_base + (size_t)G.seq * V;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float bv = -INFINITY; int bi = 0x7fffffff;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ns = gridDim.y;
+    const int per = ((V + ns - 1) / ns + 3) & ~3, i0 = min((int)blockIdx.y * per, V), i1 = min(i0 + per, V);      // V is a multiple of 128
     const int32_t* ban = banned + (size_t)G.seq * (1 + BAN_MAX);
     const int nban = ban[0];
-    for (int i = tid; i < V; i += 1024) {
-        const float v = src[i];
-        dst[i] = v;
+    float bv = -INFINITY; int bi = 0x7fffffff;
+    auto take = [&](float v, int i) {
         bool allowed = true;
         for (int k = 0; k < nban; ++k) allowed = allowed && i != ban[1 + k];
-        if (allowed && v > bv) { bv = v; bi = i; }  // i ascends: the first maximum is kept
+        if (allowed && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
+    };
+    for (int i = i0 + 4 * tid; i < i1; i += 1024) {
+        const float4 v = *reinterpret_cast<const float4*>(src + i);
+        *reinterpret_cast<float4*>(dst + i) = v;
+        take(v.x, i); take(v.y, i + 1); take(v.z, i + 2); take(v.w, i + 3);
     }
+    auto reduce = [&]() {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(bv, o, 64); const int oi = __shfl_xor(bi, o, 64);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ov = __shfl_xor(bv, o, 64); const int oi = __shfl_xor(bi, o, 64);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+    };
+    reduce();
     if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
     __syncthreads();
+    const size_t slot = (size_t)blockIdx.x * ns;
     if (tid == 0) {
-        for (int w = 1; w < 16; ++w)
+        for (int w = 1; w < 4; ++w)
             if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) { bv = sv[w]; bi = si[w]; }
-        st[G.seq].next_token = bi;
+        __hip_atomic_store(part_v + slot + blockIdx.y, bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(part_i + slot + blockIdx.y, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // both have reached memory before the arrival is counted
+        s_last = __hip_atomic_fetch_add(counters + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ns - 1;
     }
+    __syncthreads();
+    if (!s_last || wave != 0) return;
+    bv = -INFINITY; bi = 0x7fffffff;
+    if (lane < ns) {
+        bv = __hip_atomic_load(part_v + slot + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bi = __hip_atomic_load(part_i + slot + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    reduce();
+    if (lane == 0) { st[G.seq].next_token = bi; counters[blockIdx.x] = 0; }
 }
 
 // a[m][f] = silu(sum_s gate) * (sum_s up) -> tiled hi/lo planes
@@ -1839,7 +1863,8 @@ hipError_t launch_chunk_head_rows(const ChunkBuffers& c, int S, int MT, const fl
 hipError_t launch_chunk_logits(const ChunkBuffers& c, int MT_head, float* logits_base, const DecodeBuffers& b, int ngroups,
                                const Geom& g, hipStream_t s) {
     (void)MT_head;
-    hipLaunchKernelGGL(k_chunk_logits, dim3(ngroups), dim3(1024), 0, s, c.part, g.V, c.tab, logits_base, b.seq_state, b.banned);
+    hipLaunchKernelGGL(k_chunk_logits, dim3(ngroups, CHUNK_LOGIT_SLICES), dim3(256), 0, s, c.part, g.V, c.tab, logits_base, b.seq_state, b.banned,
+                       c.amax_v, c.amax_i, c.amax_counters);
     return hipGetLastError();
 }
 

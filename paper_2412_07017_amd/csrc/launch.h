@@ -34,6 +34,7 @@ struct DecodeBuffers {
 constexpr int CHUNK_MAX = 2048;        // rows per forward pass of the append-chunk path (one sequence; see asynclm_ctx::pass_rows)
 constexpr int CHUNK_MAX_TASKS = 512;   // attention tiles (32 query columns of one group) per pass
 constexpr int CHUNK_MAX_GROUPS = 128;
+constexpr int CHUNK_LOGIT_SLICES = 24; // workgroups per row of logits of a batched step (at most 64: merged by one wave)
 // a batched step fills passes of at most this many rows and tiles
 constexpr int CHUNK_BATCH_ROWS = 512, CHUNK_BATCH_TASKS = 128;
 constexpr int CHUNK_ATTN_MAX_SPLIT = 128;
@@ -85,6 +86,9 @@ struct ChunkBuffers {
     size_t part_capacity;     // floats in `part`
     float* attn_o;            // [unit][dh][32]      unit = (task * Hkv + kv head) * nsplit + split
     float* attn_ml;           // [unit][2][32]
+    float* amax_v;            // [CHUNK_MAX_GROUPS][CHUNK_LOGIT_SLICES]
+    int32_t* amax_i;
+    int32_t* amax_counters;   // [CHUNK_MAX_GROUPS], zero between launches
 };
 
 // Several rows of one sequence per pass through the vector-unit kernels (decode_rows.hip): models outside the matrix-core
