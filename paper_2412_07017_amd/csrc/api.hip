@@ -202,7 +202,6 @@ hipError_t forward_single(asynclm_ctx* c, int seq, bool with_head, SplitPlan sp)
     const Geom& g = c->g;
     hipStream_t s = c->stream;
     hipError_t e;
-    if ((e = run(c, KC_EMBED, [&] { return launch_embed(dt, c->embed, c->b, g, s); }))) return e;
     // stamp mode (matrix-core attention plans): every kernel gets six stamp words, six kernels per layer, then the head
     const bool stamps = c->stamp_now && c->pipe_stamps && c->stamp_done;
     int idx = 0;
@@ -236,7 +235,6 @@ hipError_t forward_single(asynclm_ctx* c, int seq, bool with_head, SplitPlan sp)
         // logits of every sequence live in one array; the kernels pick the row from the descriptor
         const PipeSync* st = next();
         if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, c->b, g, s, st); }))) return e;
-        if ((e = run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, c->b, g, s); }))) return e;
     }
     return hipSuccess;
 }
@@ -390,7 +388,7 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
     const SplitPlan sp = pick_nsplit(c, c->len[seq] + 1, pipelined);
     // the chosen token also goes to pinned host memory, and an event marks the point: asynclm_decode_step waits for that
     // event only, so the host has the token while the forward pass is still running
-    if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->b, seq, forced, c->tok_event ? c->token_host + 4 : nullptr, c->stream); }))) return e;
+    if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, c->tok_event ? c->token_host + 4 : nullptr, c->stream); }))) return e;
     if (c->tok_event && !c->prof) {
         if ((e = hipEventRecord(c->tok_event, c->stream))) return e;
         c->tok_early = true;
@@ -540,8 +538,7 @@ hipError_t last_row_layer(asynclm_ctx* c, int l, float* x, int len_after) {
     if ((e = run(c, KC_OPROJ, [&] { return launch_oproj(dt, c->wo[l], sp.merge_in_oproj ? sp.nsplit : 0, b, g, s); }))) return e;
     if ((e = run(c, KC_GATEUP, [&] { return launch_gateup(dt, c->wgate_up[l], c->ffn_norm[l], b, g, s); }))) return e;
     if ((e = run(c, KC_DOWN, [&] { return launch_down(dt, c->wdown[l], b, g, s); }))) return e;
-    if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); }))) return e;
-    return run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, b, g, s); });
+    return run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); });
 }
 
 // One forward pass over the rows of `pb` (1..pass_rows rows in any number of groups).  Groups that want logits
@@ -633,7 +630,6 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
             const int seq = t.group[gi].seq;
             if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_last_row(cb, sp.down.s, MT, gi, c->b, g, s); }))) return e;
             if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, c->b, g, s); }))) return e;
-            if ((e = run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, c->b, g, s); }))) return e;
         }
     }
     for (int gi = 0; gi < t.ngroups; ++gi) c->len[t.group[gi].seq] = t.group[gi].pos0 + t.group[gi].n;
@@ -667,7 +663,6 @@ hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, b
         DecodeBuffers b = c->b;
         b.x = c->rb.x + (size_t)(n - 1) * g.d;
         if ((e = run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); }))) return e;
-        if ((e = run(c, KC_ARGMAX, [&] { return launch_argmax(c->logits, c->b, g, s); }))) return e;
     }
     c->len[seq] += n;
     return hipSuccess;

@@ -44,6 +44,7 @@ struct EpiOut {
     const float* rope_sin;
     int32_t rows;
     int32_t pos, seq;       // QKV: position and sequence of the row being processed
+    const int32_t* ban = nullptr;   // STORE: count and ids that the running argmax skips
 };
 
 __device__ __forceinline__ void amax_merge(float& bv, int& bi, float v, int i) {
@@ -658,13 +659,16 @@ __device__ __forceinline__ void phase_run(Slot (&ring)[RING], const Phase<WT>& p
             advance(cc, p.KT);
         }
     }
+    const int nban = EPI == EPI_STORE && eo.ban ? eo.ban[0] : 0;
     for (int ul = lane; ul < p.u1 - p.u0; ul += 64) {
         const float4 r = done[ul];          // written by lane 0 of this same wave
         const int u = p.u0 + ul;
         finish_unit<WT, EPI>(u, r.x, r.y, r.z, r.w, eo, g);
         if (EPI == EPI_STORE) {
-            amax_merge(best_v, best_i, r.x, 2 * u);
-            if (2 * u + 1 < p.rows) amax_merge(best_v, best_i, r.y, 2 * u + 1);
+            bool skip0 = false, skip1 = 2 * u + 1 >= p.rows;
+            for (int k = 0; k < nban; ++k) { const int id = eo.ban[1 + k]; skip0 = skip0 || id == 2 * u; skip1 = skip1 || id == 2 * u + 1; }
+            if (!skip0) amax_merge(best_v, best_i, r.x, 2 * u);
+            if (!skip1) amax_merge(best_v, best_i, r.y, 2 * u + 1);
         }
     }
     if (EPI == EPI_STORE) {

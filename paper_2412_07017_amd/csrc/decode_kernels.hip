@@ -20,8 +20,15 @@ namespace asynclm {
 // kernel has run instead of after the whole step.
 // pipe_abort: the give-up word of a step that runs on two streams, cleared here (this kernel runs alone, after the
 // previous step has ended and before any kernel of this one starts); the step number goes up by one.
-__global__ void k_begin_step(StepDesc* step, SeqState* st, int32_t seq, int32_t forced, int32_t* token_log, int32_t* token_early,
-                             unsigned* pipe_abort) {
+// The same launch fetches the token's embedding row into the residual stream (every workgroup looks the token up for itself;
+// next_token does not change here): a kernel of its own for that cost 4 us of a step and the boundary.
+template <typename WT>
+__global__ __launch_bounds__(256) void k_begin_step(StepDesc* step, SeqState* st, int32_t seq, int32_t forced, int32_t* token_log,
+                                                    int32_t* token_early, unsigned* pipe_abort, const WT* __restrict__ E, float* __restrict__ x,
+                                                    int d) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int32_t row = forced >= 0 ? forced : st[seq].next_token;
+    if (i < d) x[i] = Elem<WT>::load1(E + (size_t)row * d + i);
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         if (pipe_abort) *pipe_abort = 0u;
         step->epoch = (step->epoch + 1) & 0x3fffff;
@@ -37,11 +44,12 @@ __global__ void k_begin_step(StepDesc* step, SeqState* st, int32_t seq, int32_t 
     }
 }
 
+// The embedding row once more, by a kernel inside the two-stream step only: both streams fork behind it, so the first
+// product does not also pay for the start of the graph (its time stamps would show that, not the hand-over).
 template <typename WT>
-__global__ __launch_bounds__(256) void k_embed(const WT* __restrict__ E, const StepDesc* __restrict__ step,
-                                               float* __restrict__ x, int d) {
-    const WT* row = E + (size_t)step->token * d;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256) x[i] = Elem<WT>::load1(row + i);
+__global__ __launch_bounds__(256) void k_embed(const WT* __restrict__ E, const StepDesc* __restrict__ step, float* __restrict__ x, int d) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < d) x[i] = Elem<WT>::load1(E + (size_t)step->token * d + i);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -65,10 +73,52 @@ struct GemvArgs {
     const StepDesc* step;
     int32_t layer;
     int32_t y_seq_stride;   // EPI_STORE: y is the row step->seq of a [sequences][y_seq_stride] array
+    // EPI_STORE, optional: greedy choice over the stored values (the banned ids skipped) -> st[step->seq].next_token
+    float* amax_v; int32_t* amax_i; int32_t* amax_counter; SeqState* st; const int32_t* banned;
     // merged attention output as input vector (x == nullptr): see VecSource
     const float* part_acc; const float* part_ml; int32_t merge_nsplit, merge_dh, merge_hq;
     PipeSync sync;          // hand-over from / to the neighbouring kernels of a step that runs on two streams
 };
+
+// The greedy choice at the end of the output head: every workgroup leaves (maximum, lowest index) of its rows, the one that
+// arrives last merges them.  Without fences: a fence here writes back a die's whole L2 and costs about 10 us once all
+// workgroups do it; instead the partial results are written through, have arrived before the arrival is counted, and are read
+// past the caches.  A kernel of its own for the choice cost 9 us and the boundary (8B shape), 5 us (tiny).
+// All threads of the workgroup call this.
+__device__ __forceinline__ void gemv_argmax(const GemvArgs& a, float bv, int bi) {
+    __shared__ float sv[4];
+    __shared__ int si[4];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nb = gridDim.x;
+    if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 4; ++w) amax_merge(bv, bi, sv[w], si[w]);
+        __hip_atomic_store(a.amax_v + blockIdx.x, bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.amax_i + blockIdx.x, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        s_last = __hip_atomic_fetch_add(a.amax_counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    bv = -INFINITY; bi = 0x7fffffff;
+    if (tid < nb) {                                                 // nb <= ARGMAX_MAX_BLOCKS = 256
+        bv = __hip_atomic_load(a.amax_v + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bi = __hip_atomic_load(a.amax_i + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64); const int oi = __shfl_xor(bi, o, 64);
+        amax_merge(bv, bi, ov, oi);
+    }
+    if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 4; ++w) amax_merge(bv, bi, sv[w], si[w]);
+        a.st[a.step->seq].next_token = bi;
+        *a.amax_counter = 0;
+    }
+}
 
 // Every wave owns a contiguous share of the row pairs and streams them through a ring of four register
 // tiles (decode_device.h); the first tiles are requested before the input vector is staged.
@@ -112,7 +162,10 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
     eo.y = a.y; eo.res = a.res; eo.q_out = a.q_out; eo.kv_layer = a.kv_layer;
     eo.rope_cos = a.rope_cos; eo.rope_sin = a.rope_sin; eo.rows = a.rows; eo.pos = 0; eo.seq = 0;
     if (EPI == EPI_QKV) { eo.pos = a.step->pos; eo.seq = a.step->seq; }
-    if (EPI == EPI_STORE) eo.y += (size_t)a.step->seq * a.y_seq_stride;      // the logits row of the step's sequence
+    if (EPI == EPI_STORE) {
+        eo.y += (size_t)a.step->seq * a.y_seq_stride;                        // the logits row of the step's sequence
+        if (!PIPE) eo.ban = a.banned + (size_t)a.step->seq * (1 + BAN_MAX);
+    }
     if (PIPE) {
         // nothing but weights before the hand-over: the residual may come from the kernel before the previous one,
         // which is only known to be complete once the previous one is
@@ -134,6 +187,7 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
     float best_v = -INFINITY; int best_i = 0x7fffffff;
     phase_run<WT, EPI>(ring, ph, lc, lds4, plane_stride, nscale, eo, g, lane, done, best_v, best_i);
     if (PIPE) pipe_signal(a.sync, &s_go);
+    if (EPI == EPI_STORE && !PIPE && a.amax_v) gemv_argmax(a, best_v, best_i);
     if (STAMP) step_stamp_done(a.sync, t_start, t_staged);
 }
 
@@ -459,19 +513,22 @@ static hipError_t launch_gemv(int dtype, int epi, const GemvArgs& a, const Geom&
     return dtype == 0 ? launch_gemv_w<float>(epi, a, g, s) : launch_gemv_w<bf16_t>(epi, a, g, s);
 }
 
-hipError_t launch_begin_step(const DecodeBuffers& b, int seq, int forced, int32_t* token_early, hipStream_t s) {
-    hipLaunchKernelGGL(k_begin_step, dim3(1), dim3(64), 0, s, b.step, b.seq_state, seq, forced, b.token_log, token_early, b.pipe_abort);
+hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, int32_t* token_early,
+                             hipStream_t s) {
+    const dim3 grid((g.d + 255) / 256);
+    if (dtype == 0) hipLaunchKernelGGL(k_begin_step<float>, grid, dim3(256), 0, s, b.step, b.seq_state, seq, forced, b.token_log, token_early, b.pipe_abort, (const float*)E, b.x, g.d);
+    else hipLaunchKernelGGL(k_begin_step<bf16_t>, grid, dim3(256), 0, s, b.step, b.seq_state, seq, forced, b.token_log, token_early, b.pipe_abort, (const bf16_t*)E, b.x, g.d);
+    return hipGetLastError();
+}
+
+hipError_t launch_embed(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, hipStream_t s) {
+    const dim3 grid((g.d + 255) / 256);
+    if (dtype == 0) hipLaunchKernelGGL(k_embed<float>, grid, dim3(256), 0, s, (const float*)E, b.step, b.x, g.d);
+    else hipLaunchKernelGGL(k_embed<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)E, b.step, b.x, g.d);
     return hipGetLastError();
 }
 
 int decode_gemv_grid() { return g_gemv_grid; }
-
-hipError_t launch_embed(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, hipStream_t s) {
-    const int grid = (g.d + 255) / 256;
-    if (dtype == 0) hipLaunchKernelGGL(k_embed<float>, dim3(grid), dim3(256), 0, s, (const float*)E, b.step, b.x, g.d);
-    else hipLaunchKernelGGL(k_embed<bf16_t>, dim3(grid), dim3(256), 0, s, (const bf16_t*)E, b.step, b.x, g.d);
-    return hipGetLastError();
-}
 
 hipError_t launch_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b,
                       const Geom& g, hipStream_t s, const PipeSync* sync) {
@@ -520,8 +577,12 @@ hipError_t launch_lmhead(int dtype, const void* wout, const float* gain, float* 
     GemvArgs a{};
     if (sync) a.sync = *sync;
     a.W = wout; a.rows = g.V; a.K = g.d; a.units = (a.rows + 1) / 2;
-    a.x = b.x; a.gain = gain; a.y = logits_base; a.y_seq_stride = g.V; a.step = b.step;
-    return launch_gemv(dtype, EPI_STORE, a, g, s);
+    a.x = b.x; a.gain = gain; a.y = logits_base; a.y_seq_stride = g.V; a.step = b.step; a.banned = b.banned;
+    const bool pipe = a.sync.go_wait || a.sync.go_signal;
+    const bool fuse = !pipe && g_gemv_grid <= ARGMAX_MAX_BLOCKS;       // partial results of one workgroup per thread
+    if (fuse) { a.amax_v = b.amax_v; a.amax_i = b.amax_i; a.amax_counter = b.amax_counter; a.st = b.seq_state; }
+    const hipError_t e = launch_gemv(dtype, EPI_STORE, a, g, s);
+    return e || fuse || pipe ? e : launch_argmax(logits_base, b, g, s);
 }
 
 template <typename KVT, int DH, bool PAIR>

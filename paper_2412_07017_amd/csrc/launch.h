@@ -181,8 +181,9 @@ hipError_t launch_decode_attn_mfma(const ChunkBuffers& c, const void* kv_layer, 
                                    hipStream_t s, unsigned long long* stamps = nullptr, unsigned long long* done_wg = nullptr);
 hipError_t launch_stamp_init(unsigned long long* done_wg, int kernels, hipStream_t s);
 // token_early: pinned host word that also gets the chosen token (or nullptr)
-hipError_t launch_begin_step(const DecodeBuffers& b, int seq, int forced, int32_t* token_early, hipStream_t s);
 hipError_t launch_embed(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, hipStream_t s);
+hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, int32_t* token_early,
+                             hipStream_t s);
 // sync (all single-row launchers): hand-over flags when the step's kernels alternate between two streams (see PipeSync)
 hipError_t launch_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b,
                       const Geom& g, hipStream_t s, const PipeSync* sync = nullptr);
@@ -197,7 +198,8 @@ hipError_t launch_gateup(int dtype, const void* wgu, const float* gain, const De
                          hipStream_t s, const PipeSync* sync = nullptr, const float* x_in = nullptr);
 hipError_t launch_down(int dtype, const void* wd, const DecodeBuffers& b, const Geom& g, hipStream_t s, const PipeSync* sync = nullptr,
                        const float* res_in = nullptr);
-// logits_base: [sequences][V]; the kernel writes the row of the step descriptor's sequence
+// logits_base: [sequences][V]; the kernel writes the row of the step descriptor's sequence and, except in a two-stream step,
+// leaves the greedy choice (banned ids skipped) as its next token
 hipError_t launch_lmhead(int dtype, const void* wout, const float* gain, float* logits_base, const DecodeBuffers& b,
                          const Geom& g, hipStream_t s, const PipeSync* sync = nullptr);
 // True when two workgroups of every single-row kernel of this model fit one compute unit (registers, LDS), i.e. when
