@@ -97,7 +97,6 @@ struct asynclm_ctx {
     std::vector<int32_t> nban;          // host mirror of the number of banned token ids per sequence
     std::vector<char> choice_stale;     // the ban list changed after the sequence's greedy token was computed
     PassBuilder pass;                   // row table of the append-chunk pass being built
-    int32_t* chosen_host = nullptr;     // pinned, CHUNK_MAX_GROUPS ints
     // pinned staging of what the host uploads on the hot path (a pageable source would make the copy wait for the
     // stream): two copies of the row table and a small ring of ban-list rows, each reused once its event has passed
     unsigned char* tab_host[2] = {nullptr, nullptr};
@@ -811,8 +810,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         const size_t qn = (size_t)g.Hkv * cb.q_cols * g.dh;
         c->pass.G = g.Hq / g.Hkv; c->pass.Hkv = g.Hkv;
         ALLOC(cb.tab_mem, CHUNK_TAB_BYTES);
-        ALLOC(cb.chosen, (size_t)CHUNK_MAX_GROUPS);
-        ALLOC(cb.x, M * g.d);
+                ALLOC(cb.x, M * g.d);
         ALLOC(cb.nrm_hi, M * g.d); ALLOC(cb.nrm_lo, M * g.d);
         ALLOC(cb.att_hi, M * qd); ALLOC(cb.att_lo, M * qd);
         ALLOC(cb.act_hi, M * g.F); ALLOC(cb.act_lo, M * g.F);
@@ -824,7 +822,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         ALLOC(cb.amax_counters, (size_t)CHUNK_MAX_GROUPS);
         if (hipMemset(cb.amax_counters, 0, sizeof(int32_t) * CHUNK_MAX_GROUPS) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
         // rows beyond the current chunk are multiplied into discarded columns only, but must stay finite
-        if (hipMemset(cb.chosen, 0, CHUNK_MAX_GROUPS * 4) || hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
+        if (hipMemset(cb.x, 0, M * g.d * 4) || hipMemset(cb.nrm_hi, 0, M * g.d * 2) ||
             hipMemset(cb.nrm_lo, 0, M * g.d * 2) || hipMemset(cb.att_hi, 0, M * qd * 2) || hipMemset(cb.att_lo, 0, M * qd * 2) ||
             hipMemset(cb.act_hi, 0, M * g.F * 2) || hipMemset(cb.act_lo, 0, M * g.F * 2) || hipMemset(cb.q_hi, 0, qn * 2) ||
             hipMemset(cb.q_lo, 0, qn * 2))
@@ -882,7 +880,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
             hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess)
             return bail(ASYNCLM_E_DEVICE);
     }
-    if (hipHostMalloc((void**)&c->chosen_host, sizeof(int32_t) * CHUNK_MAX_GROUPS, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
+    if (c->chunk_ok && hipHostMalloc((void**)&c->cb.chosen_host, sizeof(int32_t) * CHUNK_MAX_GROUPS, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
     for (int i = 0; i < 2; ++i)
         if (hipHostMalloc((void**)&c->tab_host[i], CHUNK_TAB_BYTES, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&c->tab_ev[i], hipEventDisableTiming) != hipSuccess)
@@ -937,7 +935,7 @@ int asynclm_destroy(asynclm_ctx* c) {
     if (c->stream2) { hipStreamSynchronize(c->stream2); hipStreamDestroy(c->stream2); }
     if (c->ev_fork) hipEventDestroy(c->ev_fork);
     if (c->ev_join) hipEventDestroy(c->ev_join);
-    if (c->chosen_host) hipHostFree(c->chosen_host);
+    if (c->cb.chosen_host) hipHostFree(c->cb.chosen_host);
     for (int i = 0; i < 2; ++i) {
         if (c->tab_host[i]) hipHostFree(c->tab_host[i]);
         if (c->tab_ev[i]) hipEventDestroy(c->tab_ev[i]);
@@ -1051,10 +1049,9 @@ int asynclm_step_batch(asynclm_ctx* c, int32_t nseq, const int32_t* seqs, const 
         const int ng = pb.t.ngroups;
         HIPCK(c, forward_chunk(c, pb));
         if (tokens_out) {
-            HIPCK(c, hipMemcpyAsync(c->chosen_host, c->cb.chosen, sizeof(int32_t) * ng, hipMemcpyDeviceToHost, c->stream));
             HIPCK(c, hipStreamSynchronize(c->stream));
             for (int gi = 0; gi < ng; ++gi)
-                if (owner[gi] >= 0) tokens_out[owner[gi]] = c->chosen_host[gi];
+                if (owner[gi] >= 0) tokens_out[owner[gi]] = c->cb.chosen_host[gi];
         }
         pb.clear();
         owner.clear();

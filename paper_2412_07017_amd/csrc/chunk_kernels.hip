@@ -147,11 +147,11 @@ __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x,
 
 // First kernel of a pass, one workgroup per row: resolves the token where it is chosen on the device (first row of a
 // group), x[m] = E[token], RMSNorm with the first layer's gain -> tiled planes.  The workgroup of a group's first row also
-// records the token and grows the sequence; the one of the pass's last row fills the step descriptor that the single-row
+// records the token (in pinned host memory, where the host reads it after the pass) and grows the sequence; the one of the pass's last row fills the step descriptor that the single-row
 // kernels read (a pass over one sequence ends with them).
 // One launch instead of three (descriptor 4 us, embedding 9 us, norm 6 us for 24 rows of the 8B shape).
 __global__ __launch_bounds__(256) void k_chunk_embed_norm(const bf16_t* __restrict__ E, ChunkTab tab, int rows, StepDesc* step, SeqState* st,
-                                                          int32_t* chosen, float* __restrict__ x, const float* __restrict__ gain, float eps,
+                                                          int32_t* chosen_host, float* __restrict__ x, const float* __restrict__ gain, float eps,
                                                           int d, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo) {
     __shared__ float red[4];
     const int m = blockIdx.x, tid = threadIdx.x, d4 = d >> 2;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void k_chunk_embed_norm(const bf16_t* __restri
     const int tok = R.token >= 0 ? R.token : st[R.seq].next_token;
     if (tid == 0) {
         if (m == R.row0) {
-            if (R.group >= 0) chosen[R.group] = tok;
+            if (R.group >= 0) chosen_host[R.group] = tok;
             st[R.seq].len = R.pos + R.n;
         }
         if (m == rows - 1) { step->token = -1; step->pos = R.pos; step->seq = R.seq; step->rows = rows; }
@@ -298,53 +298,104 @@ __global__ __launch_bounds__(256) void k_chunk_swiglu(const float* __restrict__ 
 }
 
 // Rotary embedding of q and k, K/V cache write (row-major planes and the transposed V planes), scaled q
-// as hi/lo planes [Hkv][q_cols][dh] with the columns of a group ordered [q head in the kv group][row].
-// grid (heads, rows), dh/2 threads; P holds the heads from h0 on (h0 = Hq: keys and values only).
-__global__ void k_chunk_rope_kv(const float* __restrict__ P, int S, size_t s_stride, int n_stride, Geom g,
-                                ChunkTab tab, const float* __restrict__ rope_cos,
-                                const float* __restrict__ rope_sin, bf16_t* __restrict__ kv_layer,
-                                bf16_t* __restrict__ q_hi, bf16_t* __restrict__ q_lo, int q_cols, int h0) {
-    const int h = blockIdx.x + h0, m = blockIdx.y, i = threadIdx.x, half = g.dh >> 1;
-    const ChunkRow R = tab.row[m];
-    const int pos = R.pos;
-    const size_t seq_off = (size_t)R.seq * g.kv_seq_stride;
-    // all partial products and the rotation of this thread in one round of loads, added in split order
-    float pa[CHUNK_GEMM_MAX_SPLIT], pb[CHUNK_GEMM_MAX_SPLIT];
+// as hi/lo planes [Hkv][q_cols][dh] with the columns of a group ordered [q head in the kv group][row] (head_dim 128).
+// P holds the heads from h0 on (h0 = Hq: keys and values only).
+// The first `nrot` workgroups rotate: 16 threads per (row, q or k head), four pairs (i, i + 64) each, 16-byte loads and 8-byte
+// stores.  The others write values: a workgroup takes `vrows` consecutive rows of the pass and two heads, a thread one channel;
+// the row that starts a run of eight positions (or a group) takes the whole run, because eight positions of a channel lie
+// side by side in the transposed planes: one 16-byte store per plane instead of eight of 2 bytes 16 bytes apart from their
+// neighbours'.  2048 rows of the 70B shape 45 -> 28 us, 1019 of the 8B shape 20 -> 15, 24 rows 5.1 as before (latency).
+constexpr int ROPE_ITEMS = 16;      // (row, head) pairs per rotating workgroup
+__global__ __launch_bounds__(256) void k_chunk_rope_kv(const float* __restrict__ P, int S, size_t s_stride, int n_stride, Geom g, ChunkTab tab,
+                                                       int rows, const float* __restrict__ rope_cos, const float* __restrict__ rope_sin,
+                                                       bf16_t* __restrict__ kv_layer, bf16_t* __restrict__ q_hi, bf16_t* __restrict__ q_lo, int q_cols,
+                                                       int h0, int nrot, int vrows) {
+    constexpr int DH = 128, half = 64;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < nrot) {
+        const int nh = g.Hq + g.Hkv - h0, item = blockIdx.x * ROPE_ITEMS + (tid >> 4);
+        if (item >= rows * nh) return;
+        const int m = item / nh, hl = item - m * nh, h = hl + h0, i = 4 * (tid & 15);
+        const ChunkRow R = tab.row[m];
+        // all partial products of this thread in one round of loads, added in split order
+        float4 pa[CHUNK_GEMM_MAX_SPLIT], pb[CHUNK_GEMM_MAX_SPLIT];
 #pragma unroll
-    for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s) {
-        const float* p = P + (size_t)min(s, S - 1) * s_stride + (size_t)m * n_stride + blockIdx.x * g.dh;
-        pa[s] = p[i]; pb[s] = p[i + half];
-    }
-    const float c = rope_cos[(size_t)pos * half + i], sn = rope_sin[(size_t)pos * half + i];
-    float a = 0.f, b = 0.f;
+        for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s) {
+            const float* p = P + (size_t)min(s, S - 1) * s_stride + (size_t)m * n_stride + hl * DH + i;
+            pa[s] = *reinterpret_cast<const float4*>(p); pb[s] = *reinterpret_cast<const float4*>(p + half);
+        }
+        const float4 c = *reinterpret_cast<const float4*>(rope_cos + (size_t)R.pos * half + i);
+        const float4 sn = *reinterpret_cast<const float4*>(rope_sin + (size_t)R.pos * half + i);
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
 #pragma unroll
-    for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s)
-        if (s < S) { a += pa[s]; b += pb[s]; }
-    if (h < g.Hq + g.Hkv) {
-        const float ra = a * c - b * sn, rb = b * c + a * sn;
-        a = ra; b = rb;
-    }
-    bf16_t ahi, alo, bhi, blo;
-    if (h < g.Hq) {
-        split_bf16(a * g.scale, ahi, alo); split_bf16(b * g.scale, bhi, blo);
-        const int G = g.Hq / g.Hkv, kvh = h / G, gq = h - kvh * G;
-        const size_t o = ((size_t)kvh * q_cols + (size_t)G * R.row0 + (size_t)gq * R.n + (m - R.row0)) * g.dh;
-        q_hi[o + i] = ahi; q_lo[o + i] = alo; q_hi[o + i + half] = bhi; q_lo[o + i + half] = blo;
+        for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s)
+            if (s < S) {
+                a.x += pa[s].x; a.y += pa[s].y; a.z += pa[s].z; a.w += pa[s].w;
+                b.x += pb[s].x; b.y += pb[s].y; b.z += pb[s].z; b.w += pb[s].w;
+            }
+        float ra[4] = {a.x * c.x - b.x * sn.x, a.y * c.y - b.y * sn.y, a.z * c.z - b.z * sn.z, a.w * c.w - b.w * sn.w};
+        float rb[4] = {b.x * c.x + a.x * sn.x, b.y * c.y + a.y * sn.y, b.z * c.z + a.z * sn.z, b.w * c.w + a.w * sn.w};
+        bf16_t *hi, *lo;
+        if (h < g.Hq) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { ra[e] *= g.scale; rb[e] *= g.scale; }
+            const int G = g.Hq / g.Hkv, kvh = h / G, gq = h - kvh * G;
+            const size_t o = ((size_t)kvh * q_cols + (size_t)G * R.row0 + (size_t)gq * R.n + (m - R.row0)) * DH + i;
+            hi = q_hi + o; lo = q_lo + o;
+        } else {
+            hi = kv_layer + (size_t)R.seq * g.kv_seq_stride + (size_t)(h - g.Hq) * g.kv_head_stride + (size_t)R.pos * DH + i;
+            lo = hi + g.kv_lo_offset;
+        }
+        uint32_t h2[4], l2[4];
+        split_pair(ra[0], ra[1], h2[0], l2[0]); split_pair(ra[2], ra[3], h2[1], l2[1]);
+        split_pair(rb[0], rb[1], h2[2], l2[2]); split_pair(rb[2], rb[3], h2[3], l2[3]);
+        *reinterpret_cast<uint2*>(hi) = make_uint2(h2[0], h2[1]); *reinterpret_cast<uint2*>(hi + half) = make_uint2(h2[2], h2[3]);
+        *reinterpret_cast<uint2*>(lo) = make_uint2(l2[0], l2[1]); *reinterpret_cast<uint2*>(lo + half) = make_uint2(l2[2], l2[3]);
         return;
     }
-    split_bf16(a, ahi, alo); split_bf16(b, bhi, blo);
-    if (h < g.Hq + g.Hkv) {
-        bf16_t* kp = kv_layer + seq_off + (size_t)(h - g.Hq) * g.kv_head_stride + (size_t)pos * g.dh;
-        kp[i] = ahi; kp[i + half] = bhi; kp[g.kv_lo_offset + i] = alo; kp[g.kv_lo_offset + i + half] = blo;
-    } else {
-        const int vh = h - g.Hq - g.Hkv;
-        if (g.kv_v_offset) {       // row-major values are only kept for the single-row attention kernel
-            bf16_t* vp = kv_layer + g.kv_v_offset + seq_off + (size_t)vh * g.kv_head_stride + (size_t)pos * g.dh;
-            vp[i] = ahi; vp[i + half] = bhi; vp[g.kv_lo_offset + i] = alo; vp[g.kv_lo_offset + i + half] = blo;
+    const int hp = (g.Hkv + 1) / 2, item = blockIdx.x - nrot, vh = (item % hp) * 2 + (tid >> 7), ch = tid & 127;
+    const int m0 = item / hp * vrows;
+    if (vh >= g.Hkv) return;
+    for (int mm = m0; mm < min(m0 + vrows, rows); ++mm) {
+        const ChunkRow R = tab.row[mm];
+        if ((R.pos & 7) != 0 && mm != R.row0) continue;             // in the run of an earlier row
+        const int cnt = min(8 - (R.pos & 7), R.row0 + R.n - mm);
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = 0.f;
+        const float* p = P + (size_t)mm * n_stride + (size_t)(g.Hq + g.Hkv - h0 + vh) * DH + ch;
+        for (int s = 0; s < S; ++s) {
+            float t[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) t[k] = p[s * s_stride + (size_t)min(k, cnt - 1) * n_stride];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += t[k];
         }
-        bf16_t* vt = kv_layer + g.kv_vt_offset + seq_off + (size_t)vh * g.kv_head_stride;
-        const size_t oa = vt_tile_off(pos, i), ob = vt_tile_off(pos, i + half);
-        vt[oa] = ahi; vt[ob] = bhi; vt[g.kv_lo_offset + oa] = alo; vt[g.kv_lo_offset + ob] = blo;
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) split_pair(v[2 * k], v[2 * k + 1], hi[k], lo[k]);
+        bf16_t* head = kv_layer + (size_t)R.seq * g.kv_seq_stride + (size_t)vh * g.kv_head_stride;
+        bf16_t* vt = head + g.kv_vt_offset + vt_tile_off(R.pos, ch);
+        if (cnt == 8) {
+            *reinterpret_cast<uint4*>(vt) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            *reinterpret_cast<uint4*>(vt + g.kv_lo_offset) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < cnt) {
+                    vt[k] = (bf16_t)(hi[k >> 1] >> (16 * (k & 1)));
+                    vt[g.kv_lo_offset + k] = (bf16_t)(lo[k >> 1] >> (16 * (k & 1)));
+                }
+        }
+        if (g.kv_v_offset) {               // row-major values are only kept for the single-row attention kernel
+            bf16_t* vr = head + g.kv_v_offset + (size_t)R.pos * DH + ch;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < cnt) {
+                    vr[(size_t)k * DH] = (bf16_t)(hi[k >> 1] >> (16 * (k & 1)));
+                    vr[g.kv_lo_offset + (size_t)k * DH] = (bf16_t)(lo[k >> 1] >> (16 * (k & 1)));
+                }
+        }
     }
 }
 
@@ -1840,7 +1891,7 @@ hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, bool add_partials, int
 hipError_t launch_chunk_embed_norm(const void* E, const ChunkBuffers& c, const float* gain, int rows, const DecodeBuffers& b, const Geom& g,
                                    hipStream_t s) {
     if (!row_kernel_ok(g, 1)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_chunk_embed_norm, dim3(rows), dim3(256), 0, s, (const bf16_t*)E, c.tab, rows, b.step, b.seq_state, c.chosen, c.x, gain,
+    hipLaunchKernelGGL(k_chunk_embed_norm, dim3(rows), dim3(256), 0, s, (const bf16_t*)E, c.tab, rows, b.step, b.seq_state, c.chosen_host, c.x, gain,
                        g.eps, g.d, c.nrm_hi, c.nrm_lo);
     return hipGetLastError();
 }
@@ -1876,9 +1927,13 @@ hipError_t launch_chunk_swiglu(const ChunkBuffers& c, int S, int MT, int rows, c
 
 hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, const DecodeBuffers& b, int rows, int MT,
                                 const Geom& g, hipStream_t s, bool kv_only) {
-    const int h0 = kv_only ? g.Hq : 0, heads = g.Hq + 2 * g.Hkv - h0, n_qkv = heads * g.dh;
-    hipLaunchKernelGGL(k_chunk_rope_kv, dim3(heads, rows), dim3(g.dh / 2), 0, s, c.part, S, (size_t)MT * 32 * n_qkv,
-                       n_qkv, g, c.tab, b.rope_cos, b.rope_sin, (bf16_t*)kv_layer, c.q_hi, c.q_lo, c.q_cols, h0);
+    const int h0 = kv_only ? g.Hq : 0, n_qkv = (g.Hq + 2 * g.Hkv - h0) * g.dh;
+    const int nrot = (rows * (g.Hq + g.Hkv - h0) + ROPE_ITEMS - 1) / ROPE_ITEMS, vrows = rows > 256 ? 8 : 1, nval = (rows + vrows - 1) / vrows * ((g.Hkv + 1) / 2);
+    // few rows: a workgroup per row, most of them with nothing to do, because the runs of several rows one after the other are a
+    // chain (16 sequences, 40 rows: 18 us with eight rows per workgroup)
+    if (g.dh != 128 || S < 1 || S > CHUNK_GEMM_MAX_SPLIT) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_chunk_rope_kv, dim3(nrot + nval), dim3(256), 0, s, c.part, S, (size_t)MT * 32 * n_qkv, n_qkv, g, c.tab, rows,
+                       b.rope_cos, b.rope_sin, (bf16_t*)kv_layer, c.q_hi, c.q_lo, c.q_cols, h0, nrot, vrows);
     return hipGetLastError();
 }
 

@@ -73,7 +73,7 @@ constexpr size_t CHUNK_TAB_BYTES = sizeof(ChunkGroup) * CHUNK_MAX_GROUPS + sizeo
 struct ChunkBuffers {
     unsigned char* tab_mem;   // [CHUNK_TAB_BYTES]
     ChunkTab tab;             // the running pass's entries in it
-    int32_t* chosen;          // [CHUNK_MAX_GROUPS] token chosen for the first row of each group
+    int32_t* chosen_host;     // pinned, [CHUNK_MAX_GROUPS]: token chosen for the first row of each group
     float* x;                 // [pass rows][d] residual stream
     // inputs of the products, as many rows each, stored in matrix-core operand order (tiled planes)
     bf16_t *nrm_hi, *nrm_lo;  // d columns:     normalised input of the QKV, gate/up and output-head products

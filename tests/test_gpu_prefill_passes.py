@@ -107,4 +107,5 @@ def test_shared_key_attention_on_short_interrupts(ctx, rows):
         lm.close()
     (ka, va, la), (kb, vb, lb) = got
     assert _worst(ka, kb) <= TOL, _worst(ka, kb)
+    assert _worst(va, vb) <= TOL, _worst(va, vb)        # runs of values that start and end inside eight positions
     assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
