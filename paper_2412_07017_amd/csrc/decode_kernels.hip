@@ -191,6 +191,112 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
     if (STAMP) step_stamp_done(a.sync, t_start, t_staged);
 }
 
+// Small products (at most one row pair per wave of the device and one tile of columns per row: the tiny preset): a wave per
+// row pair, everything it needs requested at once and held in registers - its two rows, the whole input vector (through the
+// caches, no LDS), the gain, the epilogue's operands - and one round of sums.  Such a product is a chain of latencies; the
+// streaming kernel above adds to it by requesting a ring of four tiles where one exists, staging the vector in LDS behind a
+// barrier, and starting all 256 workgroups.  Tiny preset's step, QKV 6.3 -> 2.7 us, O (with the merge) 7.1 -> 3.4, gate/up 5.5 -> 2.6, down
+// 5.2 -> 2.7, head (with the choice) 8.2 -> 5.5; its session 2.95 -> 2.15 ms.
+// NS: wave-wide loads per row (1, 2 or 4).
+template <typename WT, int EPI, int NS>
+__global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
+    constexpr int EPL = Elem<WT>::EPL, NP = EPL / 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int unit = blockIdx.x * 4 + wave, u = min(unit, a.units - 1), Kg = a.K / EPL;
+    int rA, rB;
+    unit_rows<EPI>(u, a.rows, g, rA, rB);
+    const WT* pa = (const WT*)a.W + (size_t)rA * a.K;
+    const WT* pb = (const WT*)a.W + (size_t)rB * a.K;
+    float4 xv[NS][NP], gn[NS][NP];
+    uint4 wa[NS], wb[NS];
+    float ms[NS][NP][MERGE_MAX_SPLIT], ls[NS][NP][MERGE_MAX_SPLIT];
+    float4 raw[NS][NP][MERGE_MAX_SPLIT];
+    const bool merge = EPI == EPI_RESID && !a.x;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int gi = min(s * 64 + lane, Kg - 1);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const size_t k = (size_t)gi * EPL + 4 * q;
+            if (EPI == EPI_RESID && merge) {                        // uniform: the attention output from its key splits, as in stage_vector
+                const int h = (int)k / a.merge_dh, dim = (int)k - h * a.merge_dh;
+                const float* pm = a.part_ml + (size_t)h * a.merge_nsplit * 2;
+                const float* pp = a.part_acc + (size_t)h * a.merge_nsplit * a.merge_dh + dim;
+#pragma unroll
+                for (int t = 0; t < MERGE_MAX_SPLIT; ++t) {
+                    const int sc = min(t, a.merge_nsplit - 1);
+                    ms[s][q][t] = load_f32(pm + 2 * sc); ls[s][q][t] = load_f32(pm + 2 * sc + 1);
+                    raw[s][q][t] = as_float4(load16(pp + (size_t)sc * a.merge_dh));
+                }
+            } else xv[s][q] = as_float4(load16(a.x + k));
+            if (EPI != EPI_RESID) gn[s][q] = as_float4(load16(a.gain + k));
+        }
+        wa[s] = load16_stream(pa + (size_t)gi * EPL); wb[s] = load16_stream(pb + (size_t)gi * EPL);
+    }
+    EpiOut eo;
+    eo.y = a.y; eo.res = a.res; eo.q_out = a.q_out; eo.kv_layer = a.kv_layer;
+    eo.rope_cos = a.rope_cos; eo.rope_sin = a.rope_sin; eo.rows = a.rows; eo.pos = 0; eo.seq = 0;
+    if (EPI == EPI_QKV) { eo.pos = a.step->pos; eo.seq = a.step->seq; }
+    if (EPI == EPI_STORE) eo.y += (size_t)a.step->seq * a.y_seq_stride;
+    float e0 = 0.f, e1 = 0.f;
+    if (EPI == EPI_RESID) { e0 = load_f32(a.res + rA); e1 = load_f32(a.res + rB); }
+    if (EPI == EPI_QKV) {
+        const int hs = g.dh == 128 ? 6 : 5;
+        const size_t ri = ((size_t)eo.pos << hs) + (u & ((1 << hs) - 1));
+        e0 = load_f32(a.rope_cos + ri); e1 = load_f32(a.rope_sin + ri);
+    }
+    float sa = 0.f, sb = 0.f, ss = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const bool live = s * 64 + lane < Kg;
+        float fa[EPL], fb[EPL];
+        Elem<WT>::expand(wa[s], fa); Elem<WT>::expand(wb[s], fb);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            float4 x;
+            if (EPI == EPI_RESID && merge) {
+                float M = -INFINITY, L = 0.f;
+#pragma unroll
+                for (int t = 0; t < MERGE_MAX_SPLIT; ++t) if (t < a.merge_nsplit) M = fmaxf(M, ms[s][q][t]);
+                x = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int t = 0; t < MERGE_MAX_SPLIT; ++t) {
+                    const float w = (t < a.merge_nsplit && ms[s][q][t] > -INFINITY) ? expf(ms[s][q][t] - M) : 0.f;
+                    L += ls[s][q][t] * w;
+                    x.x = fmaf(raw[s][q][t].x, w, x.x); x.y = fmaf(raw[s][q][t].y, w, x.y);
+                    x.z = fmaf(raw[s][q][t].z, w, x.z); x.w = fmaf(raw[s][q][t].w, w, x.w);
+                }
+                const float inv = 1.f / L;
+                x = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+            } else x = xv[s][q];
+            if (!live) x = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (EPI != EPI_RESID) {
+                ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+                x = make_float4(x.x * gn[s][q].x, x.y * gn[s][q].y, x.z * gn[s][q].z, x.w * gn[s][q].w);
+            }
+            sa = fmaf(fa[4 * q], x.x, sa); sa = fmaf(fa[4 * q + 1], x.y, sa); sa = fmaf(fa[4 * q + 2], x.z, sa); sa = fmaf(fa[4 * q + 3], x.w, sa);
+            sb = fmaf(fb[4 * q], x.x, sb); sb = fmaf(fb[4 * q + 1], x.y, sb); sb = fmaf(fb[4 * q + 2], x.z, sb); sb = fmaf(fb[4 * q + 3], x.w, sb);
+        }
+    }
+    sa = wave_sum_all(sa); sb = wave_sum_all(sb);
+    if (EPI != EPI_RESID) {
+        const float sc = rsqrtf(wave_sum_all(ss) / (float)a.K + g.eps);
+        sa *= sc; sb *= sc;
+    }
+    if (lane == 0 && unit < a.units) finish_unit<WT, EPI>(u, sa, sb, e0, e1, eo, g);
+    if (EPI == EPI_STORE && a.amax_v) {
+        float bv = -INFINITY; int bi = 0x7fffffff;
+        if (unit < a.units) {
+            const int32_t* ban = a.banned + (size_t)a.step->seq * (1 + BAN_MAX);
+            bool skip0 = false, skip1 = 2 * u + 1 >= a.rows;
+            for (int k = 0; k < ban[0]; ++k) { skip0 = skip0 || ban[1 + k] == 2 * u; skip1 = skip1 || ban[1 + k] == 2 * u + 1; }
+            if (!skip0) amax_merge(bv, bi, sa, 2 * u);
+            if (!skip1) amax_merge(bv, bi, sb, 2 * u + 1);
+        }
+        gemv_argmax(a, bv, bi);
+    }
+}
+
 // The finishing-time words of every workgroup of every kernel of a step in stamp mode start at zero.
 __global__ void k_stamp_init(unsigned long long* done_wg, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) done_wg[i] = 0ull;
@@ -442,8 +548,20 @@ static size_t gemv_lds_bytes(int K, int units, int grid, int* done_cap) {
 }
 
 template <typename WT, int EPI>
+static const void* gemv_small_func(int ns) {
+    return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2>) : (const void*)(k_gemv_small<WT, EPI, 4>);
+}
+
+template <typename WT, int EPI>
 static hipError_t launch_gemv_t(const GemvArgs& a0, const Geom& g, hipStream_t s) {
     GemvArgs a = a0;
+    const int kg = a.K / Elem<WT>::EPL;
+    if (kg <= 256 && a.units <= 4 * g_gemv_grid && !a.sync.go_wait && !a.sync.go_signal && !a.sync.done_wg &&
+        (EPI == EPI_RESID ? !a.gain : a.x && a.gain)) {
+        Geom gg = g;
+        void* params[] = {&a, &gg};
+        return hipLaunchKernel(gemv_small_func<WT, EPI>((kg + 63) / 64), dim3((a.units + 3) / 4), dim3(256), params, 0, s);
+    }
     const size_t lds = gemv_lds_bytes<WT>(a.K, a.units, g_gemv_grid, &a.done_cap);
     a.uq = a.units / (g_gemv_grid * 4); a.ur = a.units % (g_gemv_grid * 4);
     if (lds > g_gemv_lds_limit) return hipErrorInvalidValue;
@@ -579,7 +697,7 @@ hipError_t launch_lmhead(int dtype, const void* wout, const float* gain, float* 
     a.W = wout; a.rows = g.V; a.K = g.d; a.units = (a.rows + 1) / 2;
     a.x = b.x; a.gain = gain; a.y = logits_base; a.y_seq_stride = g.V; a.step = b.step; a.banned = b.banned;
     const bool pipe = a.sync.go_wait || a.sync.go_signal;
-    const bool fuse = !pipe && g_gemv_grid <= ARGMAX_MAX_BLOCKS;       // partial results of one workgroup per thread
+    const bool fuse = !pipe && g_gemv_grid <= ARGMAX_MAX_BLOCKS;       // partial results of one workgroup per thread (a small product has no more)
     if (fuse) { a.amax_v = b.amax_v; a.amax_i = b.amax_i; a.amax_counter = b.amax_counter; a.st = b.seq_state; }
     const hipError_t e = launch_gemv(dtype, EPI_STORE, a, g, s);
     return e || fuse || pipe ? e : launch_argmax(logits_base, b, g, s);
