@@ -454,8 +454,9 @@ struct ChunkPlans { GemmPlan qkv, o, gu, down; };
 // A product with N output rows and K columns over MT row tiles.  Up to four row tiles: (N / 128) S workgroups, one per
 // compute unit at a time: S = the split that comes closest to one workgroup per unit, with at least two 128-column blocks
 // per workgroup.  More: workgroups of nt weight-row tiles x 256 rows run in rounds of one per compute unit; a k-block costs
-// nt, a workgroup's start and end about as much as 14 (0.6 us each), and a partial plane of 512 x 4096 floats, written and
-// read back, about 6.5.  All within the capacity of the partial planes.  `swiglu`: pairs of gate and up rows, no split.
+// nt + 1 (the activations' share; 0.6 us each), a workgroup's start and end about 8, and a partial plane of 512 x 4096 floats,
+// written and read back, about 7.5.  Measured in a pass, down product of the 8B shape: 2048 rows nt 8 in 2 parts 372 us,
+// nt 4 unsplit 395; 1019 rows 210 (8, 4 parts) and 206 (4, 2 parts).  All within the capacity of the partial planes.  `swiglu`: pairs of gate and up rows, no split.
 GemmPlan pick_gemm_plan(const asynclm_ctx* c, int N, int K, int MT, bool swiglu = false) {
     const int nblk = K / 128;
     const int smax = std::min(CHUNK_GEMM_MAX_SPLIT, std::max(1, nblk / 2));
@@ -481,7 +482,7 @@ GemmPlan pick_gemm_plan(const asynclm_ctx* c, int N, int K, int MT, bool swiglu 
     const int my = (MT + 7) / 8;
     GemmPlan best{1, 4};
     double best_cost = 0;
-    const double plane = 6.5 * ((double)MT * 32 * N) / (512.0 * 4096.0);
+    const double plane = 7.5 * ((double)MT * 32 * N) / (512.0 * 4096.0);
     int s0 = 1, s1 = swiglu ? 1 : smax;
     if (!swiglu && c->opt_chunk_split > 0) { s0 = s1 = std::min(c->opt_chunk_split, std::max(1, nblk)); while (!fits(s1)) --s1; s0 = s1; }
     bool any = false;
@@ -490,7 +491,7 @@ GemmPlan pick_gemm_plan(const asynclm_ctx* c, int N, int K, int MT, bool swiglu 
         for (int nt = 8; nt >= 4; --nt) {
             const int tiles = (N / 32 + nt - 1) / nt * my * s;
             const int rounds = (tiles + c->n_cu - 1) / c->n_cu;
-            const double cost = rounds * ((double)((nblk + s - 1) / s) * nt + 14.0) + (swiglu ? 0.0 : plane * s);
+            const double cost = rounds * ((double)((nblk + s - 1) / s) * (nt + 1.0) + 8.0) + (swiglu ? 0.0 : plane * s);
             if (!any || cost < best_cost) { any = true; best_cost = cost; best = {s, nt}; }
         }
     }
