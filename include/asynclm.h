@@ -197,9 +197,10 @@ int asynclm_synchronize(asynclm_ctx *ctx);
 
 /* Tuning knobs; all have working defaults.  Unknown names give ASYNCLM_E_INVAL.
  *   "chunk"        rows processed per forward pass by prefill / inject (1 .. 512); 1 = token by token
- *                  through the decode kernels.  Default 512 where the matrix-core append path applies
+ *                  through the decode kernels.  Without it passes are as long as the context's buffers allow: up to
+ *                  2048 rows (512 .. 2048, by max_positions and head count) where the matrix-core append path applies
  *                  (bf16 model, paired cache, head_dim 128, d_model and ffn multiples of 128); other models take at
- *                  most 8 rows per pass (their default), through the vector units.
+ *                  most 8 rows per pass, through the vector units.
  *   "chunk_split"  0 = split-K factors of the append path's products chosen from the shapes and the number
  *                  of compute units, 1..8 = force one
  *   "fused"        1 = run a decoding step as one persistent cooperative kernel (where the device and the

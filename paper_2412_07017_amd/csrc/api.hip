@@ -558,12 +558,16 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     // 685 / 679, 4.2k 707 / 723, 16.4k 786 / 810; 48 rows (6 tasks) into 1.1k 748 / 753, 2.1k 746 / 767, 16.4k 890 / 940.
     // Batched steps of mostly single rows: 4 sequences of up to 1k 795 / 784, 16 of up to 4.2k 1217 / 1243.
     // Key splits of the first: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
-    // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).
+    // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).  One split, which needs no merge, where
+    // the blocks alone fill the units and the keys are few: 2 layers, 1019 tokens 2792 -> 2771 us, 2000 tokens 1968 -> 1956,
+    // 1300 tokens and 1024 rows after 1000 no difference; beyond, the second workgroup is worth more (1024 rows after
+    // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).
     const bool wide_attn = pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
     int wsplit = 1;
     if (wide_attn) {
         const long long wgs = (long long)t.nblocks * g.Hkv;
         wsplit = (int)std::max(1LL, std::min<long long>((2LL * c->n_cu + wgs - 1) / wgs, ((pb.max_keys + 31) / 32 + 1) / 2));
+        if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
         wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
         while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
     }
@@ -794,9 +798,10 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
     ALLOC(c->stamp_done, (size_t)c->pipe_kernels_max * STAMP_DONE_SLOTS);
     if (c->chunk_ok) {
         ChunkBuffers& cb = c->cb;
-        // Rows per pass: longer prompts take passes of up to 2048 rows (fewer partial planes, whole rounds of workgroups; one
-        // 16384-token prompt of the 8B shape: see forward_chunk), as long as the context can be that long and the partial
-        // results of the attention fit.
+        // Rows per pass: longer prompts take passes of up to 2048 rows (fewer partial planes, whole rounds of workgroups: a
+        // 16384-token prompt of the 8B shape, 2 layers, 51.2 ms in passes of 512 rows and 44.0 ms in passes of 2048, the product
+        // of more than 128 rows changed with it), as long as the context can be that long and the partial results of the
+        // attention fit.
         c->pass_rows = std::max(CHUNK_BATCH_ROWS, std::min({max_rows, g.max_pos, CHUNK_ATTN_MAX_UNITS * 32 / g.Hq / 32 * 32,
                                                             CHUNK_MAX_TASKS * 32 / (g.Hq / g.Hkv)}));
         const size_t M = c->pass_rows, MB = CHUNK_BATCH_ROWS, qd = (size_t)g.Hq * g.dh;
