@@ -559,7 +559,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     // Batched steps of mostly single rows: 4 sequences of up to 1k 795 / 784, 16 of up to 4.2k 1217 / 1243.
     // Key splits of the first: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
     // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).  One split, which needs no merge, where
-    // the blocks alone fill the units and the keys are few: 2 layers, 1019 tokens 2792 -> 2771 us, 2000 tokens 1968 -> 1956,
+    // the blocks alone fill the units and the keys are few: 1019 tokens (4 layers) 2792 -> 2771 us, 2000 (2 layers) 1968 -> 1956,
     // 1300 tokens and 1024 rows after 1000 no difference; beyond, the second workgroup is worth more (1024 rows after
     // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).
     const bool wide_attn = pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
