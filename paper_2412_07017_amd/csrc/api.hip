@@ -18,7 +18,8 @@ using namespace asynclm;
 struct PassBuilder {
     ChunkTable t{};
     int G = 1, Hkv = 1, max_keys = 0;
-    void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = 0; max_keys = 0; }
+    long long block_tiles = 0;          // key tiles of 32 over all task blocks
+    void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = 0; max_keys = 0; block_tiles = 0; }
     int tiles_of(int n) const { return (G * n + 31) / 32; }
     // batched steps: rows, attention tasks, and the attention's partial results (task x kv head x at least 4 key splits) all fit one pass
     bool fits(int n) const {
@@ -39,7 +40,7 @@ struct PassBuilder {
         Gp = ChunkGroup{};
         Gp.seq = seq; Gp.row0 = row0; Gp.n = n; Gp.pos0 = pos0; Gp.forced = forced; Gp.head = want_head ? t.nhead++ : -1;
         for (int tile = 0; tile < tiles_of(n); ++tile) {
-            if (tile % 4 == 0) t.block[t.nblocks++] = ChunkTaskBlock{t.ntasks, std::min(4, tiles_of(n) - tile)};
+            if (tile % 4 == 0) { t.block[t.nblocks++] = ChunkTaskBlock{t.ntasks, std::min(4, tiles_of(n) - tile)}; block_tiles += (pos0 + n + 31) / 32; }
             ChunkTask& T = t.task[t.ntasks++];
             T = ChunkTask{};
             T.seq = seq; T.row0 = row0; T.n = n; T.pos0 = pos0; T.tile = tile;
@@ -556,21 +557,27 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     // first loads a tile once for up to four tasks and issues its loads from four waves, the second starts sooner and runs
     // more waves of small work.  8B shape, 4 layers, whole pass: 24 rows (3 tasks) into 1.1k 668 (wide) against 664 us, 2.1k
     // 685 / 679, 4.2k 707 / 723, 16.4k 786 / 810; 48 rows (6 tasks) into 1.1k 748 / 753, 2.1k 746 / 767, 16.4k 890 / 940.
-    // Batched steps of mostly single rows: 4 sequences of up to 1k 795 / 784, 16 of up to 4.2k 1217 / 1243.
     // Key splits of the first: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
     // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).  One split, which needs no merge, where
     // the blocks alone fill the units and the keys are few: 1019 tokens (4 layers) 2792 -> 2771 us, 2000 (2 layers) 1968 -> 1956,
     // 1300 tokens and 1024 rows after 1000 no difference; beyond, the second workgroup is worth more (1024 rows after
-    // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).
-    const bool wide_attn = pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
-    int wsplit = 1;
-    if (wide_attn) {
-        const long long wgs = (long long)t.nblocks * g.Hkv;
-        wsplit = (int)std::max(1LL, std::min<long long>((2LL * c->n_cu + wgs - 1) / wgs, ((pb.max_keys + 31) / 32 + 1) / 2));
-        if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
-        wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
-        while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
-    }
+    // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).  Several sequences, most
+    // tasks alone in their block: no more workgroups than fit at a time (12 sequences of up to 3.4k with one interrupt of 24,
+    // 4 layers: 5 splits 1054 us, 6 splits 1092; but 200 rows after up to 16k and three single rows, 2 layers: 6 splits 1190, 7 splits 1085).
+    const long long wgs = (long long)t.nblocks * g.Hkv, slots = 2LL * c->n_cu;
+    int wsplit = (int)std::max(1LL, std::min<long long>((slots + (t.ngroups > 1 && t.ntasks < 2 * t.nblocks ? 0 : wgs - 1)) / wgs, ((pb.max_keys + 31) / 32 + 1) / 2));
+    if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
+    wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
+    while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
+    // The split count is one for all sequences of a pass, so a sequence much longer than the others is a chain of tiles that a
+    // quarter as many waves walk as in k_chunk_attn: the first kernel needs the longest chain to be no more than 20 tiles over
+    // the average load of a workgroup slot.  8B shape, 4 layers, one sequence of 16k and n of 500 tokens: n = 5 988 (wide)
+    // against 938 us, 7 1148 / 990, 11 1197 / 1060 (2 layers: 15 899 / 680, 31 1300 / 848); one of 4k and 5 812 / 830, 7 855 / 861, 11 885 / 883;
+    // 16 sequences of 512 to 4096 1062 / 1068, 8 of 128 to 4096 902 / 913.  Up to four tasks always take the first kernel (the
+    // chains are short in both and it has fewer partial results): 16k and 3 x 500 956 / 970, 16k and 2 x 500 880 / 898.
+    const int chain = ((pb.max_keys + 31) / 32 + wsplit - 1) / wsplit;
+    const bool even = t.ngroups == 1 || t.ntasks <= 4 || chain <= pb.block_tiles * g.Hkv / slots + 20;
+    const bool wide_attn = ((pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups) && even) || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
     const int dt = c->cfg.dtype;
     hipError_t e;
     {   // through pinned memory: the copy is asynchronous and the host goes on enqueuing the pass

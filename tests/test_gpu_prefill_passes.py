@@ -17,11 +17,11 @@ HEADER = 56                 # bytes of the image's description
 TOL = 1e-4
 
 
-def _planes(lm, model, n):
-    """Keys [layer, head, position, channel] and values [layer, head, tile, ...] of sequence 0, hi + lo."""
-    size = lm.kv_bytes(0)
+def _planes(lm, model, n, seq=0):
+    """Keys [layer, head, position, channel] and values [layer, head, tile, ...] of a sequence, hi + lo."""
+    size = lm.kv_bytes(seq)
     buf = torch.empty(size, dtype=torch.uint8, pin_memory=True)
-    lm.kv_swap_out(0, buf.data_ptr(), size)
+    lm.kv_swap_out(seq, buf.data_ptr(), size)
     L, H, dh = model.n_layers, model.n_kv_heads, model.head_dim
     k, v = H * n * dh, H * ((n + 31) // 32 * 32) * dh
     assert size == HEADER + L * 2 * (k + v) * 2 + model.vocab * 4
@@ -109,3 +109,38 @@ def test_shared_key_attention_on_short_interrupts(ctx, rows):
     assert _worst(ka, kb) <= TOL, _worst(ka, kb)
     assert _worst(va, vb) <= TOL, _worst(va, vb)        # runs of values that start and end inside eight positions
     assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
+
+
+# One sequence beyond 3072 keys among short ones: with fifteen others its key splits are few (a wave per task and split), with
+# three the four waves of a workgroup share a tile; a batch of alike lengths beyond 3072 keys does so too.
+@pytest.mark.parametrize("lens,intr", [([3400] + [40 + 3 * i for i in range(15)], {0: 5, 7: 24}), ([70, 3400, 33, 100], {1: 9}),
+                                       ([3400, 3390, 3100, 3333, 3200, 3401], {2: 30})])
+def test_batch_of_uneven_sequences_equals_one_at_a_time(lens, intr):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    tk = lambda n, sub: ai.uniform_tokens(ai.MASTER_SEED, 944, n, model.vocab, sub=sub)
+    blocks = [[int(t) for t in tk(intr.get(s, 0), 100 + s)] if s in intr else [] for s in range(len(lens))]
+    forced = [(7 * s + 3) % model.vocab for s in range(len(lens))]
+    lms = [pkg.AsyncLM(model, w, max_positions=3500, max_seqs=len(lens), stream=torch.cuda.Stream()) for _ in range(2)]
+    for lm in lms:
+        for s, n in enumerate(lens):
+            lm.prefill(s, tk(n, s))
+    for step in range(2):
+        lms[0].step_batch(range(len(lens)), forced=forced, interrupts=blocks if step == 0 else None)
+        for s in range(len(lens)):                                   # through the single-row kernels
+            lms[1].decode_step(s, forced_token=forced[s])
+            for t in blocks[s] if step == 0 else []:
+                lms[1].decode_step(s, forced_token=t)
+    for s, n in enumerate(lens):
+        total = n + 2 + len(blocks[s])
+        assert lms[0].seq_len(s) == lms[1].seq_len(s) == total
+        (ka, va), (kb, vb) = _planes(lms[0], model, total, s), _planes(lms[1], model, total, s)
+        assert _worst(ka, kb) <= TOL, (s, _worst(ka, kb))
+        assert _worst(va, vb) <= TOL, (s, _worst(va, vb))
+        la, lb = lms[0].logits(s), lms[1].logits(s)
+        assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL, s
+    for lm in lms:
+        lm.close()

@@ -1,0 +1,86 @@
+"""Which kernels the host code launches, and with how many workgroups, on a HIP runtime without a device (host_hip.c is
+preloaded into a child process; nothing is computed)."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+CHILD = r'''
+import ctypes as C, json, os, sys, types
+sys.path.insert(0, os.environ["ASYNCLM_ROOT"])
+import numpy as np
+import paper_2412_07017_amd as pkg
+hip = C.CDLL(os.environ["LD_PRELOAD"])
+hip.host_hip_peak.restype = hip.host_hip_used.restype = C.c_size_t
+
+class Stream:
+    cuda_stream = 4096
+
+class Matrix:
+    def __init__(self, a): self.a = a
+    def data_ptr(self): return self.a
+
+def context(max_positions, max_seqs=1, base=1 << 20, **model):
+    m = dict(n_layers=2, d_model=512, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn=512, vocab=512, rms_eps=1e-5, rope_theta=1e4, dtype="bf16")
+    kv = model.pop("kv_format", 0)
+    m.update(model)
+    w = {k: Matrix(base) for k in ("embed", "final_norm", "lm_head")}
+    w.update({k: [Matrix(base)] * m["n_layers"] for k in ("attn_norm", "wqkv", "wo", "ffn_norm", "wgate_up", "wdown")})
+    return pkg.AsyncLM(types.SimpleNamespace(**m), w, max_positions=max_positions, max_seqs=max_seqs, stream=Stream(), kv_format=kv)
+
+def tokens(n): return np.zeros(n, np.int32)
+
+def launches(call):
+    log = os.environ["HOST_HIP_LOG_FILE"]
+    if os.path.exists(log): os.remove(log)
+    os.environ["HOST_HIP_LOG"] = log
+    call()
+    del os.environ["HOST_HIP_LOG"]
+    return [(l.split()[0], *map(int, l.split()[1:])) for l in open(log)] if os.path.exists(log) else []
+
+def count(ls, name): return sum(name in l[0] for l in ls)
+'''
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    if shutil.which("gcc") is None:
+        pytest.skip("no C compiler")
+    import paper_2412_07017_amd as pkg
+    if not os.path.exists(pkg.library_path()):
+        from paper_2412_07017_amd.build import build_library
+        build_library()
+    tmp = tmp_path_factory.mktemp("host_hip")
+    so = str(tmp / "host_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", os.path.join(HERE, "host_hip.c"), "-o", so], check=True)
+
+    def run(body, **env):
+        e = dict(os.environ, LD_PRELOAD=so, ASYNCLM_ROOT=ROOT, HOST_HIP_LOG_FILE=str(tmp / "log"), **{k: str(v) for k, v in env.items()})
+        res = subprocess.run([sys.executable, "-c", CHILD + body], env=e, capture_output=True, text=True, timeout=120)
+        assert res.returncode == 0, res.stderr
+        return json.loads(res.stdout.splitlines()[-1])
+    return run
+
+
+# One sequence far longer than the others: the attention with a wave per task and split, which cuts it into four times as
+# many parts.  Alike lengths, and few tasks: the attention whose four waves share a tile.
+@pytest.mark.parametrize("lens,intr,wide", [([16000] + [512] * 15, {}, False), ([16000] + [512] * 31, {}, False), ([16000] + [500] * 5, {}, False),
+                                            ([16000] + [512] * 15, {3: 24}, False), ([16000] + [512] * 15, {0: 48}, False),
+                                            ([4000] + [300] * 15, {}, False), ([3500] * 16, {}, True), ([8000] * 4, {}, True),
+                                            ([16000, 100], {}, True), ([16000] + [500] * 3, {}, True), ([2000] * 16, {}, False),
+                                            ([600] * 4, {1: 200}, True)])
+def test_attention_of_a_batch_follows_the_longest_chain(host, lens, intr, wide):
+    got = host(f'''
+lens, intr = {lens!r}, {intr!r}
+lm = context(16400, len(lens), d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
+for s, n in enumerate(lens): lm.prefill(s, tokens(n))
+ls = launches(lambda: lm.step_batch(range(len(lens)), forced=[1] * len(lens), interrupts=[tokens(intr.get(s, 0)) for s in range(len(lens))]))
+print(json.dumps([count(ls, "k_chunk_attn_wide"), count(ls, "12k_chunk_attnE")]))
+''')
+    assert got == ([2, 0] if wide else [0, 2])
