@@ -83,7 +83,9 @@ typedef struct {
 
 /* Device pointers, borrowed: they must stay valid and unchanged until asynclm_destroy.
  * Matrices are row-major [out, in] in `dtype`; norm gains are fp32 whatever `dtype` is.
- * The six per-layer members are HOST arrays of n_layers device pointers (read during create). */
+ * The six per-layer members are HOST arrays of n_layers device pointers (read during create).
+ * Matrices that start at a multiple of 16 bytes (as every allocation does) take prompts in the longest passes; if one does
+ * not, passes hold at most 128 rows. */
 typedef struct {
     const void *embed;        /* [vocab, d_model] */
     const float *final_norm;  /* [d_model] */
@@ -131,7 +133,7 @@ int asynclm_inject_interrupt(asynclm_ctx *ctx, int32_t seq, const int32_t *token
  * row attends to its own sequence only); afterwards every sequence has valid logits for its next token.
  * seqs, forced, intr_tokens, intr_offsets (nseq + 1 ascending entries; NULL = no interrupts) are host pointers.
  * tokens_out (host, may be NULL): tokens_out[i] receives the token chosen for seqs[i]; NULL avoids the stream
- * synchronisation.  More rows than one pass holds (512) are processed in several passes.
+ * synchronisation.  More rows than one pass holds (512; 128 with unaligned matrices) are processed in several passes.
  * Everything is validated before any state changes (ASYNCLM_E_INVAL / _STATE / _CAPACITY as for the
  * single-sequence calls; a sequence may appear only once). */
 int asynclm_step_batch(asynclm_ctx *ctx, int32_t nseq, const int32_t *seqs, const int32_t *forced,

@@ -17,13 +17,13 @@ using namespace asynclm;
 // Host-side builder of the row table of one pass.
 struct PassBuilder {
     ChunkTable t{};
-    int G = 1, Hkv = 1, max_keys = 0;
+    int G = 1, Hkv = 1, max_keys = 0, batch_rows = CHUNK_BATCH_ROWS;
     long long block_tiles = 0;          // key tiles of 32 over all task blocks
     void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = 0; max_keys = 0; block_tiles = 0; }
     int tiles_of(int n) const { return (G * n + 31) / 32; }
     // batched steps: rows, attention tasks, and the attention's partial results (task x kv head x at least 4 key splits) all fit one pass
     bool fits(int n) const {
-        return t.rows + n <= CHUNK_BATCH_ROWS && t.ntasks + tiles_of(n) <= CHUNK_BATCH_TASKS &&
+        return t.rows + n <= batch_rows && t.ntasks + tiles_of(n) <= CHUNK_BATCH_TASKS &&
                (long long)(t.ntasks + tiles_of(n)) * Hkv * 4 <= CHUNK_ATTN_MAX_UNITS;
     }
     // Appends a group of n rows to sequence `seq` (length before: pos0).  forced: see ChunkGroup; `rest` holds the
@@ -81,7 +81,7 @@ struct asynclm_ctx {
     DecodeBuffers b{};
     ChunkBuffers cb{};
     bool chunk_ok = false;              // the matrix-core append path supports this model
-    int pass_rows = CHUNK_BATCH_ROWS;   // rows that one of its passes can hold (CHUNK_BATCH_ROWS .. CHUNK_MAX)
+    int pass_rows = CHUNK_BATCH_ROWS;   // rows that one of its passes can hold (CHUNK_BATCH_ROWS .. CHUNK_MAX; fewer: PASS_ROWS_UNALIGNED)
     RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
@@ -707,6 +707,15 @@ int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
 
 static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows);
 
+// The product of more than 128 rows moves the weights from memory straight to LDS, 16 bytes a lane, which is only known to work
+// on addresses that are multiples of 16; the products of up to 128 rows load them to registers, from any address.
+constexpr int PASS_ROWS_UNALIGNED = 128;
+static bool weights_aligned(const asynclm_config* cfg, const asynclm_weights* w) {
+    uintptr_t bits = 0;     // (the output head has at most 128 rows)
+    for (int l = 0; l < cfg->n_layers; ++l) bits |= (uintptr_t)w->wqkv[l] | (uintptr_t)w->wo[l] | (uintptr_t)w->wgate_up[l] | (uintptr_t)w->wdown[l];
+    return bits % 16 == 0;
+}
+
 extern "C" {
 
 int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream) {
@@ -811,6 +820,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         // attention fit.
         c->pass_rows = std::max(CHUNK_BATCH_ROWS, std::min({max_rows, g.max_pos, CHUNK_ATTN_MAX_UNITS * 32 / g.Hq / 32 * 32,
                                                             CHUNK_MAX_TASKS * 32 / (g.Hq / g.Hkv)}));
+        if (!weights_aligned(cfg, w)) c->pass_rows = c->pass.batch_rows = PASS_ROWS_UNALIGNED;
         const size_t M = c->pass_rows, MB = CHUNK_BATCH_ROWS, qd = (size_t)g.Hq * g.dh;
         // split-K partial planes: every split of the widest product for passes of up to 96 rows (bound by the weight
         // stream: many splits), two for the largest pass (bound by the matrix cores: few), the output head for one
@@ -1050,7 +1060,7 @@ int asynclm_step_batch(asynclm_ctx* c, int32_t nseq, const int32_t* seqs, const 
         return ASYNCLM_OK;
     }
 
-    // One weight pass per CHUNK_BATCH_ROWS rows: groups are packed in the order given; a group that does not fit is
+    // One weight pass per batch_rows rows: groups are packed in the order given; a group that does not fit is
     // continued in the next pass (its later rows see its earlier ones through the cache).
     for (int i = 0; i < nseq; ++i)
         if (forced_of(i) < 0) HIPCK(c, refresh_choice(c, seqs[i]));
@@ -1078,8 +1088,8 @@ int asynclm_step_batch(asynclm_ctx* c, int32_t nseq, const int32_t* seqs, const 
         int done = 0;                       // rows of this sequence already placed (the chosen token is row 0)
         const int total = 1 + k;
         while (done < total) {
-            int space = CHUNK_BATCH_ROWS - pb.t.rows;
-            if (space == 0 || !pb.fits(1)) { const int r = flush(); if (r) return r; space = CHUNK_BATCH_ROWS; }
+            int space = pb.batch_rows - pb.t.rows;
+            if (space == 0 || !pb.fits(1)) { const int r = flush(); if (r) return r; space = pb.batch_rows; }
             int n = std::min(space, total - done);
             while (n > 1 && !pb.fits(n)) --n;
             const int pos0 = c->len[q];     // rows placed by earlier passes are already counted

@@ -144,3 +144,34 @@ def test_batch_of_uneven_sequences_equals_one_at_a_time(lens, intr):
         assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL, s
     for lm in lms:
         lm.close()
+
+
+def test_weights_at_eight_bytes_past_an_alignment():
+    """The same weights at addresses that are no multiple of 16: passes of at most 128 rows, through registers."""
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=512, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=640, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+
+    def moved(t):
+        flat = torch.empty(t.numel() + 4, dtype=t.dtype, device=t.device)
+        flat[4:] = t.reshape(-1)
+        return flat[4:].view(t.shape)
+
+    shifted = {k: ([moved(t) for t in v] if isinstance(v, (list, tuple)) else moved(v)) if "norm" not in k else v for k, v in w.items()}
+    assert shifted["wqkv"][0].data_ptr() % 16 == 8
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 945, 900, model.vocab)
+    got = []
+    for ws in (w, shifted):
+        lm = pkg.AsyncLM(model, ws, max_positions=1000, max_seqs=2, stream=torch.cuda.Stream())
+        lm.prefill(0, toks[:600])
+        lm.prefill(1, toks[:7])
+        lm.inject_interrupt(0, toks[600:650])
+        lm.step_batch([0, 1], forced=[1, 2], interrupts=[toks[650:800], toks[800:830]])
+        lm.decode_step(0, forced_token=5)
+        got.append((*_planes(lm, model, 802), lm.logits(0), lm.logits(1)))
+        lm.close()
+    (ka, va, la, ma), (kb, vb, lb, mb) = got
+    assert _worst(ka, kb) <= TOL and _worst(va, vb) <= TOL
+    assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL and np.linalg.norm(ma - mb) / np.linalg.norm(mb) <= TOL

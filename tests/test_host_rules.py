@@ -84,3 +84,16 @@ ls = launches(lambda: lm.step_batch(range(len(lens)), forced=[1] * len(lens), in
 print(json.dumps([count(ls, "k_chunk_attn_wide"), count(ls, "12k_chunk_attnE")]))
 ''')
     assert got == ([2, 0] if wide else [0, 2])
+
+
+# A matrix that does not start at a multiple of 16 bytes: no pass reaches the product that loads weights straight to LDS
+@pytest.mark.parametrize("off,big", [(0, True), (8, False), (2, False), (16, True)])
+def test_unaligned_weights_stay_off_the_loads_to_lds(host, off, big):
+    got = host(f'''
+lm = context(2100, 4, base=(1 << 20) + {off})
+a = launches(lambda: lm.prefill(0, tokens(1300)))
+b = launches(lambda: [lm.prefill(s, tokens(3)) for s in (1, 2, 3)] + [lm.step_batch(range(4), interrupts=[tokens(n) for n in (200, 100, 50, 140)])])
+print(json.dumps([count(a, "k_chunk_gemm_big"), count(b, "k_chunk_gemm_big"), count(a, "k_chunk_embed_norm"), lm.seq_len(0), lm.seq_len(3)]))
+''')
+    assert (got[0] > 0) == big and (got[1] > 0) == big
+    assert got[2] == (1 if big else 11) and got[3:] == [1501, 144]
