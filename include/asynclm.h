@@ -198,8 +198,8 @@ int asynclm_reset(asynclm_ctx *ctx, int32_t seq);
 int asynclm_synchronize(asynclm_ctx *ctx);
 
 /* Tuning knobs; all have working defaults.  Unknown names give ASYNCLM_E_INVAL.
- *   "chunk"        rows processed per forward pass by prefill / inject (1 .. 512); 1 = token by token
- *                  through the decode kernels.  Without it passes are as long as the context's buffers allow: up to
+ *   "chunk"        largest number of rows per forward pass of prefill / inject (1 .. 512); 1 = token by token
+ *                  through the decode kernels.  0 (default): passes are as long as the context's buffers allow, up to
  *                  2048 rows (512 .. 2048, by max_positions and head count) where the matrix-core append path applies
  *                  (bf16 model, paired cache, head_dim 128, d_model and ffn multiples of 128); other models take at
  *                  most 8 rows per pass, through the vector units.

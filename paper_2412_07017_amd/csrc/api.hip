@@ -111,7 +111,7 @@ struct asynclm_ctx {
     std::vector<int> batch_owner;
 
     // options
-    int opt_chunk = 1, opt_graph = 1, opt_attn_split = 0, opt_chunk_split = 0, opt_fused = 0, opt_attn_mfma_min = 1;
+    int opt_chunk = CHUNK_MAX /* as long as the buffers allow */, opt_graph = 1, opt_attn_split = 0, opt_chunk_split = 0, opt_fused = 0, opt_attn_mfma_min = 1;
     int opt_pipeline = 0;
 
     std::map<int, hipGraphExec_t> graphs;   // captured decoding steps by graph_key(), all instantiated by rebuild_graphs()
@@ -776,7 +776,6 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         g.kv_vt_offset = c->chunk_ok ? row_planes * plane : 0;
         g.kv_layer_stride = (row_planes + (c->chunk_ok ? 2 : 0)) * plane;
         g.kv_seq_stride = g.kv_layer_stride * cfg->n_layers;
-        c->opt_chunk = c->chunk_ok ? CHUNK_MAX : ROWS_MAX;
     }
     c->len.assign(cfg->max_seqs, 0);
     c->nban.assign(cfg->max_seqs, 0);
@@ -1299,7 +1298,7 @@ int asynclm_synchronize(asynclm_ctx* c) {
 
 int asynclm_set_option(asynclm_ctx* c, const char* name, int32_t value) {
     if (!c || !name) return ASYNCLM_E_INVAL;
-    if (!std::strcmp(name, "chunk")) { if (value < 1 || value > CHUNK_BATCH_ROWS) return ASYNCLM_E_INVAL; c->opt_chunk = value; return ASYNCLM_OK; }
+    if (!std::strcmp(name, "chunk")) { if (value < 0 || value > CHUNK_BATCH_ROWS) return ASYNCLM_E_INVAL; c->opt_chunk = value ? value : CHUNK_MAX; return ASYNCLM_OK; }
     if (!std::strcmp(name, "chunk_split")) { if (value < 0 || value > CHUNK_GEMM_MAX_SPLIT) return ASYNCLM_E_INVAL; c->opt_chunk_split = value; return ASYNCLM_OK; }
     // the options below change the launch geometry of a decoding step: its captured graphs are built again (this call allocates)
     auto regraph = [&]() -> int {

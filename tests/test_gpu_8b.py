@@ -156,8 +156,9 @@ def test_step_stamps_leave_the_step_unchanged_and_are_in_order(trunc4):
 
 @pytest.mark.timeout(600)
 def test_append_chunk_sizes_agree_with_oracle_and_each_other(trunc4):
-    """The matrix-core append path for every chunk shape (ragged tails, one to three row tiles through the
-    weight-streaming product, four to eleven through the wide one with one or two row blocks, split-K factors)
+    """The matrix-core append path for every chunk shape (ragged tails, one row tile through the weight-streaming product,
+    two through the one whose waves split the k-steps, three and four through the wide one, five to eleven through the
+    large one with one or two row blocks, split-K factors)
     against the from-scratch oracle, and against the token-by-token path of the decode kernels."""
     import paper_2412_07017_amd as pkg
     wl, model, w_dev, w_cpu, spec = trunc4

@@ -236,12 +236,12 @@ def test_8b_full_depth_full_size_invariants_of_the_method():
     agree(merged, "merged token + interrupt pass")
     lm.reset(2)
     lm.prefill(1, history)                                  # stateless variant: the whole stream again
-    agree(lm.logits(1), "re-prefill in 512-row passes")
+    agree(lm.logits(1), "re-prefill of the whole stream")
     lm.reset(1)
     lm.set_option("chunk", 1)                               # the whole stream through the single-row kernels
     lm.prefill(1, history)
     agree(lm.logits(1), "token-by-token append")
-    lm.set_option("chunk", 512)
+    lm.set_option("chunk", 0)
     lm.reset(1)
     # trap: swap out, drop, swap in on another slot
     nbytes = lm.kv_bytes(0)

@@ -97,3 +97,22 @@ print(json.dumps([count(a, "k_chunk_gemm_big"), count(b, "k_chunk_gemm_big"), co
 ''')
     assert (got[0] > 0) == big and (got[1] > 0) == big
     assert got[2] == (1 if big else 11) and got[3:] == [1501, 144]
+
+
+def test_pass_size_option_bounds_a_pass_and_can_be_taken_back(host):
+    got = host('''
+out = []
+for lm, kernel, n in ((context(2100), "k_chunk_embed_norm", 1301), (context(2100, dtype="fp32", head_dim=64), "k_rows_embed", 34)):
+    for value in (None, 512, 5, 1, 0):
+        if value is not None: lm.set_option("chunk", value)
+        lm.reset(0)
+        out.append(count(launches(lambda: lm.prefill(0, tokens(n))), kernel))
+    for bad in (-1, 513):
+        try: lm.set_option("chunk", bad); out.append("taken")
+        except pkg.AsyncLMError as e: out.append(e.code)
+print(json.dumps(out))
+''')
+    # 1301 tokens: 2 passes of 512 and one of 277; 260 of five and the last token alone; 34: four of eight and one of two, or
+    # six of five and one of four
+    assert got[:7] == [1, 3, 260, 0, 1, -1, -1]
+    assert got[7:] == [5, 5, 7, 0, 5, -1, -1]
