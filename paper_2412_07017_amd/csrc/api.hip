@@ -705,7 +705,7 @@ int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
 
 }  // namespace
 
-static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows);
+static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows, int* pass_rows);
 
 // The product of more than 128 rows moves the weights from memory straight to LDS, 16 bytes a lane, which is only known to work
 // on addresses that are multiples of 16; the products of up to 128 rows load them to registers, from any address.
@@ -721,16 +721,18 @@ extern "C" {
 int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream) {
     if (out) *out = nullptr;
     if (!out || !cfg || !w) return ASYNCLM_E_INVAL;
-    // where memory is too short for the buffers of large passes, the smallest ones do
-    const int r = create_ctx(out, cfg, w, hip_stream, CHUNK_MAX);
-    if (r != ASYNCLM_E_NOMEM) return r;
+    // where memory is too short for the buffers of large passes, the smallest ones do; what does not fit may also be a graph or
+    // another object of the runtime, which reports a device error
+    int pass_rows = 0;
+    const int r = create_ctx(out, cfg, w, hip_stream, CHUNK_MAX, &pass_rows);
+    if (r == ASYNCLM_OK || pass_rows <= CHUNK_BATCH_ROWS) return r;
     (void)hipGetLastError();
-    return create_ctx(out, cfg, w, hip_stream, CHUNK_BATCH_ROWS);
+    return create_ctx(out, cfg, w, hip_stream, CHUNK_BATCH_ROWS, &pass_rows);
 }
 
 }  // extern "C"
 
-static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows) {
+static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream, int max_rows, int* pass_rows) {
     if (!config_ok(cfg)) return ASYNCLM_E_INVAL;
     if (!w->embed || !w->final_norm || !w->lm_head || !w->attn_norm || !w->wqkv || !w->wo || !w->ffn_norm ||
         !w->wgate_up || !w->wdown)
@@ -820,6 +822,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         c->pass_rows = std::max(CHUNK_BATCH_ROWS, std::min({max_rows, g.max_pos, CHUNK_ATTN_MAX_UNITS * 32 / g.Hq / 32 * 32,
                                                             CHUNK_MAX_TASKS * 32 / (g.Hq / g.Hkv)}));
         if (!weights_aligned(cfg, w)) c->pass_rows = c->pass.batch_rows = PASS_ROWS_UNALIGNED;
+        *pass_rows = c->pass_rows;
         const size_t M = c->pass_rows, MB = CHUNK_BATCH_ROWS, qd = (size_t)g.Hq * g.dh;
         // split-K partial planes: every split of the widest product for passes of up to 96 rows (bound by the weight
         // stream: many splits), two for the largest pass (bound by the matrix cores: few), the output head for one

@@ -116,3 +116,23 @@ print(json.dumps(out))
     # six of five and one of four
     assert got[:7] == [1, 3, 260, 0, 1, -1, -1]
     assert got[7:] == [5, 5, 7, 0, 5, -1, -1]
+
+
+# Memory too short for the buffers of 2048-row passes: the context is created with those of 512 rows, whether an allocation
+# fails or the graphs of the decoding steps find no room; memory too short for these as well: an error, and nothing is left
+def test_create_with_little_memory(host):
+    full = host("context(4096); print(json.dumps(hip.host_hip_peak()))")
+    body = '''
+try:
+    lm = context(4096)
+    n = count(launches(lambda: lm.prefill(0, tokens(1300))), "k_chunk_embed_norm")
+    lm.close()
+except pkg.AsyncLMError as e: n = e.code
+print(json.dumps([n, hip.host_hip_used()]))
+'''
+    assert host(body) == [1, 0]
+    assert host(body, HOST_HIP_BUDGET=full) == [1, 0]
+    assert host(body, HOST_HIP_BUDGET=full - 1) == [3, 0]
+    assert host(body, HOST_HIP_GRAPHS=full - 1) == [3, 0]
+    assert host(body, HOST_HIP_BUDGET=full // 4) == [-4, 0]
+    assert host(body, HOST_HIP_GRAPHS=full // 4) == [-5, 0]
