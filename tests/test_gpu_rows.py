@@ -1,7 +1,6 @@
 """GPU: models outside the matrix-core append path take prompts and interrupts several rows per pass through the vector-unit
 kernels.  Each case is compared with the same stream taken token by token (option chunk = 1) and, for fp32, with the oracle in
-64 bits: one shape per kernel variant (one or two row pairs at a time, vectors that fit LDS at once or in segments), row counts
-around a full pass, contexts on both sides of one key split."""
+64 bits: a shape for every kernel variant, row counts around a full pass, contexts on both sides of one key split."""
 import numpy as np
 import pytest
 import torch
@@ -25,12 +24,22 @@ def _model(d, hq, hkv, dh, ffn, dtype):
                        rope_theta=10000.0, dtype=dtype)
 
 
+# Every variant of the two kernels is taken by some product of these models (tests/test_host_rules.py checks it): k_rows_small
+# (at most 1024 row pairs and 256 loads of 16 bytes per row), else k_rows_gemv with one row pair per wave at a time (up to 2048
+# pairs) or two, the vectors in LDS as a whole (up to 4096 columns) or in segments.  On 256 compute units:
 CASES = [
-    (FP32, _model(256, 4, 4, 64, 688, "fp32")),        # a wave per row pair, one segment, last rows of a tile
-    (FP32, _model(136, 4, 2, 128, 4104, "fp32")),      # 4104 gate rows: two pairs at a time, odd counts; down: 4104 columns, two segments
-    (FP32, _model(2056, 2, 1, 64, 4104, "fp32")),      # down: two pairs at a time and two segments
-    (PAIR, _model(520, 8, 2, 64, 1032, "bf16")),       # paired cache, head_dim 64
-    (BF16, _model(264, 8, 1, 128, 8200, "bf16")),      # single-plane cache, eight heads per kv head, three segments
+    (FP32, _model(256, 4, 4, 64, 688, "fp32")),        # all products small
+    (FP32, _model(136, 4, 2, 128, 4104, "fp32")),      # QKV, O small; gate/up two pairs, odd counts; down one pair, segments
+    (FP32, _model(2056, 2, 1, 64, 4104, "fp32")),      # QKV, O one pair; gate/up two pairs; down one pair, segments
+    (FP32, _model(264, 32, 32, 64, 1032, "fp32")),     # QKV two pairs; O, gate/up, down one pair or small
+    (FP32, _model(4104, 4, 4, 64, 264, "fp32")),       # QKV, gate/up one pair, segments; O, down two pairs
+    (FP32, _model(4104, 32, 8, 128, 4104, "fp32")),    # QKV, gate/up (two rounds per wave), down two pairs, segments; O two pairs
+    (PAIR, _model(520, 8, 2, 64, 1032, "bf16")),       # paired cache, head_dim 64: gate/up one pair, the others small
+    (PAIR, _model(264, 32, 32, 64, 264, "bf16")),      # QKV two pairs; O small with four loads per row
+    (PAIR, _model(4104, 4, 4, 64, 264, "bf16")),       # QKV, gate/up one pair, segments; O, down two pairs
+    (BF16, _model(264, 8, 1, 128, 8200, "bf16")),      # single-plane cache, eight heads per kv head; down one pair, three segments
+    (BF16, _model(2056, 2, 1, 64, 2056, "bf16")),      # QKV, O, down one pair; gate/up two pairs
+    (BF16, _model(4104, 32, 8, 128, 4104, "bf16")),    # QKV, gate/up (two rounds per wave), down two pairs, segments; O two pairs
 ]
 
 
@@ -38,7 +47,7 @@ def _rel(a, b):
     return float(np.linalg.norm(a.astype(np.float64) - b) / np.linalg.norm(b))
 
 
-@pytest.mark.parametrize("kind,model", CASES, ids=["%s-d%d-f%d" % (k, m.d_model, m.ffn) for k, m in CASES])
+@pytest.mark.parametrize("kind,model", CASES, ids=["%s-d%d-h%d-f%d" % (k, m.d_model, m.n_q_heads, m.ffn) for k, m in CASES])
 def test_rows_of_a_pass_equal_token_by_token(kind, model):
     import paper_2412_07017_amd as pkg
     w = ai.make_weights(model, device=torch.device("cuda:0"))

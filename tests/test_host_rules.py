@@ -136,3 +136,24 @@ print(json.dumps([n, hip.host_hip_used()]))
     assert host(body, HOST_HIP_GRAPHS=full - 1) == [3, 0]
     assert host(body, HOST_HIP_BUDGET=full // 4) == [-4, 0]
     assert host(body, HOST_HIP_GRAPHS=full // 4) == [-5, 0]
+
+
+def test_every_variant_of_the_row_kernels_has_a_case(host):
+    from test_gpu_rows import BF16, CASES
+    models = [dict(m.__dict__, kv_format=1 if kind == BF16 else 0) for kind, m in CASES]
+    names = set(host(f'''
+names = set()
+for m in {models!r}:
+    lm = context(64, **m)
+    names |= {{l[0] for l in launches(lambda: lm.prefill(0, tokens(8)))}}
+    lm.close()
+print(json.dumps(sorted(names)))
+'''))
+    for t in "ft":                                      # fp32, bf16 (unsigned short)
+        for epi in (1, 2, 3):                           # residual, SwiGLU, QKV
+            for pairs in (1, 2):
+                for seg in (0, 1):
+                    want = f"k_rows_gemvI{t}Li{epi}ELi{pairs}ELb{seg}E"
+                    assert any(want in n for n in names), want
+        for loads in (1, 2, 4):
+            assert any(f"k_rows_smallI{t}" in n and f"ELi{loads}EEE" in n for n in names), (t, loads)
