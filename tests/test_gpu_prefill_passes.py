@@ -59,6 +59,7 @@ def test_large_passes_equal_passes_of_32_rows(n, ffn, heads, kv):
         lm.close()
     (ka, va, la), (kb, vb, lb) = got
     assert np.isfinite(ka).all() and np.isfinite(va).all() and np.isfinite(la).all()
+    assert not np.array_equal(ka[1], kb[1])              # the passes were not the same: sums in another order
     assert _worst(ka, kb) <= TOL, _worst(ka, kb)
     tail = n % 32                                        # a last tile of values that is part empty: compare as a whole
     assert _worst(va, vb) <= TOL, (_worst(va, vb), tail)
@@ -67,22 +68,82 @@ def test_large_passes_equal_passes_of_32_rows(n, ffn, heads, kv):
 
 def test_pass_size_option_still_bounds_a_pass():
     import paper_2412_07017_amd as pkg
-    model = ModelConfig(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
+    model = ModelConfig(n_layers=2, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
                         rope_theta=10000.0, dtype="bf16")
     w = ai.make_weights(model, device=torch.device("cuda:0"))
     torch.cuda.synchronize()
     toks = ai.uniform_tokens(ai.MASTER_SEED, 942, 1100, model.vocab)
+    lm = pkg.AsyncLM(model, w, max_positions=1200, stream=torch.cuda.Stream())
     out = []
-    for chunk in (None, 512):
-        lm = pkg.AsyncLM(model, w, max_positions=1200, stream=torch.cuda.Stream())
-        if chunk:
-            lm.set_option("chunk", chunk)
+    for chunk in (0, 300, 512, 0):
+        lm.set_option("chunk", chunk)
         with pytest.raises(pkg.AsyncLMError):
             lm.set_option("chunk", 513)
+        lm.reset(0)
         lm.prefill(0, toks)
-        out.append(lm.logits(0))
+        out.append((*_planes(lm, model, 1100), lm.logits(0)))
+    lm.close()
+    for keys, vals, logits in out[1:]:
+        assert _worst(keys, out[0][0]) <= TOL and _worst(vals, out[0][1]) <= TOL
+        assert np.linalg.norm(logits - out[0][2]) / np.linalg.norm(out[0][2]) <= TOL
+    # a pass of 300 rows sums in another order than one of 512 or 1100; the default again is the default
+    assert not np.array_equal(out[0][0][1], out[1][0][1]) and not np.array_equal(out[1][0][1], out[2][0][1])
+    assert all(np.array_equal(a, b) for a, b in zip(out[0], out[3]))
+
+
+# The last layer of a pass over one sequence forms keys and values of all rows and goes on with the last row alone: with one layer
+# that is the whole pass.  Prompt, interrupt, and an interrupt behind a chosen token, against the single-row kernels.
+@pytest.mark.parametrize("n,kv,layers", [(2, 1, 1), (31, 4, 1), (33, 2, 1), (100, 4, 1), (129, 4, 1), (700, 1, 1), (65, 4, 2)])
+def test_pass_that_ends_with_its_last_row(n, kv, layers):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=layers, d_model=512, n_q_heads=4, n_kv_heads=kv, head_dim=128, ffn=384, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 946, 3 * n, model.vocab)
+    lms = [pkg.AsyncLM(model, w, max_positions=3 * n + 8, stream=torch.cuda.Stream()) for _ in range(2)]
+    lms[1].set_option("chunk", 1)
+    for i, call in enumerate(("prefill", "inject", "batch")):
+        blk = toks[i * n:(i + 1) * n]
+        got = []
+        for lm in lms:
+            if call == "prefill":
+                lm.prefill(0, blk)
+            elif call == "inject":
+                lm.inject_interrupt(0, blk)
+            elif lm is lms[0]:
+                assert list(lm.step_batch([0], forced=[9], interrupts=[blk])) == [9]
+            else:
+                lm.decode_step(0, forced_token=9)
+                lm.inject_interrupt(0, blk)
+            got.append((*_planes(lm, model, lm.seq_len(0)), lm.logits(0)))
+        (ka, va, la), (kb, vb, lb) = got
+        assert _worst(ka, kb) <= TOL and _worst(va, vb) <= TOL, (call, _worst(ka, kb), _worst(va, vb))
+        assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL, call
+        assert lms[0].peek_choice(0) == int(np.argmax(la))
+    for lm in lms:
         lm.close()
-    assert np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1]) <= TOL
+
+
+# Parts of K forced by option on a pass of more than 512 rows, where the partial planes hold fewer than asked for
+@pytest.mark.parametrize("split", [1, 2, 3, 5, 8])
+def test_forced_split_on_a_long_pass(split):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=1152, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 947, 1700, model.vocab)
+    got = []
+    for opt in (split, 0):
+        lm = pkg.AsyncLM(model, w, max_positions=1800, stream=torch.cuda.Stream())
+        lm.set_option("chunk_split", opt)
+        lm.prefill(0, toks)
+        got.append((*_planes(lm, model, 1700), lm.logits(0)))
+        lm.close()
+    (ka, va, la), (kb, vb, lb) = got
+    assert _worst(ka, kb) <= TOL and _worst(va, vb) <= TOL
+    assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
 
 
 # k_chunk_attn_wide with every number of live waves in a block and of key splits: 1 to 9 query tiles over contexts below and
