@@ -26,8 +26,8 @@ struct PassBuilder {
         return t.rows + n <= batch_rows && t.ntasks + tiles_of(n) <= CHUNK_BATCH_TASKS &&
                (long long)(t.ntasks + tiles_of(n)) * Hkv * 4 <= CHUNK_ATTN_MAX_UNITS;
     }
-    // Appends a group of n rows to sequence `seq` (length before: pos0).  forced: see ChunkGroup; `rest` holds the
-    // tokens of the rows that are not chosen on the device (n of them if forced == -2, else n - 1).
+    // Appends a group of n rows to sequence `seq` (length before: pos0).  forced: the first row's token if >= 0, -1: the greedy
+    // token of the sequence's logits, -2: `rest` holds the tokens of all n rows (else of the n - 1 behind the first).
     void add(int seq, int pos0, int n, int forced, const int32_t* rest, bool want_head) {
         const int row0 = t.rows;
         for (int r = 0; r < n; ++r) {
@@ -38,7 +38,7 @@ struct PassBuilder {
         }
         ChunkGroup& Gp = t.group[t.ngroups++];
         Gp = ChunkGroup{};
-        Gp.seq = seq; Gp.row0 = row0; Gp.n = n; Gp.pos0 = pos0; Gp.forced = forced; Gp.head = want_head ? t.nhead++ : -1;
+        Gp.seq = seq; Gp.row0 = row0; Gp.n = n; Gp.pos0 = pos0; Gp.head = want_head ? t.nhead++ : -1;
         for (int tile = 0; tile < tiles_of(n); ++tile) {
             if (tile % 4 == 0) { t.block[t.nblocks++] = ChunkTaskBlock{t.ntasks, std::min(4, tiles_of(n) - tile)}; block_tiles += (pos0 + n + 31) / 32; }
             ChunkTask& T = t.task[t.ntasks++];
@@ -607,7 +607,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     for (int l = 0; l < c->cfg.n_layers; ++l) {
         void* kvl = kv_layer_ptr(c, l);
         if (l == 0) { if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_embed_norm(c->embed, cb, c->attn_norm[0], rows, c->b, g, s); }))) return e; }
-        else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, true, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
+        else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
         if (tail && l == c->cfg.n_layers - 1) {
             const char* wkv = (const char*)c->wqkv[l] + (size_t)qd * g.d * elem_bytes(c);
             if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(wkv, 2 * g.Hkv * g.dh, g.d, cb.nrm_hi, cb.nrm_lo, cb, kv_plan, MT, s); }))) return e;
@@ -620,7 +620,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
         if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, wsplit, t.ntasks, t.nblocks, g, s); }))) return e; }
         else if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn(cb, kvl, asplit, t.ntasks, g, s); }))) return e;
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb, sp.o, MT, s); }))) return e;
-        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, true, sp.o.s, MT, c->ffn_norm[l], rows, g, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, sp.o.s, MT, c->ffn_norm[l], rows, g, s); }))) return e;
         if (sp.gu.s == 1) {                 // no split-K: the SwiGLU is the product's epilogue
             if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, MT, s); }))) return e;
         } else {
@@ -634,7 +634,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
         const int MTh = (t.nhead + 31) / 32;
         if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_head_rows(cb, sp.down.s, MT, c->final_norm, t.ngroups, g, s); }))) return e;
         if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, GemmPlan{1, 4}, MTh, s); }))) return e;
-        if ((e = run(c, KC_ARGMAX, [&] { return launch_chunk_logits(cb, MTh, c->logits, c->b, t.ngroups, g, s); }))) return e;
+        if ((e = run(c, KC_ARGMAX, [&] { return launch_chunk_logits(cb, c->logits, c->b, t.ngroups, g, s); }))) return e;
     } else if (!tail) {
         for (int gi = 0; gi < t.ngroups; ++gi) {
             if (t.group[gi].head < 0) continue;
@@ -825,8 +825,9 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         *pass_rows = c->pass_rows;
         const size_t M = c->pass_rows, MB = CHUNK_BATCH_ROWS, qd = (size_t)g.Hq * g.dh;
         // split-K partial planes: every split of the widest product for passes of up to 96 rows (bound by the weight
-        // stream: many splits), two for the largest pass (bound by the matrix cores: few), the output head for one
-        // row per group
+        // stream: many splits), two of it for 512 rows, one of the widest product other than gate/up for the longest pass
+        // (more than 128 rows write gate/up through SwiGLU, unless split), the output head for one row per group; larger
+        // splits as far as pick_gemm_plan finds room here
         const size_t wmax = std::max(std::max((size_t)2 * g.F, (size_t)(g.Hq + 2 * g.Hkv) * g.dh), (size_t)g.d);
         const size_t wunsplit = std::max((size_t)(g.Hq + 2 * g.Hkv) * g.dh, (size_t)g.d);       // the widest product without SwiGLU
         cb.part_capacity = std::max({(size_t)96 * CHUNK_GEMM_MAX_SPLIT * wmax, 2 * MB * wmax, M * wunsplit, (size_t)CHUNK_MAX_GROUPS * g.V});
@@ -835,7 +836,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         const size_t qn = (size_t)g.Hkv * cb.q_cols * g.dh;
         c->pass.G = g.Hq / g.Hkv; c->pass.Hkv = g.Hkv;
         ALLOC(cb.tab_mem, CHUNK_TAB_BYTES);
-                ALLOC(cb.x, M * g.d);
+        ALLOC(cb.x, M * g.d);
         ALLOC(cb.nrm_hi, M * g.d); ALLOC(cb.nrm_lo, M * g.d);
         ALLOC(cb.att_hi, M * qd); ALLOC(cb.att_lo, M * qd);
         ALLOC(cb.act_hi, M * g.F); ALLOC(cb.act_lo, M * g.F);

@@ -96,7 +96,7 @@ __device__ __forceinline__ float row_gather(const float* __restrict__ xr, const 
                 gn[hf * HU + u] = reinterpret_cast<const float4*>(gain)[i4];
 #pragma unroll
                 for (int s = 0; s < SM; ++s)
-                    p[u][s] = Pr ? reinterpret_cast<const float4*>(Pr + (size_t)min(s, S - 1) * s_stride)[i4] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    p[u][s] = reinterpret_cast<const float4*>(Pr + (size_t)min(s, S - 1) * s_stride)[i4];
             }
 #pragma unroll
             for (int u = 0; u < HU; ++u) {
@@ -139,7 +139,7 @@ __device__ __forceinline__ void row_emit(const float4 (&v)[ROW_VEC_MAX], float s
     }
 }
 
-// x[m] += sum_s P[s][m]  (if P), then RMSNorm with `gain` -> tiled bf16 hi/lo planes.
+// x[m] += sum_s P[s][m], then RMSNorm with `gain` -> tiled bf16 hi/lo planes.
 // One workgroup per row; P has row stride n_stride and split stride s_stride (elements).
 template <int SM>
 __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x, const float* __restrict__ P, int S,
@@ -150,12 +150,10 @@ __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x,
     const int m = row_of_workgroup(gridDim.x), tid = threadIdx.x, d4 = d >> 2;
     float* xr = x + (size_t)m * d;
     float4 v[ROW_VEC_MAX], gn[ROW_VEC_MAX];
-    const float ss = row_gather<SM>(xr, P ? P + (size_t)m * n_stride : nullptr, S, s_stride, d4, tid, gain, v, gn, red);
-    if (P) {
+    const float ss = row_gather<SM>(xr, P + (size_t)m * n_stride, S, s_stride, d4, tid, gain, v, gn, red);
 #pragma unroll
-        for (int u = 0; u < ROW_VEC_MAX; ++u)
-            if (tid + 256 * u < d4) reinterpret_cast<float4*>(xr)[tid + 256 * u] = v[u];
-    }
+    for (int u = 0; u < ROW_VEC_MAX; ++u)
+        if (tid + 256 * u < d4) reinterpret_cast<float4*>(xr)[tid + 256 * u] = v[u];
     row_emit(v, rsqrtf(ss / (float)d + eps), gn, d, tid, m, out_hi, out_lo);
 }
 
@@ -418,25 +416,23 @@ __global__ __launch_bounds__(256) void k_chunk_rope_kv(const float* __restrict__
 // ---------------------------------------------------------------------------------------------
 // Which kernel takes a pass (launch_chunk_gemm): up to 32 rows this one (bound by the weight stream, a wave per 32
 // weight rows); 33-64 rows k_chunk_gemm_ks (the waves split the k-steps); 65-128 rows k_chunk_gemm_wide, a wave
-// per row tile; more rows k_chunk_gemm_big.  The template serves any MT <= 3; MT = 1 is used.
+// per row tile; more rows k_chunk_gemm_big.
 // Workgroup = 4 waves on 128 weight rows (32 per wave) and one contiguous run of 128-element k-blocks
 // (the S workgroups of a row tile split K and write separate partial planes that the consumer adds in
 // a fixed order: no atomics, results are bit-reproducible).
-//  * weights stream from HBM through a register ring of GemmRing<MT>::N tiles per wave (one tile = the wave's
+//  * weights stream from HBM through a register ring of GEMM_RING tiles per wave (one tile = the wave's
 //    32 rows x 128 columns, loaded 4 rows x 256 contiguous bytes per instruction), are transposed into
 //    operand order through a wave-private XOR-swizzled LDS tile and multiplied;
-//  * the activations of a k-block (all rows, hi and lo planes: MT x 16 KiB) are shared by the four waves
+//  * the activations of a k-block (32 rows, hi and lo planes: 16 KiB) are shared by the four waves
 //    through a double-buffered LDS tile that the workgroup fills one block ahead.
 // The loop body has no conditional code around loads or their uses: the prefetches past the end of a run
 // re-read its last block (cache hits).  The compiler sinks loads into conditional users
 // and then waits for each load right before its product; the scheduling barriers keep the instruction
 // scheduler from doing the same within the straight-line body.
 
-// weight tiles per wave in the register ring: four for one row tile, three beyond (registers)
-template <int MT> struct GemmRing { static constexpr int N = MT == 1 ? 4 : 3; };
+constexpr int GEMM_RING = 4;        // weight tiles per wave in the register ring
 
-template <int MT>
-struct BStage { uint4 v[MT][4]; };
+struct BStage { uint4 v[4]; };
 
 __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* wlane, size_t wstep, int blk) {
 #pragma unroll
@@ -450,33 +446,25 @@ __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* const (
 }
 
 // thread tid stages chunks tid and tid + 256 of the 512 16-byte chunks of each 8 KiB plane tile
-template <int MT>
-__device__ __forceinline__ void gemm_b_load(BStage<MT>& st, const bf16_t* xh, const bf16_t* xl, int nblk, int blk) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const size_t base = ((size_t)mt * nblk + blk) * 4096;
-        st.v[mt][0] = load16(xh + base); st.v[mt][1] = load16(xh + base + 2048);
-        st.v[mt][2] = load16(xl + base); st.v[mt][3] = load16(xl + base + 2048);
-    }
+__device__ __forceinline__ void gemm_b_load(BStage& st, const bf16_t* xh, const bf16_t* xl, int blk) {
+    const size_t base = (size_t)blk * 4096;
+    st.v[0] = load16(xh + base); st.v[1] = load16(xh + base + 2048);
+    st.v[2] = load16(xl + base); st.v[3] = load16(xl + base + 2048);
 }
 
-template <int MT>
-__device__ __forceinline__ void gemm_b_store(const BStage<MT>& st, uint4* buf, int tid, bool live) {
+__device__ __forceinline__ void gemm_b_store(const BStage& st, uint4* buf, int tid, bool live) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            uint4 v = st.v[mt][h];
-            v.x = live ? v.x : 0u; v.y = live ? v.y : 0u; v.z = live ? v.z : 0u; v.w = live ? v.w : 0u;
-            buf[(mt * 2 + (h >> 1)) * 512 + (h & 1) * 256 + tid] = v;
-        }
+    for (int h = 0; h < 4; ++h) {
+        uint4 v = st.v[h];
+        v.x = live ? v.x : 0u; v.y = live ? v.y : 0u; v.z = live ? v.z : 0u; v.w = live ? v.w : 0u;
+        buf[(h >> 1) * 512 + (h & 1) * 256 + tid] = v;
+    }
 }
 
 // Transposes the weight tile into operand order through the wave's LDS tile (32 rows x 16 chunks of
 // 16 bytes, chunk c of row r stored at chunk position c ^ (r & 15)), then multiplies it with the
-// activation tile in `bt` ([mt][hi | lo][k-step][lane]).
-template <int MT>
-__device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16 (&acc)[MT], uint4* at, const uint4* bt, int lane) {
+// activation tile in `bt` ([hi | lo][k-step][lane]).
+__device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16& acc, uint4* at, const uint4* bt, int lane) {
     {
         const int r0 = lane >> 4, c = lane & 15;
 #pragma unroll
@@ -492,29 +480,19 @@ __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16 (&acc
         for (int k = 0; k < 8; ++k) a[k] = at[i * 16 + ((2 * k + gh) ^ (i & 15))];
     }
     // The activation operands of k-step k + 1 are read from LDS while the products of step k run (a wave is alone on
-    // its SIMD: nothing else hides the LDS latency), and consecutive products go to different accumulators.
-    uint4 b0[MT][2], b1[MT][2];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) { b0[mt][0] = bt[(mt * 2 + 0) * 512 + lane]; b0[mt][1] = bt[(mt * 2 + 1) * 512 + lane]; }
+    // its SIMD: nothing else hides the LDS latency).
+    uint4 b0[2] = {bt[lane], bt[512 + lane]}, b1[2];
 #pragma unroll
     for (int k = 0; k < 8; k += 2) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) { b1[mt][0] = bt[(mt * 2 + 0) * 512 + (k + 1) * 64 + lane]; b1[mt][1] = bt[(mt * 2 + 1) * 512 + (k + 1) * 64 + lane]; }
+        b1[0] = bt[(k + 1) * 64 + lane]; b1[1] = bt[512 + (k + 1) * 64 + lane];
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(a[k], b0[mt][0], acc[mt]);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(a[k], b0[mt][1], acc[mt]);
+        acc = mfma_bf16(a[k], b0[0], acc);
+        acc = mfma_bf16(a[k], b0[1], acc);
         __builtin_amdgcn_sched_barrier(0);
-        if (k + 2 < 8) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) { b0[mt][0] = bt[(mt * 2 + 0) * 512 + (k + 2) * 64 + lane]; b0[mt][1] = bt[(mt * 2 + 1) * 512 + (k + 2) * 64 + lane]; }
-        }
+        if (k + 2 < 8) { b0[0] = bt[(k + 2) * 64 + lane]; b0[1] = bt[512 + (k + 2) * 64 + lane]; }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(a[k + 1], b1[mt][0], acc[mt]);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(a[k + 1], b1[mt][1], acc[mt]);
+        acc = mfma_bf16(a[k + 1], b1[0], acc);
+        acc = mfma_bf16(a[k + 1], b1[1], acc);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -526,16 +504,16 @@ __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16 (&acc
 // (act_hi, act_lo; N/2 columns) without any exchange.  The tile rows beyond rp repeat row rp - 1 (cache hits, results
 // dropped): the launcher picks rp so that the tiles divide evenly among the waves of the device (14 rows for
 // F = 14336 on 256 compute units: 1024 tiles), which a fixed 16 or 32 rows per wave would not.
-template <int MT, bool SWIGLU>
+template <bool SWIGLU>
 __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W, int N, int K,
                                                     const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo,
                                                     float* __restrict__ P, size_t s_stride, int n_stride, int S,
                                                     bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, int rp) {
-    extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][MT][2][512] activation tiles
+    extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][2][512] activation tiles
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint4* at = gemm_lds + wave * 512;
     uint4* bt = gemm_lds + 2048;
-    constexpr int BT = MT * 2 * 512;                // chunks in one activation buffer
+    constexpr int BT = 2 * 512;                     // chunks in one activation buffer
     const int n0 = SWIGLU ? (blockIdx.x * 4 + wave) * rp : blockIdx.x * 128 + wave * 32;     // SWIGLU: first gate row
     const int nr = SWIGLU ? max(0, min(rp, (N >> 1) - n0)) : 32;                              // SWIGLU: gate rows of this wave
     const int sp = blockIdx.y;
@@ -557,11 +535,9 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
     const bf16_t* xh = Xhi + tid * 8;
     const bf16_t* xl = Xlo + tid * 8;
 
-    f32x16 acc[MT];
+    f32x16 acc;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
     if (nb > 0) {
         // The workgroups walk their k-blocks in rotated order, each starting somewhere else: workgroups that all
@@ -574,34 +550,32 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
         // Waits are in issue order, so the activation loads of block t+2 are issued before the weight loads of
         // the newest block: waiting for the activations of block t+1 (to store them) then leaves the two newest
         // weight tiles in flight.
-        constexpr int RING = GemmRing<MT>::N;
+        constexpr int RING = GEMM_RING;
         uint4 ring[RING][8];
-        BStage<MT> st[2];
-        gemm_b_load<MT>(st[0], xh, xl, nblk, blk(0));
-        gemm_b_load<MT>(st[1], xh, xl, nblk, blk(1));
+        BStage st[2];
+        gemm_b_load(st[0], xh, xl, blk(0));
+        gemm_b_load(st[1], xh, xl, blk(1));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < RING - 1; ++u) {
             if (SWIGLU) gemm_a_load(ring[u], wrow, blk(u));
             else gemm_a_load(ring[u], wlane, wstep, blk(u));
         }
-        gemm_b_store<MT>(st[0], bt, tid, true);
+        gemm_b_store(st[0], bt, tid, true);
         __syncthreads();
-        // unrolled over an even number of blocks, so that ring slot (u % RING) and activation buffer (u & 1) are static
-        constexpr int UNROLL = RING % 2 ? 2 * RING : RING;
-        for (int t = 0; t < nb; t += UNROLL) {
+        static_assert(RING % 2 == 0, "ring slot (u % RING) and activation buffer (u & 1) are static");
+        for (int t = 0; t < nb; t += RING) {
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
+            for (int u = 0; u < RING; ++u) {
                 const int tt = t + u;                       // this block of the walk
-                if (UNROLL > RING && tt >= nb) break;       // long unroll only: uniform exit, nothing below is conditional
-                gemm_b_load<MT>(st[u & 1], xh, xl, nblk, blk(tt + 2));
+                gemm_b_load(st[u & 1], xh, xl, blk(tt + 2));
                 __builtin_amdgcn_sched_barrier(0);
                 if (SWIGLU) gemm_a_load(ring[(u + RING - 1) % RING], wrow, blk(tt + RING - 1));
                 else gemm_a_load(ring[(u + RING - 1) % RING], wlane, wstep, blk(tt + RING - 1));
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_tile_mma<MT>(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
+                gemm_tile_mma(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_b_store<MT>(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid, tt + 1 < nb);
+                gemm_b_store(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid, tt + 1 < nb);
                 __syncthreads();
             }
         }
@@ -611,29 +585,23 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
     if (SWIGLU) {
         const int F = N >> 1;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int slot = 8 * b + 4 * (lane >> 5) + r;
-                    if (slot < nr) {
-                        const float gt = acc[mt][4 * b + r], up = acc[mt][4 * (b + 2) + r];
-                        bf16_t hi, lo;
-                        split_bf16(gt / (1.f + expf(-gt)) * up, hi, lo);
-                        const size_t o = tiled_off(mt * 32 + (lane & 31), n0 + slot, F);
-                        act_hi[o] = hi; act_lo[o] = lo;
-                    }
+            for (int r = 0; r < 4; ++r) {
+                const int slot = 8 * b + 4 * (lane >> 5) + r;
+                if (slot < nr) {
+                    const float gt = acc[4 * b + r], up = acc[4 * (b + 2) + r];
+                    bf16_t hi, lo;
+                    split_bf16(gt / (1.f + expf(-gt)) * up, hi, lo);
+                    const size_t o = tiled_off(lane & 31, n0 + slot, F);
+                    act_hi[o] = hi; act_lo[o] = lo;
                 }
+            }
         return;
     }
+    float* prow = P + sp * s_stride + (size_t)(lane & 31) * n_stride + n0 + 4 * (lane >> 5);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        float* prow = P + sp * s_stride + (size_t)(mt * 32 + (lane & 31)) * n_stride + n0 + 4 * (lane >> 5);
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            *(float4*)(prow + 8 * b) = make_float4(acc[mt][4 * b], acc[mt][4 * b + 1], acc[mt][4 * b + 2], acc[mt][4 * b + 3]);
-    }
+    for (int b = 0; b < 4; ++b) *(float4*)(prow + 8 * b) = make_float4(acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -648,9 +616,8 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
 //  * the activations are already in operand order in global memory (tiled planes: one contiguous KiB per
 //    wave-wide load) and go straight to registers through a ring of four 2-step units, three units ahead of
 //    the products; no wave reads another wave's rows, so they never pass through LDS.
-// Workgroups that share a weight tile (row blocks of one pass) get linear ids that land on the same XCD,
-// next to each other in dispatch order, so the second reads the weights from that XCD's L2.
 
+// activations of MW row tiles (one here, two in k_chunk_gemm_ks)
 template <int MW> struct BUnit { uint4 v[MW][2][2]; };      // [row tile][k-step of the unit][hi | lo]
 
 template <int MW>
@@ -688,65 +655,44 @@ __device__ __forceinline__ void wide_step(const uint4 (&a)[4], const BUnit<MW>& 
 // takes 64 gate rows and the 64 up rows of the same columns (weight-row tiles 0, 1 and 2, 3), and its
 // epilogue writes silu(gate) * up as hi/lo planes in operand order (act_hi, act_lo; N/2 columns) instead of
 // the fp32 products: S must be 1.
-template <int NW, int MW, bool SWIGLU>
-__global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __restrict__ W, int N, int K,
+template <bool SWIGLU>
+__global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restrict__ W, int N, int K,
                                                              const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo,
                                                              float* __restrict__ P, size_t s_stride, int n_stride, int S, int MT,
                                                              bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]
-    constexpr int QN = 32 / NW;                     // weight loads per thread and block: wave w stages rows (128 / NW) w ...
+    constexpr int QN = 8;                           // weight loads per thread and block: wave w stages rows 32 w ...
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles = N >> 7, MY = (MT + NW * MW - 1) / (NW * MW);
-    int ntile, my, sp;
-    {
-        int q = blockIdx.x;
-        if ((tiles & 7) == 0) {                     // XCDs take workgroups round robin by linear id
-            const int xcd = q & 7;
-            q >>= 3;
-            my = q % MY; q /= MY;
-            ntile = (q % (tiles >> 3)) * 8 + xcd; sp = q / (tiles >> 3);
-        } else {
-            my = q % MY; q /= MY;
-            ntile = q % tiles; sp = q / tiles;
-        }
-    }
+    const int tiles = N >> 7, ntile = blockIdx.x % tiles, sp = blockIdx.x / tiles;
     const int nblk = K >> 7;
     const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S), b1 = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S);   // (K / 128) * S < 2^31
     const int nb = b1 - b0, last = b1 - 1;
     const int n0 = ntile * 128;
 
-    // weights: load q of a thread covers row (128 / NW) wave + 4 q + lane / 16 of the tile, 16-byte chunk lane % 16
+    // weights: load q of a thread covers row 32 wave + 4 q + lane / 16 of the tile, 16-byte chunk lane % 16
     const bf16_t* wq[QN];
     int wslot[QN];
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
-        const int rg = wave * (128 / NW) + 4 * q + (lane >> 4), r = rg & 31, c = lane & 15;
+        const int rg = wave * 32 + 4 * q + (lane >> 4), r = rg & 31, c = lane & 15;
         const int row = SWIGLU ? (rg < 64 ? ntile * 64 + rg : (N >> 1) + ntile * 64 + rg - 64) : n0 + rg;
         wq[q] = W + (size_t)row * K + c * 8;
         wslot[q] = (rg >> 5) * 512 + r * 16 + (c ^ (r & 15));
     }
-    // activations: row tiles (my MW + j) NW + wave of the pass; tiles past the end repeat the last one and are not stored
-    int mtile[MW];
-    const bf16_t* xh[MW];
-    const bf16_t* xl[MW];
-#pragma unroll
-    for (int j = 0; j < MW; ++j) {
-        mtile[j] = (my * MW + j) * NW + wave;
-        const size_t o = (size_t)min(mtile[j], MT - 1) * nblk * 4096 + lane * 8;
-        xh[j] = Xhi + o; xl[j] = Xlo + o;
-    }
+    // activations: a row tile per wave; waves past the last tile repeat it and store nothing
+    const size_t xo = (size_t)min(wave, MT - 1) * nblk * 4096 + lane * 8;
+    const bf16_t* xh[1] = {Xhi + xo};
+    const bf16_t* xl[1] = {Xlo + xo};
 
-    f32x16 acc[4][MW];
+    f32x16 acc[4][1];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-        for (int j = 0; j < MW; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nt][j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[nt][0][r] = 0.f;
 
     if (nb > 0) {
         uint4 wreg[QN];
-        BUnit<MW> ring[4];
+        BUnit<1> ring[4];
         auto w_load = [&](int blk) {
 #pragma unroll
             for (int q = 0; q < QN; ++q) wreg[q] = load16_stream(wq[q] + (size_t)blk * 128);
@@ -759,7 +705,7 @@ __global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __res
         w_load(b0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 3; ++u) wide_b_load<MW>(ring[u], xh, xl, b0, u);
+        for (int u = 0; u < 3; ++u) wide_b_load<1>(ring[u], xh, xl, b0, u);
         __builtin_amdgcn_sched_barrier(0);
         w_store(gemm_lds);
         w_load(min(b0 + 1, last));
@@ -776,7 +722,7 @@ __global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __res
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     // unit u + 3 of the stream: the last unit of this block, then the first three of the next
-                    wide_b_load<MW>(ring[(u + 3) & 3], xh, xl, u == 0 ? tt : min(tt + 1, last), (u + 3) & 3);
+                    wide_b_load<1>(ring[(u + 3) & 3], xh, xl, u == 0 ? tt : min(tt + 1, last), (u + 3) & 3);
                     __builtin_amdgcn_sched_barrier(0);
                     if (u == 1) {
                         // the next block's weights (requested one block ago) move to the other LDS buffer, whose
@@ -787,11 +733,11 @@ __global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __res
                     }
                     wide_a_read(a1, at, 2 * u + 1, lane);
                     __builtin_amdgcn_sched_barrier(0);
-                    wide_step<MW>(a0, ring[u], 0, acc);
+                    wide_step<1>(a0, ring[u], 0, acc);
                     __builtin_amdgcn_sched_barrier(0);
                     if (u < 3) wide_a_read(a0, at, 2 * u + 2, lane);
                     __builtin_amdgcn_sched_barrier(0);
-                    wide_step<MW>(a1, ring[u], 1, acc);
+                    wide_step<1>(a1, ring[u], 1, acc);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 __syncthreads();
@@ -800,39 +746,32 @@ __global__ __launch_bounds__(NW * 64) void k_chunk_gemm_wide(const bf16_t* __res
     }
 
     // lane (j, g) holds D[8b + 4g + r][j] in register 4b + r: four consecutive weight rows of token row j
+    if (wave >= MT) return;
+    const int m = wave * 32 + (lane & 31);
     if (SWIGLU) {
         const int F = N >> 1, f0 = ntile * 64 + 4 * (lane >> 5);
 #pragma unroll
-        for (int j = 0; j < MW; ++j) {
-            if (mtile[j] >= MT) continue;
-            const int m = mtile[j] * 32 + (lane & 31);
+        for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
+            for (int b = 0; b < 4; ++b) {
+                bf16_t hi[4], lo[4];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    bf16_t hi[4], lo[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float gt = acc[nt][j][4 * b + r], up = acc[nt + 2][j][4 * b + r];
-                        split_bf16(gt / (1.f + expf(-gt)) * up, hi[r], lo[r]);
-                    }
-                    const size_t o = tiled_off(m, f0 + nt * 32 + 8 * b, F);     // four columns inside one 8-element group
-                    *reinterpret_cast<uint2*>(act_hi + o) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-                    *reinterpret_cast<uint2*>(act_lo + o) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+                for (int r = 0; r < 4; ++r) {
+                    const float gt = acc[nt][0][4 * b + r], up = acc[nt + 2][0][4 * b + r];
+                    split_bf16(gt / (1.f + expf(-gt)) * up, hi[r], lo[r]);
                 }
-        }
+                const size_t o = tiled_off(m, f0 + nt * 32 + 8 * b, F);         // four columns inside one 8-element group
+                *reinterpret_cast<uint2*>(act_hi + o) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+                *reinterpret_cast<uint2*>(act_lo + o) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+            }
         return;
     }
+    float* prow = P + sp * s_stride + (size_t)m * n_stride + n0 + 4 * (lane >> 5);
 #pragma unroll
-    for (int j = 0; j < MW; ++j) {
-        if (mtile[j] >= MT) continue;
-        float* prow = P + sp * s_stride + (size_t)(mtile[j] * 32 + (lane & 31)) * n_stride + n0 + 4 * (lane >> 5);
+    for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                *(float4*)(prow + nt * 32 + 8 * b) = make_float4(acc[nt][j][4 * b], acc[nt][j][4 * b + 1], acc[nt][j][4 * b + 2], acc[nt][j][4 * b + 3]);
-    }
+        for (int b = 0; b < 4; ++b)
+            *(float4*)(prow + nt * 32 + 8 * b) = make_float4(acc[nt][0][4 * b], acc[nt][0][4 * b + 1], acc[nt][0][4 * b + 2], acc[nt][0][4 * b + 3]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1894,11 +1833,10 @@ __global__ __launch_bounds__(256) void k_chunk_attn_combine(const float* __restr
 
 static bool row_kernel_ok(const Geom& g, int S) { return g.d % 4 == 0 && g.d <= ROW_VEC_MAX * 1024 && S >= 1 && S <= CHUNK_GEMM_MAX_SPLIT; }
 
-hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, bool add_partials, int S, int MT, const float* gain,
+hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, int S, int MT, const float* gain,
                                    int rows, const Geom& g, hipStream_t s) {
     if (!row_kernel_ok(g, S)) return hipErrorInvalidValue;
-    const float* part = add_partials ? c.part : nullptr;
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(rows), dim3(256), 0, s, c.x, part, S, (size_t)MT * 32 * g.d, g.d, gain, g.eps, g.d, c.nrm_hi, c.nrm_lo); };
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(rows), dim3(256), 0, s, c.x, c.part, S, (size_t)MT * 32 * g.d, g.d, gain, g.eps, g.d, c.nrm_hi, c.nrm_lo); };
     if (S == 1) go(k_chunk_resid_norm<1>);
     else if (S == 2) go(k_chunk_resid_norm<2>);
     else if (S <= 4) go(k_chunk_resid_norm<4>);
@@ -1929,9 +1867,8 @@ hipError_t launch_chunk_head_rows(const ChunkBuffers& c, int S, int MT, const fl
     return hipGetLastError();
 }
 
-hipError_t launch_chunk_logits(const ChunkBuffers& c, int MT_head, float* logits_base, const DecodeBuffers& b, int ngroups,
+hipError_t launch_chunk_logits(const ChunkBuffers& c, float* logits_base, const DecodeBuffers& b, int ngroups,
                                const Geom& g, hipStream_t s) {
-    (void)MT_head;
     hipLaunchKernelGGL(k_chunk_logits, dim3(ngroups, CHUNK_LOGIT_SLICES), dim3(256), 0, s, c.part, g.V, c.tab, logits_base, b.seq_state, b.banned,
                        c.amax_v, c.amax_i, c.amax_counters);
     return hipGetLastError();
@@ -1957,7 +1894,7 @@ hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, co
 
 constexpr int ATTN_LDS_BYTES = 4 * 1024 * 16;       // k_chunk_attn: per wave one K tile, two planes
 
-static size_t gemm_lds_bytes(int MT) { return (size_t)(2048 + 2 * MT * 2 * 512) * 16; }
+constexpr int GEMM_LDS_BYTES = (2048 + 2 * 2 * 512) * 16;   // k_chunk_gemm: weight tiles, two buffers of activations
 constexpr int GEMM_WIDE_LDS_BYTES = 2 * 2048 * 16;  // k_chunk_gemm_wide: two buffers of one 128 x 128 weight block
 template <bool SWIGLU>
 static const void* big_func(int nt) {
@@ -1974,19 +1911,19 @@ static int big_lds_bytes(int nt) { return 3 * (nt * 2048 + BIG_M * 4096); }
 
 hipError_t chunk_init() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_lds_bytes(1)))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_lds_bytes(1)))) return e;
+    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_attn, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_attn_wide, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_decode_attn_mfma, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<4, 1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     for (int nt = 4; nt <= 8; ++nt) {
         if ((e = hipFuncSetAttribute(big_func<false>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
         if ((e = hipFuncSetAttribute(big_func<true>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
     }
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<4, 1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     return hipSuccess;
 }
 
@@ -2006,17 +1943,17 @@ hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, con
                              GemmPlan pl, int MT, hipStream_t s) {
     const int S = pl.s;
     const dim3 grid(N / 128, S), block(256);
-    const size_t ps = (size_t)MT * 32 * N, lds = gemm_lds_bytes(MT);
+    const size_t ps = (size_t)MT * 32 * N;
     if (S < 1 || S > CHUNK_GEMM_MAX_SPLIT || S > K / 128 || N % 128 || K % 128 || ps * S > c.part_capacity) return hipErrorInvalidValue;
     if (MT < 1 || MT > CHUNK_MAX / 32) return hipErrorInvalidValue;
     // one row tile: weight-streaming kernel, a wave per 32 weight rows; two: the waves split the k-steps; three or four:
     // a wave per row tile (128-row workgroups); more: 256-row workgroups with pl.nt weight-row tiles
     if (MT == 1) {
-        hipLaunchKernelGGL((k_chunk_gemm<1, false>), grid, block, lds, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr, 0);
+        hipLaunchKernelGGL((k_chunk_gemm<false>), grid, block, GEMM_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr, 0);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, false>), grid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, false>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<false>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
     } else return launch_big<false>((const bf16_t*)W, N, K, xhi, xlo, c.part, S, pl.nt, MT, nullptr, nullptr, s);
     return hipGetLastError();
 }
@@ -2037,11 +1974,11 @@ hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* x
         }
         rp = std::min(std::max(rp, 1), 16);
         const int tiles = (F + rp - 1) / rp;
-        hipLaunchKernelGGL((k_chunk_gemm<1, true>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(1), s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, rp);
+        hipLaunchKernelGGL((k_chunk_gemm<true>), dim3((tiles + 3) / 4, 1), dim3(256), GEMM_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, rp);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<4, 1, true>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<true>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
     } else return launch_big<true>(Wb, 2 * F, K, xhi, xlo, nullptr, 1, pl.nt, MT, c.act_hi, c.act_lo, s);
     return hipGetLastError();
 }

@@ -6,7 +6,8 @@
 // same for up to ROWS_MAX rows, so an interrupt or a prompt takes ROWS_MAX tokens per pass instead of one.  Measured, one
 // layer of the 8B shape with the single-plane cache: 152 us for eight rows (QKV 24, attention 9, O 19, gate/up 52, down 45)
 // against 8 x 94 us token by token; a short session (203 + 24 tokens appended, 16 steps, two layers) 53.4 -> 15.2 ms; the
-// tiny fp32 preset's session (64 + 8 tokens, 32 steps) 7.3 -> 3.1 ms.
+// tiny fp32 preset's session (64 + 8 tokens, 32 steps) 7.3 -> 3.1 ms with k_rows_gemv alone; 1.91 ms with the kernels for small
+// products, here and in decode_kernels.hip.
 #include "common.h"
 #include "launch.h"
 #include "decode_device.h"
@@ -337,11 +338,10 @@ __global__ __launch_bounds__(256) void k_rows_embed(const WT* __restrict__ E, Ro
 namespace {
 
 template <typename WT>
-size_t rows_lds(int K, int units, int grid, int ub, int* done_cap) {
+size_t rows_lds(int K, int units, int grid, int* done_cap) {
     constexpr int EPL = Elem<WT>::EPL, TS = ROWS_SEG / (256 * EPL);
     *done_cap = (units + grid * ROWS_NW - 1) / (grid * ROWS_NW);
     const int kt = (K / EPL + 255) / 256;
-    (void)ub;
     return (size_t)ROWS_MAX * std::min(kt, TS) * 256 * EPL * sizeof(float) + (size_t)ROWS_NW * *done_cap * 2 * ROWS_MAX * sizeof(float);
 }
 
@@ -361,7 +361,7 @@ const void* rows_func(int ub, bool seg) {
 template <typename WT>
 bool rows_fit(int K, int units) {
     int cap = 0;
-    return rows_lds<WT>(K, units, rows_grid(units), rows_ub(units), &cap) + 1024 <= ROWS_LDS_LIMIT;
+    return rows_lds<WT>(K, units, rows_grid(units), &cap) + 1024 <= ROWS_LDS_LIMIT;
 }
 
 template <typename WT, int EPI>
@@ -378,7 +378,7 @@ hipError_t launch_rows_t(RowsArgs a, const Geom& g, hipStream_t s) {
         return hipLaunchKernel(rows_small_func<WT, EPI>((kg + 63) / 64), dim3((a.units + 3) / 4), dim3(256), params, 0, s);
     }
     const int grid = rows_grid(a.units), ub = rows_ub(a.units);
-    const size_t lds = rows_lds<WT>(a.K, a.units, grid, ub, &a.done_cap);
+    const size_t lds = rows_lds<WT>(a.K, a.units, grid, &a.done_cap);
     if (lds + 1024 > ROWS_LDS_LIMIT || a.n < 1 || a.n > ROWS_MAX || a.K % 8) return hipErrorInvalidValue;
     a.uq = a.units / (grid * ROWS_NW); a.ur = a.units % (grid * ROWS_NW);
     Geom gg = g;

@@ -49,9 +49,8 @@ constexpr int CHUNK_GEMM_MAX_SPLIT = 8;
 struct ChunkRow { int32_t token, seq, pos, row0, n, group, pad1, pad2; };
 struct ChunkGroup {
     int32_t seq, row0, n, pos0;
-    int32_t forced;     // first row: >= 0 this token, -1 greedy argmax of the sequence's logits, -2 already in the row table
     int32_t head;       // row of this group in the output-head product, -1: no logits wanted
-    int32_t pad0, pad1;
+    int32_t pad0, pad1, pad2;
 };
 struct ChunkTask { int32_t seq, row0, n, pos0, tile, pad0, pad1, pad2; };         // query columns 32 tile .. 32 tile + 31 of a group
 // Every group has at least one task, so a batched pass holds at most CHUNK_MAX_GROUPS groups.  A pass uploads the used
@@ -149,7 +148,7 @@ int decode_gemv_grid();
 hipError_t chunk_init();
 hipError_t launch_chunk_embed_norm(const void* E, const ChunkBuffers& c, const float* gain, int rows, const DecodeBuffers& b, const Geom& g,
                                    hipStream_t s);
-hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, bool add_partials, int S, int MT, const float* gain, int rows,
+hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, int S, int MT, const float* gain, int rows,
                                    const Geom& g, hipStream_t s);
 // residual stream of the last row of group `group` -> the single-row path's x (and its sequence -> the step descriptor)
 hipError_t launch_chunk_last_row(const ChunkBuffers& c, int S, int MT, int group, const DecodeBuffers& b, const Geom& g,
@@ -158,7 +157,7 @@ hipError_t launch_chunk_last_row(const ChunkBuffers& c, int S, int MT, int group
 hipError_t launch_chunk_head_rows(const ChunkBuffers& c, int S, int MT, const float* gain, int ngroups, const Geom& g,
                                   hipStream_t s);
 // rows of the head product -> logits of their sequences, greedy argmax -> next_token
-hipError_t launch_chunk_logits(const ChunkBuffers& c, int MT_head, float* logits_base, const DecodeBuffers& b, int ngroups,
+hipError_t launch_chunk_logits(const ChunkBuffers& c, float* logits_base, const DecodeBuffers& b, int ngroups,
                                const Geom& g, hipStream_t s);
 hipError_t launch_chunk_swiglu(const ChunkBuffers& c, int S, int MT, int rows, const Geom& g, hipStream_t s);
 // kv_only: the product held the key and value rows only
