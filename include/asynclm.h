@@ -234,7 +234,9 @@ int asynclm_set_option(asynclm_ctx *ctx, const char *name, int32_t value);
  * every launch (graphs off for this step).  The step is a real step: the sequence grows by one.
  * names_out: receives a pointer to a static array of class names; ms_out[0..n_classes) receives the
  * summed milliseconds and launches_out[0..n_classes) the number of launches per class.
- * Returns the number of classes (>= 0) or a negative error.  Pass cap = capacity of the arrays. */
+ * Returns the number of classes (>= 0) or a negative error.  Pass cap = capacity of the arrays.
+ * The token's embedding row is fetched by the step's first kernel ("begin_step") and the next greedy choice is made inside the
+ * output head ("lm_head"): the classes "embed" and "argmax" keep their places and stay zero. */
 int asynclm_profile_step(asynclm_ctx *ctx, int32_t seq, int32_t forced_token, const char *const **names_out,
                          float *ms_out, int32_t *launches_out, int32_t cap);
 
