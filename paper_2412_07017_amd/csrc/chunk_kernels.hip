@@ -74,10 +74,13 @@ __device__ __forceinline__ int row_of_workgroup(int rows) {
 
 constexpr int ROW_VEC_MAX = 8;      // float4 groups per thread of a row kernel: d <= 8192
 
-// One row by one workgroup: v = x[m] + sum_s P[s][row pm] (S <= SM planes; all loads of the
-// row are issued before the first use, the gain's of the following norm among them), returns the sum of squares
-// over the workgroup.  Thread tid owns the float4 groups tid + 256 u.  SM: S rounded up to a power of two, because the planes
-// past S are requested too (the last one again): with eight always, 1019 rows with two planes took 27.4 instead of 23.6 us.
+// One row by one workgroup: v = x[m] + sum_s P[s][row pm] (S <= SM planes, and the gain of the following norm), returns the sum
+// of squares over the workgroup.  Thread tid owns the float4 groups tid + 256 u.  SM: S rounded up to a power of two, because
+// the planes past S are requested too (the last one again): with eight always, 1019 rows with two planes took 27.4 instead of 23.6 us.
+// Many planes (short passes, one workgroup per compute unit at most): the loads of half a row are all issued before the first use,
+// 5.3 us for 16 rows with eight planes against 7.1 one group after the other.  One or two planes (long passes, several workgroups
+// per compute unit): one group after the other, 17.4 us for 1019 rows with two planes against 20.3 all at once, 2048 rows 36.5 / 39.5,
+// with one plane 30 / 34.7.
 template <int SM>
 __device__ __forceinline__ float row_gather(const float* __restrict__ xr, const float* __restrict__ Pr, int S,
                                             size_t s_stride, int d4, int tid, const float* __restrict__ gain,
@@ -86,27 +89,31 @@ __device__ __forceinline__ float row_gather(const float* __restrict__ xr, const 
     float ss = 0.f;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
-        constexpr int HU = ROW_VEC_MAX / 2;
+        constexpr int HU = ROW_VEC_MAX / 2, AT_ONCE = SM <= 2 ? 1 : HU;
         if (hf * HU * 256 < d4) {                               // uniform: the upper half only for d > 4096
-            float4 p[HU][SM];
 #pragma unroll
-            for (int u = 0; u < HU; ++u) {
-                const int i4 = min(tid + 256 * (hf * HU + u), d4 - 1);      // past the end: a repeated load, dropped below
-                v[hf * HU + u] = x4[i4];
-                gn[hf * HU + u] = reinterpret_cast<const float4*>(gain)[i4];
+            for (int u0 = hf * HU; u0 < (hf + 1) * HU; u0 += AT_ONCE) {
+                float4 p[AT_ONCE][SM];
 #pragma unroll
-                for (int s = 0; s < SM; ++s)
-                    p[u][s] = reinterpret_cast<const float4*>(Pr + (size_t)min(s, S - 1) * s_stride)[i4];
-            }
+                for (int u = 0; u < AT_ONCE; ++u) {
+                    const int i4 = min(tid + 256 * (u0 + u), d4 - 1);       // past the end: a repeated load, dropped below
+                    v[u0 + u] = x4[i4];
+                    gn[u0 + u] = reinterpret_cast<const float4*>(gain)[i4];
 #pragma unroll
-            for (int u = 0; u < HU; ++u) {
-                float4& w = v[hf * HU + u];
-#pragma unroll
-                for (int s = 0; s < SM; ++s) {
-                    const float k = s < S ? 1.f : 0.f;
-                    w.x += k * p[u][s].x; w.y += k * p[u][s].y; w.z += k * p[u][s].z; w.w += k * p[u][s].w;
+                    for (int s = 0; s < SM; ++s)
+                        p[u][s] = reinterpret_cast<const float4*>(Pr + (size_t)min(s, S - 1) * s_stride)[i4];
                 }
-                if (tid + 256 * (hf * HU + u) < d4) ss += w.x * w.x + w.y * w.y + w.z * w.z + w.w * w.w;
+#pragma unroll
+                for (int u = 0; u < AT_ONCE; ++u) {
+                    float4& w = v[u0 + u];
+#pragma unroll
+                    for (int s = 0; s < SM; ++s) {
+                        const float k = s < S ? 1.f : 0.f;
+                        w.x += k * p[u][s].x; w.y += k * p[u][s].y; w.z += k * p[u][s].z; w.w += k * p[u][s].w;
+                    }
+                    if (tid + 256 * (u0 + u) < d4) ss += w.x * w.x + w.y * w.y + w.z * w.z + w.w * w.w;
+                }
+                if (AT_ONCE < HU) __builtin_amdgcn_sched_barrier(0);
             }
         } else {
 #pragma unroll
