@@ -192,7 +192,7 @@ def test_8b_full_depth_full_size_invariants_of_the_method():
     injected in flight), checked through properties that hold at any size, because no oracle run fits a test here:
       * Sec. 3.2 / 5.5: the live context after the in-flight inject and a stateless re-prefill of the same token
         stream give the same next-token logits (two different kernel paths: single-row decode kernels + 24-row
-        pass against 512-row prefill passes);
+        pass against one prefill pass of about 1.1k rows);
       * the same stream appended token by token through the decode kernels alone agrees as well;
       * Sec. 5.4: swapping the K/V cache out and in again reproduces the logits bit for bit, and decoding goes on
         identically from the restored sequence;

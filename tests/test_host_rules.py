@@ -16,7 +16,7 @@ import ctypes as C, json, os, sys, types
 sys.path.insert(0, os.environ["ASYNCLM_ROOT"])
 import numpy as np
 import paper_2412_07017_amd as pkg
-hip = C.CDLL(os.environ["LD_PRELOAD"])
+hip = C.CDLL(os.environ["HOST_HIP_LIBRARY"])
 hip.host_hip_peak.restype = hip.host_hip_used.restype = C.c_size_t
 
 class Stream:
@@ -61,7 +61,8 @@ def host(tmp_path_factory):
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", os.path.join(HERE, "host_hip.c"), "-o", so], check=True)
 
     def run(body, **env):
-        e = dict(os.environ, LD_PRELOAD=so, ASYNCLM_ROOT=ROOT, HOST_HIP_LOG_FILE=str(tmp / "log"), **{k: str(v) for k, v in env.items()})
+        preload = ":".join([so] + [p for p in (os.environ.get("LD_PRELOAD"),) if p])
+        e = dict(os.environ, LD_PRELOAD=preload, HOST_HIP_LIBRARY=so, ASYNCLM_ROOT=ROOT, HOST_HIP_LOG_FILE=str(tmp / "log"), **{k: str(v) for k, v in env.items()})
         res = subprocess.run([sys.executable, "-c", CHILD + body], env=e, capture_output=True, text=True, timeout=120)
         assert res.returncode == 0, res.stderr
         return json.loads(res.stdout.splitlines()[-1])
