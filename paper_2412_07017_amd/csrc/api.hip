@@ -83,6 +83,7 @@ struct asynclm_ctx {
     bool chunk_ok = false;              // the matrix-core append path supports this model
     int pass_rows = CHUNK_BATCH_ROWS;   // rows that one of its passes can hold (CHUNK_BATCH_ROWS .. CHUNK_MAX; fewer: PASS_ROWS_UNALIGNED)
     RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
+    int wide_rows = 0;                  // ... or this many on the matrix cores (forward_wide_rows); 0: not this model
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
     unsigned* bar = nullptr;            // its grid-barrier counters
@@ -420,6 +421,40 @@ hipError_t dev_alloc(asynclm_ctx* c, T** p, size_t count) {
     return hipSuccess;
 }
 
+// Buffers of forward_wide_rows, for the models that it takes.  An error leaves none of them and wide_rows = 0.
+hipError_t alloc_wide_rows(asynclm_ctx* c) {
+    const Geom& g = c->g;
+    const size_t qd = (size_t)g.Hq * g.dh, nqkv = qd + 2 * (size_t)g.Hkv * g.dh;
+    if (c->cfg.dtype != ASYNCLM_DTYPE_BF16 || g.d % 128 || g.F % 128 || qd % 128 || (2 * g.Hkv * g.dh) % 128 || g.d > 8192) return hipSuccess;
+    ChunkBuffers& cb = c->cb;
+    const size_t had = c->allocs.size(), M = std::min(WIDE_ROWS_MAX, g.max_pos), wide = std::max(nqkv, (size_t)g.d);
+    // partial planes: one of the widest product that writes any for the longest pass, every split of it for 128 rows (a down product of
+    // the 8B shape over 203 rows with room for one part only: 245 us, with four parts 75)
+    cb.part_capacity = std::max(M, (size_t)128 * CHUNK_GEMM_MAX_SPLIT) * wide;
+    const size_t plane_elems = 3 * M * ((size_t)g.d + qd + g.F);
+    bf16_t* planes = nullptr;
+    hipError_t e = chunk_init_wide();
+    if (!e) e = dev_alloc(c, &cb.tab_mem, CHUNK_TAB_BYTES);
+    if (!e) e = dev_alloc(c, &cb.x, M * g.d);
+    if (!e) e = dev_alloc(c, &cb.part, cb.part_capacity);
+    if (!e) e = dev_alloc(c, &planes, plane_elems);
+    // rows beyond the current pass are multiplied into discarded columns only, but must stay finite
+    if (!e) e = hipMemset(planes, 0, plane_elems * sizeof(bf16_t));
+    if (e) {
+        for (size_t i = had; i < c->allocs.size(); ++i) hipFree(c->allocs[i]);
+        c->allocs.resize(had);
+        cb = ChunkBuffers{};
+        return e;
+    }
+    auto take = [&](size_t n) { bf16_t* q = planes; planes += n; return q; };
+    for (bf16_t** q : {&cb.nrm_hi, &cb.nrm_lo, &cb.nrm_lo2}) *q = take(M * g.d);
+    for (bf16_t** q : {&cb.att_hi, &cb.att_lo, &cb.att_lo2}) *q = take(M * qd);
+    for (bf16_t** q : {&cb.act_hi, &cb.act_lo, &cb.act_lo2}) *q = take(M * g.F);
+    c->pass.G = g.Hq / g.Hkv; c->pass.Hkv = g.Hkv;
+    c->wide_rows = (int)M;
+    return hipSuccess;
+}
+
 bool config_ok(const asynclm_config* k) {
     if (k->n_layers <= 0 || k->d_model <= 0 || k->n_q_heads <= 0 || k->n_kv_heads <= 0 || k->ffn <= 0 || k->vocab <= 0) return false;
     if (k->head_dim != 64 && k->head_dim != 128) return false;
@@ -542,6 +577,29 @@ hipError_t last_row_layer(asynclm_ctx* c, int l, float* x, int len_after) {
     return run(c, KC_LMHEAD, [&] { return launch_lmhead(dt, c->lm_head, c->final_norm, c->logits, b, g, s); });
 }
 
+// The used part of a pass's row table, through pinned memory: the copy is asynchronous and the host goes on enqueuing the pass.
+hipError_t upload_table(asynclm_ctx* c, const ChunkTable& t) {
+    ChunkBuffers& cb = c->cb;
+    hipError_t e;
+    const int i = c->tab_next;
+    if ((e = hipEventSynchronize(c->tab_ev[i]))) return e;         // the upload that last used this copy has finished
+    size_t bytes = 0;
+    auto put = [&](const void* src, size_t n) {
+        const size_t at = bytes;
+        std::memcpy(c->tab_host[i] + at, src, n);
+        bytes += (n + 31) / 32 * 32;
+        return cb.tab_mem + at;
+    };
+    cb.tab.group = (const ChunkGroup*)put(t.group, sizeof(ChunkGroup) * t.ngroups);
+    cb.tab.task = (const ChunkTask*)put(t.task, sizeof(ChunkTask) * t.ntasks);
+    cb.tab.block = (const ChunkTaskBlock*)put(t.block, sizeof(ChunkTaskBlock) * t.nblocks);
+    cb.tab.row = (const ChunkRow*)put(t.row, sizeof(ChunkRow) * t.rows);
+    if ((e = hipMemcpyAsync(cb.tab_mem, c->tab_host[i], bytes, hipMemcpyHostToDevice, c->stream))) return e;
+    if ((e = hipEventRecord(c->tab_ev[i], c->stream))) return e;
+    c->tab_next = i ^ 1;
+    return hipSuccess;
+}
+
 // One forward pass over the rows of `pb` (1..pass_rows rows in any number of groups).  Groups that want logits
 // get them from the single-row head kernels (one group) or from one more product on the matrix cores (several).
 hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
@@ -580,24 +638,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     const bool wide_attn = ((pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups) && even) || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
     const int dt = c->cfg.dtype;
     hipError_t e;
-    {   // through pinned memory: the copy is asynchronous and the host goes on enqueuing the pass
-        const int i = c->tab_next;
-        if ((e = hipEventSynchronize(c->tab_ev[i]))) return e;         // the upload that last used this copy has finished
-        size_t bytes = 0;
-        auto put = [&](const void* src, size_t n) {
-            const size_t at = bytes;
-            std::memcpy(c->tab_host[i] + at, src, n);
-            bytes += (n + 31) / 32 * 32;
-            return cb.tab_mem + at;
-        };
-        cb.tab.group = (const ChunkGroup*)put(t.group, sizeof(ChunkGroup) * t.ngroups);
-        cb.tab.task = (const ChunkTask*)put(t.task, sizeof(ChunkTask) * t.ntasks);
-        cb.tab.block = (const ChunkTaskBlock*)put(t.block, sizeof(ChunkTaskBlock) * t.nblocks);
-        cb.tab.row = (const ChunkRow*)put(t.row, sizeof(ChunkRow) * t.rows);
-        if ((e = hipMemcpyAsync(cb.tab_mem, c->tab_host[i], bytes, hipMemcpyHostToDevice, s))) return e;
-        if ((e = hipEventRecord(c->tab_ev[i], s))) return e;
-        c->tab_next = i ^ 1;
-    }
+    if ((e = upload_table(c, t))) return e;
     // A pass over one sequence: after the last layer's keys and values nothing but its last row is needed any more, so that
     // row finishes the pass through the single-row kernels (fp32 activations; its own key and value are formed once more
     // there), and a pass that wants no logits ends with the keys and values.  One layer of n: 3 % of a prompt's time at 32
@@ -647,6 +688,72 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     return hipSuccess;
 }
 
+// Split of K of a product of forward_wide_rows: parts so that the workgroups (one per 128 weight rows, part and four row tiles) come
+// closest to whole rounds of one per compute unit; a 128-column block is one unit of time, a workgroup's start and end 1.5, a partial
+// plane 0.9 per 512 x 4096 floats written and read back (as in pick_gemm_plan for four row tiles).
+int pick_wide_split(const asynclm_ctx* c, int N, int K, int MT) {
+    const int nblk = K / 128, tiles = N / 128 * ((MT + 3) / 4);
+    const double plane = 0.9 * ((double)MT * 32 * N) / (512.0 * 4096.0);
+    int best = 1;
+    double best_cost = 0;
+    for (int s = 1; s <= std::min(CHUNK_GEMM_MAX_SPLIT, std::max(1, nblk / 2)) && (size_t)s * MT * 32 * N <= c->cb.part_capacity; ++s) {
+        const double cost = (tiles * s + c->n_cu - 1) / c->n_cu * ((double)nblk / s + 1.5) + plane * (s - 1);
+        if (s == 1 || cost < best_cost) { best_cost = cost; best = s; }
+    }
+    return best;
+}
+
+// One forward pass over n = 2..wide_rows rows of one sequence: bf16 models that keep the cache row by row (the single-plane format,
+// head_dim 64), sizes multiples of 128.  Their activations are fp32 and stay so: the products take them as three bf16 planes, which
+// together are the fp32 value, on the matrix cores (three products per weight, fp32 sums), and everything between the products is
+// fp32.  The attention is the one of the other rows path (k_attn_decode), one workgroup per (row, kv head, key split).
+// 8B shape with the single-plane cache, two layers, rows appended at a context of 64 or more, whole call: 2 rows 427 us against 461 in
+// passes of eight rows through the vector units, 8 rows 417 / 464, 24 rows 422 / 1067, 64 rows 526 / 2630, 200 rows 1176 / 8358; a session
+// (203 + 24 tokens appended, 16 steps) 14.7 -> 6.9 ms.  It is also the path for two rows, so there is no rule on the length.
+// Error against 64 bits of that session, rms over 12 seeds: 1.65e-4 before, 1.26e-4 now.
+hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
+    const int dt = c->cfg.dtype;
+    const Geom& g = c->g;
+    ChunkBuffers& cb = c->cb;
+    hipStream_t s = c->stream;
+    const RowsPass p{seq, c->len[seq], n};
+    const int MT = (n + 31) / 32, nqkv = (g.Hq + 2 * g.Hkv) * g.dh, nkv = 2 * g.Hkv * g.dh, qd = g.Hq * g.dh;
+    // Key splits: one per 256 keys, as many as the partial results hold; without any the output goes straight to the planes
+    const int most = std::min(ATTN_MAX_SPLIT, std::max(1, ROWS_MAX * ATTN_MAX_SPLIT / n));
+    int nsplit = 1;
+    if (c->opt_attn_split > 0) nsplit = std::min(c->opt_attn_split, most);
+    else
+        while (nsplit < (p.pos0 + n + 255) / 256 && 2 * nsplit <= most) nsplit *= 2;
+    const int s_qkv = pick_wide_split(c, nqkv, g.d, MT), s_kv = pick_wide_split(c, nkv, g.d, MT), s_o = pick_wide_split(c, g.d, qd, MT),
+              s_down = pick_wide_split(c, g.d, g.F, MT);
+    PassBuilder& pb = c->pass;
+    pb.clear();
+    pb.add(seq, p.pos0, n, -2, tokens, with_head);
+    hipError_t e;
+    if ((e = upload_table(c, pb.t))) return e;
+    for (int l = 0; l < c->cfg.n_layers; ++l) {
+        void* kvl = kv_layer_ptr(c, l);
+        if (l == 0) { if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_embed_norm(c->embed, cb, c->attn_norm[0], n, c->b, g, s, 3); }))) return e; }
+        else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, s_down, MT, c->attn_norm[l], n, g, s, 3); }))) return e;
+        if (l == c->cfg.n_layers - 1) {         // as in forward_chunk: keys and values of all rows, the rest for the last row only
+            const char* wkv = (const char*)c->wqkv[l] + (size_t)qd * g.d * elem_bytes(c);
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(wkv, nkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_kv, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_rows_rope_kv(cb, s_kv, MT, kvl, c->rb, c->b, p, g, s, true); }))) return e;
+            if (with_head && (e = last_row_layer(c, l, cb.x + (size_t)(n - 1) * g.d, p.pos0 + n))) return e;
+            break;
+        }
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_qkv, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_rows_rope_kv(cb, s_qkv, MT, kvl, c->rb, c->b, p, g, s, false); }))) return e;
+        if ((e = run(c, KC_ATTN, [&] { return launch_rows_attn(dt, kvl, nsplit, c->rb, p, g, s, &cb); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb.att_lo2, cb, s_o, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, s_o, MT, c->ffn_norm[l], n, g, s, 3); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb.act_lo2, cb, s_down, MT, s); }))) return e;
+    }
+    c->len[seq] += n;
+    return hipSuccess;
+}
+
 // One forward pass over n = 2..ROWS_MAX rows of one sequence (models outside the matrix-core append path).
 hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
     const int dt = c->cfg.dtype;
@@ -683,13 +790,17 @@ hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, b
 int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
     // the one-kernel and the two-stream step are asked for by option: then every token takes such a step
     const bool rows_path = !c->chunk_ok && !c->opt_fused && !c->opt_pipeline && rows_supported(c->cfg.dtype, c->g);
-    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, c->pass_rows) : rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
+    const bool wide_path = c->wide_rows > 0 && !c->opt_fused && !c->opt_pipeline;
+    const int chunk = c->chunk_ok ? std::min(c->opt_chunk, c->pass_rows) : wide_path ? std::min(c->opt_chunk, c->wide_rows) :
+                      rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
     int i = 0;
     while (i < n) {
         const int rows = std::min(chunk, n - i);
         const bool last = i + rows == n;
         if (rows == 1) {
             HIPCK(c, step_one_token(c, seq, tokens[i], last));
+        } else if (wide_path) {
+            HIPCK(c, forward_wide_rows(c, seq, tokens + i, rows, last));
         } else if (!c->chunk_ok) {
             HIPCK(c, forward_rows(c, seq, tokens + i, rows, last));
         } else {
@@ -721,7 +832,7 @@ extern "C" {
 int asynclm_create(asynclm_ctx** out, const asynclm_config* cfg, const asynclm_weights* w, void* hip_stream) {
     if (out) *out = nullptr;
     if (!out || !cfg || !w) return ASYNCLM_E_INVAL;
-    // where memory is too short for the buffers of large passes, the smallest ones do; what does not fit may also be a graph or
+    // where memory is too short for the buffers of large passes, the smallest ones (none, for models of forward_wide_rows) do; what does not fit may also be a graph or
     // another object of the runtime, which reports a device error
     int pass_rows = 0;
     const int r = create_ctx(out, cfg, w, hip_stream, CHUNK_MAX, &pass_rows);
@@ -857,11 +968,16 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
     if (!c->chunk_ok) {
         if ((e = rows_init(cfg->dtype)) != hipSuccess) { report_hip("rows_init", e); return bail(ASYNCLM_E_DEVICE); }
         const size_t R = ROWS_MAX, qd = (size_t)g.Hq * g.dh;
-        ALLOC(c->rb.x, R * g.d); ALLOC(c->rb.q, R * qd); ALLOC(c->rb.o, R * qd); ALLOC(c->rb.a, R * g.F);
+        ALLOC(c->rb.x, R * g.d); ALLOC(c->rb.o, R * qd); ALLOC(c->rb.a, R * g.F);
         ALLOC(c->rb.part_acc, R * qd * ATTN_MAX_SPLIT);
         ALLOC(c->rb.part_ml, R * g.Hq * ATTN_MAX_SPLIT * 2);
-        ALLOC(c->rb.counters, R * g.Hkv);
-        if (hipMemset(c->rb.counters, 0, sizeof(int32_t) * R * g.Hkv) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
+        // where memory is too short for the buffers of larger passes (or was, see asynclm_create), passes of ROWS_MAX rows do
+        if (max_rows > CHUNK_BATCH_ROWS && (e = alloc_wide_rows(c)) != hipSuccess) { report_hip("buffers of wide passes", e); (void)hipGetLastError(); }
+        if (c->wide_rows) *pass_rows = max_rows;
+        const size_t RP = std::max<size_t>(R, c->wide_rows);
+        ALLOC(c->rb.q, RP * qd);
+        ALLOC(c->rb.counters, RP * g.Hkv);
+        if (hipMemset(c->rb.counters, 0, sizeof(int32_t) * RP * g.Hkv) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     }
     // cache rows that were never written are read (and masked) by the chunk attention: keep them finite
     if (hipMemset(c->kv, 0, g.kv_seq_stride * (size_t)cfg->max_seqs * elem_bytes(c)) != hipSuccess) return bail(ASYNCLM_E_DEVICE);

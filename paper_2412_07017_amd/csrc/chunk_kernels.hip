@@ -51,12 +51,6 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint3
     lo = pack_bf16x2(x - __uint_as_float(hi << 16), y - __uint_as_float(hi & 0xffff0000u));
 }
 
-// offset (elements) of (row m, column k) in a tiled plane with K columns
-__device__ __forceinline__ size_t tiled_off(int m, int k, int K) {
-    const int kk = k & 127;
-    return ((((size_t)(m >> 5) * (K >> 7) + (k >> 7)) * 8 + (kk >> 4)) * 2 + ((kk >> 3) & 1)) * 256 + (size_t)(m & 31) * 8 + (kk & 7);
-}
-
 // ---------------------------------------------------------------------------------------------
 // bookkeeping and small row-wise kernels
 // ---------------------------------------------------------------------------------------------
@@ -127,32 +121,44 @@ __device__ __forceinline__ float row_gather(const float* __restrict__ xr, const 
     return red[0] + red[1] + red[2] + red[3];
 }
 
-// v * sc * gain -> tiled bf16 hi/lo planes at row `mo`
+// four consecutive columns (inside one 8-element group) of one plane
+template <int PL>
+__device__ __forceinline__ uint2 plane_quad(const bf16_t (&p)[4][PL], int i) {
+    return make_uint2(p[0][i] | ((uint32_t)p[1][i] << 16), p[2][i] | ((uint32_t)p[3][i] << 16));
+}
+
+// v * sc * gain -> tiled bf16 planes (PL = 2 or 3) at row `mo`
+template <int PL>
 __device__ __forceinline__ void row_emit(const float4 (&v)[ROW_VEC_MAX], float sc, const float4 (&gain)[ROW_VEC_MAX], int d,
-                                         int tid, int mo, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo) {
+                                         int tid, int mo, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo, bf16_t* __restrict__ out_lo2) {
     const int d4 = d >> 2;
 #pragma unroll
     for (int u = 0; u < ROW_VEC_MAX; ++u) {
         const int i4 = tid + 256 * u;
         if (i4 < d4) {
             const float4 gn = gain[u];
-            bf16_t h0, l0, h1, l1, h2, l2, h3, l3;
-            split_bf16(v[u].x * sc * gn.x, h0, l0); split_bf16(v[u].y * sc * gn.y, h1, l1);
-            split_bf16(v[u].z * sc * gn.z, h2, l2); split_bf16(v[u].w * sc * gn.w, h3, l3);
+            bf16_t e[4][PL];
+            split_planes<PL>(v[u].x * sc * gn.x, e[0]); split_planes<PL>(v[u].y * sc * gn.y, e[1]);
+            split_planes<PL>(v[u].z * sc * gn.z, e[2]); split_planes<PL>(v[u].w * sc * gn.w, e[3]);
             const size_t o = tiled_off(mo, 4 * i4, d);       // 4 consecutive columns stay inside one 8-element group
-            *reinterpret_cast<uint2*>(out_hi + o) = make_uint2(h0 | ((uint32_t)h1 << 16), h2 | ((uint32_t)h3 << 16));
-            *reinterpret_cast<uint2*>(out_lo + o) = make_uint2(l0 | ((uint32_t)l1 << 16), l2 | ((uint32_t)l3 << 16));
+            *reinterpret_cast<uint2*>(out_hi + o) = plane_quad<PL>(e, 0);
+            *reinterpret_cast<uint2*>(out_lo + o) = plane_quad<PL>(e, 1);
+            if (PL > 2) *reinterpret_cast<uint2*>(out_lo2 + o) = plane_quad<PL>(e, PL - 1);
         }
     }
 }
 
+// (three planes carry all of a float: the scale is then formed without the approximate reciprocal root)
+template <int PL>
+__device__ __forceinline__ float row_scale(float ss, int d, float eps) { return PL > 2 ? 1.f / sqrtf(ss / (float)d + eps) : rsqrtf(ss / (float)d + eps); }
+
 // x[m] += sum_s P[s][m], then RMSNorm with `gain` -> tiled bf16 hi/lo planes.
 // One workgroup per row; P has row stride n_stride and split stride s_stride (elements).
-template <int SM>
+template <int SM, int PL>
 __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x, const float* __restrict__ P, int S,
                                                           size_t s_stride, int n_stride, const float* __restrict__ gain,
                                                           float eps, int d, bf16_t* __restrict__ out_hi,
-                                                          bf16_t* __restrict__ out_lo) {
+                                                          bf16_t* __restrict__ out_lo, bf16_t* __restrict__ out_lo2) {
     __shared__ float red[4];
     const int m = row_of_workgroup(gridDim.x), tid = threadIdx.x, d4 = d >> 2;
     float* xr = x + (size_t)m * d;
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < ROW_VEC_MAX; ++u)
         if (tid + 256 * u < d4) reinterpret_cast<float4*>(xr)[tid + 256 * u] = v[u];
-    row_emit(v, rsqrtf(ss / (float)d + eps), gn, d, tid, m, out_hi, out_lo);
+    row_emit<PL>(v, row_scale<PL>(ss, d, eps), gn, d, tid, m, out_hi, out_lo, out_lo2);
 }
 
 // First kernel of a pass, one workgroup per row: resolves the token where it is chosen on the device (first row of a
@@ -169,9 +175,10 @@ __global__ __launch_bounds__(256) void k_chunk_resid_norm(float* __restrict__ x,
 // records the token (in pinned host memory, where the host reads it after the pass) and grows the sequence; the one of the pass's last row fills the step descriptor that the single-row
 // kernels read (a pass over one sequence ends with them).
 // One launch instead of three (descriptor 4 us, embedding 9 us, norm 6 us for 24 rows of the 8B shape).
+template <int PL>
 __global__ __launch_bounds__(256) void k_chunk_embed_norm(const bf16_t* __restrict__ E, ChunkTab tab, int rows, StepDesc* step, SeqState* st,
                                                           int32_t* chosen_host, float* __restrict__ x, const float* __restrict__ gain, float eps,
-                                                          int d, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo) {
+                                                          int d, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo, bf16_t* __restrict__ out_lo2) {
     __shared__ float red[4];
     const int m = row_of_workgroup(rows), tid = threadIdx.x, d4 = d >> 2;
     const ChunkRow R = tab.row[m];
@@ -206,7 +213,7 @@ __global__ __launch_bounds__(256) void k_chunk_embed_norm(const bf16_t* __restri
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
     ss = red[0] + red[1] + red[2] + red[3];
-    row_emit(v, rsqrtf(ss / (float)d + eps), gn, d, tid, m, out_hi, out_lo);
+    row_emit<PL>(v, row_scale<PL>(ss, d, eps), gn, d, tid, m, out_hi, out_lo, out_lo2);
 }
 
 // Last row of group `group` only: out[:] = x[row] + sum_s P[s][row]  (residual stream handed to the
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(256) void k_chunk_head_rows(const float* __restrict
     const int row = G.row0 + G.n - 1, tid = threadIdx.x, d4 = d >> 2;
     float4 v[ROW_VEC_MAX], gn[ROW_VEC_MAX];
     const float ss = row_gather<CHUNK_GEMM_MAX_SPLIT>(x + (size_t)row * d, P + (size_t)row * n_stride, S, s_stride, d4, tid, gain, v, gn, red);
-    row_emit(v, rsqrtf(ss / (float)d + eps), gn, d, tid, G.head, out_hi, out_lo);
+    row_emit<2>(v, rsqrtf(ss / (float)d + eps), gn, d, tid, G.head, out_hi, out_lo, nullptr);
 }
 
 // Row `head` of the output-head product of every group that wants logits -> logits of its sequence, greedy argmax (lowest
@@ -439,7 +446,7 @@ __global__ __launch_bounds__(256) void k_chunk_rope_kv(const float* __restrict__
 
 constexpr int GEMM_RING = 4;        // weight tiles per wave in the register ring
 
-struct BStage { uint4 v[4]; };
+template <int PL> struct BStage { uint4 v[2 * PL]; };
 
 __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* wlane, size_t wstep, int blk) {
 #pragma unroll
@@ -453,15 +460,17 @@ __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* const (
 }
 
 // thread tid stages chunks tid and tid + 256 of the 512 16-byte chunks of each 8 KiB plane tile
-__device__ __forceinline__ void gemm_b_load(BStage& st, const bf16_t* xh, const bf16_t* xl, int blk) {
+template <int PL>
+__device__ __forceinline__ void gemm_b_load(BStage<PL>& st, const bf16_t* const (&x)[PL], int blk) {
     const size_t base = (size_t)blk * 4096;
-    st.v[0] = load16(xh + base); st.v[1] = load16(xh + base + 2048);
-    st.v[2] = load16(xl + base); st.v[3] = load16(xl + base + 2048);
+#pragma unroll
+    for (int p = 0; p < PL; ++p) { st.v[2 * p] = load16(x[p] + base); st.v[2 * p + 1] = load16(x[p] + base + 2048); }
 }
 
-__device__ __forceinline__ void gemm_b_store(const BStage& st, uint4* buf, int tid, bool live) {
+template <int PL>
+__device__ __forceinline__ void gemm_b_store(const BStage<PL>& st, uint4* buf, int tid, bool live) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
+    for (int h = 0; h < 2 * PL; ++h) {
         uint4 v = st.v[h];
         v.x = live ? v.x : 0u; v.y = live ? v.y : 0u; v.z = live ? v.z : 0u; v.w = live ? v.w : 0u;
         buf[(h >> 1) * 512 + (h & 1) * 256 + tid] = v;
@@ -470,7 +479,9 @@ __device__ __forceinline__ void gemm_b_store(const BStage& st, uint4* buf, int t
 
 // Transposes the weight tile into operand order through the wave's LDS tile (32 rows x 16 chunks of
 // 16 bytes, chunk c of row r stored at chunk position c ^ (r & 15)), then multiplies it with the
-// activation tile in `bt` ([hi | lo][k-step][lane]).
+// activation tile in `bt` ([plane][k-step][lane]).  Three planes: the sums of a block of 128 columns start at zero, smallest plane
+// first, and are added to the total as a whole, so that a long row costs about as little accuracy as the vector units' tree of sums.
+template <int PL>
 __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16& acc, uint4* at, const uint4* bt, int lane) {
     {
         const int r0 = lane >> 4, c = lane & 15;
@@ -485,6 +496,22 @@ __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16& acc,
         const int i = lane & 31, gh = lane >> 5;
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] = at[i * 16 + ((2 * k + gh) ^ (i & 15))];
+    }
+    if (PL == 3) {
+        f32x16 t;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t[r] = 0.f;
+        auto b_read = [&](int i) { return bt[(2 - i / 8) * 512 + (i % 8) * 64 + lane]; };      // product i: plane 2 - i / 8, step i % 8
+        uint4 b[3] = {b_read(0), b_read(1), b_read(2)};
+#pragma unroll
+        for (int i = 0; i < 24; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+            t = mfma_bf16(a[i % 8], b[i % 3], t);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 3 < 24) b[i % 3] = b_read(i + 3);
+        }
+        acc += t;
+        return;
     }
     // The activation operands of k-step k + 1 are read from LDS while the products of step k run (a wave is alone on
     // its SIMD: nothing else hides the LDS latency).
@@ -511,16 +538,16 @@ __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16& acc,
 // (act_hi, act_lo; N/2 columns) without any exchange.  The tile rows beyond rp repeat row rp - 1 (cache hits, results
 // dropped): the launcher picks rp so that the tiles divide evenly among the waves of the device (14 rows for
 // F = 14336 on 256 compute units: 1024 tiles), which a fixed 16 or 32 rows per wave would not.
-template <bool SWIGLU>
+template <bool SWIGLU, int PL>
 __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W, int N, int K,
-                                                    const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo,
+                                                    const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo, const bf16_t* __restrict__ Xlo2,
                                                     float* __restrict__ P, size_t s_stride, int n_stride, int S,
-                                                    bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, int rp) {
-    extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][2][512] activation tiles
+                                                    bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2, int rp) {
+    extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][PL][512] activation tiles
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint4* at = gemm_lds + wave * 512;
     uint4* bt = gemm_lds + 2048;
-    constexpr int BT = 2 * 512;                     // chunks in one activation buffer
+    constexpr int BT = PL * 512;                    // chunks in one activation buffer
     const int n0 = SWIGLU ? (blockIdx.x * 4 + wave) * rp : blockIdx.x * 128 + wave * 32;     // SWIGLU: first gate row
     const int nr = SWIGLU ? max(0, min(rp, (N >> 1) - n0)) : 32;                              // SWIGLU: gate rows of this wave
     const int sp = blockIdx.y;
@@ -539,8 +566,9 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
             wrow[q] = wlane + (size_t)((q < 4 ? 0 : N >> 1) + g0 + min(slot, max(nr, 1) - 1)) * K;
         }
     }
-    const bf16_t* xh = Xhi + tid * 8;
-    const bf16_t* xl = Xlo + tid * 8;
+    const bf16_t* x[PL];
+    x[0] = Xhi + tid * 8; x[1] = Xlo + tid * 8;
+    if (PL > 2) x[PL - 1] = Xlo2 + tid * 8;
 
     f32x16 acc;
 #pragma unroll
@@ -559,30 +587,30 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
         // weight tiles in flight.
         constexpr int RING = GEMM_RING;
         uint4 ring[RING][8];
-        BStage st[2];
-        gemm_b_load(st[0], xh, xl, blk(0));
-        gemm_b_load(st[1], xh, xl, blk(1));
+        BStage<PL> st[2];
+        gemm_b_load<PL>(st[0], x, blk(0));
+        gemm_b_load<PL>(st[1], x, blk(1));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < RING - 1; ++u) {
             if (SWIGLU) gemm_a_load(ring[u], wrow, blk(u));
             else gemm_a_load(ring[u], wlane, wstep, blk(u));
         }
-        gemm_b_store(st[0], bt, tid, true);
+        gemm_b_store<PL>(st[0], bt, tid, true);
         __syncthreads();
         static_assert(RING % 2 == 0, "ring slot (u % RING) and activation buffer (u & 1) are static");
         for (int t = 0; t < nb; t += RING) {
 #pragma unroll
             for (int u = 0; u < RING; ++u) {
                 const int tt = t + u;                       // this block of the walk
-                gemm_b_load(st[u & 1], xh, xl, blk(tt + 2));
+                gemm_b_load<PL>(st[u & 1], x, blk(tt + 2));
                 __builtin_amdgcn_sched_barrier(0);
                 if (SWIGLU) gemm_a_load(ring[(u + RING - 1) % RING], wrow, blk(tt + RING - 1));
                 else gemm_a_load(ring[(u + RING - 1) % RING], wlane, wstep, blk(tt + RING - 1));
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_tile_mma(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
+                gemm_tile_mma<PL>(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_b_store(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid, tt + 1 < nb);
+                gemm_b_store<PL>(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid, tt + 1 < nb);
                 __syncthreads();
             }
         }
@@ -598,10 +626,11 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
                 const int slot = 8 * b + 4 * (lane >> 5) + r;
                 if (slot < nr) {
                     const float gt = acc[4 * b + r], up = acc[4 * (b + 2) + r];
-                    bf16_t hi, lo;
-                    split_bf16(gt / (1.f + expf(-gt)) * up, hi, lo);
+                    bf16_t e[PL];
+                    split_planes<PL>(gt / (1.f + expf(-gt)) * up, e);
                     const size_t o = tiled_off(lane & 31, n0 + slot, F);
-                    act_hi[o] = hi; act_lo[o] = lo;
+                    act_hi[o] = e[0]; act_lo[o] = e[1];
+                    if (PL > 2) act_lo2[o] = e[PL - 1];
                 }
             }
         return;
@@ -625,18 +654,17 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
 //    the products; no wave reads another wave's rows, so they never pass through LDS.
 
 // activations of MW row tiles (one here, two in k_chunk_gemm_ks)
-template <int MW> struct BUnit { uint4 v[MW][2][2]; };      // [row tile][k-step of the unit][hi | lo]
+template <int MW, int PL = 2> struct BUnit { uint4 v[MW][2][PL]; };      // [row tile][k-step of the unit][plane]
 
-template <int MW>
-__device__ __forceinline__ void wide_b_load(BUnit<MW>& b, const bf16_t* (&xh)[MW], const bf16_t* (&xl)[MW],
-                                            int blk, int unit) {
+template <int MW, int PL>
+__device__ __forceinline__ void wide_b_load(BUnit<MW, PL>& b, const bf16_t* (&x)[MW][PL], int blk, int unit) {
 #pragma unroll
     for (int j = 0; j < MW; ++j)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
             const size_t o = ((size_t)blk * 8 + unit * 2 + st) * 512;
-            b.v[j][st][0] = load16(xh[j] + o);
-            b.v[j][st][1] = load16(xl[j] + o);
+#pragma unroll
+            for (int p = 0; p < PL; ++p) b.v[j][st][p] = load16(x[j][p] + o);
         }
 }
 
@@ -657,20 +685,41 @@ __device__ __forceinline__ void wide_step(const uint4 (&a)[4], const BUnit<MW>& 
             for (int j = 0; j < MW; ++j) acc[nt][j] = mfma_bf16(a[nt], b.v[j][st][pl], acc[nt][j]);
 }
 
+// The products of three planes: `t` takes the largest, `tl` the other two.
+__device__ __forceinline__ void wide_step3(const uint4 (&a)[4], const BUnit<1, 3>& b, int st, f32x16 (&t)[4], f32x16 (&tl)[4]) {
+#pragma unroll
+    for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            f32x16& d = pl ? tl[nt] : t[nt];
+            d = mfma_bf16(a[nt], b.v[0][st][pl], d);
+        }
+}
+
+// Three planes (PL = 3): any number of row tiles, four per workgroup; the workgroups of one weight tile sit next to each other on one
+// XCD and share the weights in its L2.  The sums of a block of 128 columns start at zero and are added to the total as a whole (see
+// gemm_tile_mma); the two small planes have a total of their own.
 //
 // SWIGLU: W holds the gate rows [0, N/2) and the up rows [N/2, N) of a feed-forward block.  The workgroup
 // takes 64 gate rows and the 64 up rows of the same columns (weight-row tiles 0, 1 and 2, 3), and its
 // epilogue writes silu(gate) * up as hi/lo planes in operand order (act_hi, act_lo; N/2 columns) instead of
 // the fp32 products: S must be 1.
-template <bool SWIGLU>
+template <bool SWIGLU, int PL>
 __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restrict__ W, int N, int K,
-                                                             const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo,
+                                                             const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo, const bf16_t* __restrict__ Xlo2,
                                                              float* __restrict__ P, size_t s_stride, int n_stride, int S, int MT,
-                                                             bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo) {
+                                                             bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]
     constexpr int QN = 8;                           // weight loads per thread and block: wave w stages rows 32 w ...
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles = N >> 7, ntile = blockIdx.x % tiles, sp = blockIdx.x / tiles;
+    const int tiles = N >> 7;
+    int q0 = blockIdx.x, my = 0;
+    if (PL == 3) {
+        const int MY = (MT + 3) >> 2, total = gridDim.x / MY;       // weight tiles x splits
+        if ((total & 7) == 0) { const int r = q0 >> 3; my = r % MY; q0 = (r / MY) * 8 + (q0 & 7); }
+        else { my = q0 % MY; q0 /= MY; }
+    }
+    const int ntile = q0 % tiles, sp = q0 / tiles, mtile = my * 4 + wave;
     const int nblk = K >> 7;
     const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S), b1 = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S);   // (K / 128) * S < 2^31
     const int nb = b1 - b0, last = b1 - 1;
@@ -687,19 +736,25 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
         wslot[q] = (rg >> 5) * 512 + r * 16 + (c ^ (r & 15));
     }
     // activations: a row tile per wave; waves past the last tile repeat it and store nothing
-    const size_t xo = (size_t)min(wave, MT - 1) * nblk * 4096 + lane * 8;
-    const bf16_t* xh[1] = {Xhi + xo};
-    const bf16_t* xl[1] = {Xlo + xo};
+    const size_t xo = (size_t)min(mtile, MT - 1) * nblk * 4096 + lane * 8;
+    const bf16_t* x[1][PL];
+    x[0][0] = Xhi + xo; x[0][1] = Xlo + xo;
+    if (PL > 2) x[0][PL - 1] = Xlo2 + xo;
 
     f32x16 acc[4][1];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[nt][0][r] = 0.f;
+    f32x16 bs[PL > 2 ? 4 : 1], tl[PL > 2 ? 4 : 1];                 // three planes: sums of a block, total of the small planes
+    if constexpr (PL > 2) {
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) tl[nt] = acc[nt][0];
+    }
 
     if (nb > 0) {
         uint4 wreg[QN];
-        BUnit<1> ring[4];
+        BUnit<1, PL> ring[4];
         auto w_load = [&](int blk) {
 #pragma unroll
             for (int q = 0; q < QN; ++q) wreg[q] = load16_stream(wq[q] + (size_t)blk * 128);
@@ -712,7 +767,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
         w_load(b0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 3; ++u) wide_b_load<1>(ring[u], xh, xl, b0, u);
+        for (int u = 0; u < 3; ++u) wide_b_load<1, PL>(ring[u], x, b0, u);
         __builtin_amdgcn_sched_barrier(0);
         w_store(gemm_lds);
         w_load(min(b0 + 1, last));
@@ -726,10 +781,16 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
                 const uint4* at = gemm_lds + h * 2048;
                 uint4 a0[4], a1[4];
                 wide_a_read(a0, at, 0, lane);
+                if constexpr (PL > 2) {
+#pragma unroll
+                    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) bs[nt][r] = 0.f;
+                }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     // unit u + 3 of the stream: the last unit of this block, then the first three of the next
-                    wide_b_load<1>(ring[(u + 3) & 3], xh, xl, u == 0 ? tt : min(tt + 1, last), (u + 3) & 3);
+                    wide_b_load<1, PL>(ring[(u + 3) & 3], x, u == 0 ? tt : min(tt + 1, last), (u + 3) & 3);
                     __builtin_amdgcn_sched_barrier(0);
                     if (u == 1) {
                         // the next block's weights (requested one block ago) move to the other LDS buffer, whose
@@ -740,36 +801,47 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
                     }
                     wide_a_read(a1, at, 2 * u + 1, lane);
                     __builtin_amdgcn_sched_barrier(0);
-                    wide_step<1>(a0, ring[u], 0, acc);
+                    if constexpr (PL > 2) wide_step3(a0, ring[u], 0, bs, tl);
+                    else wide_step<1>(a0, ring[u], 0, acc);
                     __builtin_amdgcn_sched_barrier(0);
                     if (u < 3) wide_a_read(a0, at, 2 * u + 2, lane);
                     __builtin_amdgcn_sched_barrier(0);
-                    wide_step<1>(a1, ring[u], 1, acc);
+                    if constexpr (PL > 2) wide_step3(a1, ring[u], 1, bs, tl);
+                    else wide_step<1>(a1, ring[u], 1, acc);
                     __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (PL > 2) {
+#pragma unroll
+                    for (int nt = 0; nt < 4; ++nt) acc[nt][0] += bs[nt];
                 }
                 __syncthreads();
             }
         }
+        if constexpr (PL > 2) {
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) acc[nt][0] += tl[nt];
+        }
     }
 
     // lane (j, g) holds D[8b + 4g + r][j] in register 4b + r: four consecutive weight rows of token row j
-    if (wave >= MT) return;
-    const int m = wave * 32 + (lane & 31);
+    if (mtile >= MT) return;
+    const int m = mtile * 32 + (lane & 31);
     if (SWIGLU) {
         const int F = N >> 1, f0 = ntile * 64 + 4 * (lane >> 5);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                bf16_t hi[4], lo[4];
+                bf16_t e[4][PL];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float gt = acc[nt][0][4 * b + r], up = acc[nt + 2][0][4 * b + r];
-                    split_bf16(gt / (1.f + expf(-gt)) * up, hi[r], lo[r]);
+                    split_planes<PL>(gt / (1.f + expf(-gt)) * up, e[r]);
                 }
                 const size_t o = tiled_off(m, f0 + nt * 32 + 8 * b, F);         // four columns inside one 8-element group
-                *reinterpret_cast<uint2*>(act_hi + o) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-                *reinterpret_cast<uint2*>(act_lo + o) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+                *reinterpret_cast<uint2*>(act_hi + o) = plane_quad<PL>(e, 0);
+                *reinterpret_cast<uint2*>(act_lo + o) = plane_quad<PL>(e, 1);
+                if (PL > 2) *reinterpret_cast<uint2*>(act_lo2 + o) = plane_quad<PL>(e, PL - 1);
             }
         return;
     }
@@ -1050,12 +1122,11 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
     const bf16_t* wlane = W + (size_t)(wrow + (lane >> 4)) * K + (lane & 15) * 8;
     const size_t wstep = (size_t)4 * K;
     const int wr0 = lane >> 4, wc = lane & 15;
-    const bf16_t* xh[MT];
-    const bf16_t* xl[MT];
+    const bf16_t* x[MT][2];
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
         const size_t o = (size_t)j * nblk * 4096 + lane * 8;
-        xh[j] = Xhi + o; xl[j] = Xlo + o;
+        x[j][0] = Xhi + o; x[j][1] = Xlo + o;
     }
 
     f32x16 acc[4][MT];
@@ -1089,7 +1160,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
         w_load(wreg[0], blk(0));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < RING - 1; ++i) wide_b_load<MT>(ring[i], xh, xl, blk(i), wave);
+        for (int i = 0; i < RING - 1; ++i) wide_b_load<MT, 2>(ring[i], x, blk(i), wave);
         __builtin_amdgcn_sched_barrier(0);
         w_store(wreg[0], gemm_lds);
         w_load(wreg[NSET - 1], blk(1));
@@ -1102,7 +1173,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                 if (tt >= nb) break;                        // uniform
                 const uint4* at = gemm_lds + (u & 1) * 2048;
                 uint4* other = gemm_lds + ((u & 1) ^ 1) * 2048;   // its readers passed the barrier that ended the previous block
-                wide_b_load<MT>(ring[(u + RING - 1) % RING], xh, xl, blk(tt + RING - 1), wave);
+                wide_b_load<MT, 2>(ring[(u + RING - 1) % RING], x, blk(tt + RING - 1), wave);
                 __builtin_amdgcn_sched_barrier(0);
                 w_load(wreg[u & 1], blk(tt + 2));           // this set's previous block was stored one block ago
                 __builtin_amdgcn_sched_barrier(0);
@@ -1843,22 +1914,29 @@ __global__ __launch_bounds__(256) void k_chunk_attn_combine(const float* __restr
 
 static bool row_kernel_ok(const Geom& g, int S) { return g.d % 4 == 0 && g.d <= ROW_VEC_MAX * 1024 && S >= 1 && S <= CHUNK_GEMM_MAX_SPLIT; }
 
-hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, int S, int MT, const float* gain,
-                                   int rows, const Geom& g, hipStream_t s) {
-    if (!row_kernel_ok(g, S)) return hipErrorInvalidValue;
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(rows), dim3(256), 0, s, c.x, c.part, S, (size_t)MT * 32 * g.d, g.d, gain, g.eps, g.d, c.nrm_hi, c.nrm_lo); };
-    if (S == 1) go(k_chunk_resid_norm<1>);
-    else if (S == 2) go(k_chunk_resid_norm<2>);
-    else if (S <= 4) go(k_chunk_resid_norm<4>);
-    else go(k_chunk_resid_norm<CHUNK_GEMM_MAX_SPLIT>);
+template <int PL>
+static hipError_t resid_norm_t(const ChunkBuffers& c, int S, int MT, const float* gain, int rows, const Geom& g, hipStream_t s) {
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(rows), dim3(256), 0, s, c.x, c.part, S, (size_t)MT * 32 * g.d, g.d, gain, g.eps, g.d, c.nrm_hi, c.nrm_lo, c.nrm_lo2); };
+    if (S == 1) go(k_chunk_resid_norm<1, PL>);
+    else if (S == 2) go(k_chunk_resid_norm<2, PL>);
+    else if (S <= 4) go(k_chunk_resid_norm<4, PL>);
+    else go(k_chunk_resid_norm<CHUNK_GEMM_MAX_SPLIT, PL>);
     return hipGetLastError();
 }
 
+hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, int S, int MT, const float* gain,
+                                   int rows, const Geom& g, hipStream_t s, int planes) {
+    if (!row_kernel_ok(g, S)) return hipErrorInvalidValue;
+    return planes == 3 ? resid_norm_t<3>(c, S, MT, gain, rows, g, s) : resid_norm_t<2>(c, S, MT, gain, rows, g, s);
+}
+
 hipError_t launch_chunk_embed_norm(const void* E, const ChunkBuffers& c, const float* gain, int rows, const DecodeBuffers& b, const Geom& g,
-                                   hipStream_t s) {
+                                   hipStream_t s, int planes) {
     if (!row_kernel_ok(g, 1)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_chunk_embed_norm, dim3(rows), dim3(256), 0, s, (const bf16_t*)E, c.tab, rows, b.step, b.seq_state, c.chosen_host, c.x, gain,
-                       g.eps, g.d, c.nrm_hi, c.nrm_lo);
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(rows), dim3(256), 0, s, (const bf16_t*)E, c.tab, rows, b.step, b.seq_state, c.chosen_host, c.x, gain,
+                                               g.eps, g.d, c.nrm_hi, c.nrm_lo, c.nrm_lo2); };
+    if (planes == 3) go(k_chunk_embed_norm<3>);
+    else go(k_chunk_embed_norm<2>);
     return hipGetLastError();
 }
 
@@ -1904,7 +1982,7 @@ hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, co
 
 constexpr int ATTN_LDS_BYTES = 4 * 1024 * 16;       // k_chunk_attn: per wave one K tile, two planes
 
-constexpr int GEMM_LDS_BYTES = (2048 + 2 * 2 * 512) * 16;   // k_chunk_gemm: weight tiles, two buffers of activations
+constexpr int gemm_lds_bytes(int planes) { return (2048 + 2 * planes * 512) * 16; }    // k_chunk_gemm: weight tiles, two buffers of activations
 constexpr int GEMM_WIDE_LDS_BYTES = 2 * 2048 * 16;  // k_chunk_gemm_wide: two buffers of one 128 x 128 weight block
 template <bool SWIGLU>
 static const void* big_func(int nt) {
@@ -1921,19 +1999,28 @@ static int big_lds_bytes(int nt) { return 3 * (nt * 2048 + BIG_M * 4096); }
 
 hipError_t chunk_init() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm<true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm<false, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes(2)))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm<true, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes(2)))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_attn, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_attn_wide, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_decode_attn_mfma, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_ks<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<false>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm_wide<false, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     for (int nt = 4; nt <= 8; ++nt) {
         if ((e = hipFuncSetAttribute(big_func<false>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
         if ((e = hipFuncSetAttribute(big_func<true>(nt), hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(nt)))) return e;
     }
-    if ((e = hipFuncSetAttribute((const void*)k_chunk_gemm_wide<true>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm_wide<true, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    return hipSuccess;
+}
+
+hipError_t chunk_init_wide() {
+    hipError_t e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm<false, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes(3)))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm<true, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes(3)))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm_wide<false, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
+    if ((e = hipFuncSetAttribute((const void*)(k_chunk_gemm_wide<true, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_WIDE_LDS_BYTES))) return e;
     return hipSuccess;
 }
 
@@ -1959,13 +2046,24 @@ hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, con
     // one row tile: weight-streaming kernel, a wave per 32 weight rows; two: the waves split the k-steps; three or four:
     // a wave per row tile (128-row workgroups); more: 256-row workgroups with pl.nt weight-row tiles
     if (MT == 1) {
-        hipLaunchKernelGGL((k_chunk_gemm<false>), grid, block, GEMM_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr, 0);
+        hipLaunchKernelGGL((k_chunk_gemm<false, 2>), grid, block, gemm_lds_bytes(2), s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, nullptr, nullptr, nullptr, 0);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, false>), grid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<false>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, MT, nullptr, nullptr);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<false, 2>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, MT, nullptr, nullptr, nullptr);
     } else return launch_big<false>((const bf16_t*)W, N, K, xhi, xlo, c.part, S, pl.nt, MT, nullptr, nullptr, s);
     return hipGetLastError();
+}
+
+// Gate rows per wave-tile of k_chunk_gemm: the fewest whole rounds of tiles over the device's waves that 16 rows per tile allow.
+static int gate_rows_per_wave(int F) {
+    const int waves = 4 * std::max(1, decode_gemv_grid());
+    int rp = 16;
+    for (int m = 1; m <= 64; ++m) {
+        rp = (F + waves * m - 1) / (waves * m);
+        if (rp <= 16) break;
+    }
+    return std::min(std::max(rp, 1), 16);
 }
 
 // Gate/up product with the SwiGLU in its epilogue (no split-K): W = [gate rows | up rows] (2F x K), result in
@@ -1975,21 +2073,39 @@ hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* x
     if (MT < 1 || MT > CHUNK_MAX / 32 || F < 1 || K % 128 || (MT > 1 && F % 64)) return hipErrorInvalidValue;
     const bf16_t* Wb = (const bf16_t*)W;
     if (MT == 1) {
-        // gate rows per wave-tile: the fewest whole rounds of tiles over the device's waves that 16 rows per tile allow
-        const int waves = 4 * std::max(1, decode_gemv_grid());
-        int rp = 16;
-        for (int m = 1; m <= 64; ++m) {
-            rp = (F + waves * m - 1) / (waves * m);
-            if (rp <= 16) break;
-        }
-        rp = std::min(std::max(rp, 1), 16);
-        const int tiles = (F + rp - 1) / rp;
-        hipLaunchKernelGGL((k_chunk_gemm<true>), dim3((tiles + 3) / 4, 1), dim3(256), GEMM_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, rp);
+        const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
+        hipLaunchKernelGGL((k_chunk_gemm<true, 2>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(2), s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, nullptr, rp);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<true>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<true, 2>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo, nullptr);
     } else return launch_big<true>(Wb, 2 * F, K, xhi, xlo, nullptr, 1, pl.nt, MT, c.act_hi, c.act_lo, s);
+    return hipGetLastError();
+}
+
+// Inputs of three planes: one row tile k_chunk_gemm, more k_chunk_gemm_wide.
+hipError_t launch_wide_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c, int S,
+                            int MT, hipStream_t s) {
+    const size_t ps = (size_t)MT * 32 * N;
+    if (S < 1 || S > CHUNK_GEMM_MAX_SPLIT || S > K / 128 || N % 128 || K % 128 || ps * S > c.part_capacity || MT < 1 || MT > WIDE_ROWS_MAX / 32) return hipErrorInvalidValue;
+    if (MT == 1)
+        hipLaunchKernelGGL((k_chunk_gemm<false, 3>), dim3(N / 128, S), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, N, K, xhi, xlo, xlo2, c.part, ps, N, S, nullptr, nullptr, nullptr, 0);
+    else
+        hipLaunchKernelGGL((k_chunk_gemm_wide<false, 3>), dim3((unsigned)(N / 128) * S * ((MT + 3) / 4)), dim3(256), GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, xlo2,
+                           c.part, ps, N, S, MT, nullptr, nullptr, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c,
+                                   int MT, hipStream_t s) {
+    if (F < 1 || F % 64 || K % 128 || MT < 1 || MT > WIDE_ROWS_MAX / 32) return hipErrorInvalidValue;
+    if (MT == 1) {
+        const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
+        hipLaunchKernelGGL((k_chunk_gemm<true, 3>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2, nullptr, (size_t)0, 0, 1,
+                           c.act_hi, c.act_lo, c.act_lo2, rp);
+    } else
+        hipLaunchKernelGGL((k_chunk_gemm_wide<true, 3>), dim3((unsigned)(F / 64) * ((MT + 3) / 4)), dim3(256), GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2,
+                           nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo, c.act_lo2);
     return hipGetLastError();
 }
 

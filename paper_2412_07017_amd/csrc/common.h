@@ -89,6 +89,23 @@ template <> struct Elem<bf16_t> {
     __device__ static __forceinline__ void store1(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
+// Offset (elements) of (row m, column k) in a tiled plane with K columns: the inputs of the products on the matrix cores, stored
+// in operand order (chunk_kernels.hip).
+__device__ __forceinline__ size_t tiled_off(int m, int k, int K) {
+    const int kk = k & 127;
+    return ((((size_t)(m >> 5) * (K >> 7) + (k >> 7)) * 8 + (kk >> 4)) * 2 + ((kk >> 3) & 1)) * 256 + (size_t)(m & 31) * 8 + (kk & 7);
+}
+
+// v as PL bf16 planes, each the rounded remainder of the ones before it: two keep about 16 bits of mantissa, three all 24.
+template <int PL>
+__device__ __forceinline__ void split_planes(float v, bf16_t (&p)[PL]) {
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+        p[i] = f32_to_bf16(v);
+        v -= __uint_as_float((uint32_t)p[i] << 16);
+    }
+}
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // 16-byte loads through pointers that are known to be global memory (a pointer read from a table in

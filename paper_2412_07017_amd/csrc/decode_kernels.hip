@@ -323,6 +323,7 @@ struct AttnArgs {
     int32_t nsplit;
     int32_t defer_merge;    // 1: leave the partials to the O projection (no merge here, even for one split)
     int32_t pos0, seq;      // MODE 2: position of row 0 and sequence (the step descriptor is not read)
+    bf16_t *o_hi, *o_lo, *o_lo2;    // MODE 2, optional: the output goes to these tiled planes instead of o
     PipeSync sync;
 };
 
@@ -346,6 +347,14 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs
         a.q += r * g.Hq * DH; a.o += r * g.Hq * DH; a.counters += r * g.Hkv;
         a.part_acc += r * g.Hq * nsplit * DH; a.part_ml += r * g.Hq * nsplit * 2;
     }
+    auto put = [&](int hq, int dim, float v) {
+        if (ROWS && a.o_hi) {
+            bf16_t p[3];
+            split_planes<3>(v, p);
+            const size_t o = tiled_off((int)blockIdx.z, hq * DH + dim, g.Hq * DH);
+            a.o_hi[o] = p[0]; a.o_lo[o] = p[1]; a.o_lo2[o] = p[2];
+        } else store_coherent(a.o + hq * DH + dim, v);
+    };
     if (PIPE) pipe_stamp(a.sync, 0);
     if (PIPE && !pipe_wait(a.sync, &s_go)) return;
     // split boundaries: equal shares rounded up to whole workgroup rounds
@@ -367,7 +376,7 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs
         for (int hh = 1; hh < G; ++hh) if (hh == h) { M = mh[hh]; L = lh[hh]; }
         const int hq = kvh * G + h;
         if (nsplit == 1 && !a.defer_merge) {
-            store_coherent(a.o + hq * DH + dim, A / L);
+            put(hq, dim, A / L);
         } else {
             store_coherent(a.part_acc + ((size_t)hq * nsplit + split) * DH + dim, A);
             if (dim == 0) {
@@ -435,9 +444,8 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs
             __syncthreads();
             if (half == 0 && t < NO) {
                 const float4 o2 = s_half[tid];
-                float* op = a.o + (size_t)hq * DH + 4 * d4;
-                store_coherent(op, r.x + o2.x); store_coherent(op + 1, r.y + o2.y);
-                store_coherent(op + 2, r.z + o2.z); store_coherent(op + 3, r.w + o2.w);
+                put(hq, 4 * d4, r.x + o2.x); put(hq, 4 * d4 + 1, r.y + o2.y);
+                put(hq, 4 * d4 + 2, r.z + o2.z); put(hq, 4 * d4 + 3, r.w + o2.w);
             }
             __syncthreads();
         }
@@ -743,9 +751,12 @@ hipError_t launch_attn_decode(int dtype, const void* kv_layer, int nsplit, bool 
     return g.dh == 64 ? launch_attn_t<bf16_t, 64, false>(a, g, s) : launch_attn_t<bf16_t, 128, false>(a, g, s);
 }
 
-hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s) {
-    if (nsplit < 1 || nsplit > ATTN_MAX_SPLIT || p.n < 1 || p.n > ROWS_MAX) return hipErrorInvalidValue;
+hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s,
+                            const ChunkBuffers* planes) {
+    if (nsplit < 1 || nsplit > ATTN_MAX_SPLIT || p.n < 1 || p.n > (planes ? WIDE_ROWS_MAX : ROWS_MAX)) return hipErrorInvalidValue;
+    if (nsplit > 1 && p.n * nsplit > ROWS_MAX * ATTN_MAX_SPLIT) return hipErrorInvalidValue;
     AttnArgs a{};
+    if (planes) { a.o_hi = planes->att_hi; a.o_lo = planes->att_lo; a.o_lo2 = planes->att_lo2; }
     a.q = rb.q; a.kv_layer = kv_layer; a.o = rb.o; a.part_acc = rb.part_acc; a.part_ml = rb.part_ml; a.counters = rb.counters;
     a.nsplit = nsplit; a.pos0 = p.pos0; a.seq = p.seq;
     if (dtype == 0) return g.dh == 64 ? launch_attn_t<float, 64, false>(a, g, s, p.n) : launch_attn_t<float, 128, false>(a, g, s, p.n);

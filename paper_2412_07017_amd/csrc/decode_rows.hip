@@ -1,11 +1,12 @@
-// Several consecutive rows of one sequence per pass over the weights, for the models outside the matrix-core append
-// path (fp32 models, head_dim 64, the single-plane cache, sizes that are no multiple of 128).  The arithmetic of a row is
+// Several consecutive rows of one sequence per pass over the weights, for the models outside the matrix-core paths (fp32 models,
+// sizes that are no multiple of 128; bf16 models of such sizes with head_dim 64 or the single-plane cache take passes of
+// up to 512 rows on the matrix cores, forward_wide_rows, where memory allows).  The arithmetic of a row is
 // that of the single-row kernels: fp32 activations, fp32 accumulation on the vector units, the same epilogues.
 //
 // A single-row pass is bound by the weight stream (8B shape) or by the launches (small models); either cost is nearly the
 // same for up to ROWS_MAX rows, so an interrupt or a prompt takes ROWS_MAX tokens per pass instead of one.  Measured, one
 // layer of the 8B shape with the single-plane cache: 152 us for eight rows (QKV 24, attention 9, O 19, gate/up 52, down 45)
-// against 8 x 94 us token by token; a short session (203 + 24 tokens appended, 16 steps, two layers) 53.4 -> 15.2 ms; the
+// against 8 x 94 us token by token (128 us for up to 32 rows on the matrix cores); the
 // tiny fp32 preset's session (64 + 8 tokens, 32 steps) 7.3 -> 3.1 ms with k_rows_gemv alone; 1.91 ms with the kernels for small
 // products, here and in decode_kernels.hip.
 #include "common.h"
@@ -333,6 +334,60 @@ __global__ __launch_bounds__(256) void k_rows_embed(const WT* __restrict__ E, Ro
     for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256) x[(size_t)r * d + i] = Elem<WT>::load1(row + i);
 }
 
+// Passes of forward_wide_rows, between the QKV product and the attention: the partial planes of the product are added in split order,
+// queries and keys rotated, keys and values stored row by row (rounded to bf16, with the remainder where the cache has a lo plane),
+// queries left in fp32.  dh / 8 threads per (row, head), four pairs (i, i + dh / 2) each.  P holds the heads from h0 on.
+template <int DH>
+__global__ __launch_bounds__(256) void k_rows_rope_kv(const float* __restrict__ P, int S, size_t s_stride, int n_stride, Geom g, RowsPass p,
+                                                      const float* __restrict__ rope_cos, const float* __restrict__ rope_sin, bf16_t* __restrict__ kv_layer,
+                                                      float* __restrict__ q, int h0) {
+    constexpr int half = DH / 2, LPI = DH / 8;
+    const int nh = g.Hq + 2 * g.Hkv - h0, item = blockIdx.x * (256 / LPI) + threadIdx.x / LPI, i = 4 * (threadIdx.x % LPI);
+    if (item >= p.n * nh) return;
+    const int m = item / nh, hl = item - m * nh, h = hl + h0, pos = p.pos0 + m;
+    float4 pa[CHUNK_GEMM_MAX_SPLIT], pb[CHUNK_GEMM_MAX_SPLIT];
+#pragma unroll
+    for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s) {
+        const float* src = P + (size_t)min(s, S - 1) * s_stride + (size_t)m * n_stride + hl * DH + i;
+        pa[s] = *reinterpret_cast<const float4*>(src); pb[s] = *reinterpret_cast<const float4*>(src + half);
+    }
+    float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < CHUNK_GEMM_MAX_SPLIT; ++s)
+        if (s < S) {
+            a[0] += pa[s].x; a[1] += pa[s].y; a[2] += pa[s].z; a[3] += pa[s].w;
+            b[0] += pb[s].x; b[1] += pb[s].y; b[2] += pb[s].z; b[3] += pb[s].w;
+        }
+    if (h < g.Hq + g.Hkv) {                                         // values are not rotated
+        const float4 c4 = *reinterpret_cast<const float4*>(rope_cos + (size_t)pos * half + i), s4 = *reinterpret_cast<const float4*>(rope_sin + (size_t)pos * half + i);
+        const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float ra = a[e] * c[e] - b[e] * sn[e], rb = b[e] * c[e] + a[e] * sn[e];
+            a[e] = ra; b[e] = rb;
+        }
+    }
+    if (h < g.Hq) {
+        float* o = q + ((size_t)m * g.Hq + h) * DH + i;
+        *reinterpret_cast<float4*>(o) = make_float4(a[0], a[1], a[2], a[3]);
+        *reinterpret_cast<float4*>(o + half) = make_float4(b[0], b[1], b[2], b[3]);
+        return;
+    }
+    const int hk = h - g.Hq;
+    bf16_t* dst = kv_layer + (size_t)p.seq * g.kv_seq_stride + (hk < g.Hkv ? (size_t)hk * g.kv_head_stride : g.kv_v_offset + (size_t)(hk - g.Hkv) * g.kv_head_stride) +
+                  (size_t)pos * DH + i;
+    bf16_t ea[4][2], eb[4][2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { split_planes<2>(a[e], ea[e]); split_planes<2>(b[e], eb[e]); }
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl) {
+        if (pl && !g.kv_lo_offset) break;
+        bf16_t* o = dst + (pl ? g.kv_lo_offset : 0);
+        *reinterpret_cast<uint2*>(o) = make_uint2(ea[0][pl] | ((uint32_t)ea[1][pl] << 16), ea[2][pl] | ((uint32_t)ea[3][pl] << 16));
+        *reinterpret_cast<uint2*>(o + half) = make_uint2(eb[0][pl] | ((uint32_t)eb[1][pl] << 16), eb[2][pl] | ((uint32_t)eb[3][pl] << 16));
+    }
+}
+
 // ---- launchers ------------------------------------------------------------------------------------------------------
 
 namespace {
@@ -421,6 +476,17 @@ hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, con
     const dim3 grid((g.d + 255) / 256, p.n);
     if (dtype == 0) hipLaunchKernelGGL(k_rows_embed<float>, grid, dim3(256), 0, s, (const float*)E, tk, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
     else hipLaunchKernelGGL(k_rows_embed<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)E, tk, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_rope_kv(const ChunkBuffers& c, int S, int MT, void* kv_layer, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
+                               const Geom& g, hipStream_t s, bool kv_only) {
+    const int h0 = kv_only ? g.Hq : 0, nh = g.Hq + 2 * g.Hkv - h0, per = 256 / (g.dh / 8);
+    if ((g.dh != 64 && g.dh != 128) || S < 1 || S > CHUNK_GEMM_MAX_SPLIT || p.n < 1 || p.n > MT * 32 || !g.kv_v_offset) return hipErrorInvalidValue;
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((p.n * nh + per - 1) / per), dim3(256), 0, s, c.part, S, (size_t)MT * 32 * nh * g.dh, nh * g.dh, g, p,
+                                               b.rope_cos, b.rope_sin, (bf16_t*)kv_layer, rb.q, h0); };
+    if (g.dh == 128) go(k_rows_rope_kv<128>);
+    else go(k_rows_rope_kv<64>);
     return hipGetLastError();
 }
 

@@ -74,10 +74,11 @@ struct ChunkBuffers {
     ChunkTab tab;             // the running pass's entries in it
     int32_t* chosen_host;     // pinned, [CHUNK_MAX_GROUPS]: token chosen for the first row of each group
     float* x;                 // [pass rows][d] residual stream
-    // inputs of the products, as many rows each, stored in matrix-core operand order (tiled planes)
-    bf16_t *nrm_hi, *nrm_lo;  // d columns:     normalised input of the QKV, gate/up and output-head products
-    bf16_t *att_hi, *att_lo;  // Hq*dh columns: attention output
-    bf16_t *act_hi, *act_lo;  // F columns:     SwiGLU output
+    // inputs of the products, as many rows each, stored in matrix-core operand order (tiled planes); the third plane
+    // (lo2, the remainder of the other two) exists for the models of forward_wide_rows only
+    bf16_t *nrm_hi, *nrm_lo, *nrm_lo2;  // d columns:     normalised input of the QKV, gate/up and output-head products
+    bf16_t *att_hi, *att_lo, *att_lo2;  // Hq*dh columns: attention output
+    bf16_t *act_hi, *act_lo, *act_lo2;  // F columns:     SwiGLU output
     // rotated, scaled queries [Hkv][q_cols][dh]: the columns of a group are [q head within the kv group][row]
     bf16_t *q_hi, *q_lo;
     int q_cols;               // G * pass rows + 32 (a tile may read up to 31 columns past its group)
@@ -94,16 +95,17 @@ struct ChunkBuffers {
 // append path.  Eight rows: the vectors of 4096 columns fill 128 of the 160 KiB of LDS, and the 2 x 8 products per weight
 // element take the vector units about two thirds of the time that the weight stream takes.
 constexpr int ROWS_MAX = 8;
+constexpr int WIDE_ROWS_MAX = 512;      // rows per pass of forward_wide_rows
 struct RowsTokens { int32_t t[ROWS_MAX]; };
 struct RowsPass { int32_t seq, pos0, n; };
 struct RowsBuffers {
     float* x;               // [ROWS_MAX][d]
-    float* q;               // [ROWS_MAX][Hq*dh]
+    float* q;               // [rows of a pass][Hq*dh]: ROWS_MAX, or those of forward_wide_rows
     float* o;               // [ROWS_MAX][Hq*dh]
     float* a;               // [ROWS_MAX][F]
     float* part_acc;        // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][dh]
     float* part_ml;         // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][2]
-    int32_t* counters;      // [ROWS_MAX][Hkv], zero between launches
+    int32_t* counters;      // [rows of a pass][Hkv], zero between launches
 };
 // whether the vectors and the parked results of every product fit LDS with the present number of workgroups
 bool rows_supported(int dtype, const Geom& g);
@@ -112,7 +114,13 @@ hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, con
                              const Geom& g, hipStream_t s);
 hipError_t launch_rows_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const RowsBuffers& rb, const DecodeBuffers& b,
                            const RowsPass& p, const Geom& g, hipStream_t s);
-hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
+// planes: null, or the buffers whose att planes take the output as three bf16 planes (any number of rows; rows x nsplit bounded
+// by the partial results' size as long as there is more than one split)
+hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s,
+                            const ChunkBuffers* planes = nullptr);
+// bf16 models: sums the partial planes of a QKV product (kv_only: of its key and value rows), rotates, writes the row-major cache and rb.q
+hipError_t launch_rows_rope_kv(const ChunkBuffers& c, int S, int MT, void* kv_layer, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
+                               const Geom& g, hipStream_t s, bool kv_only);
 hipError_t launch_rows_oproj(int dtype, const void* wo, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
 hipError_t launch_rows_gateup(int dtype, const void* wgu, const float* gain, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
 hipError_t launch_rows_down(int dtype, const void* wd, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
@@ -145,11 +153,13 @@ hipError_t launch_decode_fused(int dtype, const FusedPlan& plan, const FusedLaun
 hipError_t decode_init(int dtype, int max_k);
 void decode_set_gemv_grid(int grid);
 int decode_gemv_grid();
-hipError_t chunk_init();
+hipError_t chunk_init();         // dynamic LDS of the append path's kernels
+hipError_t chunk_init_wide();    // ... of those of forward_wide_rows
+// planes: 2, or 3 (see forward_wide_rows)
 hipError_t launch_chunk_embed_norm(const void* E, const ChunkBuffers& c, const float* gain, int rows, const DecodeBuffers& b, const Geom& g,
-                                   hipStream_t s);
+                                   hipStream_t s, int planes = 2);
 hipError_t launch_chunk_resid_norm(const ChunkBuffers& c, int S, int MT, const float* gain, int rows,
-                                   const Geom& g, hipStream_t s);
+                                   const Geom& g, hipStream_t s, int planes = 2);
 // residual stream of the last row of group `group` -> the single-row path's x (and its sequence -> the step descriptor)
 hipError_t launch_chunk_last_row(const ChunkBuffers& c, int S, int MT, int group, const DecodeBuffers& b, const Geom& g,
                                  hipStream_t s);
@@ -170,6 +180,11 @@ hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, con
                              GemmPlan pl, int MT, hipStream_t s);
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
                                     GemmPlan pl, int MT, hipStream_t s);
+// The same products with inputs of three planes (xlo2 / c.act_lo2 the third), any number of row tiles.
+hipError_t launch_wide_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c, int S,
+                            int MT, hipStream_t s);
+hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c,
+                                   int MT, hipStream_t s);
 hipError_t launch_chunk_attn(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, const Geom& g, hipStream_t s);
 hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, int nblocks, const Geom& g,
                                   hipStream_t s);

@@ -158,3 +158,31 @@ print(json.dumps(sorted(names)))
                     assert any(want in n for n in names), want
         for loads in (1, 2, 4):
             assert any(f"k_rows_smallI{t}" in n and f"ELi{loads}EEE" in n for n in names), (t, loads)
+
+
+# Models of the wide rows path (bf16, the cache row by row): where their buffers find no room, or the graphs after them, the context is
+# created without them and takes passes of eight rows; option chunk bounds a pass as everywhere
+def test_wide_rows_and_little_memory(host):
+    model = "context(1024, kv_format=1, d_model=1024, ffn=2048)"
+    full = host(f"{model}; print(json.dumps(hip.host_hip_peak()))")
+    body = f'''
+try:
+    lm = {model}
+    out = []
+    for value in (0, 100, 1):
+        lm.set_option("chunk", value); lm.reset(0)
+        ls = launches(lambda: lm.prefill(0, tokens(600)))
+        out.append([count(ls, "k_chunk_embed_norm"), count(ls, "k_rows_embed")])
+    lm.close()
+except pkg.AsyncLMError as e: out = e.code
+print(json.dumps([out, hip.host_hip_used()]))
+'''
+    wide, rows = [[2, 0], [6, 0], [0, 0]], [[0, 75], [0, 75], [0, 0]]
+    assert host(body) == [wide, 0] and host(body, HOST_HIP_BUDGET=full) == [wide, 0]
+    assert host(body, HOST_HIP_BUDGET=full - 1) == [rows, 0]
+    assert host(body, HOST_HIP_GRAPHS=full - 1) == [rows, 0]
+    assert host(body, HOST_HIP_BUDGET=full // 100) == [-4, 0]
+    # sizes that are no multiples of 128, fp32: the rows path as before
+    for other in ("ffn=2056", "d_model=1032", "dtype='fp32'"):
+        kw = "kv_format=0, " if "fp32" in other else "kv_format=1, "
+        assert host(f"lm = context(1024, {kw}{other}); print(json.dumps(count(launches(lambda: lm.prefill(0, tokens(16))), 'k_rows_embed')))") == 2
