@@ -83,6 +83,7 @@ struct asynclm_ctx {
     bool chunk_ok = false;              // the matrix-core append path supports this model
     int pass_rows = CHUNK_BATCH_ROWS;   // rows that one of its passes can hold (CHUNK_BATCH_ROWS .. CHUNK_MAX; fewer: PASS_ROWS_UNALIGNED)
     RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
+    int rows_pass = ROWS_MAX;           // ... this many at most (what the buffers hold)
     int wide_rows = 0;                  // ... or this many on the matrix cores (forward_wide_rows); 0: not this model
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
@@ -703,6 +704,16 @@ int pick_wide_split(const asynclm_ctx* c, int N, int K, int MT) {
     return best;
 }
 
+// Key splits of the attention of n rows: one per 256 keys (one pass of its inner loop), as many as the partial results hold; merged by
+// the last workgroup of a (row, kv head).
+int pick_rows_split(const asynclm_ctx* c, int keys, int n) {
+    const int most = std::min(ATTN_MAX_SPLIT, std::max(1, ROWS_MAX * ATTN_MAX_SPLIT / n));
+    if (c->opt_attn_split > 0) return std::min(c->opt_attn_split, most);
+    int nsplit = 1;
+    while (nsplit < (keys + 255) / 256 && 2 * nsplit <= most) nsplit *= 2;
+    return nsplit;
+}
+
 // One forward pass over n = 2..wide_rows rows of one sequence: bf16 models that keep the cache row by row (the single-plane format,
 // head_dim 64), sizes multiples of 128.  Their activations are fp32 and stay so: the products take them as three bf16 planes, which
 // together are the fp32 value, on the matrix cores (three products per weight, fp32 sums), and everything between the products is
@@ -718,12 +729,7 @@ hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int
     hipStream_t s = c->stream;
     const RowsPass p{seq, c->len[seq], n};
     const int MT = (n + 31) / 32, nqkv = (g.Hq + 2 * g.Hkv) * g.dh, nkv = 2 * g.Hkv * g.dh, qd = g.Hq * g.dh;
-    // Key splits: one per 256 keys, as many as the partial results hold; without any the output goes straight to the planes
-    const int most = std::min(ATTN_MAX_SPLIT, std::max(1, ROWS_MAX * ATTN_MAX_SPLIT / n));
-    int nsplit = 1;
-    if (c->opt_attn_split > 0) nsplit = std::min(c->opt_attn_split, most);
-    else
-        while (nsplit < (p.pos0 + n + 255) / 256 && 2 * nsplit <= most) nsplit *= 2;
+    const int nsplit = pick_rows_split(c, p.pos0 + n, n);
     const int s_qkv = pick_wide_split(c, nqkv, g.d, MT), s_kv = pick_wide_split(c, nkv, g.d, MT), s_o = pick_wide_split(c, g.d, qd, MT),
               s_down = pick_wide_split(c, g.d, g.F, MT);
     PassBuilder& pb = c->pass;
@@ -754,21 +760,20 @@ hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int
     return hipSuccess;
 }
 
-// One forward pass over n = 2..ROWS_MAX rows of one sequence (models outside the matrix-core append path).
+// One forward pass over n = 2..rows_pass rows of one sequence (models outside the matrix-core paths).
 hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
     const int dt = c->cfg.dtype;
     const Geom& g = c->g;
     hipStream_t s = c->stream;
     const RowsPass p{seq, c->len[seq], n};
-    RowsTokens tk{};
-    for (int r = 0; r < n; ++r) tk.t[r] = tokens[r];
-    // Key splits: one per 256 keys (one pass of the attention's inner loop), merged by the last workgroup of a (row, kv head).
-    int nsplit = 1;
-    if (c->opt_attn_split > 0) nsplit = std::min(c->opt_attn_split, ATTN_MAX_SPLIT);
-    else
-        while (nsplit < (p.pos0 + n + 255) / 256 && nsplit < ATTN_MAX_SPLIT) nsplit *= 2;
+    const int nsplit = pick_rows_split(c, p.pos0 + n, n);
     hipError_t e;
-    if ((e = run(c, KC_EMBED, [&] { return launch_rows_embed(dt, c->embed, tk, c->rb, c->b, p, g, s); }))) return e;
+    for (int r0 = 0; r0 < n; r0 += ROWS_MAX) {
+        RowsTokens tk{};
+        const int m = std::min(ROWS_MAX, n - r0);
+        for (int r = 0; r < m; ++r) tk.t[r] = tokens[r0 + r];
+        if ((e = run(c, KC_EMBED, [&] { return launch_rows_embed(dt, c->embed, tk, r0, m, c->rb, c->b, p, g, s); }))) return e;
+    }
     for (int l = 0; l < c->cfg.n_layers; ++l) {
         void* kvl = kv_layer_ptr(c, l);
         if ((e = run(c, KC_QKV, [&] { return launch_rows_qkv(dt, c->wqkv[l], c->attn_norm[l], kvl, c->rb, c->b, p, g, s); }))) return e;
@@ -792,7 +797,7 @@ int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
     const bool rows_path = !c->chunk_ok && !c->opt_fused && !c->opt_pipeline && rows_supported(c->cfg.dtype, c->g);
     const bool wide_path = c->wide_rows > 0 && !c->opt_fused && !c->opt_pipeline;
     const int chunk = c->chunk_ok ? std::min(c->opt_chunk, c->pass_rows) : wide_path ? std::min(c->opt_chunk, c->wide_rows) :
-                      rows_path ? std::min(c->opt_chunk, ROWS_MAX) : 1;
+                      rows_path ? std::min({c->opt_chunk, c->rows_pass, rows_per_pass(c->cfg.dtype, c->g)}) : 1;
     int i = 0;
     while (i < n) {
         const int rows = std::min(chunk, n - i);
@@ -967,10 +972,11 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
     }
     if (!c->chunk_ok) {
         if ((e = rows_init(cfg->dtype)) != hipSuccess) { report_hip("rows_init", e); return bail(ASYNCLM_E_DEVICE); }
-        const size_t R = ROWS_MAX, qd = (size_t)g.Hq * g.dh;
+        c->rows_pass = rows_per_pass(cfg->dtype, g);
+        const size_t R = c->rows_pass, qd = (size_t)g.Hq * g.dh;
         ALLOC(c->rb.x, R * g.d); ALLOC(c->rb.o, R * qd); ALLOC(c->rb.a, R * g.F);
-        ALLOC(c->rb.part_acc, R * qd * ATTN_MAX_SPLIT);
-        ALLOC(c->rb.part_ml, R * g.Hq * ATTN_MAX_SPLIT * 2);
+        ALLOC(c->rb.part_acc, ROWS_MAX * qd * ATTN_MAX_SPLIT);
+        ALLOC(c->rb.part_ml, (size_t)ROWS_MAX * g.Hq * ATTN_MAX_SPLIT * 2);
         // where memory is too short for the buffers of larger passes (or was, see asynclm_create), passes of ROWS_MAX rows do
         if (max_rows > CHUNK_BATCH_ROWS && (e = alloc_wide_rows(c)) != hipSuccess) { report_hip("buffers of wide passes", e); (void)hipGetLastError(); }
         if (c->wide_rows) *pass_rows = max_rows;

@@ -753,7 +753,7 @@ hipError_t launch_attn_decode(int dtype, const void* kv_layer, int nsplit, bool 
 
 hipError_t launch_rows_attn(int dtype, const void* kv_layer, int nsplit, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s,
                             const ChunkBuffers* planes) {
-    if (nsplit < 1 || nsplit > ATTN_MAX_SPLIT || p.n < 1 || p.n > (planes ? WIDE_ROWS_MAX : ROWS_MAX)) return hipErrorInvalidValue;
+    if (nsplit < 1 || nsplit > ATTN_MAX_SPLIT || p.n < 1 || p.n > (planes ? WIDE_ROWS_MAX : ROWS_PASS_SMALL)) return hipErrorInvalidValue;
     if (nsplit > 1 && p.n * nsplit > ROWS_MAX * ATTN_MAX_SPLIT) return hipErrorInvalidValue;
     AttnArgs a{};
     if (planes) { a.o_hi = planes->att_hi; a.o_lo = planes->att_lo; a.o_lo2 = planes->att_lo2; }

@@ -256,10 +256,21 @@ __global__ __launch_bounds__(ROWS_NW * 64) void k_rows_gemv(RowsArgs a, Geom g) 
 // Small products (at most one row pair per wave of the device, one tile of columns per row): the same without ring and staging,
 // as k_gemv_small: a wave per row pair, its two rows and the input vectors in registers.  Tiny preset, eight rows: QKV 7.7 -> 4.3 us,
 // O 8.4 -> 3.8, gate/up 6.9 -> 4.4, down 8.4 -> 5.8; its session 2.15 -> 1.91 ms.
+// Eight rows per workgroup, any number of workgroups beside each other (grid y): where all products are small a pass is as long as
+// 128 rows, because eight rows use few of the compute units and a launch costs nearly the same: 64 rows of the tiny preset take 5.5 us for QKV
+// (eight: 4.5), 3.9 for O (3.5), 6.9 for gate/up (4.4), 6.0 for down (5.8); its session 1906 -> 1624 us.
 template <typename WT, int EPI, int NS>
 __global__ __launch_bounds__(256) void k_rows_small(RowsArgs a, Geom g) {
     constexpr int EPL = Elem<WT>::EPL, NP = EPL / 4, R = ROWS_MAX;
     __shared__ float sums[4][3 * R];                // per wave: dot products of the two rows, squares
+    {                                               // this workgroup's eight rows of the pass
+        const int r0 = blockIdx.y * R;
+        a.n = min(a.n - r0, R); a.pos0 += r0;
+        a.x += (size_t)r0 * a.K;
+        if (EPI == EPI_QKV) a.q_out += (size_t)r0 * g.Hq * g.dh;
+        else a.y += (size_t)r0 * a.y_stride;
+        if (EPI == EPI_RESID) a.res += (size_t)r0 * a.y_stride;
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int unit = blockIdx.x * 4 + wave, u = min(unit, a.units - 1), Kg = a.K / EPL;
     int rA, rB;
@@ -323,15 +334,15 @@ __global__ __launch_bounds__(256) void k_rows_small(RowsArgs a, Geom g) {
 
 // Rows of the residual stream of a pass; the sequence grows and the step descriptor gets its number for the output head.
 template <typename WT>
-__global__ __launch_bounds__(256) void k_rows_embed(const WT* __restrict__ E, RowsTokens tk, int pos0, int seq, int n, float* __restrict__ x,
+__global__ __launch_bounds__(256) void k_rows_embed(const WT* __restrict__ E, RowsTokens tk, int row0, int pos0, int seq, int n, float* __restrict__ x,
                                                     int d, StepDesc* step, SeqState* st) {
     const int r = blockIdx.y;
-    if (blockIdx.x == 0 && r == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && r == 0 && row0 == 0 && threadIdx.x == 0) {
         step->token = -1; step->pos = pos0; step->seq = seq; step->rows = n;
         st[seq].len = pos0 + n;
     }
     const WT* row = E + (size_t)tk.t[r] * d;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256) x[(size_t)r * d + i] = Elem<WT>::load1(row + i);
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256) x[(size_t)(row0 + r) * d + i] = Elem<WT>::load1(row + i);
 }
 
 // Passes of forward_wide_rows, between the QKV product and the attention: the partial planes of the product are added in split order,
@@ -419,6 +430,10 @@ bool rows_fit(int K, int units) {
     return rows_lds<WT>(K, units, rows_grid(units), &cap) + 1024 <= ROWS_LDS_LIMIT;
 }
 
+// k_rows_small takes the product
+template <typename WT>
+bool rows_small(int K, int units) { return K / Elem<WT>::EPL <= 256 && units <= 4 * decode_gemv_grid(); }
+
 template <typename WT, int EPI>
 const void* rows_small_func(int ns) {
     return ns <= 1 ? (const void*)(k_rows_small<WT, EPI, 1>) : ns == 2 ? (const void*)(k_rows_small<WT, EPI, 2>) : (const void*)(k_rows_small<WT, EPI, 4>);
@@ -426,11 +441,10 @@ const void* rows_small_func(int ns) {
 
 template <typename WT, int EPI>
 hipError_t launch_rows_t(RowsArgs a, const Geom& g, hipStream_t s) {
-    const int kg = a.K / Elem<WT>::EPL;
-    if (kg <= 256 && a.units <= 4 * decode_gemv_grid() && a.n >= 1 && a.n <= ROWS_MAX && a.K % 8 == 0) {
+    if (rows_small<WT>(a.K, a.units) && a.n >= 1 && a.n <= ROWS_PASS_SMALL && a.K % 8 == 0) {
         Geom gg = g;
         void* params[] = {&a, &gg};
-        return hipLaunchKernel(rows_small_func<WT, EPI>((kg + 63) / 64), dim3((a.units + 3) / 4), dim3(256), params, 0, s);
+        return hipLaunchKernel(rows_small_func<WT, EPI>((a.K / Elem<WT>::EPL + 63) / 64), dim3((a.units + 3) / 4, (a.n + ROWS_MAX - 1) / ROWS_MAX), dim3(256), params, 0, s);
     }
     const int grid = rows_grid(a.units), ub = rows_ub(a.units);
     const size_t lds = rows_lds<WT>(a.K, a.units, grid, &a.done_cap);
@@ -469,13 +483,22 @@ bool rows_supported(int dtype, const Geom& g) {
                       : rows_fit<bf16_t>(g.d, nqkv / 2) && rows_fit<bf16_t>(qd, dp) && rows_fit<bf16_t>(g.d, g.F) && rows_fit<bf16_t>(g.F, dp);
 }
 
+template <typename WT>
+static bool rows_all_small(const Geom& g) {
+    const int nqkv = (g.Hq + 2 * g.Hkv) * g.dh, qd = g.Hq * g.dh, dp = (g.d + 1) / 2;
+    return rows_small<WT>(g.d, nqkv / 2) && rows_small<WT>(qd, dp) && rows_small<WT>(g.d, g.F) && rows_small<WT>(g.F, dp);
+}
+
+int rows_per_pass(int dtype, const Geom& g) { return (dtype == 0 ? rows_all_small<float>(g) : rows_all_small<bf16_t>(g)) ? ROWS_PASS_SMALL : ROWS_MAX; }
+
 hipError_t rows_init(int dtype) { return dtype == 0 ? rows_attrs<float>() : rows_attrs<bf16_t>(); }
 
-hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
+hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, int row0, int n, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
                              const Geom& g, hipStream_t s) {
-    const dim3 grid((g.d + 255) / 256, p.n);
-    if (dtype == 0) hipLaunchKernelGGL(k_rows_embed<float>, grid, dim3(256), 0, s, (const float*)E, tk, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
-    else hipLaunchKernelGGL(k_rows_embed<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)E, tk, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
+    if (n < 1 || n > ROWS_MAX || row0 < 0 || row0 + n > p.n) return hipErrorInvalidValue;
+    const dim3 grid((g.d + 255) / 256, n);
+    if (dtype == 0) hipLaunchKernelGGL(k_rows_embed<float>, grid, dim3(256), 0, s, (const float*)E, tk, row0, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
+    else hipLaunchKernelGGL(k_rows_embed<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)E, tk, row0, p.pos0, p.seq, p.n, rb.x, g.d, b.step, b.seq_state);
     return hipGetLastError();
 }
 

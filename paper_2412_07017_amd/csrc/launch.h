@@ -95,22 +95,26 @@ struct ChunkBuffers {
 // append path.  Eight rows: the vectors of 4096 columns fill 128 of the 160 KiB of LDS, and the 2 x 8 products per weight
 // element take the vector units about two thirds of the time that the weight stream takes.
 constexpr int ROWS_MAX = 8;
+constexpr int ROWS_PASS_SMALL = 128;    // rows per pass of a model whose products are all small (k_rows_small)
 constexpr int WIDE_ROWS_MAX = 512;      // rows per pass of forward_wide_rows
 struct RowsTokens { int32_t t[ROWS_MAX]; };
 struct RowsPass { int32_t seq, pos0, n; };
-struct RowsBuffers {
-    float* x;               // [ROWS_MAX][d]
-    float* q;               // [rows of a pass][Hq*dh]: ROWS_MAX, or those of forward_wide_rows
-    float* o;               // [ROWS_MAX][Hq*dh]
-    float* a;               // [ROWS_MAX][F]
-    float* part_acc;        // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][dh]
-    float* part_ml;         // [ROWS_MAX][Hq][ATTN_MAX_SPLIT][2]
-    int32_t* counters;      // [rows of a pass][Hkv], zero between launches
+struct RowsBuffers {        // R rows: as many as a pass can have (ROWS_MAX or ROWS_PASS_SMALL; q and the counters: those of forward_wide_rows too)
+    float* x;               // [R][d]
+    float* q;               // [R][Hq*dh]
+    float* o;               // [R][Hq*dh]
+    float* a;               // [R][F]
+    float* part_acc;        // [ROWS_MAX * ATTN_MAX_SPLIT rows x splits][Hq][dh]
+    float* part_ml;         // [ROWS_MAX * ATTN_MAX_SPLIT][Hq][2]
+    int32_t* counters;      // [R][Hkv], zero between launches
 };
 // whether the vectors and the parked results of every product fit LDS with the present number of workgroups
 bool rows_supported(int dtype, const Geom& g);
+// rows per pass: ROWS_MAX, or ROWS_PASS_SMALL where all products are small
+int rows_per_pass(int dtype, const Geom& g);
 hipError_t rows_init(int dtype);
-hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
+// Rows row0 .. row0 + n - 1 of the pass (n <= ROWS_MAX: their tokens travel in the kernel's arguments).
+hipError_t launch_rows_embed(int dtype, const void* E, const RowsTokens& tk, int row0, int n, const RowsBuffers& rb, const DecodeBuffers& b, const RowsPass& p,
                              const Geom& g, hipStream_t s);
 hipError_t launch_rows_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const RowsBuffers& rb, const DecodeBuffers& b,
                            const RowsPass& p, const Geom& g, hipStream_t s);

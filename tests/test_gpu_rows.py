@@ -77,3 +77,22 @@ def test_rows_of_a_pass_equal_token_by_token(kind, model):
     assert _rel(lms[0].logits(0), lms[1].logits(0)) <= TOL[kind]
     for lm in lms:
         lm.close()
+
+
+# Models whose products are all small: passes of up to 128 rows, eight per workgroup; around that, around multiples of eight, and with
+# key splits that 128 rows can hold no more than four of
+@pytest.mark.parametrize("kind,model", [(FP32, _model(256, 4, 4, 64, 688, "fp32")), (PAIR, _model(264, 8, 2, 64, 1000, "bf16")), (BF16, _model(136, 4, 1, 128, 264, "bf16"))])
+def test_long_passes_of_small_models(kind, model):
+    import paper_2412_07017_amd as pkg
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    tk = lambda n, sub: [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 932, n, model.vocab, sub=sub)]
+    lms = [pkg.AsyncLM(model, w, max_positions=2000, stream=torch.cuda.Stream(), kv_format=pkg.KV_BF16 if kind == BF16 else pkg.KV_AUTO) for _ in range(2)]
+    lms[1].set_option("chunk", 8)
+    for step, n in enumerate([64, 127, 128, 129, 9, 1200, 121]):
+        for lm in lms:
+            (lm.prefill if step == 0 else lm.inject_interrupt)(0, tk(n, step))
+        a, b = lms[0].logits(0), lms[1].logits(0)
+        assert np.isfinite(a).all() and _rel(a, b) <= TOL[kind], (n, _rel(a, b))
+    for lm in lms:
+        lm.close()
