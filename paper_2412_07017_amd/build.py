@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libasynclm.so")
 ROOT = os.path.dirname(HERE)
 PROBE_SRC = os.path.join(ROOT, "traffic_probe.hip")   # stand-alone C-ABI consumer for hardware-counter runs (beside bench.py)
 PROBE = os.path.join(ROOT, "traffic_probe")
-SOURCES = ["api.hip", "decode_kernels.hip", "decode_rows.hip", "decode_fused.hip", "chunk_kernels.hip"]
+SOURCES = ["api.hip", "decode_kernels.hip", "decode_small.hip", "decode_rows.hip", "decode_fused.hip", "chunk_kernels.hip"]
 
 
 def hipcc_path() -> str:

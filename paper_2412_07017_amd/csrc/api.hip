@@ -85,6 +85,7 @@ struct asynclm_ctx {
     RowsBuffers rb{};                   // the other models: several rows per pass through the vector-unit kernels
     int rows_pass = ROWS_MAX;           // ... this many at most (what the buffers hold)
     int wide_rows = 0;                  // ... or this many on the matrix cores (forward_wide_rows); 0: not this model
+    SmallBuffers small{};               // decoding step of small models; null: not this model
     FusedPlan fused{};                  // single-kernel decoding step
     void* layers_dev = nullptr;         // per-layer pointer table of the fused step
     unsigned* bar = nullptr;            // its grid-barrier counters
@@ -173,7 +174,7 @@ void* kv_layer_ptr(const asynclm_ctx* c, int layer) {
 // Attention splits for a context of len_after tokens.  Up to 2048 tokens: at most MERGE_MAX_SPLIT splits, which
 // the O projection merges while it stages its input (no merge step at all).  Longer: up to ATTN_MAX_SPLIT
 // splits with a merge step of their own.
-struct SplitPlan { int nsplit; bool merge_in_oproj; bool mfma; };
+struct SplitPlan { int nsplit; bool merge_in_oproj; bool mfma; bool small = false /* forward_single_small */; };
 
 SplitPlan pick_nsplit(const asynclm_ctx* c, int len_after, bool single_row_kernel = false) {
     const bool no_v_rows = c->g.kv_v_offset == 0;      // the single-row kernel has nothing to read: matrix cores at any length
@@ -196,6 +197,34 @@ SplitPlan pick_nsplit(const asynclm_ctx* c, int len_after, bool single_row_kerne
     int n = 1;
     while (n < want && n < cap) n *= 2;
     return {n, merged, false};
+}
+
+// The plan of a decoding step.  Small models with few keys: forward_single_small.
+SplitPlan pick_step_plan(const asynclm_ctx* c, int len_after, bool pipelined) {
+    if (c->small.parts && !pipelined && c->opt_attn_split == 0 && len_after <= SMALL_MAX_KEYS && small_step_supported(c->cfg.dtype, c->g)) return {1, false, false, true};
+    return pick_nsplit(c, len_after, pipelined);
+}
+
+// Such a step of few launches is issued launch by launch: a graph starts later than a launch.  Tiny preset with 1 / 2 / 3 / 4 / 6 layers: 28.2 / 40.5 /
+// 52.8 / 65.6 / 92 us per step as a graph, 22.7 / 37.2 / 52.0 / 67.8 / 97 launch by launch, where the host becomes the slower side.
+bool small_direct(const asynclm_ctx* c, SplitPlan sp) { return sp.small && c->cfg.n_layers <= SMALL_DIRECT_LAYERS; }
+
+// Step of a small model behind its first kernel (launch_small_first, which is launched with the token and position as arguments):
+// see decode_small.hip.  The residual stream alternates between two vectors, because the workgroup that writes it is not the only one
+// that reads it.
+hipError_t forward_single_small(asynclm_ctx* c, bool with_head) {
+    const int dt = c->cfg.dtype, nl = c->cfg.n_layers;
+    const Geom& g = c->g;
+    hipStream_t s = c->stream;
+    float* xb[2] = {c->b.x, c->b.x2};
+    hipError_t e;
+    for (int l = 0; l < nl; ++l) {
+        void* kvl = kv_layer_ptr(c, l);
+        if (l > 0 && (e = run(c, KC_QKV, [&] { return launch_small_qkv(dt, c->wqkv[l], c->attn_norm[l], kvl, c->small, c->b, g, xb[(l - 1) & 1], xb[l & 1], s); }))) return e;
+        if ((e = run(c, KC_ATTN, [&] { return launch_small_attn_o(dt, kvl, c->wo[l], c->small, c->b, g, s); }))) return e;
+        if ((e = run(c, KC_GATEUP, [&] { return launch_small_mlp(dt, c->wgate_up[l], c->wdown[l], c->ffn_norm[l], xb[l & 1], c->small, g, s); }))) return e;
+    }
+    return with_head ? run(c, KC_LMHEAD, [&] { return launch_small_head(dt, c->lm_head, c->final_norm, c->logits, c->small, c->b, g, xb[(nl - 1) & 1], s); }) : hipSuccess;
 }
 
 // One forward pass of a single row whose token/position are already in the step descriptor.
@@ -311,7 +340,7 @@ bool use_pipeline(const asynclm_ctx* c, int len_after) {
 // Captured steps.  The kernels read token, position and sequence from the step descriptor, so a graph depends only on
 // the launch geometry: the attention plan, whether the pass ends with the output head, one or two streams.
 int graph_key(SplitPlan sp, bool with_head, bool pipelined) {
-    return ((((sp.nsplit << 1 | (sp.merge_in_oproj ? 1 : 0)) << 1 | (sp.mfma ? 1 : 0)) << 1 | (with_head ? 1 : 0)) << 1) | (pipelined ? 1 : 0);
+    return (((((sp.nsplit << 1 | (sp.merge_in_oproj ? 1 : 0)) << 1 | (sp.mfma ? 1 : 0)) << 1 | (with_head ? 1 : 0)) << 1) | (pipelined ? 1 : 0)) << 1 | (sp.small ? 1 : 0);
 }
 
 hipError_t capture_step(asynclm_ctx* c, SplitPlan sp, bool with_head, bool pipelined, hipGraphExec_t* out) {
@@ -319,6 +348,7 @@ hipError_t capture_step(asynclm_ctx* c, SplitPlan sp, bool with_head, bool pipel
     hipGraph_t graph = nullptr;
     if ((e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed))) return e;
     if (pipelined) e = forward_single_pipelined(c, 0, with_head, sp);
+    else if (sp.small) e = forward_single_small(c, with_head);
     else {
         // stamp mode: the captured kernels carry their stamp words (the graphs are rebuilt when the option changes)
         c->stamp_now = c->opt_step_stamps && sp.mfma;
@@ -346,11 +376,12 @@ hipError_t rebuild_graphs(asynclm_ctx* c) {
     hipError_t e = hipSuccess;
     for (int len_after = 1; len_after <= c->cfg.max_positions && !e; ++len_after) {
         const bool pipelined = use_pipeline(c, len_after);
-        const SplitPlan sp = pick_nsplit(c, len_after, pipelined);
+        const SplitPlan sp = pick_step_plan(c, len_after, pipelined);
         for (int with_head = 0; with_head < 2 && !e; ++with_head) {
             const int key = graph_key(sp, with_head != 0, pipelined);
             if (c->graphs.count(key)) continue;
             hipGraphExec_t exec = nullptr;
+            if (small_direct(c, sp)) continue;
             if ((e = capture_step(c, sp, with_head != 0, pipelined, &exec)) == hipSuccess) c->graphs.emplace(key, exec);
         }
     }
@@ -387,10 +418,13 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
         return hipSuccess;
     }
     const bool pipelined = use_pipeline(c, c->len[seq] + 1);
-    const SplitPlan sp = pick_nsplit(c, c->len[seq] + 1, pipelined);
+    const SplitPlan sp = pick_step_plan(c, c->len[seq] + 1, pipelined);
     // the chosen token also goes to pinned host memory, and an event marks the point: asynclm_decode_step waits for that
     // event only, so the host has the token while the forward pass is still running
-    if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, c->tok_event ? c->token_host + 4 : nullptr, c->stream); }))) return e;
+    if (sp.small) {
+        if ((e = run(c, KC_QKV, [&] { return launch_small_first(c->cfg.dtype, c->embed, c->wqkv[0], c->attn_norm[0], kv_layer_ptr(c, 0), c->b, c->g, seq, c->len[seq],
+                                                                forced, c->tok_event ? c->token_host + 4 : nullptr, c->b.x, c->stream); }))) return e;
+    } else if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, c->tok_event ? c->token_host + 4 : nullptr, c->stream); }))) return e;
     if (c->tok_event && !c->prof) {
         if ((e = hipEventRecord(c->tok_event, c->stream))) return e;
         c->tok_early = true;
@@ -402,6 +436,7 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
     auto g_it = (c->opt_graph && !c->prof) ? c->graphs.find(graph_key(sp, with_head, pipelined)) : c->graphs.end();
     if (g_it != c->graphs.end()) e = hipGraphLaunch(g_it->second, c->stream);
     else if (pipelined) e = forward_single_pipelined(c, seq, with_head, sp);
+    else if (sp.small) e = forward_single_small(c, with_head);
     else {
         c->stamp_now = stamp_mode;
         e = forward_single(c, seq, with_head, sp);
@@ -985,6 +1020,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         ALLOC(c->rb.counters, RP * g.Hkv);
         if (hipMemset(c->rb.counters, 0, sizeof(int32_t) * RP * g.Hkv) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     }
+    if (!c->chunk_ok && small_step_supported(cfg->dtype, g)) ALLOC(c->small.parts, (size_t)(g.Hkv + small_mlp_parts(g)) * g.d);
     // cache rows that were never written are read (and masked) by the chunk attention: keep them finite
     if (hipMemset(c->kv, 0, g.kv_seq_stride * (size_t)cfg->max_seqs * elem_bytes(c)) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     float *rc = nullptr, *rs = nullptr;

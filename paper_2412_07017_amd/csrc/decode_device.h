@@ -108,7 +108,9 @@ __host__ __device__ constexpr int attn_lds_floats() {
 //   3. P V: the same lane groups walk the values, the probabilities come from LDS.
 // On return (after a __syncthreads) lds holds NPART = 4 * PPW partial accumulators [part][G][DH] starting at
 // attn_part_offset, all relative to the same maximum; m_out[h], l_out[h] are valid in every thread.
-template <typename KVT, int DH, int G, bool PAIR>
+// UN: rounds whose loads are issued together; with more than four (a kernel of few waves, bound by latency) the values of a chunk's first
+// UN rounds are requested with its first keys.  (Elsewhere the registers for that cost waves: 203 rows of the 8B shape 31.6 -> 35.8 us.)
+template <typename KVT, int DH, int G, bool PAIR, int UN = 4>
 __device__ __forceinline__ void attn_split(const float* __restrict__ q, const KVT* __restrict__ Kp,
                                            const KVT* __restrict__ Vp, size_t lo_offset, int kvh, int s0, int s1,
                                            float scale, float* lds, float (&m_out)[G], float (&l_out)[G]) {
@@ -116,7 +118,7 @@ __device__ __forceinline__ void attn_split(const float* __restrict__ q, const KV
     constexpr int LPR = DH / EPL;       // lanes that cover one cached row
     constexpr int PPW = 64 / LPR;       // positions per wave-wide load
     constexpr int PPR = 4 * PPW;        // positions per workgroup-wide round
-    constexpr int UN = 4;               // rounds whose loads are issued together
+    constexpr bool EARLY_V = UN > 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane / LPR, c = lane % LPR;
     float* sc = lds;                            // [ATTN_CHUNK][G] scores, then probabilities
@@ -144,6 +146,15 @@ __device__ __forceinline__ void attn_split(const float* __restrict__ q, const KV
 
     for (int c0 = s0; c0 < s1; c0 += ATTN_CHUNK) {
         const int c1 = min(c0 + ATTN_CHUNK, s1), nc = c1 - c0;
+        uint4 vr[UN], vrl[PAIR ? UN : 1];
+        auto load_v = [&](int r0) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int p = min(c0 + r0 + u * PPR + wave * PPW + sub, s1 - 1);
+                vr[u] = load16(Vp + (size_t)p * DH + c * EPL);
+                if (PAIR) vrl[u] = load16(Vp + lo_offset + (size_t)p * DH + c * EPL);
+            }
+        };
         // ---- 1. scores
         for (int r0 = 0; r0 < nc; r0 += PPR * UN) {
             uint4 kr[UN], krl[PAIR ? UN : 1];
@@ -153,6 +164,7 @@ __device__ __forceinline__ void attn_split(const float* __restrict__ q, const KV
                 kr[u] = load16(Kp + (size_t)p * DH + c * EPL);
                 if (PAIR) krl[u] = load16(Kp + lo_offset + (size_t)p * DH + c * EPL);
             }
+            if (EARLY_V && r0 == 0) load_v(0);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int pl = r0 + u * PPR + wave * PPW + sub;      // position within the chunk
@@ -208,13 +220,7 @@ __device__ __forceinline__ void attn_split(const float* __restrict__ q, const KV
         }
         // ---- 3. P V
         for (int r0 = 0; r0 < nc; r0 += PPR * UN) {
-            uint4 vr[UN], vrl[PAIR ? UN : 1];
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int p = min(c0 + r0 + u * PPR + wave * PPW + sub, s1 - 1);
-                vr[u] = load16(Vp + (size_t)p * DH + c * EPL);
-                if (PAIR) vrl[u] = load16(Vp + lo_offset + (size_t)p * DH + c * EPL);
-            }
+            if (!EARLY_V || r0 > 0) load_v(r0);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int pl = r0 + u * PPR + wave * PPW + sub;

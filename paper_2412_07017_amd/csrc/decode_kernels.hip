@@ -77,6 +77,9 @@ struct GemvArgs {
     float* amax_v; int32_t* amax_i; int32_t* amax_counter; SeqState* st; const int32_t* banned;
     // merged attention output as input vector (x == nullptr): see VecSource
     const float* part_acc; const float* part_ml; int32_t merge_nsplit, merge_dh, merge_hq;
+    // steps of small models (decode_small.hip): x + nparts partial vectors, or the embedding of the step's token, is the input and goes to x_out
+    const float* parts; int32_t nparts; float* x_out;
+    const void* E; StepDesc* step_w; int32_t seq, pos, forced; int32_t* token_log; int32_t* token_early; unsigned* pipe_abort;
     PipeSync sync;          // hand-over from / to the neighbouring kernels of a step that runs on two streams
 };
 
@@ -198,10 +201,13 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
 // streaming kernel above adds to it by requesting a ring of four tiles where one exists, staging the vector in LDS behind a
 // barrier, and starting all 256 workgroups.  Tiny preset's step, QKV 6.3 -> 2.7 us, O (with the merge) 7.1 -> 3.4, gate/up 5.5 -> 2.6, down
 // 5.2 -> 2.7, head (with the choice) 8.2 -> 5.5; its session 2.95 -> 2.15 ms.
-// NS: wave-wide loads per row (1, 2 or 4).
-template <typename WT, int EPI, int NS>
+// NS: wave-wide loads per row (1, 2 or 4).  SRC: where the input vector comes from: 0 as it stands (or the key splits of the attention),
+// 1 a vector and partial vectors of other kernels, which the four waves add a quarter each, 2 the embedding of the step's token; this
+// is the first kernel of a step then and does what k_begin_step does (it reads nothing that it changes: the position is an argument).
+template <typename WT, int EPI, int NS, int SRC>
 __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     constexpr int EPL = Elem<WT>::EPL, NP = EPL / 4;
+    __shared__ float4 xp[SRC == 1 ? 4 : 1][SRC == 1 ? 64 * NS * NP : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int unit = blockIdx.x * 4 + wave, u = min(unit, a.units - 1), Kg = a.K / EPL;
     int rA, rB;
@@ -213,12 +219,27 @@ __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     float ms[NS][NP][MERGE_MAX_SPLIT], ls[NS][NP][MERGE_MAX_SPLIT];
     float4 raw[NS][NP][MERGE_MAX_SPLIT];
     const bool merge = EPI == EPI_RESID && !a.x;
+    const WT* erow = nullptr;
+    if (SRC == 2) {
+        const int32_t tok = a.forced >= 0 ? a.forced : a.st[a.seq].next_token;
+        erow = (const WT*)a.E + (size_t)tok * a.K;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *a.pipe_abort = 0u;
+            a.step_w->epoch = (a.step_w->epoch + 1) & 0x3fffff;
+            a.step_w->token = tok; a.step_w->pos = a.pos; a.step_w->seq = a.seq; a.step_w->rows = 1;
+            a.st[a.seq].len = a.pos + 1;
+            *a.token_log = tok;
+            if (a.token_early) *a.token_early = tok;
+        }
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int gi = min(s * 64 + lane, Kg - 1);
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             const size_t k = (size_t)gi * EPL + 4 * q;
+            if (SRC == 2) xv[s][q] = make_float4(Elem<WT>::load1(erow + k), Elem<WT>::load1(erow + k + 1), Elem<WT>::load1(erow + k + 2), Elem<WT>::load1(erow + k + 3));
+            else
             if (EPI == EPI_RESID && merge) {                        // uniform: the attention output from its key splits, as in stage_vector
                 const int h = (int)k / a.merge_dh, dim = (int)k - h * a.merge_dh;
                 const float* pm = a.part_ml + (size_t)h * a.merge_nsplit * 2;
@@ -237,8 +258,56 @@ __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     EpiOut eo;
     eo.y = a.y; eo.res = a.res; eo.q_out = a.q_out; eo.kv_layer = a.kv_layer;
     eo.rope_cos = a.rope_cos; eo.rope_sin = a.rope_sin; eo.rows = a.rows; eo.pos = 0; eo.seq = 0;
-    if (EPI == EPI_QKV) { eo.pos = a.step->pos; eo.seq = a.step->seq; }
+    if (EPI == EPI_QKV) { eo.pos = SRC == 2 ? a.pos : a.step->pos; eo.seq = SRC == 2 ? a.seq : a.step->seq; }
     if (EPI == EPI_STORE) eo.y += (size_t)a.step->seq * a.y_seq_stride;
+    if (SRC == 1) {
+        constexpr int PB = 16;                                      // partial vectors requested together
+        float4 sum[NS][NP];
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) sum[s][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int p0 = wave; p0 < a.nparts; p0 += 4 * PB)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const size_t k = (size_t)min(s * 64 + lane, Kg - 1) * EPL + 4 * q;
+                    float4 t[PB];
+#pragma unroll
+                    for (int j = 0; j < PB; ++j) t[j] = as_float4(load16(a.parts + (size_t)min(p0 + 4 * j, a.nparts - 1) * a.K + k));
+#pragma unroll
+                    for (int j = 0; j < PB; ++j)
+                        if (p0 + 4 * j >= a.nparts) t[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int w = PB / 2; w > 0; w /= 2)             // as a tree: fewer roundings than one after the other
+#pragma unroll
+                        for (int j = 0; j < w; ++j) { t[j].x += t[j + w].x; t[j].y += t[j + w].y; t[j].z += t[j + w].z; t[j].w += t[j + w].w; }
+                    sum[s][q].x += t[0].x; sum[s][q].y += t[0].y; sum[s][q].z += t[0].z; sum[s][q].w += t[0].w;
+                }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) xp[wave][(s * NP + q) * 64 + lane] = sum[s][q];
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int i = (s * NP + q) * 64 + lane;
+                const float4 t0 = xp[0][i], t1 = xp[1][i], t2 = xp[2][i], t3 = xp[3][i];
+                float4& x = xv[s][q];
+                x = make_float4(x.x + ((t0.x + t1.x) + (t2.x + t3.x)), x.y + ((t0.y + t1.y) + (t2.y + t3.y)),
+                                x.z + ((t0.z + t1.z) + (t2.z + t3.z)), x.w + ((t0.w + t1.w) + (t2.w + t3.w)));
+            }
+    }
+    if (SRC > 0 && EPI == EPI_QKV && blockIdx.x == 0 && wave == 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                if (s * 64 + lane < Kg) *reinterpret_cast<float4*>(a.x_out + (size_t)(s * 64 + lane) * EPL + 4 * q) = xv[s][q];
+    }
     float e0 = 0.f, e1 = 0.f;
     if (EPI == EPI_RESID) { e0 = load_f32(a.res + rA); e1 = load_f32(a.res + rB); }
     if (EPI == EPI_QKV) {
@@ -556,20 +625,24 @@ static size_t gemv_lds_bytes(int K, int units, int grid, int* done_cap) {
     return (size_t)(kt * 256 + 64) * Elem<WT>::EPL * sizeof(float) + (size_t)4 * (*done_cap) * sizeof(float4);
 }
 
-template <typename WT, int EPI>
+template <typename WT, int EPI, int SRC>
 static const void* gemv_small_func(int ns) {
-    return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2>) : (const void*)(k_gemv_small<WT, EPI, 4>);
+    if constexpr (SRC > 0) return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, SRC>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2, SRC>) : nullptr;
+    else return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, 0>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2, 0>) : (const void*)(k_gemv_small<WT, EPI, 4, 0>);
 }
+
+// k_gemv_small takes the product
+template <typename WT>
+static bool gemv_small(int K, int units) { return K / Elem<WT>::EPL <= 256 && units <= 4 * g_gemv_grid; }
 
 template <typename WT, int EPI>
 static hipError_t launch_gemv_t(const GemvArgs& a0, const Geom& g, hipStream_t s) {
     GemvArgs a = a0;
-    const int kg = a.K / Elem<WT>::EPL;
-    if (kg <= 256 && a.units <= 4 * g_gemv_grid && !a.sync.go_wait && !a.sync.go_signal && !a.sync.done_wg &&
+    if (gemv_small<WT>(a.K, a.units) && !a.sync.go_wait && !a.sync.go_signal && !a.sync.done_wg &&
         (EPI == EPI_RESID ? !a.gain : a.x && a.gain)) {
         Geom gg = g;
         void* params[] = {&a, &gg};
-        return hipLaunchKernel(gemv_small_func<WT, EPI>((kg + 63) / 64), dim3((a.units + 3) / 4), dim3(256), params, 0, s);
+        return hipLaunchKernel(gemv_small_func<WT, EPI, 0>((a.K / Elem<WT>::EPL + 63) / 64), dim3((a.units + 3) / 4), dim3(256), params, 0, s);
     }
     const size_t lds = gemv_lds_bytes<WT>(a.K, a.units, g_gemv_grid, &a.done_cap);
     a.uq = a.units / (g_gemv_grid * 4); a.ur = a.units % (g_gemv_grid * 4);
@@ -710,6 +783,55 @@ hipError_t launch_lmhead(int dtype, const void* wout, const float* gain, float* 
     if (fuse) { a.amax_v = b.amax_v; a.amax_i = b.amax_i; a.amax_counter = b.amax_counter; a.st = b.seq_state; }
     const hipError_t e = launch_gemv(dtype, EPI_STORE, a, g, s);
     return e || fuse || pipe ? e : launch_argmax(logits_base, b, g, s);
+}
+
+// ---- steps of small models ----
+
+template <typename WT>
+static bool gemv_all_small_t(const Geom& g) {
+    return g_gemv_grid <= ARGMAX_MAX_BLOCKS && gemv_small<WT>(g.d, (g.Hq + 2 * g.Hkv) * g.dh / 2) && gemv_small<WT>(g.Hq * g.dh, (g.d + 1) / 2) && gemv_small<WT>(g.d, g.F) &&
+           gemv_small<WT>(g.F, (g.d + 1) / 2) && gemv_small<WT>(g.d, (g.V + 1) / 2);
+}
+bool gemv_all_small(int dtype, const Geom& g) { return dtype == 0 ? gemv_all_small_t<float>(g) : gemv_all_small_t<bf16_t>(g); }
+
+template <typename WT, int EPI, int SRC>
+static hipError_t launch_small_t(GemvArgs a, const Geom& g, hipStream_t s) {
+    const void* f = gemv_small_func<WT, EPI, SRC>((a.K / Elem<WT>::EPL + 63) / 64);
+    if (!f || !gemv_small<WT>(a.K, a.units) || !a.gain) return hipErrorInvalidValue;
+    Geom gg = g;
+    void* params[] = {&a, &gg};
+    return hipLaunchKernel(f, dim3((a.units + 3) / 4), dim3(256), params, 0, s);
+}
+
+static GemvArgs small_qkv_args(const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, float* x_out) {
+    GemvArgs a{};
+    a.W = wqkv; a.rows = (g.Hq + 2 * g.Hkv) * g.dh; a.K = g.d; a.units = a.rows / 2; a.gain = gain; a.q_out = b.q; a.kv_layer = kv_layer;
+    a.rope_cos = b.rope_cos; a.rope_sin = b.rope_sin; a.step = b.step; a.x_out = x_out;
+    return a;
+}
+
+hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
+                              int forced, int32_t* token_early, float* x_out, hipStream_t s) {
+    GemvArgs a = small_qkv_args(wqkv, gain, kv_layer, b, g, x_out);
+    a.E = E; a.step_w = b.step; a.st = b.seq_state; a.seq = seq; a.pos = pos; a.forced = forced; a.token_log = b.token_log; a.token_early = token_early;
+    a.pipe_abort = b.pipe_abort;
+    return dtype == 0 ? launch_small_t<float, EPI_QKV, 2>(a, g, s) : launch_small_t<bf16_t, EPI_QKV, 2>(a, g, s);
+}
+
+hipError_t launch_small_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
+                            const float* x_in, float* x_out, hipStream_t s) {
+    GemvArgs a = small_qkv_args(wqkv, gain, kv_layer, b, g, x_out);
+    a.x = x_in; a.parts = sb.parts; a.nparts = g.Hkv + small_mlp_parts(g);
+    return dtype == 0 ? launch_small_t<float, EPI_QKV, 1>(a, g, s) : launch_small_t<bf16_t, EPI_QKV, 1>(a, g, s);
+}
+
+hipError_t launch_small_head(int dtype, const void* wout, const float* gain, float* logits_base, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
+                             const float* x_in, hipStream_t s) {
+    GemvArgs a{};
+    a.W = wout; a.rows = g.V; a.K = g.d; a.units = (a.rows + 1) / 2;
+    a.x = x_in; a.parts = sb.parts; a.nparts = g.Hkv + small_mlp_parts(g); a.gain = gain; a.y = logits_base; a.y_seq_stride = g.V; a.step = b.step; a.banned = b.banned;
+    a.amax_v = b.amax_v; a.amax_i = b.amax_i; a.amax_counter = b.amax_counter; a.st = b.seq_state;
+    return dtype == 0 ? launch_small_t<float, EPI_STORE, 1>(a, g, s) : launch_small_t<bf16_t, EPI_STORE, 1>(a, g, s);
 }
 
 template <typename KVT, int DH, bool PAIR>

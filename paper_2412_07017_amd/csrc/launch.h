@@ -129,6 +129,28 @@ hipError_t launch_rows_oproj(int dtype, const void* wo, const RowsBuffers& rb, c
 hipError_t launch_rows_gateup(int dtype, const void* wgu, const float* gain, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
 hipError_t launch_rows_down(int dtype, const void* wd, const RowsBuffers& rb, const RowsPass& p, const Geom& g, hipStream_t s);
 
+// Decoding step of small models with partial vectors between the kernels (decode_small.hip).
+constexpr size_t SMALL_O_BYTES = 128 * 1024;    // columns of the O projection that belong to one kv head: read by one compute unit
+constexpr int SMALL_MAX_KV_HEADS = 16;
+// One workgroup per kv head walks all keys, the other kernels split them.  Tiny preset, us per step here / there (both as graphs): 100 keys
+// 41.4 / 47.5, 240 44.5 / 47.6, 360 46.7 / 48.3, 400 49.0 / 48.2, 490 49.3 / 48.2.
+constexpr int SMALL_MAX_KEYS = 384;
+constexpr int SMALL_DIRECT_LAYERS = 3;          // up to this many layers a step's launches are issued one by one, see step_one_token
+struct SmallBuffers { float* parts; };          // [Hkv + small_mlp_parts][d]
+bool gemv_all_small(int dtype, const Geom& g);  // every product of a step, output head included, is one of k_gemv_small
+bool small_step_supported(int dtype, const Geom& g);
+int small_mlp_parts(const Geom& g);
+// First kernel of such a step: the token (forced, or the sequence's greedy one) and what k_begin_step does for it, its embedding, the first layer's QKV product
+hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
+                              int forced, int32_t* token_early, float* x_out, hipStream_t s);
+// QKV product of a later layer: x_in + all partial vectors -> x_out
+hipError_t launch_small_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
+                            const float* x_in, float* x_out, hipStream_t s);
+hipError_t launch_small_attn_o(int dtype, const void* kv_layer, const void* wo, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g, hipStream_t s);
+hipError_t launch_small_mlp(int dtype, const void* wgu, const void* wdown, const float* gain, const float* x, const SmallBuffers& sb, const Geom& g, hipStream_t s);
+hipError_t launch_small_head(int dtype, const void* wout, const float* gain, float* logits_base, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
+                             const float* x_in, hipStream_t s);
+
 // Fused (persistent, single-kernel) decoding step.
 struct FusedPlan {
     bool supported;
