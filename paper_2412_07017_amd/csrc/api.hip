@@ -93,9 +93,9 @@ struct asynclm_ctx {
     bool want_trace = false;
     std::vector<unsigned long long> last_trace;  // raw stamps [stamp][workgroup] of the last profiled fused step
     int last_trace_stamps = 0;
-    int32_t* token_host = nullptr;      // pinned, 16 ints: [0..1] staging of read-backs, [4] the token of the running step (early copy)
-    hipEvent_t tok_event = nullptr;     // recorded right after the step's token has been chosen
-    bool tok_early = false;             // the last decoding step left its token in token_host[4] behind tok_event
+    int32_t* token_host = nullptr;      // pinned, 16 ints: [0..1] staging of read-backs, [4..5] token and number of the running step (TokenWord)
+    uint32_t tok_serial = 0;            // number of the last decoding step
+    bool tok_early = false;             // the last decoding step leaves its token in that word as soon as it is chosen
 
     std::vector<int32_t> len;           // host mirror of the sequence lengths
     std::vector<int32_t> nban;          // host mirror of the number of banned token ids per sequence
@@ -397,6 +397,29 @@ hipError_t refresh_choice(asynclm_ctx* c, int seq) {
     return launch_argmax(c->logits, c->b, c->g, c->stream, seq);
 }
 
+// Waits for the word that the first kernel of the running step writes.  An event recorded behind that kernel, as a marker, cost 3 us
+// of every step between the two launches (tiny preset 41.0 -> 38.1 us as a graph).  Every wait ends: from time to time the stream is
+// asked for its state, and once it has run dry or failed the word will not change any more (`seen` false: take the token the long way).
+hipError_t wait_token(asynclm_ctx* c, int32_t* token, bool* seen) {
+    const unsigned long long* word = reinterpret_cast<const unsigned long long*>(c->token_host + 4);
+    auto look = [&] {
+        const unsigned long long v = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(v >> 32) != c->tok_serial) return false;
+        *token = (int32_t)(uint32_t)v;
+        return *seen = true;
+    };
+    for (;;) {
+        for (int i = 0; i < 4096; ++i) {
+            if (look()) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
+        if (!e) look();
+        return e;
+    }
+}
+
 hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
     hipError_t e;
     c->tok_early = false;
@@ -419,16 +442,14 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
     }
     const bool pipelined = use_pipeline(c, c->len[seq] + 1);
     const SplitPlan sp = pick_step_plan(c, c->len[seq] + 1, pipelined);
-    // the chosen token also goes to pinned host memory, and an event marks the point: asynclm_decode_step waits for that
-    // event only, so the host has the token while the forward pass is still running
+    // the chosen token also goes to pinned host memory: asynclm_decode_step waits for that word only, so the host has the token while
+    // the forward pass is still running
+    const TokenWord tok{reinterpret_cast<unsigned long long*>(c->token_host + 4), ++c->tok_serial};
     if (sp.small) {
         if ((e = run(c, KC_QKV, [&] { return launch_small_first(c->cfg.dtype, c->embed, c->wqkv[0], c->attn_norm[0], kv_layer_ptr(c, 0), c->b, c->g, seq, c->len[seq],
-                                                                forced, c->tok_event ? c->token_host + 4 : nullptr, c->b.x, c->stream); }))) return e;
-    } else if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, c->tok_event ? c->token_host + 4 : nullptr, c->stream); }))) return e;
-    if (c->tok_event && !c->prof) {
-        if ((e = hipEventRecord(c->tok_event, c->stream))) return e;
-        c->tok_early = true;
-    }
+                                                                forced, tok, c->b.x, c->stream); }))) return e;
+    } else if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, tok, c->stream); }))) return e;
+    c->tok_early = !c->prof;
     c->pipe_kernels = pipelined ? 5 * c->cfg.n_layers + (with_head ? 1 : 0) : 0;
     const bool stamp_mode = c->opt_step_stamps && !pipelined && sp.mfma && !c->prof;
     if (stamp_mode) c->pipe_kernels = 6 * c->cfg.n_layers + (with_head ? 1 : 0);
@@ -1053,7 +1074,6 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         return bail(ASYNCLM_E_DEVICE);
     if (hipHostMalloc((void**)&c->token_host, 64, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
     std::memset(c->token_host, 0, 64);
-    if (hipEventCreateWithFlags(&c->tok_event, hipEventDisableTiming) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     if (hipMemset(c->b.pipe_abort, 0, sizeof(unsigned) * PIPE_LINE_WORDS) != hipSuccess ||
         hipMemset(c->pipe_go, 0xff, sizeof(unsigned) * PIPE_REGIONS * PIPE_MAX_WORKGROUPS * PIPE_LINE_WORDS) != hipSuccess ||
         hipMemset(c->pipe_counters, 0, sizeof(unsigned) * c->pipe_kernels_max * PIPE_LINE_WORDS) != hipSuccess)
@@ -1115,7 +1135,6 @@ int asynclm_destroy(asynclm_ctx* c) {
     for (hipEvent_t ev : c->prof_events) hipEventDestroy(ev);
     for (void* p : c->allocs) hipFree(p);
     if (c->token_host) hipHostFree(c->token_host);
-    if (c->tok_event) hipEventDestroy(c->tok_event);
     if (c->stream2) { hipStreamSynchronize(c->stream2); hipStreamDestroy(c->stream2); }
     if (c->ev_fork) hipEventDestroy(c->ev_fork);
     if (c->ev_join) hipEventDestroy(c->ev_join);
@@ -1149,9 +1168,9 @@ int asynclm_decode_step(asynclm_ctx* c, int32_t seq, int32_t forced_token, int32
     HIPCK(c, step_one_token(c, seq, forced_token < 0 ? -1 : forced_token, true));
     if (token_out) {
         if (c->tok_early) {                         // per-operation step: wait for the choice only
-            HIPCK(c, hipEventSynchronize(c->tok_event));
-            *token_out = c->token_host[4];
-            return ASYNCLM_OK;
+            bool seen = false;
+            HIPCK(c, wait_token(c, token_out, &seen));
+            if (seen) return ASYNCLM_OK;
         }
         HIPCK(c, hipMemcpyAsync(c->token_host, c->b.token_log, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         HIPCK(c, hipStreamSynchronize(c->stream));

@@ -125,6 +125,12 @@ __device__ __forceinline__ uint4 load16(const void* p) {
 }
 __device__ __forceinline__ float load_f32(const float* p) { return *(global_f32_ptr)(uintptr_t)p; }
 
+// The token of a decoding step and the step's number for the host, in one 8-byte word of pinned memory.
+struct TokenWord { unsigned long long* word; uint32_t serial; };
+__device__ __forceinline__ void store_token(const TokenWord& t, int32_t token) {
+    if (t.word) __hip_atomic_store(t.word, (unsigned long long)t.serial << 32 | (uint32_t)token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Write-through stores.  The dies of the device have an L2 cache each; data that one running kernel hands to another
 // (no kernel boundary in between) is stored with relaxed atomic stores at device scope, which go through to memory,
 // and the reader only touches it after the hand-over (PipeSync), on lines that no cache of its die can hold.

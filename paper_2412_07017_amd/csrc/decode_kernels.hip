@@ -16,7 +16,7 @@ namespace asynclm {
 
 // Chooses the token of this step (forced, or the greedy one left by the previous forward pass),
 // publishes it and its position to the step descriptor, and grows the sequence by one.
-// token_early: optional host-visible word that also receives the token, so that the host can read it as soon as this
+// token_early: host-visible word that also receives the token, so that the host can read it as soon as this
 // kernel has run instead of after the whole step.
 // pipe_abort: the give-up word of a step that runs on two streams, cleared here (this kernel runs alone, after the
 // previous step has ended and before any kernel of this one starts); the step number goes up by one.
@@ -24,7 +24,7 @@ namespace asynclm {
 // next_token does not change here): a kernel of its own for that cost 4 us of a step and the boundary.
 template <typename WT>
 __global__ __launch_bounds__(256) void k_begin_step(StepDesc* step, SeqState* st, int32_t seq, int32_t forced, int32_t* token_log,
-                                                    int32_t* token_early, unsigned* pipe_abort, const WT* __restrict__ E, float* __restrict__ x,
+                                                    TokenWord token_early, unsigned* pipe_abort, const WT* __restrict__ E, float* __restrict__ x,
                                                     int d) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int32_t row = forced >= 0 ? forced : st[seq].next_token;
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void k_begin_step(StepDesc* step, SeqState* st
         step->rows = 1;
         st[seq].len = s.len + 1;
         *token_log = tok;
-        if (token_early) *token_early = tok;
+        store_token(token_early, tok);
     }
 }
 
@@ -79,7 +79,7 @@ struct GemvArgs {
     const float* part_acc; const float* part_ml; int32_t merge_nsplit, merge_dh, merge_hq;
     // steps of small models (decode_small.hip): x + nparts partial vectors, or the embedding of the step's token, is the input and goes to x_out
     const float* parts; int32_t nparts; float* x_out;
-    const void* E; StepDesc* step_w; int32_t seq, pos, forced; int32_t* token_log; int32_t* token_early; unsigned* pipe_abort;
+    const void* E; StepDesc* step_w; int32_t seq, pos, forced; int32_t* token_log; TokenWord token_early; unsigned* pipe_abort;
     PipeSync sync;          // hand-over from / to the neighbouring kernels of a step that runs on two streams
 };
 
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
             a.step_w->token = tok; a.step_w->pos = a.pos; a.step_w->seq = a.seq; a.step_w->rows = 1;
             a.st[a.seq].len = a.pos + 1;
             *a.token_log = tok;
-            if (a.token_early) *a.token_early = tok;
+            store_token(a.token_early, tok);
         }
     }
 #pragma unroll
@@ -713,7 +713,7 @@ static hipError_t launch_gemv(int dtype, int epi, const GemvArgs& a, const Geom&
     return dtype == 0 ? launch_gemv_w<float>(epi, a, g, s) : launch_gemv_w<bf16_t>(epi, a, g, s);
 }
 
-hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, int32_t* token_early,
+hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, TokenWord token_early,
                              hipStream_t s) {
     const dim3 grid((g.d + 255) / 256);
     if (dtype == 0) hipLaunchKernelGGL(k_begin_step<float>, grid, dim3(256), 0, s, b.step, b.seq_state, seq, forced, b.token_log, token_early, b.pipe_abort, (const float*)E, b.x, g.d);
@@ -811,7 +811,7 @@ static GemvArgs small_qkv_args(const void* wqkv, const float* gain, void* kv_lay
 }
 
 hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
-                              int forced, int32_t* token_early, float* x_out, hipStream_t s) {
+                              int forced, TokenWord token_early, float* x_out, hipStream_t s) {
     GemvArgs a = small_qkv_args(wqkv, gain, kv_layer, b, g, x_out);
     a.E = E; a.step_w = b.step; a.st = b.seq_state; a.seq = seq; a.pos = pos; a.forced = forced; a.token_log = b.token_log; a.token_early = token_early;
     a.pipe_abort = b.pipe_abort;

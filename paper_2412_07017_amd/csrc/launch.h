@@ -142,7 +142,7 @@ bool small_step_supported(int dtype, const Geom& g);
 int small_mlp_parts(const Geom& g);
 // First kernel of such a step: the token (forced, or the sequence's greedy one) and what k_begin_step does for it, its embedding, the first layer's QKV product
 hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
-                              int forced, int32_t* token_early, float* x_out, hipStream_t s);
+                              int forced, TokenWord token_early, float* x_out, hipStream_t s);
 // QKV product of a later layer: x_in + all partial vectors -> x_out
 hipError_t launch_small_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
                             const float* x_in, float* x_out, hipStream_t s);
@@ -220,9 +220,9 @@ hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, i
 hipError_t launch_decode_attn_mfma(const ChunkBuffers& c, const void* kv_layer, int nsplit, const DecodeBuffers& b, const Geom& g,
                                    hipStream_t s, unsigned long long* stamps = nullptr, unsigned long long* done_wg = nullptr);
 hipError_t launch_stamp_init(unsigned long long* done_wg, int kernels, hipStream_t s);
-// token_early: pinned host word that also gets the chosen token (or nullptr)
+// token_early: pinned host word that also gets the chosen token
 hipError_t launch_embed(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, hipStream_t s);
-hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, int32_t* token_early,
+hipError_t launch_begin_step(int dtype, const void* E, const DecodeBuffers& b, const Geom& g, int seq, int forced, TokenWord token_early,
                              hipStream_t s);
 // sync (all single-row launchers): hand-over flags when the step's kernels alternate between two streams (see PipeSync)
 hipError_t launch_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b,

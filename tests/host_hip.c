@@ -53,6 +53,7 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, s
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return OK; }
 int hipStreamDestroy(void *s) { free(s); return OK; }
 int hipStreamSynchronize(void *s) { (void)s; return OK; }
+int hipStreamQuery(void *s) { (void)s; return OK; }
 int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return OK; }
 int hipEventCreate(void **e) { *e = malloc(1); return OK; }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return hipEventCreate(e); }

@@ -186,3 +186,13 @@ print(json.dumps([out, hip.host_hip_used()]))
     for other in ("ffn=2056", "d_model=1032", "dtype='fp32'"):
         kw = "kv_format=0, " if "fp32" in other else "kv_format=1, "
         assert host(f"lm = context(1024, {kw}{other}); print(json.dumps(count(launches(lambda: lm.prefill(0, tokens(16))), 'k_rows_embed')))") == 2
+
+
+# A stream that has run dry without the word of the step's token having been written: the wait for it ends
+@pytest.mark.parametrize("model", ["d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688"])
+def test_wait_for_a_token_ends(host, model):
+    assert host(f'''
+lm = context(64, {model})
+lm.prefill(0, tokens(5))
+print(json.dumps([lm.decode_step(0, forced_token=3), lm.decode_step(0), lm.seq_len(0)]))
+''') == [0, 0, 7]
