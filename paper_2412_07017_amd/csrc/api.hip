@@ -19,7 +19,7 @@ struct PassBuilder {
     ChunkTable t{};
     int G = 1, Hkv = 1, max_keys = 0, batch_rows = CHUNK_BATCH_ROWS;
     long long block_tiles = 0;          // key tiles of 32 over all task blocks
-    void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = 0; max_keys = 0; block_tiles = 0; }
+    void clear() { t.rows = t.ngroups = t.ntasks = t.nhead = t.nblocks = t.npieces = 0; max_keys = 0; block_tiles = 0; }
     int tiles_of(int n) const { return (G * n + 31) / 32; }
     // batched steps: rows, attention tasks, and the attention's partial results (task x kv head x at least 4 key splits) all fit one pass
     bool fits(int n) const {
@@ -614,6 +614,58 @@ int pick_chunk_attn_split(const asynclm_ctx* c, int max_keys, int ntasks) {
     return n;
 }
 
+// Key splits of every task, and the workgroups of the shared-key attention (`wide`), into the table.
+// One sequence: `nsplit` parts of every block of tasks; with one part, longest first, and where all workgroups are resident at once (two per compute unit), those
+// of the second half go the other way round, so that a unit gets a long and a short one.  8B shape, two layers, prompts of 700 / 1500 /
+// 2048 tokens 1002 -> 993, 1593 -> 1587, 1998 -> 1973 us; 1019 (four layers) 2693 -> 2665, 16384 18.36 -> 18.08 ms; 70B shape, 4096 12.59 ->
+// 12.37 ms.  (Cutting the long blocks of a prompt as well: the same.)
+// Several sequences: parts of at most `per` key tiles each, as few tiles as keep the workgroups to two per compute unit, because with
+// one number of parts for all the longest sequence decides.  Four layers: 16 sequences of 512 to 4096 1181 -> 1137 us (attention 80 -> 74 a
+// layer), 12 of up to 3400 1049 -> 1015, 8 of 128 to 4096 1224 -> 1202; four per compute unit 1154, 1035, 1276.
+void plan_attention(const asynclm_ctx* c, ChunkTable& t, bool wide, int nsplit) {
+    const int Hkv = c->g.Hkv;
+    t.npieces = 0;
+    if (!wide) {
+        for (int i = 0; i < t.ntasks; ++i) { t.task[i].nsplit = nsplit; t.task[i].unit0 = i * nsplit; }
+        return;
+    }
+    const int slots = 2 * c->n_cu;
+    int tiles[CHUNK_MAX_GROUPS], longest = 1;           // of the keys that matter to a block, as the kernel counts them
+    for (int b = 0; b < t.nblocks; ++b) {
+        const ChunkTaskBlock& B = t.block[b];
+        const ChunkTask& T = t.task[B.task0];
+        tiles[b] = (T.pos0 + std::min((32 * T.tile) % T.n + 32 * B.n, T.n) + 31) / 32;
+        longest = std::max(longest, tiles[b]);
+    }
+    auto parts = [&](int b, int per) { return (tiles[b] + per - 1) / per; };
+    int per = 0;
+    if (t.ngroups > 1)
+        for (per = 2; per < longest; ++per) {
+            long long n = 0, units = 0;
+            int most = 0;
+            for (int b = 0; b < t.nblocks; ++b) { const int k = parts(b, per); n += k; units += (long long)k * t.block[b].n; most = std::max(most, k); }
+            if (n * Hkv <= slots && units * Hkv <= CHUNK_ATTN_MAX_UNITS && most <= CHUNK_ATTN_MAX_SPLIT) break;
+        }
+    int unit = 0;
+    for (int b = 0; b < t.nblocks; ++b) {
+        const int k = per ? parts(b, per) : nsplit;
+        for (int i = 0; i < t.block[b].n; ++i) { ChunkTask& T = t.task[t.block[b].task0 + i]; T.nsplit = k; T.unit0 = unit; unit += k; }
+    }
+    for (int b = 0, e = 0; b < t.nblocks; b = e) {      // the blocks of one sequence that read the same keys next to each other: one XCD, its L2
+        int most = 0;
+        auto splits = [&](int i) { return t.task[t.block[i].task0].nsplit; };
+        for (e = b; e < t.nblocks && t.task[t.block[e].task0].row0 == t.task[t.block[b].task0].row0; ++e) most = std::max(most, splits(e));
+        for (int s = 0; s < most; ++s)
+            for (int i = b; i < e; ++i)
+                if (s < splits(i)) t.piece[t.npieces++] = ChunkPiece{(int16_t)i, (int16_t)s};
+    }
+    if (t.ngroups == 1 && nsplit == 1) {
+        std::stable_sort(t.piece, t.piece + t.npieces, [&](const ChunkPiece& x, const ChunkPiece& y) { return tiles[x.block] > tiles[y.block]; });
+        const int first = c->n_cu / Hkv;                // pieces that give every compute unit its first workgroup
+        if (t.npieces > first && t.npieces * Hkv <= slots) std::reverse(t.piece + first, t.piece + t.npieces);
+    }
+}
+
 // Layer `l` and the output head for one row of a pass, x its residual stream, whose position and sequence are in the step
 // descriptor: the kernels of a decoding step.
 hipError_t last_row_layer(asynclm_ctx* c, int l, float* x, int len_after) {
@@ -650,6 +702,7 @@ hipError_t upload_table(asynclm_ctx* c, const ChunkTable& t) {
     cb.tab.group = (const ChunkGroup*)put(t.group, sizeof(ChunkGroup) * t.ngroups);
     cb.tab.task = (const ChunkTask*)put(t.task, sizeof(ChunkTask) * t.ntasks);
     cb.tab.block = (const ChunkTaskBlock*)put(t.block, sizeof(ChunkTaskBlock) * t.nblocks);
+    cb.tab.piece = (const ChunkPiece*)put(t.piece, sizeof(ChunkPiece) * t.npieces);
     cb.tab.row = (const ChunkRow*)put(t.row, sizeof(ChunkRow) * t.rows);
     if ((e = hipMemcpyAsync(cb.tab_mem, c->tab_host[i], bytes, hipMemcpyHostToDevice, c->stream))) return e;
     if ((e = hipEventRecord(c->tab_ev[i], c->stream))) return e;
@@ -659,11 +712,11 @@ hipError_t upload_table(asynclm_ctx* c, const ChunkTable& t) {
 
 // One forward pass over the rows of `pb` (1..pass_rows rows in any number of groups).  Groups that want logits
 // get them from the single-row head kernels (one group) or from one more product on the matrix cores (several).
-hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
+hipError_t forward_chunk(asynclm_ctx* c, PassBuilder& pb) {
     const Geom& g = c->g;
     ChunkBuffers& cb = c->cb;
     hipStream_t s = c->stream;
-    const ChunkTable& t = pb.t;
+    ChunkTable& t = pb.t;
     const int rows = t.rows, MT = (rows + 31) / 32;
     const ChunkPlans sp = chunk_plans(c, MT);
     const int nqkv = (g.Hq + 2 * g.Hkv) * g.dh, qd = g.Hq * g.dh;
@@ -684,7 +737,9 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
     wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
     while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
-    // The split count is one for all sequences of a pass, so a sequence much longer than the others is a chain of tiles that a
+    // k_chunk_attn has one split count for all sequences of a pass, and four times as many waves that each walk a chain of their own;
+    // measured while the first kernel had one count for all too (plan_attention cuts every sequence by its own length now): a
+    // sequence much longer than the others is a chain of tiles that a
     // quarter as many waves walk as in k_chunk_attn: the first kernel needs the longest chain to be no more than 20 tiles over
     // the average load of a workgroup slot.  8B shape, 4 layers, one sequence of 16k and n of 500 tokens: n = 5 988 (wide)
     // against 938 us, 7 1148 / 990, 11 1197 / 1060 (2 layers: 15 899 / 680, 31 1300 / 848); one of 4k and 5 812 / 830, 7 855 / 861, 11 885 / 883;
@@ -695,6 +750,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
     const bool wide_attn = ((pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups) && even) || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
     const int dt = c->cfg.dtype;
     hipError_t e;
+    plan_attention(c, t, wide_attn, wide_attn ? wsplit : asplit);
     if ((e = upload_table(c, t))) return e;
     // A pass over one sequence: after the last layer's keys and values nothing but its last row is needed any more, so that
     // row finishes the pass through the single-row kernels (fp32 activations; its own key and value are formed once more
@@ -715,7 +771,7 @@ hipError_t forward_chunk(asynclm_ctx* c, const PassBuilder& pb) {
         }
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.qkv, MT, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, sp.qkv.s, kvl, c->b, rows, MT, g, s); }))) return e;
-        if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, wsplit, t.ntasks, t.nblocks, g, s); }))) return e; }
+        if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, t.npieces > t.nblocks, t.ntasks, t.npieces, g, s); }))) return e; }
         else if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn(cb, kvl, asplit, t.ntasks, g, s); }))) return e;
         if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb, sp.o, MT, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, sp.o.s, MT, c->ffn_norm[l], rows, g, s); }))) return e;

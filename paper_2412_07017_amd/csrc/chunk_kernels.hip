@@ -1258,7 +1258,7 @@ struct ChunkAttnArgs {
     float* part_o;      // [unit][128][32]
     float* part_ml;     // [unit][2][32]
     bf16_t* out_hi; bf16_t* out_lo;             // tiled planes (one split: no merge)
-    int32_t nsplit, q_cols;
+    int32_t nsplit /* k_chunk_attn */, q_cols;
 };
 
 // K tile (32 keys x 128 channels, one plane) as loaded: instruction q covers rows 4q .. 4q+3, lane l holds
@@ -1728,16 +1728,18 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 31, gh = lane >> 5;
     const int G = g.Hq / g.Hkv;
-    const int kvh = blockIdx.x % g.Hkv, split = blockIdx.y;
-    const ChunkTaskBlock B = a.tab.block[blockIdx.x / g.Hkv];
+    const int kvh = blockIdx.x % g.Hkv;
+    const ChunkPiece piece = a.tab.piece[blockIdx.x / g.Hkv];
+    const int split = piece.split;
+    const ChunkTaskBlock B = a.tab.block[piece.block];
     const bool live = wave < B.n;
     const int task = B.task0 + min(wave, B.n - 1);
     const ChunkTask T0 = a.tab.task[B.task0];
     const ChunkTask T = a.tab.task[task];
     // keys that matter to the block's columns (its tasks are consecutive tiles of one group), split evenly
     const int Lk = T0.pos0 + min((32 * T0.tile) % T0.n + 32 * B.n, T0.n);
-    const int ntile = (Lk + 31) >> 5;
-    const int tps = (ntile + a.nsplit - 1) / a.nsplit;
+    const int ntile = (Lk + 31) >> 5, nsplit = T0.nsplit;
+    const int tps = (ntile + nsplit - 1) / nsplit;
     const int t0 = split * tps, t1 = min(ntile, t0 + tps);
     // and to this wave's own columns: later tiles are loaded for the other waves but not multiplied here
     const int Lw = T.pos0 + min((32 * T.tile) % T.n + 32, T.n);
@@ -1789,7 +1791,7 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
     st.lrun += __shfl_xor(st.lrun, 32, 64);
     if (!live) return;
 
-    if (a.nsplit == 1) {                                            // nothing to merge: the output goes straight to the tiled planes
+    if (nsplit == 1) {                                              // nothing to merge: the output goes straight to the tiled planes
         if (col >= G * T.n) return;
         const float inv = st.lrun > 0.f ? 1.f / st.lrun : 0.f;
         const int gq = col / T.n, m = T.row0 + col - gq * T.n, hq = kvh * G + gq;
@@ -1806,7 +1808,7 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
             }
         return;
     }
-    const size_t unit = ((size_t)task * g.Hkv + kvh) * a.nsplit + split;
+    const size_t unit = (size_t)T.unit0 * g.Hkv + (size_t)kvh * nsplit + split;
     float* po = a.part_o + unit * DH * 32;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -1821,7 +1823,7 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
 // Merge the key splits of one (task, kv head) and emit the attention output as tiled hi/lo planes
 // (K = Hq*128).  grid (tasks * Hkv, 4): workgroup y handles channels 32 y .. 32 y + 31.
 __global__ __launch_bounds__(256) void k_chunk_attn_combine(const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                            int nsplit, Geom g, ChunkTab tab,
+                                                            Geom g, ChunkTab tab,
                                                             bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo) {
     constexpr int DH = 128;
     __shared__ float f[CHUNK_ATTN_MAX_SPLIT][32];          // running maximum of every split, then its weight
@@ -1831,9 +1833,12 @@ __global__ __launch_bounds__(256) void k_chunk_attn_combine(const float* __restr
     const int G = g.Hq / g.Hkv;
     const int kvh = blockIdx.x % g.Hkv;
     const ChunkTask T = tab.task[blockIdx.x / g.Hkv];
-    const float* ml = part_ml + (size_t)blockIdx.x * nsplit * 64;
+    const int nsplit = T.nsplit;
+    if (nsplit == 1) return;                               // the attention has written the output itself
+    const size_t unit = (size_t)T.unit0 * g.Hkv + (size_t)kvh * nsplit;
+    const float* ml = part_ml + unit * 64;
     const int j = tid & 31, dl = tid >> 5;                 // column, channel within a run of 8
-    const float* po = part_o + (size_t)blockIdx.x * nsplit * DH * 32 + (size_t)(blockIdx.y * 32 + dl) * 32 + j;
+    const float* po = part_o + unit * DH * 32 + (size_t)(blockIdx.y * 32 + dl) * 32 + j;
     constexpr int PB = 8;                                  // splits whose partial results are requested together
     float p[PB][4];
     auto p_load = [&](int s0) {
@@ -2122,25 +2127,22 @@ hipError_t launch_chunk_attn(const ChunkBuffers& c, const void* kv_layer, int ns
     hipLaunchKernelGGL(k_chunk_attn, dim3(ntasks * g.Hkv, nsplit), dim3(64), ATTN_LDS_BYTES / 4, s, a, g);
     hipError_t e = hipGetLastError();
     if (e) return e;
-    hipLaunchKernelGGL(k_chunk_attn_combine, dim3(ntasks * g.Hkv, 4), dim3(256), 0, s, c.attn_o, c.attn_ml, nsplit, g, c.tab,
+    hipLaunchKernelGGL(k_chunk_attn_combine, dim3(ntasks * g.Hkv, 4), dim3(256), 0, s, c.attn_o, c.attn_ml, g, c.tab,
                        c.att_hi, c.att_lo);
     return hipGetLastError();
 }
 
-// The variant for passes made of large groups: one workgroup per block of up to four tasks, any number of key splits.
-hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, int nblocks, const Geom& g,
-                                  hipStream_t s) {
-    if (nsplit < 1 || nsplit > CHUNK_ATTN_MAX_SPLIT || ntasks < 1 || ntasks > CHUNK_MAX_TASKS || nblocks < 1 || nblocks > ntasks ||
-        (long long)ntasks * g.Hkv * nsplit > CHUNK_ATTN_MAX_UNITS)
-        return hipErrorInvalidValue;
+// The variant for passes made of large groups: one workgroup per kv head, block of up to four tasks and key split of it.
+hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, bool merge, int ntasks, int npieces, const Geom& g, hipStream_t s) {
+    if (ntasks < 1 || ntasks > CHUNK_MAX_TASKS || npieces < 1 || npieces > CHUNK_ATTN_MAX_UNITS) return hipErrorInvalidValue;
     ChunkAttnArgs a{};
     a.q_hi = c.q_hi; a.q_lo = c.q_lo; a.kv_layer = (const bf16_t*)kv_layer; a.tab = c.tab;
-    a.part_o = c.attn_o; a.part_ml = c.attn_ml; a.nsplit = nsplit; a.q_cols = c.q_cols;
+    a.part_o = c.attn_o; a.part_ml = c.attn_ml; a.q_cols = c.q_cols;
     a.out_hi = c.att_hi; a.out_lo = c.att_lo;
-    hipLaunchKernelGGL(k_chunk_attn_wide, dim3(nblocks * g.Hkv, nsplit), dim3(256), ATTN_LDS_BYTES, s, a, g);
+    hipLaunchKernelGGL(k_chunk_attn_wide, dim3(npieces * g.Hkv), dim3(256), ATTN_LDS_BYTES, s, a, g);
     hipError_t e = hipGetLastError();
-    if (e || nsplit == 1) return e;
-    hipLaunchKernelGGL(k_chunk_attn_combine, dim3(ntasks * g.Hkv, 4), dim3(256), 0, s, c.attn_o, c.attn_ml, nsplit, g, c.tab,
+    if (e || !merge) return e;
+    hipLaunchKernelGGL(k_chunk_attn_combine, dim3(ntasks * g.Hkv, 4), dim3(256), 0, s, c.attn_o, c.attn_ml, g, c.tab,
                        c.att_hi, c.att_lo);
     return hipGetLastError();
 }

@@ -52,21 +52,25 @@ struct ChunkGroup {
     int32_t head;       // row of this group in the output-head product, -1: no logits wanted
     int32_t pad0, pad1, pad2;
 };
-struct ChunkTask { int32_t seq, row0, n, pos0, tile, pad0, pad1, pad2; };         // query columns 32 tile .. 32 tile + 31 of a group
+// query columns 32 tile .. 32 tile + 31 of a group; its attention has nsplit key splits, whose partial results start at unit0 (x kv heads)
+struct ChunkTask { int32_t seq, row0, n, pos0, tile, nsplit, unit0, pad; };
 // Every group has at least one task, so a batched pass holds at most CHUNK_MAX_GROUPS groups.  A pass uploads the used
 // entries only, packed one after the other (ChunkTab): under 1 KB for an interrupt.
 struct ChunkTaskBlock { int32_t task0, n; };   // up to four consecutive tasks of one group (they share keys and values)
+struct ChunkPiece { int16_t block, split; };   // a workgroup (per kv head) of the shared-key attention
 struct ChunkTable {
     int32_t rows, ngroups, ntasks, nhead, nblocks;
     ChunkGroup group[CHUNK_MAX_GROUPS];
     ChunkTask task[CHUNK_MAX_TASKS];
     ChunkTaskBlock block[CHUNK_MAX_GROUPS];     // at most four tasks each: as many as groups in a batched pass, tasks / 4 for one group
+    int32_t npieces;
+    ChunkPiece piece[CHUNK_ATTN_MAX_UNITS];
     ChunkRow row[CHUNK_MAX];
 };
 
-struct ChunkTab { const ChunkGroup* group; const ChunkTask* task; const ChunkTaskBlock* block; const ChunkRow* row; };
+struct ChunkTab { const ChunkGroup* group; const ChunkTask* task; const ChunkTaskBlock* block; const ChunkPiece* piece; const ChunkRow* row; };
 constexpr size_t CHUNK_TAB_BYTES = sizeof(ChunkGroup) * CHUNK_MAX_GROUPS + sizeof(ChunkTask) * CHUNK_MAX_TASKS +
-                                   (sizeof(ChunkTaskBlock) * CHUNK_MAX_GROUPS + 31) / 32 * 32 + sizeof(ChunkRow) * CHUNK_MAX;
+                                   (sizeof(ChunkTaskBlock) * CHUNK_MAX_GROUPS + 31) / 32 * 32 + sizeof(ChunkPiece) * CHUNK_ATTN_MAX_UNITS + sizeof(ChunkRow) * CHUNK_MAX;
 
 // Device buffers of the append-chunk path (bf16 models).  "hi/lo" are the two bf16 planes of a value.
 struct ChunkBuffers {
@@ -212,8 +216,8 @@ hipError_t launch_wide_gemm(const void* W, int N, int K, const bf16_t* xhi, cons
 hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c,
                                    int MT, hipStream_t s);
 hipError_t launch_chunk_attn(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, const Geom& g, hipStream_t s);
-hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, int nblocks, const Geom& g,
-                                  hipStream_t s);
+// The key splits of every task are in the table; merge: some task has more than one.
+hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, bool merge, int ntasks, int npieces, const Geom& g, hipStream_t s);
 // single-row decoding attention on the matrix cores (long contexts): b.q -> b.o through the chunk attention
 // stamps / done_wg: null, or the stamp words (2 x 6) and finishing-time words (2 x STAMP_DONE_SLOTS) of the attention
 // kernel and of its merge kernel (see step_stamp_done)

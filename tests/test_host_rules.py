@@ -196,3 +196,36 @@ lm = context(64, {model})
 lm.prefill(0, tokens(5))
 print(json.dumps([lm.decode_step(0, forced_token=3), lm.decode_step(0), lm.seq_len(0)]))
 ''') == [0, 0, 7]
+
+
+# The shared-key attention of a batch: every sequence cut by its own length, at most two workgroups per compute unit, each with about
+# as many key tiles; single rows among interrupts (blocks of several tasks) too.  A prompt: a workgroup per kv head and block.
+@pytest.mark.parametrize("lens,intr", [([3500] * 16, {}), ([8000] * 4, {}), ([16000, 100], {}), ([16000] + [500] * 3, {}), ([600] * 4, {1: 200}),
+                                       ([512 + 230 * i for i in range(16)], {0: 24})])
+def test_attention_of_a_batch_is_cut_evenly(host, lens, intr):
+    got = host(f'''
+lens, intr = {lens!r}, {intr!r}
+lm = context(16400, len(lens), d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
+for s, n in enumerate(lens): lm.prefill(s, tokens(n))
+ls = launches(lambda: lm.step_batch(range(len(lens)), forced=[1] * len(lens), interrupts=[tokens(intr.get(s, 0)) for s in range(len(lens))]))
+print(json.dumps([l[1] for l in ls if "k_chunk_attn_wide" in l[0]]))
+''')
+    blocks = []                                             # key tiles of every block of up to four tasks
+    for s, n in enumerate(lens):
+        rows = 1 + intr.get(s, 0)
+        tasks = (4 * rows + 31) // 32
+        for t in range(0, tasks, 4):
+            blocks.append((n + min(32 * t % rows + 32 * min(4, tasks - t), rows) + 31) // 32)
+    per = next(p for p in range(2, max(blocks) + 1) if p == max(blocks) or 8 * sum(-(-b // p) for b in blocks) <= 512)
+    assert got == [8 * sum(-(-b // per) for b in blocks)] * 2 and got[0] <= 512
+
+
+def test_attention_of_a_prompt_has_a_workgroup_per_block(host):
+    assert host('''
+lm = context(2100, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
+out = []
+for n in (1019, 2048):
+    lm.reset(0)
+    out.append([l[1] for l in launches(lambda: lm.prefill(0, tokens(n))) if "k_chunk_attn_wide" in l[0]])
+print(json.dumps(out))
+''') == [[256], [512]]
