@@ -816,14 +816,26 @@ int pick_wide_split(const asynclm_ctx* c, int N, int K, int MT) {
     return best;
 }
 
-// Key splits of the attention of n rows: one per 256 keys (one pass of its inner loop), as many as the partial results hold; merged by
-// the last workgroup of a (row, kv head).
+// Key splits of the attention of n rows, merged by the last workgroup of a (row, kv head): a power of two, as many as the partial
+// results hold.  A workgroup takes 256 keys per pass of its inner loop, about 15 us; a merge makes every workgroup publish its part with a
+// device-wide fence, which costs 0.07 us per workgroup of the whole launch (they queue up for it) and half as much again for each
+// (row, kv head) beyond 192.  Hence the split with the least sum of both: with one split per 256 keys, as it was, the merge took most
+// of the time (200 rows at any context 550 us a layer, all but 40 to 150 of it fences).  Whole call, two layers of the 8B shape,
+// single-plane cache, us with 1 / 2 / 4 / 8 / 16 splits: context 300, 24 rows 463 / 479 / 496 / 558 / 675, 256 rows 756 / 1361;
+// context 1000, 8 rows 493 / 474 / 459 / 466 / 512, 64 rows 603 / 678 / 768 / 946; context 4000, 2 rows 685 / 562 / 493 / 463 / 456,
+// 16 rows 709 / 598 / 541 / 557 / 613, 64 rows 795 / 804 / 849 / 988; context 16000, 16 rows 1498 / 998 / 756 / 734 / 807, 128 rows
+// 2226 / 2009 / 1991.
 int pick_rows_split(const asynclm_ctx* c, int keys, int n) {
     const int most = std::min(ATTN_MAX_SPLIT, std::max(1, ROWS_MAX * ATTN_MAX_SPLIT / n));
     if (c->opt_attn_split > 0) return std::min(c->opt_attn_split, most);
-    int nsplit = 1;
-    while (nsplit < (keys + 255) / 256 && 2 * nsplit <= most) nsplit *= 2;
-    return nsplit;
+    const int passes = (keys + 255) / 256, units = n * c->g.Hkv;
+    int best = 1;
+    double best_cost = 15.0 * passes;
+    for (int s = 2; s <= most && s / 2 < passes; s *= 2) {
+        const double cost = 15.0 * ((passes + s - 1) / s) + 0.07 * s * units + 0.14 * std::max(0, units - 192);
+        if (cost < best_cost) { best_cost = cost; best = s; }
+    }
+    return best;
 }
 
 // One forward pass over n = 2..wide_rows rows of one sequence: bf16 models that keep the cache row by row (the single-plane format,
@@ -831,9 +843,9 @@ int pick_rows_split(const asynclm_ctx* c, int keys, int n) {
 // together are the fp32 value, on the matrix cores (three products per weight, fp32 sums), and everything between the products is
 // fp32.  The attention is the one of the other rows path (k_attn_decode), one workgroup per (row, kv head, key split).
 // 8B shape with the single-plane cache, two layers, rows appended at a context of 64 or more, whole call: 2 rows 427 us against 461 in
-// passes of eight rows through the vector units, 8 rows 417 / 464, 24 rows 422 / 1067, 64 rows 526 / 2630, 200 rows 1176 / 8358; a session
+// passes of eight rows through the vector units, 8 rows 417 / 464, 24 rows 422 / 1067, 64 rows 493 / 2630, 200 rows 693 / 8358; a session
 // (203 + 24 tokens appended, 16 steps) 14.7 -> 6.9 ms.  It is also the path for two rows, so there is no rule on the length.
-// Error against 64 bits of that session, rms over 12 seeds: 1.65e-4 before, 1.26e-4 now.
+// Error against 64 bits of that session, rms over 40 seeds: 1.35e-4 before, 1.34e-4 now.
 hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
     const int dt = c->cfg.dtype;
     const Geom& g = c->g;

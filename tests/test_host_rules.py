@@ -229,3 +229,15 @@ for n in (1019, 2048):
     out.append([l[1] for l in launches(lambda: lm.prefill(0, tokens(n))) if "k_chunk_attn_wide" in l[0]])
 print(json.dumps(out))
 ''') == [[256], [512]]
+
+
+# Attention of the rows of a pass: its keys are cut only where the merge of the parts costs less than the shorter chain gives
+@pytest.mark.parametrize("ctx,n,want", [(100, 8, 1), (300, 2, 2), (300, 24, 1), (300, 200, 1), (1000, 8, 4), (1000, 64, 1), (4000, 2, 16), (4000, 16, 4), (4000, 200, 1),
+                                        (16000, 2, 32), (16000, 16, 8), (16000, 128, 4), (16000, 300, 1)])
+def test_attention_of_rows_is_cut_where_the_merge_pays(host, ctx, n, want):
+    got = host(f'''
+lm = context(16400, 1, kv_format=1, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
+lm.prefill(0, tokens({ctx}))
+print(json.dumps([l[1:4] for l in launches(lambda: lm.inject_interrupt(0, tokens({n}))) if "k_attn_decode" in l[0]][0]))
+''')
+    assert got == [8, want, n]
