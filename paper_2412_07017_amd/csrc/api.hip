@@ -209,7 +209,7 @@ SplitPlan pick_step_plan(const asynclm_ctx* c, int len_after, bool pipelined) {
 // 52.8 / 65.6 / 92 us per step as a graph, 22.7 / 37.2 / 52.0 / 67.8 / 97 launch by launch, where the host becomes the slower side.
 bool small_direct(const asynclm_ctx* c, SplitPlan sp) { return sp.small && c->cfg.n_layers <= SMALL_DIRECT_LAYERS; }
 
-// Step of a small model behind its first kernel (launch_small_first, which is launched with the token and position as arguments):
+// Step of a small model behind its first kernel (launch_small_first, which is launched with sequence and forced token as arguments):
 // see decode_small.hip.  The residual stream alternates between two vectors, because the workgroup that writes it is not the only one
 // that reads it.
 hipError_t forward_single_small(asynclm_ctx* c, bool with_head) {
@@ -221,7 +221,7 @@ hipError_t forward_single_small(asynclm_ctx* c, bool with_head) {
     for (int l = 0; l < nl; ++l) {
         void* kvl = kv_layer_ptr(c, l);
         if (l > 0 && (e = run(c, KC_QKV, [&] { return launch_small_qkv(dt, c->wqkv[l], c->attn_norm[l], kvl, c->small, c->b, g, xb[(l - 1) & 1], xb[l & 1], s); }))) return e;
-        if ((e = run(c, KC_ATTN, [&] { return launch_small_attn_o(dt, kvl, c->wo[l], c->small, c->b, g, s); }))) return e;
+        if ((e = run(c, KC_ATTN, [&] { return launch_small_attn_o(dt, kvl, c->wo[l], c->small, c->b, g, l == 0, s); }))) return e;
         if ((e = run(c, KC_GATEUP, [&] { return launch_small_mlp(dt, c->wgate_up[l], c->wdown[l], c->ffn_norm[l], xb[l & 1], c->small, g, s); }))) return e;
     }
     return with_head ? run(c, KC_LMHEAD, [&] { return launch_small_head(dt, c->lm_head, c->final_norm, c->logits, c->small, c->b, g, xb[(nl - 1) & 1], s); }) : hipSuccess;
@@ -446,7 +446,7 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
     // the forward pass is still running
     const TokenWord tok{reinterpret_cast<unsigned long long*>(c->token_host + 4), ++c->tok_serial};
     if (sp.small) {
-        if ((e = run(c, KC_QKV, [&] { return launch_small_first(c->cfg.dtype, c->embed, c->wqkv[0], c->attn_norm[0], kv_layer_ptr(c, 0), c->b, c->g, seq, c->len[seq],
+        if ((e = run(c, KC_QKV, [&] { return launch_small_first(c->cfg.dtype, c->embed, c->wqkv[0], c->attn_norm[0], kv_layer_ptr(c, 0), c->b, c->g, seq,
                                                                 forced, tok, c->b.x, c->stream); }))) return e;
     } else if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, tok, c->stream); }))) return e;
     c->tok_early = !c->prof;

@@ -79,7 +79,7 @@ struct GemvArgs {
     const float* part_acc; const float* part_ml; int32_t merge_nsplit, merge_dh, merge_hq;
     // steps of small models (decode_small.hip): x + nparts partial vectors, or the embedding of the step's token, is the input and goes to x_out
     const float* parts; int32_t nparts; float* x_out;
-    const void* E; StepDesc* step_w; int32_t seq, pos, forced; int32_t* token_log; TokenWord token_early; unsigned* pipe_abort;
+    const void* E; StepDesc* step_w; int32_t seq, forced; int32_t* token_log; TokenWord token_early; unsigned* pipe_abort;
     PipeSync sync;          // hand-over from / to the neighbouring kernels of a step that runs on two streams
 };
 
@@ -203,7 +203,8 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
 // 5.2 -> 2.7, head (with the choice) 8.2 -> 5.5; its session 2.95 -> 2.15 ms.
 // NS: wave-wide loads per row (1, 2 or 4).  SRC: where the input vector comes from: 0 as it stands (or the key splits of the attention),
 // 1 a vector and partial vectors of other kernels, which the four waves add a quarter each, 2 the embedding of the step's token; this
-// is the first kernel of a step then and does what k_begin_step does (it reads nothing that it changes: the position is an argument).
+// is the first kernel of a step then and does what k_begin_step does, but for the sequence's length, which every wave of it reads: the
+// next kernel (k_small_attn_o) lets the sequence grow.
 template <typename WT, int EPI, int NS, int SRC>
 __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     constexpr int EPL = Elem<WT>::EPL, NP = EPL / 4;
@@ -220,14 +221,15 @@ __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     float4 raw[NS][NP][MERGE_MAX_SPLIT];
     const bool merge = EPI == EPI_RESID && !a.x;
     const WT* erow = nullptr;
+    int32_t pos = 0;
     if (SRC == 2) {
+        pos = a.st[a.seq].len;
         const int32_t tok = a.forced >= 0 ? a.forced : a.st[a.seq].next_token;
         erow = (const WT*)a.E + (size_t)tok * a.K;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             *a.pipe_abort = 0u;
             a.step_w->epoch = (a.step_w->epoch + 1) & 0x3fffff;
-            a.step_w->token = tok; a.step_w->pos = a.pos; a.step_w->seq = a.seq; a.step_w->rows = 1;
-            a.st[a.seq].len = a.pos + 1;
+            a.step_w->token = tok; a.step_w->pos = pos; a.step_w->seq = a.seq; a.step_w->rows = 1;
             *a.token_log = tok;
             store_token(a.token_early, tok);
         }
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(256) void k_gemv_small(GemvArgs a, Geom g) {
     EpiOut eo;
     eo.y = a.y; eo.res = a.res; eo.q_out = a.q_out; eo.kv_layer = a.kv_layer;
     eo.rope_cos = a.rope_cos; eo.rope_sin = a.rope_sin; eo.rows = a.rows; eo.pos = 0; eo.seq = 0;
-    if (EPI == EPI_QKV) { eo.pos = SRC == 2 ? a.pos : a.step->pos; eo.seq = SRC == 2 ? a.seq : a.step->seq; }
+    if (EPI == EPI_QKV) { eo.pos = SRC == 2 ? pos : a.step->pos; eo.seq = SRC == 2 ? a.seq : a.step->seq; }
     if (EPI == EPI_STORE) eo.y += (size_t)a.step->seq * a.y_seq_stride;
     if (SRC == 1) {
         constexpr int PB = 16;                                      // partial vectors requested together
@@ -810,10 +812,10 @@ static GemvArgs small_qkv_args(const void* wqkv, const float* gain, void* kv_lay
     return a;
 }
 
-hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
+hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq,
                               int forced, TokenWord token_early, float* x_out, hipStream_t s) {
     GemvArgs a = small_qkv_args(wqkv, gain, kv_layer, b, g, x_out);
-    a.E = E; a.step_w = b.step; a.st = b.seq_state; a.seq = seq; a.pos = pos; a.forced = forced; a.token_log = b.token_log; a.token_early = token_early;
+    a.E = E; a.step_w = b.step; a.st = b.seq_state; a.seq = seq; a.forced = forced; a.token_log = b.token_log; a.token_early = token_early;
     a.pipe_abort = b.pipe_abort;
     return dtype == 0 ? launch_small_t<float, EPI_QKV, 2>(a, g, s) : launch_small_t<bf16_t, EPI_QKV, 2>(a, g, s);
 }

@@ -27,6 +27,7 @@ struct SmallArgs {
     const float* x; const float* gain;
     const float* parts_in;              // partial vectors of the O projection [Hkv][d]
     float* parts_out;                   // [Hkv][d], [F / MLP_F][d]
+    SeqState* grow;                     // the attention of the first layer: sequences, of which the step's one is a token longer now; else null
 };
 
 template <int N>
@@ -54,6 +55,7 @@ __global__ __launch_bounds__(256) void k_small_attn_o(SmallArgs a, Geom g) {
     };
     load(0);
     __builtin_amdgcn_sched_barrier(0);
+    if (a.grow && kvh == 0 && tid == 0) a.grow[a.step->seq].len = len;
     const WT* Kp = (const WT*)a.kv_layer + (size_t)a.step->seq * g.kv_seq_stride + (size_t)kvh * g.kv_head_stride;
     float mh[G], lh[G];
     attn_split<WT, DH, G, PAIR, 8>(a.q, Kp, Kp + g.kv_v_offset, g.kv_lo_offset, kvh, 0, len, g.scale, lds, mh, lh);
@@ -227,8 +229,9 @@ static hipError_t launch_attn_o_t(const SmallArgs& a, const Geom& g, hipStream_t
     }
 }
 
-hipError_t launch_small_attn_o(int dtype, const void* kv_layer, const void* wo, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g, hipStream_t s) {
+hipError_t launch_small_attn_o(int dtype, const void* kv_layer, const void* wo, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g, bool first_layer, hipStream_t s) {
     SmallArgs a{};
+    if (first_layer) a.grow = b.seq_state;
     a.q = b.q; a.kv_layer = kv_layer; a.step = b.step; a.w = wo; a.parts_out = sb.parts;
     if (dtype == 0) return g.dh == 64 ? launch_attn_o_t<float, 64, false>(a, g, s) : launch_attn_o_t<float, 128, false>(a, g, s);
     if (g.kv_lo_offset) return g.dh == 64 ? launch_attn_o_t<bf16_t, 64, true>(a, g, s) : launch_attn_o_t<bf16_t, 128, true>(a, g, s);

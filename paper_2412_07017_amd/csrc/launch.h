@@ -144,13 +144,15 @@ struct SmallBuffers { float* parts; };          // [Hkv + small_mlp_parts][d]
 bool gemv_all_small(int dtype, const Geom& g);  // every product of a step, output head included, is one of k_gemv_small
 bool small_step_supported(int dtype, const Geom& g);
 int small_mlp_parts(const Geom& g);
-// First kernel of such a step: the token (forced, or the sequence's greedy one) and what k_begin_step does for it, its embedding, the first layer's QKV product
-hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq, int pos,
+// First kernel of such a step: the token (forced, or the sequence's greedy one) and what k_begin_step does for it, its embedding, the first layer's QKV product.
+// The position is read from the device, as everywhere in a decoding step: a step that the caller has captured goes on with every replay.
+hipError_t launch_small_first(int dtype, const void* E, const void* wqkv, const float* gain, void* kv_layer, const DecodeBuffers& b, const Geom& g, int seq,
                               int forced, TokenWord token_early, float* x_out, hipStream_t s);
 // QKV product of a later layer: x_in + all partial vectors -> x_out
 hipError_t launch_small_qkv(int dtype, const void* wqkv, const float* gain, void* kv_layer, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
                             const float* x_in, float* x_out, hipStream_t s);
-hipError_t launch_small_attn_o(int dtype, const void* kv_layer, const void* wo, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g, hipStream_t s);
+// first_layer: the sequence grows by the step's token
+hipError_t launch_small_attn_o(int dtype, const void* kv_layer, const void* wo, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g, bool first_layer, hipStream_t s);
 hipError_t launch_small_mlp(int dtype, const void* wgu, const void* wdown, const float* gain, const float* x, const SmallBuffers& sb, const Geom& g, hipStream_t s);
 hipError_t launch_small_head(int dtype, const void* wout, const float* gain, float* logits_base, const SmallBuffers& sb, const DecodeBuffers& b, const Geom& g,
                              const float* x_in, hipStream_t s);

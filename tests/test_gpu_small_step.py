@@ -83,3 +83,38 @@ def test_small_steps_equal_the_other_kernels(kind, model):
     assert _rel(lms[0].logits(1), lms[1].logits(1)) <= TOL[kind] and lms[0].seq_len(1) == lms[1].seq_len(1) == 9
     for lm in lms:
         lm.close()
+
+
+# A step that the caller captures on its stream (plain launches, no token asked for): every replay appends one more token, because
+# position and length are read from the device; small steps and, with forced key splits, those of the other kernels
+@pytest.mark.parametrize("split", [0, 2])
+@pytest.mark.parametrize("layers", [1, 2, 5])
+def test_a_step_captured_by_the_caller_goes_on_with_every_replay(layers, split):
+    import paper_2412_07017_amd as pkg
+    model = _model(256, 4, 2, 64, 264, "fp32", layers=layers)
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    lms = [pkg.AsyncLM(model, w, max_positions=64, stream=s) for s in streams]
+    lms[0].set_option("graph", 0)
+    for lm in lms:
+        lm.set_option("attn_split", split)
+        lm.prefill(0, [1, 2, 3])
+        lm.decode_step(0, forced_token=9)
+        lm.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=streams[0], capture_error_mode="relaxed"):
+        lms[0].decode_step(0, want_token=False)
+    for _ in range(4):
+        with torch.cuda.stream(streams[0]):
+            graph.replay()
+        torch.cuda.synchronize()
+        lms[1].decode_step(0)
+        assert np.array_equal(lms[0].logits(0), lms[1].logits(0))
+    for lm in lms:                                          # and the context is as good as new
+        lm.reset(0)
+        lm.prefill(0, [4, 5])
+        assert lm.decode_step(0, forced_token=6) == 6 and lm.seq_len(0) == 3
+    assert np.array_equal(lms[0].logits(0), lms[1].logits(0))
+    for lm in lms:
+        lm.close()
