@@ -844,7 +844,7 @@ int pick_rows_split(const asynclm_ctx* c, int keys, int n) {
 // fp32.  The attention is the one of the other rows path (k_attn_decode), one workgroup per (row, kv head, key split).
 // 8B shape with the single-plane cache, two layers, rows appended at a context of 64 or more, whole call: 2 rows 427 us against 461 in
 // passes of eight rows through the vector units, 8 rows 417 / 464, 24 rows 422 / 1067, 64 rows 493 / 2630, 200 rows 693 / 8358; a session
-// (203 + 24 tokens appended, 16 steps) 14.7 -> 6.9 ms.  It is also the path for two rows, so there is no rule on the length.
+// (203 + 24 tokens appended, 16 steps) 14.7 -> 6.9 ms.  Short passes of smaller models stay with forward_rows (rows_are_faster).
 // Error against 64 bits of that session, rms over 40 seeds: 1.35e-4 before, 1.34e-4 now.
 hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, bool with_head) {
     const int dt = c->cfg.dtype;
@@ -915,6 +915,23 @@ hipError_t forward_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int n, b
     return hipSuccess;
 }
 
+// Of the models that both forward_wide_rows and forward_rows take: is forward_rows the faster one for a pass of n rows?  It has five
+// launches a layer against eight (and a table to upload), but its time grows with the weights of every group of eight rows.  Whole call in
+// us, wide / rows, after a context of 200 (d model, layers, Mi weights per layer): 2 and 8 rows: d 256, 2 layers (0.8) 110 / 78, 117 / 89; d 512,
+// 8 layers (2.1) 440 / 248, 475 / 294; d 2048, 4 layers (11) 286 / 198, 304 / 219; d 1024, 6 layers (14.5) 385 / 318, 431 / 370; d 2048, 8 layers (48)
+// 681 / 617, 749 / 715, but 2 layers 176 / 173, 188 / 198, because the wide pass ends with its last row; d 2048, 16 layers (58) 1340 / 1291, 1519 / 1511;
+// the 8B shape, 2 layers (208) 292 / 333, 295 / 342.  Contexts up to 16000 move the crossing little (8 rows at 16000: d 1024, 4 layers (5.5) 435 / 376;
+// d 2048, 8 layers (48) 1510 / 1478; d 1024, 2 layers (14.5) 215 / 233).  More rows, where all products are small: 16, 24 and 32 rows at d 256, 4 layers
+// 267 / 211, 310 / 273, 291 / 256; d 512, 4 layers 259 / 190, 273 / 228, 298 / 262, but 2 layers 127 / 109, 133 / 128, 138 / 141; d 1024, 4 layers (5.5)
+// 306 / 253, 356 / 350, 345 / 354; d 1920, 4 layers (8.9) 353 / 346, 399 / 487; 48 rows at d 512, 4 layers 388 / 365, d 1024, 4 layers 475 / 521.
+bool rows_are_faster(const asynclm_ctx* c, int n) {
+    const Geom& g = c->g;
+    const long long Mi = 1 << 20, nl = c->cfg.n_layers, groups = (n + ROWS_MAX - 1) / ROWS_MAX;
+    const long long weights = ((long long)(2 * g.Hq + 2 * g.Hkv) * g.dh + 3LL * g.F) * g.d;      // of a layer
+    if (n <= ROWS_MAX) return weights <= std::min(48LL, 16 * nl) * Mi;
+    return n <= 32 && n <= std::min(c->rows_pass, rows_per_pass(c->cfg.dtype, g)) && nl >= 4 && groups * weights <= 12 * Mi;
+}
+
 // Append n >= 1 tokens to a sequence and leave logits for the token after them.
 int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
     // the one-kernel and the two-stream step are asked for by option: then every token takes such a step
@@ -928,7 +945,7 @@ int append_tokens(asynclm_ctx* c, int seq, const int32_t* tokens, int n) {
         const bool last = i + rows == n;
         if (rows == 1) {
             HIPCK(c, step_one_token(c, seq, tokens[i], last));
-        } else if (wide_path) {
+        } else if (wide_path && !(rows_path && rows_are_faster(c, rows))) {
             HIPCK(c, forward_wide_rows(c, seq, tokens + i, rows, last));
         } else if (!c->chunk_ok) {
             HIPCK(c, forward_rows(c, seq, tokens + i, rows, last));

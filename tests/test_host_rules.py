@@ -188,6 +188,47 @@ print(json.dumps([out, hip.host_hip_used()]))
         assert host(f"lm = context(1024, {kw}{other}); print(json.dumps(count(launches(lambda: lm.prefill(0, tokens(16))), 'k_rows_embed')))") == 2
 
 
+# Which of the two paths a pass of a row-major bf16 model takes: few rows of small models the vector units (five launches a layer and the
+# head, eight tokens per launch of the embedding), all else the matrix cores
+@pytest.mark.parametrize("model,rows,wide", [
+    (dict(d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=768), [2, 8], [9, 32, 200]),               # two layers
+    (dict(d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=768, n_layers=4), [2, 8, 9, 32], [33, 200]),
+    (dict(d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, ffn=1024, n_layers=4), [8, 16], [17, 64]),
+    (dict(d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, ffn=4096, n_layers=4), [2, 8], [9, 24]),      # not all products small
+    (dict(d_model=2048, n_q_heads=16, n_kv_heads=8, ffn=6144, n_layers=3, kv_format=1), [2, 8], [9]),
+    (dict(d_model=2048, n_q_heads=16, n_kv_heads=8, ffn=6144, n_layers=2, kv_format=1), [], [2, 8, 9]),
+    (dict(d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=14336, n_layers=4, kv_format=1), [], [2, 8, 24]),
+])
+def test_short_passes_of_small_models_take_the_vector_units(host, model, rows, wide):
+    got = host(f'''
+model = {model!r}
+lm = context(1024, **model)
+lm.prefill(0, tokens(40))
+out = []
+for n in {rows + wide!r}:
+    ls = launches(lambda: lm.inject_interrupt(0, tokens(n)))
+    out.append([count(ls, "k_rows_embed"), count(ls, "k_chunk_embed_norm"), len(ls)])
+print(json.dumps(out))
+''')
+    nl = model.get("n_layers", 2)
+    for n, g in zip(rows + wide, got):
+        groups = (n + 7) // 8
+        assert g == ([groups, 0, groups + 5 * nl + 1] if n in rows else [0, 1, g[2]]), n
+        assert n in rows or g[2] == 8 * nl + 1, n
+
+
+def test_every_pass_of_a_call_takes_its_own_path(host):
+    assert host('''
+lm = context(1024, d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=768)
+out = []
+for chunk, n in ((0, 515), (8, 20), (1, 3)):
+    lm.set_option("chunk", chunk); lm.reset(0)
+    ls = launches(lambda: lm.prefill(0, tokens(n)))
+    out.append([count(ls, "k_rows_embed"), count(ls, "k_chunk_embed_norm"), lm.seq_len(0)])
+print(json.dumps(out))
+''') == [[1, 1, 515], [3, 0, 20], [0, 0, 3]]
+
+
 # A stream that has run dry without the word of the step's token having been written: the wait for it ends
 @pytest.mark.parametrize("model", ["d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688"])
 def test_wait_for_a_token_ends(host, model):
