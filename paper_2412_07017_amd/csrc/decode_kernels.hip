@@ -394,16 +394,16 @@ struct AttnArgs {
     int32_t nsplit;
     int32_t defer_merge;    // 1: leave the partials to the O projection (no merge here, even for one split)
     int32_t pos0, seq;      // MODE 2: position of row 0 and sequence (the step descriptor is not read)
-    bf16_t *o_hi, *o_lo, *o_lo2;    // MODE 2, optional: the output goes to these tiled planes instead of o
+    bf16_t *o_hi, *o_lo, *o_lo2;    // MODE 3: the output goes to these tiled planes instead of o
     PipeSync sync;
 };
 
 // MODE 0: the default kernel; 2 (ROWS): blockIdx.z is one of several rows of a pass, with its own query, length and partial
-// results; 1 (PIPE): see k_gemv.  The query and the newest cache row come from the QKV kernel of the same step, which may still be
+// results; 3: the same with the output as three bf16 planes; 1 (PIPE): see k_gemv.  The query and the newest cache row come from the QKV kernel of the same step, which may still be
 // running when this kernel starts: neither the query nor any cache row is read before its hand-over.
 template <typename KVT, int DH, int G, bool PAIR, int MODE>
 __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs a, Geom g) {
-    constexpr bool PIPE = MODE == 1, ROWS = MODE == 2;
+    constexpr bool PIPE = MODE == 1, ROWS = MODE >= 2, PLANES = MODE == 3;
     constexpr int EPL = Elem<KVT>::EPL;
     constexpr int PPW = 64 / (DH / EPL);        // positions per wave-wide load
     extern __shared__ float lds[];
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_attn_decode(AttnArgs
         a.part_acc += r * g.Hq * nsplit * DH; a.part_ml += r * g.Hq * nsplit * 2;
     }
     auto put = [&](int hq, int dim, float v) {
-        if (ROWS && a.o_hi) {
+        if constexpr (PLANES) {
             bf16_t p[3];
             split_planes<3>(v, p);
             const size_t o = tiled_off((int)blockIdx.z, hq * DH + dim, g.Hq * DH);
@@ -836,31 +836,31 @@ hipError_t launch_small_head(int dtype, const void* wout, const float* gain, flo
     return dtype == 0 ? launch_small_t<float, EPI_STORE, 1>(a, g, s) : launch_small_t<bf16_t, EPI_STORE, 1>(a, g, s);
 }
 
+template <typename KVT, int DH, bool PAIR, int G>
+static hipError_t launch_attn_g(AttnArgs a, Geom g, hipStream_t s, int rows) {
+    const void* f = (const void*)(k_attn_decode<KVT, DH, G, PAIR, 0>);
+    if (rows) f = (const void*)(k_attn_decode<KVT, DH, G, PAIR, 2>);
+    else if (a.sync.go_wait || a.sync.go_signal) f = (const void*)(k_attn_decode<KVT, DH, G, PAIR, 1>);
+    if (rows && a.o_hi) {
+        if constexpr (sizeof(KVT) == 2) f = (const void*)(k_attn_decode<KVT, DH, G, PAIR, 3>);     // (bf16 models only)
+        else return hipErrorInvalidValue;
+    }
+    const size_t lds = sizeof(float) * attn_lds_floats<KVT, DH, G>();
+    if (lds > 48 * 1024)
+        if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) return e;
+    void* params[] = {&a, &g};
+    return hipLaunchKernel(f, dim3(g.Hkv, a.nsplit, rows > 0 ? rows : 1), dim3(256), params, lds, s);
+}
+
 template <typename KVT, int DH, bool PAIR>
 static hipError_t launch_attn_t(const AttnArgs& a, const Geom& g, hipStream_t s, int rows = 0) {
-    const dim3 grid(g.Hkv, a.nsplit, rows > 0 ? rows : 1), block(256);
-    const bool pipe = a.sync.go_wait || a.sync.go_signal;
-#define ATTN_CASE(GG)                                                                                                   \
-    case GG: {                                                                                                          \
-        const size_t lds = sizeof(float) * attn_lds_floats<KVT, DH, GG>();                                              \
-        if (lds > 48 * 1024) {                                                                                          \
-            hipError_t e = hipFuncSetAttribute(rows ? (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 2>)                \
-                                               : pipe ? (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 1>)              \
-                                                      : (const void*)(k_attn_decode<KVT, DH, GG, PAIR, 0>),             \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
-            if (e) return e;                                                                                            \
-        }                                                                                                               \
-        if (rows) hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 2>), grid, block, lds, s, a, g);                 \
-        else if (pipe) hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 1>), grid, block, lds, s, a, g);            \
-        else hipLaunchKernelGGL((k_attn_decode<KVT, DH, GG, PAIR, 0>), grid, block, lds, s, a, g);                      \
-        break;                                                                                                          \
-    }
     switch (g.Hq / g.Hkv) {
-        ATTN_CASE(1) ATTN_CASE(2) ATTN_CASE(4) ATTN_CASE(8)
+        case 1: return launch_attn_g<KVT, DH, PAIR, 1>(a, g, s, rows);
+        case 2: return launch_attn_g<KVT, DH, PAIR, 2>(a, g, s, rows);
+        case 4: return launch_attn_g<KVT, DH, PAIR, 4>(a, g, s, rows);
+        case 8: return launch_attn_g<KVT, DH, PAIR, 8>(a, g, s, rows);
         default: return hipErrorInvalidValue;
     }
-#undef ATTN_CASE
-    return hipGetLastError();
 }
 
 hipError_t launch_attn_decode(int dtype, const void* kv_layer, int nsplit, bool merge_in_oproj, const DecodeBuffers& b,
