@@ -4,6 +4,7 @@
 #include "launch.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -96,6 +97,8 @@ struct asynclm_ctx {
     int32_t* token_host = nullptr;      // pinned, 16 ints: [0..1] staging of read-backs, [4..5] token and number of the running step (TokenWord)
     uint32_t tok_serial = 0;            // number of the last decoding step
     bool tok_early = false;             // the last decoding step leaves its token in that word as soon as it is chosen
+    hipEvent_t tok_event = nullptr;     // behind the kernel that chooses it (long steps), see wait_token
+    bool tok_marked = false;            // ... recorded there in the last step
 
     std::vector<int32_t> len;           // host mirror of the sequence lengths
     std::vector<int32_t> nban;          // host mirror of the number of banned token ids per sequence
@@ -397,9 +400,20 @@ hipError_t refresh_choice(asynclm_ctx* c, int seq) {
     return launch_argmax(c->logits, c->b, c->g, c->stream, seq);
 }
 
-// Waits for the word that the first kernel of the running step writes.  An event recorded behind that kernel, as a marker, cost 3 us
-// of every step between the two launches (tiny preset 41.0 -> 38.1 us as a graph).  Every wait ends: from time to time the stream is
-// asked for its state, and once it has run dry or failed the word will not change any more (`seen` false: take the token the long way).
+// Is a decoding step expected to take less than SHORT_STEP_US (six launches a layer and the weights at the memory rate)?  An event behind
+// its first kernel is a marker packet of its own, 3 us between two launches of such a step (tiny preset 41.0 -> 38.1 us as a graph without
+// it); nothing at the 8B shape, where the queue is never empty.
+constexpr int SHORT_STEP_US = 200, TOKEN_SPIN_US = 300;
+bool short_step(const asynclm_ctx* c) {
+    const Geom& g = c->g;
+    const double layer = ((2.0 * g.Hq + 2.0 * g.Hkv) * g.dh + 3.0 * g.F) * g.d;
+    return 20.0 * c->cfg.n_layers + (layer * c->cfg.n_layers + (double)g.V * g.d) * elem_bytes(c) / 6.6e6 < SHORT_STEP_US;
+}
+
+// Waits for the word that the first kernel of the running step writes.  Long steps have an event behind that kernel, whose wait is the
+// runtime's own (with its scheduling flags).  In short steps the host looks at the word, for TOKEN_SPIN_US at most: with more in front of the step,
+// a prompt for instance, it waits for an event behind all of it, which is a short step late.  `seen` false: the stream has run dry or
+// failed without the word (take the token the long way).
 hipError_t wait_token(asynclm_ctx* c, int32_t* token, bool* seen) {
     const unsigned long long* word = reinterpret_cast<const unsigned long long*>(c->token_host + 4);
     auto look = [&] {
@@ -408,16 +422,20 @@ hipError_t wait_token(asynclm_ctx* c, int32_t* token, bool* seen) {
         *token = (int32_t)(uint32_t)v;
         return *seen = true;
     };
-    for (;;) {
-        for (int i = 0; i < 4096; ++i) {
-            if (look()) return hipSuccess;
-            __builtin_ia32_pause();
-        }
-        const hipError_t e = hipStreamQuery(c->stream);
-        if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
-        if (!e) look();
-        return e;
+    hipError_t e;
+    if (!c->tok_marked) {
+        const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(TOKEN_SPIN_US);
+        do {
+            for (int i = 0; i < 64; ++i) {
+                if (look()) return hipSuccess;
+                __builtin_ia32_pause();
+            }
+        } while (std::chrono::steady_clock::now() < end);
+        if ((e = hipEventRecord(c->tok_event, c->stream))) return e;
     }
+    if ((e = hipEventSynchronize(c->tok_event))) return e;
+    look();
+    return hipSuccess;
 }
 
 hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
@@ -449,6 +467,8 @@ hipError_t step_one_token(asynclm_ctx* c, int seq, int forced, bool with_head) {
         if ((e = run(c, KC_QKV, [&] { return launch_small_first(c->cfg.dtype, c->embed, c->wqkv[0], c->attn_norm[0], kv_layer_ptr(c, 0), c->b, c->g, seq,
                                                                 forced, tok, c->b.x, c->stream); }))) return e;
     } else if ((e = run(c, KC_BEGIN, [&] { return launch_begin_step(c->cfg.dtype, c->embed, c->b, c->g, seq, forced, tok, c->stream); }))) return e;
+    c->tok_marked = !c->prof && !short_step(c);
+    if (c->tok_marked && (e = hipEventRecord(c->tok_event, c->stream))) return e;
     c->tok_early = !c->prof;
     c->pipe_kernels = pipelined ? 5 * c->cfg.n_layers + (with_head ? 1 : 0) : 0;
     const bool stamp_mode = c->opt_step_stamps && !pipelined && sp.mfma && !c->prof;
@@ -1159,6 +1179,7 @@ static int create_ctx(asynclm_ctx** out, const asynclm_config* cfg, const asyncl
         return bail(ASYNCLM_E_DEVICE);
     if (hipHostMalloc((void**)&c->token_host, 64, hipHostMallocDefault) != hipSuccess) return bail(ASYNCLM_E_NOMEM);
     std::memset(c->token_host, 0, 64);
+    if (hipEventCreateWithFlags(&c->tok_event, hipEventDisableTiming) != hipSuccess) return bail(ASYNCLM_E_DEVICE);
     if (hipMemset(c->b.pipe_abort, 0, sizeof(unsigned) * PIPE_LINE_WORDS) != hipSuccess ||
         hipMemset(c->pipe_go, 0xff, sizeof(unsigned) * PIPE_REGIONS * PIPE_MAX_WORKGROUPS * PIPE_LINE_WORDS) != hipSuccess ||
         hipMemset(c->pipe_counters, 0, sizeof(unsigned) * c->pipe_kernels_max * PIPE_LINE_WORDS) != hipSuccess)
@@ -1220,6 +1241,7 @@ int asynclm_destroy(asynclm_ctx* c) {
     for (hipEvent_t ev : c->prof_events) hipEventDestroy(ev);
     for (void* p : c->allocs) hipFree(p);
     if (c->token_host) hipHostFree(c->token_host);
+    if (c->tok_event) hipEventDestroy(c->tok_event);
     if (c->stream2) { hipStreamSynchronize(c->stream2); hipStreamDestroy(c->stream2); }
     if (c->ev_fork) hipEventDestroy(c->ev_fork);
     if (c->ev_join) hipEventDestroy(c->ev_join);

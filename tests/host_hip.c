@@ -7,9 +7,10 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <time.h>
 
 typedef struct { unsigned x, y, z; } dim3;
-enum { OK = 0, INVALID = 1, OOM = 2 };
+enum { OK = 0, INVALID = 1, OOM = 2, NOT_READY = 600 };
 
 static size_t used, peak, n_blocks;
 static struct { void *p; size_t bytes; } blocks[1 << 16];
@@ -20,6 +21,11 @@ static size_t cfg_lds;
 static void *cfg_stream;
 
 static size_t limit(const char *name) { const char *v = getenv(name); return v ? strtoull(v, NULL, 10) : (size_t)-1; }
+
+static double now(void) { struct timespec t; clock_gettime(CLOCK_MONOTONIC, &t); return t.tv_sec + 1e-9 * t.tv_nsec; }
+static double busy_until;
+/* streams and events are not done for so many seconds from now */
+void host_hip_busy(double seconds) { busy_until = now() + seconds; }
 
 size_t host_hip_peak(void) { return peak; }
 size_t host_hip_used(void) { return used; }
@@ -53,13 +59,17 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, s
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return OK; }
 int hipStreamDestroy(void *s) { free(s); return OK; }
 int hipStreamSynchronize(void *s) { (void)s; return OK; }
-int hipStreamQuery(void *s) { (void)s; return OK; }
+int hipStreamQuery(void *s) { (void)s; return now() < busy_until ? NOT_READY : OK; }
 int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return OK; }
 int hipEventCreate(void **e) { *e = malloc(1); return OK; }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return hipEventCreate(e); }
 int hipEventDestroy(void *e) { free(e); return OK; }
 int hipEventRecord(void *e, void *s) { (void)e; (void)s; return OK; }
-int hipEventSynchronize(void *e) { (void)e; return OK; }
+int hipEventSynchronize(void *e) {
+    (void)e;
+    while (now() < busy_until) { struct timespec t = {0, 1000000}; nanosleep(&t, NULL); }
+    return OK;
+}
 int hipStreamBeginCapture(void *s, int m) { (void)s; (void)m; return OK; }
 int hipStreamEndCapture(void *s, void **g) { (void)s; *g = malloc(1); return OK; }
 int hipGraphInstantiate(void **x, void *g, void *n, char *l, size_t b) {

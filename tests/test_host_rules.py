@@ -239,6 +239,22 @@ print(json.dumps([lm.decode_step(0, forced_token=3), lm.decode_step(0), lm.seq_l
 ''') == [0, 0, 7]
 
 
+# A step behind much other work: the host does not keep a core busy until its token is there
+@pytest.mark.parametrize("model", ["n_layers=16, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=14336", "d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688"])
+def test_wait_for_a_token_leaves_the_core(host, model):
+    wall, cpu = host(f'''
+import time
+hip.host_hip_busy.argtypes = [C.c_double]
+lm = context(64, {model})
+lm.prefill(0, tokens(5))
+hip.host_hip_busy(0.5)
+t, p = time.monotonic(), time.thread_time()
+assert lm.decode_step(0) == 0
+print(json.dumps([time.monotonic() - t, time.thread_time() - p]))
+''')
+    assert wall >= 0.45 and cpu <= 0.1
+
+
 # The shared-key attention of a batch: every sequence cut by its own length, at most two workgroups per compute unit, each with about
 # as many key tiles; single rows among interrupts (blocks of several tasks) too.  A prompt: a workgroup per kv head and block.
 @pytest.mark.parametrize("lens,intr", [([3500] * 16, {}), ([8000] * 4, {}), ([16000, 100], {}), ([16000] + [500] * 3, {}), ([600] * 4, {1: 200}),
