@@ -7,7 +7,9 @@ import pytest
 import torch
 
 import asynclm_inputs as ai
+import plane_model as pm
 from asynclm_inputs.configs import ModelConfig
+from oracle import asynclm_oracle as orc
 
 pytestmark = pytest.mark.gpu
 
@@ -26,6 +28,7 @@ CASES = [
     ("bf16", _model(512, 8, 2, 128, 1152), [257, 40]),               # key splits: 257 rows hold one, 40 rows two
     ("bf16", _model(1024, 4, 4, 128, 640), [96, 129, 64, 65]),
     ("bf16", _model(128, 2, 1, 64, 128), [3, 7]),                    # one block of columns in every product
+    ("bf16", _model(128, 2, 1, 64, 128), [9, 40]),                   # ... in passes that do take the matrix cores
     ("bf16", _model(640, 8, 1, 128, 2432, layers=1), [200, 8]),      # one layer: the pass is its last row
     ("bf16", _model(384, 4, 2, 64, 256, layers=3), [513, 2]),        # a pass of 512 and a single row
     ("pair", _model(512, 8, 2, 64, 896), [24, 100, 300]),
@@ -65,3 +68,23 @@ def test_wide_passes_equal_token_by_token(kind, model, blocks):
         assert _rel(lms[0].logits(seq), lms[1].logits(seq)) <= TOL[kind]
     for lm in lms:
         lm.close()
+
+
+# All three planes of every producer (first norm, norm of the residual, attention with and without a merge of key splits, SwiGLU, the last layer's
+# K and V) in both kernels of the products: the logits are differences that only the third plane carries, against the oracle in 64 bits
+@pytest.mark.parametrize("split", [0, 2])
+@pytest.mark.parametrize("rows", [9, 32, 40, 140])
+@pytest.mark.parametrize("kind,dh", [("pair", 64), ("bf16", 128), ("bf16", 64)])
+def test_products_see_all_bits_of_their_inputs(kind, dh, rows, split):
+    import paper_2412_07017_amd as pkg
+    model, toks = pm.model(dh), pm.tokens(rows)
+    w = pm.weights(dh, rows, torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    dec = orc.CachedDecoder(orc.Shape.of(model), ai.weights_to_numpy(w), kv_round=kind == "bf16")
+    dec.prefill(toks)
+    lm = pkg.AsyncLM(model, w, max_positions=256, stream=torch.cuda.Stream(), kv_format=pkg.KV_BF16 if kind == "bf16" else pkg.KV_AUTO)
+    lm.set_option("attn_split", split)
+    lm.prefill(0, toks)
+    errors = pm.errors(lm.logits(0), dec.logits)
+    assert max(errors.values()) <= pm.BOUND, errors
+    lm.close()
