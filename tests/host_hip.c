@@ -1,6 +1,6 @@
 /* A HIP runtime without a device, preloaded by tests of the library's host code: device memory is only counted, kernels are
  * only written down (device name, grid and workgroup size, one line each), copies and waits do nothing.
- *   HOST_HIP_LOG      file that takes the launches
+ *   HOST_HIP_LOG      file that takes the launches (of a graph: one line)
  *   HOST_HIP_BUDGET   bytes of device memory (default: no limit); an allocation past it fails with hipErrorOutOfMemory
  *   HOST_HIP_GRAPHS   bytes that may be allocated for a graph to be instantiated (default: no limit)
  */
@@ -80,7 +80,13 @@ int hipGraphInstantiate(void **x, void *g, void *n, char *l, size_t b) {
 }
 int hipGraphDestroy(void *g) { free(g); return OK; }
 int hipGraphExecDestroy(void *x) { free(x); return OK; }
-int hipGraphLaunch(void *x, void *s) { (void)x; (void)s; return OK; }
+int hipGraphLaunch(void *x, void *s) {
+    (void)x; (void)s;
+    const char *log = getenv("HOST_HIP_LOG");
+    FILE *o = log ? fopen(log, "a") : NULL;
+    if (o) { fputs("graph 0 0 0 0\n", o); fclose(o); }
+    return OK;
+}
 
 void **__hipRegisterFatBinary(const void *d) { (void)d; static void *h; return &h; }
 void __hipUnregisterFatBinary(void **h) { (void)h; }

@@ -118,3 +118,35 @@ def test_a_step_captured_by_the_caller_goes_on_with_every_replay(layers, split):
     assert np.array_equal(lms[0].logits(0), lms[1].logits(0))
     for lm in lms:
         lm.close()
+
+
+# Models of four layers and more replay the short step as a graph behind its first kernel: the same bits as launch by launch, the oracle's
+# logits, two sequences in turn, and over the end of the short step at 384 keys (an even and an odd number of layers: the
+# residual stream alternates between two vectors)
+@pytest.mark.parametrize("layers", [4, 5])
+@pytest.mark.parametrize("kind", ["fp32", "bf16"])
+def test_short_steps_as_a_graph(kind, layers):
+    import paper_2412_07017_amd as pkg
+    model = _model(256, 4, 2, 64, 264, "fp32" if kind == "fp32" else "bf16", layers=layers)
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 973, 420, model.vocab)]
+    lms = [pkg.AsyncLM(model, w, max_positions=420, max_seqs=2, stream=torch.cuda.Stream(), kv_format=pkg.KV_BF16 if kind == "bf16" else pkg.KV_AUTO) for _ in range(2)]
+    lms[1].set_option("graph", 0)
+    starts = [(0, 20), (1, 376)]
+    for lm in lms:
+        for seq, n in starts:
+            lm.prefill(seq, toks[:n])
+    for step in range(20):
+        for seq, n in starts:
+            for lm in lms:
+                assert lm.decode_step(seq, forced_token=toks[n + step]) == toks[n + step]
+            a = lms[0].logits(seq)
+            assert np.isfinite(a).all() and np.array_equal(a, lms[1].logits(seq)), (seq, step)
+    if kind == "fp32":
+        for seq, n in starts:
+            dec = orc.CachedDecoder(orc.Shape.of(model), ai.weights_to_numpy(w), dtype=np.float64)
+            dec.prefill(toks[:n + 20])
+            assert _rel(lms[0].logits(seq), dec.logits) <= TOL[kind]
+    for lm in lms:
+        lm.close()

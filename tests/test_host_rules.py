@@ -229,8 +229,25 @@ print(json.dumps(out))
 ''') == [[1, 1, 515], [3, 0, 20], [0, 0, 3]]
 
 
+# The short step of small models: launch by launch up to three layers, from four on one kernel and a graph, past 384 keys the ordinary step
+@pytest.mark.parametrize("layers", [2, 3, 4, 5])
+def test_launches_of_the_short_step(host, layers):
+    got = host(f'''
+lm = context(500, dtype="fp32", d_model=256, n_kv_heads=4, head_dim=64, ffn=688, n_layers={layers})
+out = []
+for ctx, graph in ((20, 1), (20, 0), (383, 1), (384, 1)):
+    lm.set_option("graph", graph); lm.reset(0); lm.prefill(0, tokens(ctx))
+    ls = launches(lambda: lm.decode_step(0, forced_token=1))
+    out.append([sum(l[0] == "graph" for l in ls), len(ls), count(ls, "k_small_attn_o"), count(ls, "k_begin_step")])
+print(json.dumps(out))
+''')
+    plain, graph = [0, 3 * layers + 1, layers, 0], [1, 2, 0, 0]
+    short = graph if layers > 3 else plain
+    assert got == [short, plain, short, [1, 2, 0, 1]]
+
+
 # A stream that has run dry without the word of the step's token having been written: the wait for it ends
-@pytest.mark.parametrize("model", ["d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688"])
+@pytest.mark.parametrize("model", ["d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688", "dtype='fp32', d_model=256, n_kv_heads=4, head_dim=64, ffn=688"])
 def test_wait_for_a_token_ends(host, model):
     assert host(f'''
 lm = context(64, {model})
@@ -240,7 +257,7 @@ print(json.dumps([lm.decode_step(0, forced_token=3), lm.decode_step(0), lm.seq_l
 
 
 # A step behind much other work: the host does not keep a core busy until its token is there
-@pytest.mark.parametrize("model", ["n_layers=16, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=14336", "d_model=512", "dtype='fp32', d_model=256, head_dim=64, ffn=688"])
+@pytest.mark.parametrize("model", ["n_layers=16, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=14336", "d_model=512", "dtype='fp32', d_model=256, n_kv_heads=4, head_dim=64, ffn=688"])
 def test_wait_for_a_token_leaves_the_core(host, model):
     wall, cpu = host(f'''
 import time
