@@ -48,7 +48,15 @@ int hipHostFree(void *p) { free(p); return OK; }
 int hipMemset(void *p, int v, size_t n) { (void)p; (void)v; (void)n; return OK; }
 int hipMemsetAsync(void *p, int v, size_t n, void *s) { (void)p; (void)v; (void)n; (void)s; return OK; }
 int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)d; (void)s; (void)n; (void)k; return OK; }
-int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)d; (void)s; (void)n; (void)k; (void)st; return OK; }
+/* the last upload (row table of a pass): its bytes, as many as fit */
+static unsigned char uploaded[1 << 18];
+static size_t n_uploaded;
+size_t host_hip_uploaded(void *out, size_t cap) { memcpy(out, uploaded, cap < n_uploaded ? cap : n_uploaded); return n_uploaded; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) {
+    (void)d; (void)st;
+    if (k == 1 /* host to device */ && n <= sizeof uploaded) memcpy(uploaded, s, n_uploaded = n);
+    return OK;
+}
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return OK; }      /* compute units */
 int hipDeviceSynchronize(void) { return OK; }

@@ -207,6 +207,34 @@ def test_batch_of_uneven_sequences_equals_one_at_a_time(lens, intr):
         lm.close()
 
 
+# Interrupts of several tasks next to single rows, every sequence cut into another number of parts: blocks of one to four tasks
+def test_blocks_of_several_tasks_cut_differently_in_one_batch():
+    import paper_2412_07017_amd as pkg
+    lens, intr = [3300, 1500, 700, 3000], {0: 40, 1: 24, 2: 70}
+    model = ModelConfig(n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=1024, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    tk = lambda n, sub: [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 948, n, model.vocab, sub=sub)]
+    blocks = [tk(intr[s], 100 + s) if s in intr else [] for s in range(len(lens))]
+    lms = [pkg.AsyncLM(model, w, max_positions=3500, max_seqs=len(lens), stream=torch.cuda.Stream()) for _ in range(2)]
+    for lm in lms:
+        for s, n in enumerate(lens):
+            lm.prefill(s, tk(n, s))
+    lms[0].step_batch(range(len(lens)), forced=[3, 5, 7, 9], interrupts=blocks)
+    for s, n in enumerate(lens):                            # through the single-row kernels
+        lms[1].decode_step(s, forced_token=[3, 5, 7, 9][s])
+        for t in blocks[s]:
+            lms[1].decode_step(s, forced_token=t)
+        total = n + 1 + len(blocks[s])
+        (ka, va), (kb, vb) = _planes(lms[0], model, total, s), _planes(lms[1], model, total, s)
+        assert _worst(ka, kb) <= TOL and _worst(va, vb) <= TOL, (s, _worst(ka, kb), _worst(va, vb))
+        la, lb = lms[0].logits(s), lms[1].logits(s)
+        assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL, s
+    for lm in lms:
+        lm.close()
+
+
 def test_weights_at_eight_bytes_past_an_alignment():
     """The same weights at addresses that are no multiple of 16: passes of at most 128 rows, through registers."""
     import paper_2412_07017_amd as pkg

@@ -6,6 +6,7 @@ import shutil
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -272,26 +273,61 @@ print(json.dumps([time.monotonic() - t, time.thread_time() - p]))
     assert wall >= 0.45 and cpu <= 0.1
 
 
-# The shared-key attention of a batch: every sequence cut by its own length, at most two workgroups per compute unit, each with about
-# as many key tiles; single rows among interrupts (blocks of several tasks) too.  A prompt: a workgroup per kv head and block.
-@pytest.mark.parametrize("lens,intr", [([3500] * 16, {}), ([8000] * 4, {}), ([16000, 100], {}), ([16000] + [500] * 3, {}), ([600] * 4, {1: 200}),
-                                       ([512 + 230 * i for i in range(16)], {0: 24})])
-def test_attention_of_a_batch_is_cut_evenly(host, lens, intr):
-    got = host(f'''
+# The shared-key attention of a batch: every sequence cut by its own length, at most two workgroups per compute unit, and no other cut
+# with as many workgroups has a shorter longest part.  From the row table as it is uploaded (groups, tasks, blocks, pieces): every part of every
+# block is there once, none is empty, and no two share the place of their partial results.  Single rows among interrupts (blocks of several
+# tasks) too.  (The last case is that of a test on the device.)
+@pytest.mark.parametrize("lens,intr,heads", [([3500] * 16, {}, (32, 8)), ([8000] * 4, {}, (32, 8)), ([16000, 100], {}, (32, 8)), ([16000] + [500] * 3, {}, (32, 8)),
+                                             ([600] * 4, {1: 200}, (32, 8)), ([512 + 230 * i for i in range(16)], {0: 24}, (32, 8)),
+                                             ([3300, 1500, 700, 3000], {0: 40, 1: 24, 2: 70}, (8, 2))])
+def test_attention_of_a_batch_is_cut_evenly(host, lens, intr, heads):
+    grids, tab = host(f'''
 lens, intr = {lens!r}, {intr!r}
-lm = context(16400, len(lens), d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
+lm = context(16400, len(lens), d_model=1024, n_q_heads={heads[0]}, n_kv_heads={heads[1]}, ffn=1024)
 for s, n in enumerate(lens): lm.prefill(s, tokens(n))
 ls = launches(lambda: lm.step_batch(range(len(lens)), forced=[1] * len(lens), interrupts=[tokens(intr.get(s, 0)) for s in range(len(lens))]))
-print(json.dumps([l[1] for l in ls if "k_chunk_attn_wide" in l[0]]))
+buf = (C.c_ubyte * (1 << 18))()
+hip.host_hip_uploaded.restype = C.c_size_t
+n = hip.host_hip_uploaded(buf, C.c_size_t(1 << 18))
+print(json.dumps([[l[1] for l in ls if "k_chunk_attn_wide" in l[0]], list(buf)[:n]]))
 ''')
-    blocks = []                                             # key tiles of every block of up to four tasks
-    for s, n in enumerate(lens):
-        rows = 1 + intr.get(s, 0)
-        tasks = (4 * rows + 31) // 32
-        for t in range(0, tasks, 4):
-            blocks.append((n + min(32 * t % rows + 32 * min(4, tasks - t), rows) + 31) // 32)
-    per = next(p for p in range(2, max(blocks) + 1) if p == max(blocks) or 8 * sum(-(-b // p) for b in blocks) <= 512)
-    assert got == [8 * sum(-(-b // per) for b in blocks)] * 2 and got[0] <= 512
+    rows = [1 + intr.get(s, 0) for s in range(len(lens))]
+    G, Hkv = heads[0] // heads[1], heads[1]
+    ntasks = [(G * r + 31) // 32 for r in rows]
+    nblocks = sum((t + 3) // 4 for t in ntasks)
+    npieces = grids[0] // Hkv
+    assert grids == [npieces * Hkv] * 2 and npieces * Hkv <= 512
+    tab, at = np.array(tab, np.uint8), 32 * len(lens)
+    tasks = tab[at:at + 32 * sum(ntasks)].view(np.int32).reshape(-1, 8)         # seq, row0, n, pos0, tile, nsplit, unit0
+    at += 32 * sum(ntasks)
+    blocks = tab[at:at + 8 * nblocks].view(np.int32).reshape(-1, 2)             # task0, n
+    at += (8 * nblocks + 31) // 32 * 32
+    pieces = tab[at:at + 4 * npieces].view(np.int16).reshape(-1, 2)             # block, split
+    assert list(tasks[:, 0]) == [s for s in range(len(lens)) for _ in range(ntasks[s])]
+    assert [t for b, n in blocks for t in range(b, b + n)] == list(range(sum(ntasks)))
+    tiles, splits = [], []                                  # key tiles and parts of every block
+    for task0, n in blocks:
+        seq, row0, r, pos0, tile = tasks[task0][:5]
+        assert len({tuple(t[:4]) + (t[5],) for t in tasks[task0:task0 + n]}) == 1 and 1 <= n <= 4
+        columns = range(32 * tile, min(32 * (tile + n), G * r))                 # (query head, row) pairs: a tile may run from one head into the next
+        tiles.append(-(-(pos0 + max(c % r for c in columns) + 1) // 32))
+        splits.append(int(tasks[task0][5]))
+    assert sorted(map(tuple, pieces)) == [(b, s) for b in range(nblocks) for s in range(splits[b])]
+    for t, k in zip(tiles, splits):
+        per = -(-t // k)
+        assert per * (k - 1) < t                            # the last part has tiles
+    if any(k > 1 for k in splits):
+        used = [u for t in tasks for u in range(t[6], t[6] + t[5])]
+        assert len(set(used)) == len(used) and max(used) < 4096 // Hkv
+    best = [1] * nblocks                                    # one more part for the longest, as long as there is room
+    part = lambda i: -(-tiles[i] // best[i])
+    while True:
+        i = max(range(nblocks), key=part)
+        k = next((k for k in range(best[i] + 1, tiles[i] + 1) if -(-tiles[i] // k) < part(i)), None)
+        if k is None or part(i) <= 2 or (sum(best) - best[i] + k) * Hkv > 512:
+            break
+        best[i] = k
+    assert max(-(-t // k) for t, k in zip(tiles, splits)) == max(map(part, range(nblocks)))
 
 
 def test_attention_of_a_prompt_has_a_workgroup_per_block(host):
