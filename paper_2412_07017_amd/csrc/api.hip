@@ -202,9 +202,10 @@ SplitPlan pick_nsplit(const asynclm_ctx* c, int len_after, bool single_row_kerne
     return {n, merged, false};
 }
 
-// The plan of a decoding step.  Small models with few keys: forward_single_small.
+// The plan of a decoding step.  Small models with few keys, where it pays: forward_single_small.
 SplitPlan pick_step_plan(const asynclm_ctx* c, int len_after, bool pipelined) {
-    if (c->small.parts && !pipelined && c->opt_attn_split == 0 && len_after <= SMALL_MAX_KEYS && small_step_supported(c->cfg.dtype, c->g)) return {1, false, false, true};
+    if (c->small.parts && !pipelined && c->opt_attn_split == 0 && small_step_supported(c->cfg.dtype, c->g) && small_step_pays(c->cfg.dtype, c->g, c->cfg.n_layers, len_after))
+        return {1, false, false, true};
     return pick_nsplit(c, len_after, pipelined);
 }
 

@@ -629,8 +629,11 @@ static size_t gemv_lds_bytes(int K, int units, int grid, int* done_cap) {
 
 template <typename WT, int EPI, int SRC>
 static const void* gemv_small_func(int ns) {
-    if constexpr (SRC > 0) return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, SRC>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2, SRC>) : nullptr;
-    else return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, 0>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2, 0>) : (const void*)(k_gemv_small<WT, EPI, 4, 0>);
+    if constexpr (SRC > 0) {
+        if constexpr (SMALL_MAX_D > 64 * Elem<WT>::EPL)
+            if (ns == 2) return (const void*)(k_gemv_small<WT, EPI, 2, SRC>);
+        return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, SRC>) : nullptr;
+    } else return ns <= 1 ? (const void*)(k_gemv_small<WT, EPI, 1, 0>) : ns == 2 ? (const void*)(k_gemv_small<WT, EPI, 2, 0>) : (const void*)(k_gemv_small<WT, EPI, 4, 0>);
 }
 
 // k_gemv_small takes the product

@@ -201,11 +201,27 @@ __global__ __launch_bounds__(256) void k_small_mlp(SmallArgs a, Geom g) {
 template <typename WT>
 static bool small_step_t(const Geom& g) {
     const int cols = g.Hq / g.Hkv * g.dh, lps = cols / Elem<WT>::EPL;
-    return lps >= 8 && lps <= 64 && g.d <= 128 * Elem<WT>::EPL && (size_t)g.d * cols * sizeof(WT) <= SMALL_O_BYTES && g.Hkv <= SMALL_MAX_KV_HEADS && g.d % 8 == 0 && g.F % 8 == 0 && g.F >= 8;
+    return lps >= 8 && lps <= 64 && g.d <= SMALL_MAX_D && (size_t)g.d * cols * sizeof(WT) <= SMALL_O_BYTES && g.Hkv <= SMALL_MAX_KV_HEADS && g.d % 8 == 0 && g.F % 8 == 0 && g.F >= 8;
 }
 
 bool small_step_supported(int dtype, const Geom& g) {
     return gemv_all_small(dtype, g) && g.kv_v_offset && (dtype == 0 ? small_step_t<float>(g) : small_step_t<bf16_t>(g));
+}
+
+// The short step saves the launch that starts a step, two per layer and, launch by launch, the start of a graph; but one workgroup per
+// kv head walks all keys and reads all its columns of the O projection, and every workgroup of the next product reads all partial vectors,
+// where the other kernels split these.  Difference of the two in us, fitted to 372 random shapes of 1 to 16 layers at six contexts from 10 to 350
+// (rms 4 % of a step) and shifted by 1 + 0.6 per layer to the other kernels' side.  On 363 other shapes (2178 points) the choice is more than 3 %
+// slower than the other kernels at 3 points (4 % at most), and 0.5 % slower than the better of the two on average (10 % at most).  Short step / the other kernels, us per step: tiny preset's
+// shape 32 / 44 (350 keys 38 / 44), with 5 layers 75 / 88 at 110 keys and 81 / 87 at 200; bf16 d 256, 5 layers 89 / 102; but bf16 d 512 with 1024 features,
+// 5 layers 105 / 103, two heads per kv head 125 / 108 (144 / 107 at 350 keys), d 1024 163 / 109, eight heads per kv head 153 / 143 (201 / 143 at 275).
+bool small_step_pays(int dtype, const Geom& g, int n_layers, int keys) {
+    const int es = dtype == 0 ? 4 : 2, G = g.Hq / g.Hkv, w = 4 / es * G;                          // w: bf16 has twice the channels per lane
+    const int o_batches = (int)(((size_t)g.d * G * g.dh * es + 65535) / 65536);                    // of the O projection's loads (O_BATCH)
+    const int key_batches = (keys - 1) / (2048 * (16 / es) / g.dh), chunks = (keys - 1) / 256;      // beyond the first (attn_split)
+    const double part_bytes = (double)(g.Hkv + small_mlp_parts(g)) * g.d * sizeof(float), cache = dtype == 0 ? 0. : g.kv_lo_offset ? 0.9 : -0.4;
+    const double layer = 2.4 * (o_batches - 1) + 0.6 * part_bytes / 65536 + 1.4 * key_batches + 0.48 * chunks * w + 0.5 * w + cache - 0.34 * (g.Hq - g.Hkv) - 2.2;
+    return keys <= SMALL_MAX_KEYS && layer * n_layers < (n_layers <= SMALL_DIRECT_LAYERS ? 8.2 : 4.0);
 }
 
 int small_mlp_parts(const Geom& g) { return (g.F + MLP_F - 1) / MLP_F; }
@@ -242,7 +258,9 @@ template <typename WT>
 static hipError_t launch_mlp_t(const SmallArgs& a, const Geom& g, hipStream_t s) {
     const int ns = (g.d / Elem<WT>::EPL + 63) / 64;
     auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3(small_mlp_parts(g)), dim3(256), 0, s, a, g); return hipGetLastError(); };
-    return ns <= 1 ? go(k_small_mlp<WT, 1>) : ns == 2 ? go(k_small_mlp<WT, 2>) : hipErrorInvalidValue;
+    if constexpr (SMALL_MAX_D > 64 * Elem<WT>::EPL)
+        if (ns == 2) return go(k_small_mlp<WT, 2>);
+    return ns <= 1 ? go(k_small_mlp<WT, 1>) : hipErrorInvalidValue;
 }
 
 hipError_t launch_small_mlp(int dtype, const void* wgu, const void* wdown, const float* gain, const float* x, const SmallBuffers& sb, const Geom& g, hipStream_t s) {

@@ -135,14 +135,14 @@ hipError_t launch_rows_down(int dtype, const void* wd, const RowsBuffers& rb, co
 
 // Decoding step of small models with partial vectors between the kernels (decode_small.hip).
 constexpr size_t SMALL_O_BYTES = 128 * 1024;    // columns of the O projection that belong to one kv head: read by one compute unit
-constexpr int SMALL_MAX_KV_HEADS = 16;
-// One workgroup per kv head walks all keys, the other kernels split them.  Tiny preset, us per step here / there (both as graphs): 100 keys
-// 41.4 / 47.5, 240 44.5 / 47.6, 360 46.7 / 48.3, 400 49.0 / 48.2, 490 49.3 / 48.2.
-constexpr int SMALL_MAX_KEYS = 384;
+constexpr int SMALL_MAX_KV_HEADS = 16, SMALL_MAX_D = 512;
+constexpr int SMALL_MAX_KEYS = 384;             // see small_step_pays
 constexpr int SMALL_DIRECT_LAYERS = 3;          // up to this many layers a step's launches are issued one by one, see step_one_token
 struct SmallBuffers { float* parts; };          // [Hkv + small_mlp_parts][d]
 bool gemv_all_small(int dtype, const Geom& g);  // every product of a step, output head included, is one of k_gemv_small
 bool small_step_supported(int dtype, const Geom& g);
+// whether such a step over so many keys is faster than the kernels of the other models
+bool small_step_pays(int dtype, const Geom& g, int n_layers, int keys);
 int small_mlp_parts(const Geom& g);
 // First kernel of such a step: the token (forced, or the sequence's greedy one) and what k_begin_step does for it, its embedding, the first layer's QKV product.
 // The position is read from the device, as everywhere in a decoding step: a step that the caller has captured goes on with every replay.

@@ -31,6 +31,26 @@ CASES = [
     ("pair", _model(1000, 6, 6, 64, 104, "bf16")),
     ("bf16", _model(256, 8, 2, 128, 512, "bf16")),
     ("bf16", _model(264, 8, 1, 64, 688, "bf16")),                   # eight query heads per kv head
+    # Not all of the models above take the short step (at most 128 KB of the O projection per kv head).  These do, at the shorter contexts
+    # at least: every variant of its kernels (heads per kv head, head_dim, cache), and two loads per row
+    ("fp32", _model(264, 4, 4, 64, 712, "fp32", layers=3)),
+    ("fp32", _model(128, 4, 2, 64, 264, "fp32")),
+    ("fp32", _model(136, 2, 2, 128, 8, "fp32", layers=1)),
+    ("fp32", _model(128, 4, 2, 128, 136, "fp32", layers=3)),
+    ("pair", _model(256, 6, 6, 64, 104, "bf16")),
+    ("pair", _model(264, 4, 2, 64, 200, "bf16")),
+    ("pair", _model(128, 8, 2, 64, 344, "bf16")),
+    ("pair", _model(120, 8, 1, 64, 264, "bf16", layers=1)),
+    ("pair", _model(136, 3, 3, 128, 264, "bf16", layers=3)),
+    ("pair", _model(136, 4, 2, 128, 264, "bf16")),
+    ("pair", _model(120, 8, 2, 128, 264, "bf16")),
+    ("bf16", _model(512, 4, 4, 64, 1000, "bf16")),
+    ("bf16", _model(256, 8, 4, 64, 264, "bf16", layers=3)),
+    ("bf16", _model(128, 8, 2, 64, 264, "bf16", vocab=33)),
+    ("bf16", _model(128, 16, 2, 64, 264, "bf16")),
+    ("bf16", _model(256, 2, 2, 128, 512, "bf16")),
+    ("bf16", _model(128, 4, 2, 128, 264, "bf16")),
+    ("bf16", _model(128, 8, 2, 128, 264, "bf16")),
 ]
 
 
@@ -121,19 +141,21 @@ def test_a_step_captured_by_the_caller_goes_on_with_every_replay(layers, split):
 
 
 # Models of four layers and more replay the short step as a graph behind its first kernel: the same bits as launch by launch, the oracle's
-# logits, two sequences in turn, and over the end of the short step at 384 keys (an even and an odd number of layers: the
+# logits, two sequences in turn, one of them over the end of the short step at `last` keys (an even and an odd number of layers: the
 # residual stream alternates between two vectors)
-@pytest.mark.parametrize("layers", [4, 5])
-@pytest.mark.parametrize("kind", ["fp32", "bf16"])
-def test_short_steps_as_a_graph(kind, layers):
+GRAPHS = [("fp32", _model(256, 4, 2, 64, 264, "fp32", layers=4), 128), ("fp32", _model(256, 4, 4, 64, 264, "fp32", layers=5), 256),
+          ("bf16", _model(256, 4, 2, 64, 264, "bf16", layers=5), 256), ("pair", _model(256, 4, 4, 64, 264, "bf16", layers=4), 256)]
+
+
+@pytest.mark.parametrize("kind,model,last", GRAPHS, ids=["%s-%d" % (k, m.n_layers) for k, m, _ in GRAPHS])
+def test_short_steps_as_a_graph(kind, model, last):
     import paper_2412_07017_amd as pkg
-    model = _model(256, 4, 2, 64, 264, "fp32" if kind == "fp32" else "bf16", layers=layers)
     w = ai.make_weights(model, device=torch.device("cuda:0"))
     torch.cuda.synchronize()
     toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 973, 420, model.vocab)]
     lms = [pkg.AsyncLM(model, w, max_positions=420, max_seqs=2, stream=torch.cuda.Stream(), kv_format=pkg.KV_BF16 if kind == "bf16" else pkg.KV_AUTO) for _ in range(2)]
     lms[1].set_option("graph", 0)
-    starts = [(0, 20), (1, 376)]
+    starts = [(0, 20), (1, last - 8)]
     for lm in lms:
         for seq, n in starts:
             lm.prefill(seq, toks[:n])

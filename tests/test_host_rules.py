@@ -230,13 +230,13 @@ print(json.dumps(out))
 ''') == [[1, 1, 515], [3, 0, 20], [0, 0, 3]]
 
 
-# The short step of small models: launch by launch up to three layers, from four on one kernel and a graph, past 384 keys the ordinary step
-@pytest.mark.parametrize("layers", [2, 3, 4, 5])
-def test_launches_of_the_short_step(host, layers):
+# The short step of small models: launch by launch up to three layers, from four on one kernel and a graph, past its last key the ordinary step
+@pytest.mark.parametrize("layers,last", [(2, 384), (3, 384), (4, 256), (5, 256), (16, 256)])
+def test_launches_of_the_short_step(host, layers, last):
     got = host(f'''
 lm = context(500, dtype="fp32", d_model=256, n_kv_heads=4, head_dim=64, ffn=688, n_layers={layers})
 out = []
-for ctx, graph in ((20, 1), (20, 0), (383, 1), (384, 1)):
+for ctx, graph in ((20, 1), (20, 0), ({last} - 1, 1), ({last}, 1)):
     lm.set_option("graph", graph); lm.reset(0); lm.prefill(0, tokens(ctx))
     ls = launches(lambda: lm.decode_step(0, forced_token=1))
     out.append([sum(l[0] == "graph" for l in ls), len(ls), count(ls, "k_small_attn_o"), count(ls, "k_begin_step")])
@@ -245,6 +245,47 @@ print(json.dumps(out))
     plain, graph = [0, 3 * layers + 1, layers, 0], [1, 2, 0, 0]
     short = graph if layers > 3 else plain
     assert got == [short, plain, short, [1, 2, 0, 1]]
+
+
+def test_short_steps_of_the_device_tests_are_short_steps(host):
+    from test_gpu_small_step import CASES, GRAPHS
+    models = [dict(m.__dict__, kv_format=1 if kind == "bf16" else 0) for kind, m in CASES]
+    graphs = [(dict(m.__dict__, kv_format=1 if kind == "bf16" else 0), last) for kind, m, last in GRAPHS]
+    names, short = host(f'''
+names, short = set(), []
+for m in {models!r}:
+    lm = context(64, **m)
+    lm.prefill(0, tokens(1))
+    names |= {{l[0] for l in launches(lambda: lm.decode_step(0, forced_token=1))}}
+    lm.close()
+for m, last in {graphs!r}:
+    lm = context(420, **m)
+    for ctx in (20, last - 1, last):
+        lm.reset(0); lm.prefill(0, tokens(ctx))
+        ls = launches(lambda: lm.decode_step(0, forced_token=1))
+        short.append([sum(l[0] == "graph" for l in ls), count(ls, "k_begin_step")])
+    lm.close()
+print(json.dumps([sorted(names), short]))
+''')
+    assert short == [[1, 0], [1, 0], [1, 1]] * len(GRAPHS)
+    want = ["k_small_attn_oIfLi%dELi%dELb0E" % v for v in ((64, 1), (64, 2), (64, 4), (128, 1), (128, 2))]
+    want += ["k_small_attn_oItLi%dELi%dELb%dE" % (dh, G, pair) for dh in (64, 128) for G in (1, 2, 4, 8) if G * dh < 1024 for pair in (0, 1)]
+    want += ["k_small_mlpIfLi1E", "k_small_mlpIfLi2E", "k_small_mlpItLi1E"]
+    want += ["k_gemv_smallI%sLi%dELi%dELi%dEE" % (t, epi, ns, src) for t, ns in (("f", 1), ("f", 2), ("t", 1)) for epi, src in ((3, 1), (3, 2), (0, 1))]
+    assert [w for w in want if not any(w in n for n in names)] == []
+
+
+# Where the short step is the slower one: measured for each of these, the first two far beyond what it gains elsewhere
+@pytest.mark.parametrize("model,ctx", [
+    ("d_model=512, n_q_heads=8, n_kv_heads=4, head_dim=64, ffn=1024, n_layers=4", 340), ("d_model=128, n_q_heads=16, n_kv_heads=2, head_dim=64, ffn=384", 280),
+    ("d_model=512, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=1024, n_layers=5", 20), ("d_model=1024, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=1024", 20),
+    ("dtype='fp32', d_model=512, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=1024, n_layers=5", 20), ("dtype='fp32', d_model=128, n_q_heads=2, n_kv_heads=2, ffn=384", 360)])
+def test_short_step_only_where_it_pays(host, model, ctx):
+    assert host(f'''
+lm = context(500, {model})
+lm.prefill(0, tokens({ctx}))
+print(json.dumps(count(launches(lambda: lm.decode_step(0, forced_token=1)), "k_begin_step")))
+''') == 1
 
 
 # A stream that has run dry without the word of the step's token having been written: the wait for it ends
