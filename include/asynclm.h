@@ -30,11 +30,15 @@
  *     that return data to the host synchronise that stream, the others may return before the GPU
  *     has finished.
  *   - All memory the library needs (K/V cache, rotary table, activations, logits, pinned staging, the captured
- *     graphs of the decoding steps for every context length up to max_positions) is allocated in asynclm_create.
+ *     graphs of the decoding steps for every context length up to max_positions; short steps of small models of up to three layers
+ *     are launched kernel by kernel instead) is allocated in asynclm_create.
  *     Of the other calls only asynclm_set_option allocates (options that change the launch geometry of a decoding
  *     step build its graphs again) and asynclm_profile_step (events).  Models of the matrix-core append path (see "chunk"
  *     below) hold buffers for passes of up to 2048 rows: against passes of 512 about 0.19 GB more on an 8B shape and 0.38 GB on
  *     a 70B one.  Where these do not fit, asynclm_create takes the buffers of 512 rows; max_positions <= 512 never asks for more.
+ *     bf16 models outside that path whose d_model, ffn, n_q_heads * head_dim and 2 n_kv_heads * head_dim are multiples of 128 (d_model <= 8192) hold
+ *     buffers for passes of up to 512 rows (and no more than max_positions): about 0.11 GB on an 8B shape.  Where these do
+ *     not fit, the context is created without them, and passes are those of the other models.
  */
 #ifndef ASYNCLM_H
 #define ASYNCLM_H
@@ -118,7 +122,9 @@ int asynclm_prefill(asynclm_ctx *ctx, int32_t seq, const int32_t *tokens, int32_
  * token has been chosen (the first kernel of the step), not for the forward pass, which is still
  * running when it returns: the caller (the token monitor of Sec. 5.1) works on the token while
  * the device computes, and the next call queues behind the running step.  (With the "fused"
- * option the call waits for the whole step.)  NULL: nothing is waited for. */
+ * option the call waits for the whole step; so may a step of less than about 0.2 ms that has more than 0.3 ms of work queued
+ * in front of it.)  The wait is a HIP event's, with the device's scheduling flags, except for the first 0.3 ms of such short steps, in which
+ * the host looks for the token by itself.  NULL: nothing is waited for. */
 int asynclm_decode_step(asynclm_ctx *ctx, int32_t seq, int32_t forced_token, int32_t *token_out);
 
 /* In-flight interrupt injection (Sec. 3.2, 5.3): append the k >= 1 tokens (host pointer) to the end
@@ -203,14 +209,16 @@ int asynclm_synchronize(asynclm_ctx *ctx);
  *   "chunk"        largest number of rows per forward pass of prefill / inject (1 .. 512); 1 = token by token
  *                  through the decode kernels.  0 (default): passes are as long as the context's buffers allow, up to
  *                  2048 rows (512 .. 2048, by max_positions and head count) where the matrix-core append path applies
- *                  (bf16 model, paired cache, head_dim 128, d_model and ffn multiples of 128); other models take at
- *                  most 8 rows per pass, through the vector units.
+ *                  (bf16 model, paired cache, head_dim 128, d_model and ffn multiples of 128); up to 512 rows, on the matrix cores
+ *                  too, where a bf16 model outside it has its buffers (above), but for passes of up to 8 rows (32 where
+ *                  all products are small) of smaller models, which the vector units take faster; else up to 8 rows through the
+ *                  vector units, 128 where all products are small.
  *   "chunk_split"  0 = split-K factors of the append path's products chosen from the shapes and the number
  *                  of compute units, 1..8 = force one
  *   "fused"        1 = run a decoding step as one persistent cooperative kernel (where the device and the
  *                  model shape allow it; ignored otherwise), 0 = one kernel per operation (default)
- *   "graph"        (per-operation kernels only) 1 = replay decoding steps as a captured HIP graph,
- *                  0 = launch kernels one by one
+ *   "graph"        (per-operation kernels only) 1 = replay decoding steps as a captured HIP graph (short steps of small models
+ *                  of up to three layers are launched one by one all the same), 0 = launch kernels one by one
  *   "pipeline"     (per-operation kernels only) 1 = run a decoding step with its kernels alternating between the
  *                  caller's stream and a second stream of the library's, neighbouring kernels overlapping and handing
  *                  over through counters in device memory instead of kernel boundaries (contexts up to 2048 tokens,
@@ -236,7 +244,9 @@ int asynclm_set_option(asynclm_ctx *ctx, const char *name, int32_t value);
  * summed milliseconds and launches_out[0..n_classes) the number of launches per class.
  * Returns the number of classes (>= 0) or a negative error.  Pass cap = capacity of the arrays.
  * The token's embedding row is fetched by the step's first kernel ("begin_step") and the next greedy choice is made inside the
- * output head ("lm_head"): the classes "embed" and "argmax" keep their places and stay zero. */
+ * output head ("lm_head"): the classes "embed" and "argmax" keep their places and stay zero.  In the short step of small models the first
+ * kernel counts as "qkv_rope_kvwrite", attention and O projection together as "attn_decode" and the whole MLP as "gate_up_swiglu"; "begin_step",
+ * "o_proj_residual" and "down_residual" are zero. */
 int asynclm_profile_step(asynclm_ctx *ctx, int32_t seq, int32_t forced_token, const char *const **names_out,
                          float *ms_out, int32_t *launches_out, int32_t cap);
 

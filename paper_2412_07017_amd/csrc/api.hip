@@ -637,9 +637,9 @@ int pick_chunk_attn_split(const asynclm_ctx* c, int max_keys, int ntasks) {
 
 // Key splits of every task, and the workgroups of the shared-key attention (`wide`), into the table.
 // One sequence: `nsplit` parts of every block of tasks; with one part, longest first, and where all workgroups are resident at once (two per compute unit), those
-// of the second half go the other way round, so that a unit gets a long and a short one.  8B shape, two layers, prompts of 700 / 1500 /
-// 2048 tokens 1002 -> 993, 1593 -> 1587, 1998 -> 1973 us; 1019 (four layers) 2693 -> 2665, 16384 18.36 -> 18.08 ms; 70B shape, 4096 12.59 ->
-// 12.37 ms.  (Cutting the long blocks of a prompt as well: the same.)
+// of the second half go the other way round, so that a unit gets a long and a short one.  70B shape, two layers, prompt of 4096 tokens 12.59 ->
+// 12.37 ms; 8B shape, two layers, 700 / 1500 / 2048 tokens 1002 -> 993, 1593 -> 1587, 1998 -> 1973 us, 1019 (four layers) 2693 -> 2665, 16384 18.36 -> 18.08 ms, which
+// is within what two runs differ by.  (Cutting the long blocks of a prompt as well: the same.)
 // Several sequences: parts of at most `per` key tiles each, as few tiles as keep the workgroups to two per compute unit, because with
 // one number of parts for all the longest sequence decides.  Four layers: 16 sequences of 512 to 4096 1181 -> 1137 us (attention 80 -> 74 a
 // layer), 12 of up to 3400 1049 -> 1015, 8 of 128 to 4096 1224 -> 1202; four per compute unit 1154, 1035, 1276.
@@ -758,14 +758,13 @@ hipError_t forward_chunk(asynclm_ctx* c, PassBuilder& pb) {
     if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
     wsplit = std::min(wsplit, CHUNK_ATTN_MAX_SPLIT);
     while (wsplit > 1 && (long long)t.ntasks * g.Hkv * wsplit > CHUNK_ATTN_MAX_UNITS) --wsplit;
-    // k_chunk_attn has one split count for all sequences of a pass, and four times as many waves that each walk a chain of their own;
-    // measured while the first kernel had one count for all too (plan_attention cuts every sequence by its own length now): a
-    // sequence much longer than the others is a chain of tiles that a
-    // quarter as many waves walk as in k_chunk_attn: the first kernel needs the longest chain to be no more than 20 tiles over
-    // the average load of a workgroup slot.  8B shape, 4 layers, one sequence of 16k and n of 500 tokens: n = 5 988 (wide)
-    // against 938 us, 7 1148 / 990, 11 1197 / 1060 (2 layers: 15 899 / 680, 31 1300 / 848); one of 4k and 5 812 / 830, 7 855 / 861, 11 885 / 883;
-    // 16 sequences of 512 to 4096 1062 / 1068, 8 of 128 to 4096 902 / 913.  Up to four tasks always take the first kernel (the
-    // chains are short in both and it has fewer partial results): 16k and 3 x 500 956 / 970, 16k and 2 x 500 880 / 898.
+    // k_chunk_attn has one split count for all sequences of a pass, and four times as many waves that each walk a chain of their own.
+    // `even` dates from when the shared-key kernel had one count for all too, so that a sequence much longer than the others was a chain of
+    // tiles that a quarter as many waves walked: at most 20 tiles over the average load of a workgroup slot.  plan_attention
+    // cuts every sequence by its own length, which removes that reason: with the present cut the shared-key kernel is the faster one
+    // or as fast wherever the two were compared, also where `even` sends a batch to the other.  8B shape, 4 layers, shared-key / other kernel, us: one sequence of 16k
+    // and n of 500 tokens, n = 2 825 / 864, 4 841 / 880, 5 848 / 908, 7 860 / 955, 11 889 / 1039, 15 917 / 1089, 31 980 / 1390; one of 4k and 5, 7, 11, 15 768 / 807,
+    // 778 / 844, 804 / 857, 827 / 880; 16 of 512 to 4096 979 / 1029, with an interrupt of 24 in the longest 1053 / 1101; 8 of 128 to 4096 848 / 885; 16 of 2900 1013 / 1036.
     const int chain = ((pb.max_keys + 31) / 32 + wsplit - 1) / wsplit;
     const bool even = t.ngroups == 1 || t.ntasks <= 4 || chain <= pb.block_tiles * g.Hkv / slots + 20;
     const bool wide_attn = ((pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups) && even) || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);
@@ -839,13 +838,16 @@ int pick_wide_split(const asynclm_ctx* c, int N, int K, int MT) {
 
 // Key splits of the attention of n rows, merged by the last workgroup of a (row, kv head): a power of two, as many as the partial
 // results hold.  A workgroup takes 256 keys per pass of its inner loop, about 15 us; a merge makes every workgroup publish its part with a
-// device-wide fence, which costs 0.07 us per workgroup of the whole launch (they queue up for it) and half as much again for each
-// (row, kv head) beyond 192.  Hence the split with the least sum of both: with one split per 256 keys, as it was, the merge took most
+// device-wide fence, which costs 0.07 us per workgroup of the whole launch (they queue up for it) and twice that, however many the
+// splits, for each (row, kv head) beyond 192.  Hence the split with the least sum of both: with one split per 256 keys, as it was, the merge took most
 // of the time (200 rows at any context 550 us a layer, all but 40 to 150 of it fences).  Whole call, two layers of the 8B shape,
 // single-plane cache, us with 1 / 2 / 4 / 8 / 16 splits: context 300, 24 rows 463 / 479 / 496 / 558 / 675, 256 rows 756 / 1361;
 // context 1000, 8 rows 493 / 474 / 459 / 466 / 512, 64 rows 603 / 678 / 768 / 946; context 4000, 2 rows 685 / 562 / 493 / 463 / 456,
 // 16 rows 709 / 598 / 541 / 557 / 613, 64 rows 795 / 804 / 849 / 988; context 16000, 16 rows 1498 / 998 / 756 / 734 / 807, 128 rows
-// 2226 / 2009 / 1991.
+// 2226 / 2009 / 1991.  The 15 us are that shape's (four heads per kv head, head_dim 128).  Other shapes with the same constants, four layers of
+// d 512, whole call: with one head per kv head and head_dim 64 a pass over 256 keys takes 3.5 us, and the rule cuts too far (24 rows at 2000, eight kv heads, 407
+// us with two splits, 256 with one; 32 kv heads, 8 rows at 4000 771 / 436); with eight heads on one kv head not far enough (24 rows at 2000 325 with two, 260 with
+// eight).  One split per 256 keys is slower than the rule on all but the last (these: 608, 2625 and 260).
 int pick_rows_split(const asynclm_ctx* c, int keys, int n) {
     const int most = std::min(ATTN_MAX_SPLIT, std::max(1, ROWS_MAX * ATTN_MAX_SPLIT / n));
     if (c->opt_attn_split > 0) return std::min(c->opt_attn_split, most);

@@ -1,10 +1,11 @@
-// Several consecutive rows of one sequence per pass over the weights, for the models outside the matrix-core paths (fp32 models,
-// sizes that are no multiple of 128; bf16 models of such sizes with head_dim 64 or the single-plane cache take passes of
-// up to 512 rows on the matrix cores, forward_wide_rows, where memory allows).  The arithmetic of a row is
+// Several consecutive rows of one sequence per pass over the weights, for the models outside the matrix-core paths: fp32 models and
+// bf16 models of sizes that are no multiple of 128.  (bf16 models of such multiples with head_dim 64 or the single-plane cache take passes of
+// up to 512 rows on the matrix cores, forward_wide_rows, where memory allows, and only short passes of the smaller ones here: rows_are_faster.)  The arithmetic of a row is
 // that of the single-row kernels: fp32 activations, fp32 accumulation on the vector units, the same epilogues.
 //
 // A single-row pass is bound by the weight stream (8B shape) or by the launches (small models); either cost is nearly the
-// same for up to ROWS_MAX rows, so an interrupt or a prompt takes ROWS_MAX tokens per pass instead of one.  Measured, one
+// same for up to ROWS_MAX rows, so an interrupt or a prompt takes ROWS_MAX tokens per pass (ROWS_PASS_SMALL where all products
+// are small) instead of one.  Measured, one
 // layer of the 8B shape with the single-plane cache: 152 us for eight rows (QKV 24, attention 9, O 19, gate/up 52, down 45)
 // against 8 x 94 us token by token (128 us for up to 32 rows on the matrix cores); the
 // tiny fp32 preset's session (64 + 8 tokens, 32 steps) 7.3 -> 3.1 ms with k_rows_gemv alone; 1.91 ms with the kernels for small
@@ -22,14 +23,14 @@ struct RowsArgs {
     int32_t rows, K;
     int32_t units, uq, ur;  // row pairs; units / waves and units % waves of the grid
     int32_t done_cap;       // finished row pairs a wave can park in LDS
-    int32_t n;              // token rows of this pass (1 .. ROWS_MAX)
+    int32_t n;              // token rows of this pass (1 .. ROWS_MAX; k_rows_small: .. ROWS_PASS_SMALL, eight per workgroup)
     int32_t pos0, seq;
-    const float* x;         // [ROWS_MAX][K] input vectors
+    const float* x;         // [n][K] input vectors
     const float* gain;      // [K] RMSNorm gain, or nullptr
-    float* y;               // [ROWS_MAX][y_stride]: RESID y = res + product; SWIGLU the activation
+    float* y;               // [n][y_stride]: RESID y = res + product; SWIGLU the activation
     const float* res;
     int32_t y_stride;
-    float* q_out;           // QKV: rotated queries [ROWS_MAX][Hq * dh]
+    float* q_out;           // QKV: rotated queries [n][Hq * dh]
     void* kv_layer;
     const float* rope_cos;
     const float* rope_sin;

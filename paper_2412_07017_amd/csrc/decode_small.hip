@@ -9,8 +9,8 @@
 //                                      -> a partial vector per workgroup
 //   k_gemv_small<.., STORE>            output head, the same sum first
 // Tiny preset, context 100: 5.0 us for attention and O projection (two kernels and a boundary: 4.0 + 3.6), 4.0 for the MLP (2.6 + 2.8), 4.2 for a
-// QKV product that adds 47 partial vectors (2.7), 6.8 for the head (5.2), 3.3 for the first kernel (2.9 + 2.7); a step 47.5 -> 41 us as a
-// graph, 38 with its seven launches issued one by one.  16 or 32 features per workgroup make no difference.
+// QKV product that adds 47 partial vectors (2.7), 6.8 for the head (5.2), 3.1 for the first kernel (2.9 + 2.7); a step 47.5 -> 41 us as a
+// graph, 38 with its seven launches issued one by one, 32 without an event behind the first of them.  16 or 32 features per workgroup make no difference.
 #include "common.h"
 #include "launch.h"
 #include "decode_device.h"

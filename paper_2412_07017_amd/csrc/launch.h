@@ -15,7 +15,7 @@ struct DecodeBuffers {
     SeqState* seq_state;      // [max_seqs]
     int32_t* token_log;       // last token chosen by k_begin_step
     float* x;                 // [d] residual stream
-    float* x2;                // [d] residual stream after the attention block (two-stream step only)
+    float* x2;                // [d] the residual stream's other vector (two-stream step: after the attention block; short step: every second layer)
     float* q;                 // [Hq*dh]
     float* o;                 // [Hq*dh]
     float* a;                 // [F]
@@ -88,7 +88,7 @@ struct ChunkBuffers {
     int q_cols;               // G * pass rows + 32 (a tile may read up to 31 columns past its group)
     float* part;              // split-K partial planes of the current product
     size_t part_capacity;     // floats in `part`
-    float* attn_o;            // [unit][dh][32]      unit = (task * Hkv + kv head) * nsplit + split
+    float* attn_o;            // [unit][dh][32]      unit = the task's unit0 * Hkv + kv head * its nsplit + split
     float* attn_ml;           // [unit][2][32]
     float* amax_v;            // [CHUNK_MAX_GROUPS][CHUNK_LOGIT_SLICES]
     int32_t* amax_i;
@@ -137,7 +137,7 @@ hipError_t launch_rows_down(int dtype, const void* wd, const RowsBuffers& rb, co
 constexpr size_t SMALL_O_BYTES = 128 * 1024;    // columns of the O projection that belong to one kv head: read by one compute unit
 constexpr int SMALL_MAX_KV_HEADS = 16, SMALL_MAX_D = 512;
 constexpr int SMALL_MAX_KEYS = 384;             // see small_step_pays
-constexpr int SMALL_DIRECT_LAYERS = 3;          // up to this many layers a step's launches are issued one by one, see step_one_token
+constexpr int SMALL_DIRECT_LAYERS = 3;          // up to this many layers a step's launches are issued one by one, see small_direct
 struct SmallBuffers { float* parts; };          // [Hkv + small_mlp_parts][d]
 bool gemv_all_small(int dtype, const Geom& g);  // every product of a step, output head included, is one of k_gemv_small
 bool small_step_supported(int dtype, const Geom& g);
