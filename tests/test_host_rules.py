@@ -371,6 +371,24 @@ print(json.dumps([[l[1] for l in ls if "k_chunk_attn_wide" in l[0]], list(buf)[:
     assert max(-(-t // k) for t, k in zip(tiles, splits)) == max(map(part, range(nblocks)))
 
 
+# ... and found in a few looks: the host's part of a batched step of 120 long sequences is a few times that of 16, not seven times
+def test_cut_of_many_long_sequences_costs_the_host_little(host):
+    few, many = host('''
+import time
+out = []
+for n in (16, 120):
+    lm = context(16600, n, d_model=1024, n_q_heads=32, n_kv_heads=8, ffn=1024)
+    for s in range(n): lm.prefill(s, tokens(16000))
+    ts = []
+    for _ in range(30):
+        t = time.perf_counter(); lm.step_batch(range(n), forced=[1] * n, want_tokens=False); ts.append(time.perf_counter() - t)
+    out.append(min(ts))
+    lm.close()
+print(json.dumps(out))
+''')
+    assert many <= 4 * few
+
+
 def test_attention_of_a_prompt_has_a_workgroup_per_block(host):
     assert host('''
 lm = context(2100, d_model=4096, n_q_heads=32, n_kv_heads=8, ffn=1024)
