@@ -491,24 +491,23 @@ __device__ __forceinline__ void advance(Cursor& c, int KT) {
 }
 
 // Requests tile (c.u, c.kt): rows (rA, rB) of the unit, k-steps 4 kt .. 4 kt + 3.  Past the end of the
-// wave's range the last tile is requested again (a cache hit); addresses always stay inside W.
+// wave's range, or of a row, nothing is fetched (weight_run).
 template <typename WT, int EPI>
 __device__ __forceinline__ void tile_load_w(Slot& sl, const Phase<WT>& p, const Cursor& c, int lane, const Geom& g) {
     uint4 (&v)[8] = sl.v;
-    constexpr int EPL = Elem<WT>::EPL;
     const bool past = c.u >= p.u1;
-    const int u = past ? max(min(p.u1, p.units) - 1, 0) : c.u;
-    int kt = (past ? p.KT - 1 : c.kt) + p.rot;
+    const int u = past ? 0 : c.u;
+    int kt = c.kt + p.rot;
     kt = kt >= p.KT ? kt - p.KT : kt;
     int rA, rB;
     unit_rows<EPI>(u, p.rows, g, rA, rB);
-    const WT* pa = p.W + (size_t)rA * p.K;
-    const WT* pb = p.W + (size_t)rB * p.K;
+    const uint32_t bytes = past ? 0u : (uint32_t)(p.Kg * 16);
+    const __amdgpu_buffer_rsrc_t ra = weight_run(p.W + (size_t)rA * p.K, bytes), rb = weight_run(p.W + (size_t)rB * p.K, bytes);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        const int gi = min((kt * 4 + s) * 64 + lane, p.Kg - 1);
-        v[2 * s] = load16_stream(pa + (size_t)gi * EPL);
-        v[2 * s + 1] = load16_stream(pb + (size_t)gi * EPL);
+        const uint32_t off = (uint32_t)(((kt * 4 + s) * 64 + lane) * 16);
+        v[2 * s] = load16_run(ra, off);
+        v[2 * s + 1] = load16_run(rb, off);
     }
 }
 

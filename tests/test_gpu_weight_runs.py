@@ -1,0 +1,64 @@
+"""The streaming kernels request weights past the end of a wave's share; those requests are dropped by the loads' range check.  Rows that end
+inside a tile of columns, waves without rows and with fewer tiles than the ring holds, against the oracle; and matrices that start at any
+multiple of their element size give the same bits as aligned ones, because the same kernels run."""
+import numpy as np
+import pytest
+import torch
+
+import asynclm_inputs as ai
+from asynclm_inputs.configs import ModelConfig
+from oracle import asynclm_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+# name, model, largest error allowed relative to the largest logit: as in test_gpu_tiny (fp32 sums) and test_gpu_shapes (bf16 pairs in the cache)
+MODELS = [
+    ("bf16 rows of 257 pieces", ModelConfig(2, 2056, 4, 2, 64, 1000, 520, 1e-5, 10000.0, "bf16"), 2e-4),
+    ("bf16 head_dim 128, three tiles a row", ModelConfig(1, 4616, 2, 2, 128, 264, 1030, 1e-5, 10000.0, "bf16"), 2e-4),
+    ("fp32 rows of 258 pieces", ModelConfig(2, 1032, 4, 1, 64, 2504, 301, 1e-5, 10000.0, "fp32"), 1e-5),
+]
+
+
+def _stream(model, w, toks):
+    import paper_2412_07017_amd as pkg
+    lm = pkg.AsyncLM(model, w, max_positions=64, stream=torch.cuda.Stream())
+    lm.prefill(0, toks[:1])
+    out = [lm.logits(0)]
+    for t in toks[1:]:
+        lm.decode_step(0, forced_token=int(t))
+        out.append(lm.logits(0))
+    lm.close()
+    return out
+
+
+@pytest.mark.parametrize("name,model,rel", MODELS, ids=[m[0] for m in MODELS])
+def test_rows_that_end_inside_a_tile(name, model, rel):
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 971, 6, model.vocab)]
+    conv = lambda t: t.detach().to("cpu").to(torch.float32).numpy()
+    dec = orc.CachedDecoder(orc.Shape.of(model), {k: ([conv(t) for t in v] if isinstance(v, list) else conv(v)) for k, v in w.items()}, dtype=np.float64)
+    got = _stream(model, w, toks)
+    dec.prefill(toks[:1])
+    for i, g in enumerate(got):
+        if i:
+            dec.inject(toks[i:i + 1])
+        assert np.abs(g - dec.logits).max() <= rel * np.abs(dec.logits).max(), (name, i)
+
+
+@pytest.mark.parametrize("elems", [1, 2, 4])
+@pytest.mark.parametrize("name,model,rel", MODELS[::2], ids=[m[0] for m in MODELS[::2]])
+def test_matrices_at_any_multiple_of_their_element_size(name, model, rel, elems):
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+
+    def moved(t):
+        flat = torch.empty(t.numel() + elems, dtype=t.dtype, device=t.device)
+        flat[elems:] = t.reshape(-1)
+        return flat[elems:].view(t.shape)
+
+    shifted = {k: ([moved(t) for t in v] if isinstance(v, (list, tuple)) else moved(v)) if "norm" not in k else v for k, v in w.items()}
+    torch.cuda.synchronize()
+    assert shifted["wdown"][0].data_ptr() % 16 == elems * w["wdown"][0].element_size() % 16
+    toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 972, 4, model.vocab)]
+    for a, b in zip(_stream(model, w, toks), _stream(model, shifted, toks)):
+        assert np.array_equal(a, b)
