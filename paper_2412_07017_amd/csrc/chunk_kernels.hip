@@ -448,15 +448,22 @@ constexpr int GEMM_RING = 4;        // weight tiles per wave in the register rin
 
 template <int PL> struct BStage { uint4 v[2 * PL]; };
 
-__device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* wlane, size_t wstep, int blk) {
+// Block `blk` of a wave's weight tile, row q of the lane = tile row 4 q + lane / 16: rows 0..15 start at w0, rows 16..31 at w1 (both the same
+// for the whole wave), off[q] is the lane's byte offset from there.  Not `live` (past the end of the run): zeros, nothing is fetched.
+struct WeightTile { const bf16_t *w0, *w1; uint32_t off[8]; };
+__device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const WeightTile& t, int blk, bool live) {
+    const uint32_t bytes = live ? 0xffffffffu : 0u, base = live ? (uint32_t)blk * 256 : 0u;
+    const __amdgpu_buffer_rsrc_t r0 = weight_run(t.w0, bytes), r1 = weight_run(t.w1, bytes);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = load16_stream(wlane + (size_t)blk * 128 + q * wstep);
+    for (int q = 0; q < 8; ++q) a[q] = load16_run(q < 4 ? r0 : r1, t.off[q], base);
 }
-
-// The same tile from eight rows of the lane's own choice (row q of the lane = tile row 4 q + lane / 16).
-__device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const bf16_t* const (&wrow)[8], int blk) {
+// 32 consecutive rows of K columns from w on
+__device__ __forceinline__ WeightTile weight_tile(const bf16_t* w, int K, int lane) {
+    WeightTile t;
+    t.w0 = t.w1 = w;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = load16_stream(wrow[q] + (size_t)blk * 128);
+    for (int q = 0; q < 8; ++q) t.off[q] = (uint32_t)(4 * q + (lane >> 4)) * (uint32_t)K * 2 + (lane & 15) * 16;
+    return t;
 }
 
 // thread tid stages chunks tid and tid + 256 of the 512 16-byte chunks of each 8 KiB plane tile
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
                                                     float* __restrict__ P, size_t s_stride, int n_stride, int S,
                                                     bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2, int rp) {
     extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][PL][512] activation tiles
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint4* at = gemm_lds + wave * 512;
     uint4* bt = gemm_lds + 2048;
     constexpr int BT = PL * 512;                    // chunks in one activation buffer
@@ -555,16 +562,12 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
     const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S), b1 = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S);   // (K / 128) * S < 2^31
     const int nb = b1 - b0;
 
-    const bf16_t* wlane = W + (size_t)(SWIGLU ? 0 : n0 + (lane >> 4)) * K + (lane & 15) * 8;   // row l/16 (+4q), chunk l%16
-    const size_t wstep = (size_t)4 * K;
-    const bf16_t* wrow[8];
+    WeightTile wt = weight_tile(W + (SWIGLU ? 0 : (size_t)n0 * K), K, lane);
     if (SWIGLU) {
         const int g0 = min(n0, (N >> 1) - 1);
+        wt.w0 = W + (size_t)g0 * K; wt.w1 = W + (size_t)((N >> 1) + g0) * K;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int slot = 4 * (q & 3) + (lane >> 4);
-            wrow[q] = wlane + (size_t)((q < 4 ? 0 : N >> 1) + g0 + min(slot, max(nr, 1) - 1)) * K;
-        }
+        for (int q = 0; q < 8; ++q) wt.off[q] = (uint32_t)min(4 * (q & 3) + (lane >> 4), max(nr, 1) - 1) * (uint32_t)K * 2 + (lane & 15) * 16;
     }
     const bf16_t* x[PL];
     x[0] = Xhi + tid * 8; x[1] = Xlo + tid * 8;
@@ -592,10 +595,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
         gemm_b_load<PL>(st[1], x, blk(1));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < RING - 1; ++u) {
-            if (SWIGLU) gemm_a_load(ring[u], wrow, blk(u));
-            else gemm_a_load(ring[u], wlane, wstep, blk(u));
-        }
+        for (int u = 0; u < RING - 1; ++u) gemm_a_load(ring[u], wt, blk(u), u < nb);
         gemm_b_store<PL>(st[0], bt, tid, true);
         __syncthreads();
         static_assert(RING % 2 == 0, "ring slot (u % RING) and activation buffer (u & 1) are static");
@@ -605,8 +605,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
                 const int tt = t + u;                       // this block of the walk
                 gemm_b_load<PL>(st[u & 1], x, blk(tt + 2));
                 __builtin_amdgcn_sched_barrier(0);
-                if (SWIGLU) gemm_a_load(ring[(u + RING - 1) % RING], wrow, blk(tt + RING - 1));
-                else gemm_a_load(ring[(u + RING - 1) % RING], wlane, wstep, blk(tt + RING - 1));
+                gemm_a_load(ring[(u + RING - 1) % RING], wt, blk(tt + RING - 1), tt + RING - 1 < nb);
                 __builtin_amdgcn_sched_barrier(0);
                 gemm_tile_mma<PL>(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
                 __builtin_amdgcn_sched_barrier(0);
@@ -711,7 +710,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
                                                              bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]
     constexpr int QN = 8;                           // weight loads per thread and block: wave w stages rows 32 w ...
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = N >> 7;
     int q0 = blockIdx.x, my = 0;
     if (PL == 3) {
@@ -726,14 +725,13 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
     const int n0 = ntile * 128;
 
     // weights: load q of a thread covers row 32 wave + 4 q + lane / 16 of the tile, 16-byte chunk lane % 16
-    const bf16_t* wq[QN];
+    const int wrow = SWIGLU ? (wave < 2 ? 0 : N >> 1) + ntile * 64 + (wave & 1) * 32 : n0 + wave * 32;
+    const WeightTile wt = weight_tile(W + (size_t)wrow * K, K, lane);
     int wslot[QN];
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
-        const int rg = wave * 32 + 4 * q + (lane >> 4), r = rg & 31, c = lane & 15;
-        const int row = SWIGLU ? (rg < 64 ? ntile * 64 + rg : (N >> 1) + ntile * 64 + rg - 64) : n0 + rg;
-        wq[q] = W + (size_t)row * K + c * 8;
-        wslot[q] = (rg >> 5) * 512 + r * 16 + (c ^ (r & 15));
+        const int r = 4 * q + (lane >> 4), c = lane & 15;
+        wslot[q] = wave * 512 + r * 16 + (c ^ (r & 15));
     }
     // activations: a row tile per wave; waves past the last tile repeat it and store nothing
     const size_t xo = (size_t)min(mtile, MT - 1) * nblk * 4096 + lane * 8;
@@ -755,10 +753,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
     if (nb > 0) {
         uint4 wreg[QN];
         BUnit<1, PL> ring[4];
-        auto w_load = [&](int blk) {
-#pragma unroll
-            for (int q = 0; q < QN; ++q) wreg[q] = load16_stream(wq[q] + (size_t)blk * 128);
-        };
+        auto w_load = [&](int blk) { gemm_a_load(wreg, wt, blk, blk <= last); };
         auto w_store = [&](uint4* at) {
 #pragma unroll
             for (int q = 0; q < QN; ++q) at[wslot[q]] = wreg[q];
@@ -770,7 +765,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
         for (int u = 0; u < 3; ++u) wide_b_load<1, PL>(ring[u], x, b0, u);
         __builtin_amdgcn_sched_barrier(0);
         w_store(gemm_lds);
-        w_load(min(b0 + 1, last));
+        w_load(b0 + 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         for (int t = 0; t < nb; t += 2) {
@@ -796,7 +791,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
                         // the next block's weights (requested one block ago) move to the other LDS buffer, whose
                         // readers passed the barrier that ended the previous block; then the block after is requested
                         w_store(gemm_lds + (h ^ 1) * 2048);
-                        w_load(min(tt + 2, last));
+                        w_load(tt + 2);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     wide_a_read(a1, at, 2 * u + 1, lane);
@@ -1110,7 +1105,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                                                        float* __restrict__ P, size_t s_stride, int n_stride, int S,
                                                        bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]; reused by the final sum
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntile = blockIdx.x, sp = blockIdx.y;
     const int nblk = K >> 7;
     const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S), b1 = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S);   // (K / 128) * S < 2^31
@@ -1119,8 +1114,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
 
     // weights: load q of a thread covers row 32 wave + 4 q + lane / 16 of the tile, 16-byte chunk lane % 16
     const int wrow = SWIGLU ? (wave < 2 ? ntile * 64 + wave * 32 : (N >> 1) + ntile * 64 + (wave - 2) * 32) : n0 + wave * 32;
-    const bf16_t* wlane = W + (size_t)(wrow + (lane >> 4)) * K + (lane & 15) * 8;
-    const size_t wstep = (size_t)4 * K;
+    const WeightTile wt = weight_tile(W + (size_t)wrow * K, K, lane);
     const int wr0 = lane >> 4, wc = lane & 15;
     const bf16_t* x[MT][2];
 #pragma unroll
@@ -1148,7 +1142,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
         constexpr int NSET = 2, RING = 3, UNROLL = 6;   // LDS buffer u % 2 and ring slot u % RING are static
         uint4 wreg[NSET][8];
         BUnit<MT> ring[RING];
-        auto w_load = [&](uint4 (&set)[8], int blk) { gemm_a_load(set, wlane, wstep, blk); };
+        auto w_load = [&](uint4 (&set)[8], int i) { gemm_a_load(set, wt, blk(i), i < nb); };      // block i of the walk
         auto w_store = [&](const uint4 (&set)[8], uint4* at) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
@@ -1157,13 +1151,13 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
             }
         };
         // issue order = completion order: weights of the first block, activations of the first two, weights of the second
-        w_load(wreg[0], blk(0));
+        w_load(wreg[0], 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < RING - 1; ++i) wide_b_load<MT, 2>(ring[i], x, blk(i), wave);
         __builtin_amdgcn_sched_barrier(0);
         w_store(wreg[0], gemm_lds);
-        w_load(wreg[NSET - 1], blk(1));
+        w_load(wreg[NSET - 1], 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         for (int t = 0; t < nb; t += UNROLL) {
@@ -1175,7 +1169,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                 uint4* other = gemm_lds + ((u & 1) ^ 1) * 2048;   // its readers passed the barrier that ended the previous block
                 wide_b_load<MT, 2>(ring[(u + RING - 1) % RING], x, blk(tt + RING - 1), wave);
                 __builtin_amdgcn_sched_barrier(0);
-                w_load(wreg[u & 1], blk(tt + 2));           // this set's previous block was stored one block ago
+                w_load(wreg[u & 1], tt + 2);           // this set's previous block was stored one block ago
                 __builtin_amdgcn_sched_barrier(0);
                 uint4 a0[4], a1[4];
                 wide_a_read(a0, at, 2 * wave, lane);

@@ -128,7 +128,7 @@ __device__ __forceinline__ uint4 load16(const void* p) {
 // a load that may or may not happen makes the compiler wait for all of them; with the last tile in their place (streaming loads leave
 // no lines behind, so it came from memory again) the gate/up product of the 8B shape fetched 243 instead of 235 MB in a decoding step.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_run(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 __device__ __forceinline__ uint4 load16_run(__amdgpu_buffer_rsrc_t run, uint32_t offset, uint32_t base = 0) {
     constexpr int STREAM = 2;                   // as load16_stream

@@ -62,3 +62,38 @@ def test_matrices_at_any_multiple_of_their_element_size(name, model, rel, elems)
     toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 972, 4, model.vocab)]
     for a, b in zip(_stream(model, w, toks), _stream(model, shifted, toks)):
         assert np.array_equal(a, b)
+
+
+# rows of a pass: one tile (weight stream), two (k-split), three and four (a wave per row tile); d and ffn leave runs of one block and of unequal length
+@pytest.mark.parametrize("dh,kv", [(128, 0), (128, 1)], ids=["paired cache", "single plane"])
+def test_products_of_several_rows_at_any_multiple_of_the_element_size(dh, kv):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(2, 640, 4, 2, dh, 1408, 512, 1e-5, 10000.0, "bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    conv = lambda t: t.detach().to("cpu").to(torch.float32).numpy()
+    host = {k: ([conv(t) for t in v] if isinstance(v, list) else conv(v)) for k, v in w.items()}
+
+    def moved(t):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.reshape(-1)
+        return flat[1:].view(t.shape)
+
+    shifted = {k: ([moved(t) for t in v] if isinstance(v, (list, tuple)) else moved(v)) if "norm" not in k else v for k, v in w.items()}
+    torch.cuda.synchronize()
+    toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 973, 260, model.vocab)]
+    cuts = [0, 23, 63, 147, 258, 260]
+    got = []
+    for ws in (w, shifted):
+        lm = pkg.AsyncLM(model, ws, max_positions=300, stream=torch.cuda.Stream(), kv_format=kv)
+        out = []
+        for a, b in zip(cuts, cuts[1:]):
+            (lm.prefill if a == 0 else lm.inject_interrupt)(0, toks[a:b])
+            out.append(lm.logits(0))
+        lm.close()
+        got.append(out)
+    dec = orc.CachedDecoder(orc.Shape.of(model), host, dtype=np.float32)
+    for i, (a, b) in enumerate(zip(cuts, cuts[1:])):
+        assert np.array_equal(got[0][i], got[1][i]), (a, b)
+        if kv == 0:                             # (a single plane rounds keys and values, which the oracle here does not)
+            (dec.prefill if a == 0 else dec.inject)(toks[a:b])
+            assert np.abs(got[0][i] - dec.logits).max() <= 2e-4 * np.abs(dec.logits).max(), (a, b)
