@@ -285,8 +285,7 @@ __device__ __forceinline__ float4 as_float4(const uint4& v) {
 
 // Stages K elements into the planar LDS layout (plane p of group grp holds elements 4p..4p+3 of the group of
 // EPL elements; planes are plane_stride float4 apart) and returns the sum of squares of the unscaled vector
-// (valid after the trailing __syncthreads).  With `pad`, groups [Kg, 256 KT) and the last 64 groups of each
-// plane are zero-filled.
+// (valid after the trailing __syncthreads).  With `pad`, groups [Kg, 256 KT) are zero-filled.
 // All loads of a batch are issued before the first is used.
 template <typename WT, int NB = 4>
 __device__ __forceinline__ float stage_vector(float4* xs, int plane_stride, const VecSource& src, int K, int Kg, int KT,
@@ -375,11 +374,8 @@ __device__ __forceinline__ float stage_vector(float4* xs, int plane_stride, cons
         for (int grp = Kg + tid; grp < KT * 256; grp += 256)
 #pragma unroll
             for (int pl = 0; pl < NP; ++pl) xs[pl * plane_stride + grp] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (tid < 64)
-#pragma unroll
-            for (int pl = 0; pl < NP; ++pl) xs[pl * plane_stride + plane_stride - 64 + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    ss = wave_sum(ss);
+    ss = wave_sum_all(ss);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
     return red[0] + red[1] + red[2] + red[3];
@@ -414,9 +410,6 @@ __device__ __forceinline__ float early_stage(const EarlyBatch<NB, GAIN>& b, floa
     if (Kg + tid < KT * 256)
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl) xs[pl * plane_stride + Kg + tid] = zero;
-    if (tid < 64)
-#pragma unroll
-        for (int pl = 0; pl < NP; ++pl) xs[pl * plane_stride + plane_stride - 64 + tid] = zero;
     float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -429,7 +422,7 @@ __device__ __forceinline__ float early_stage(const EarlyBatch<NB, GAIN>& b, floa
             xs[pl * plane_stride + grp] = v;
         }
     }
-    ss = wave_sum(ss);
+    ss = wave_sum_all(ss);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
     return red[0] + red[1] + red[2] + red[3];
@@ -571,21 +564,28 @@ __device__ __forceinline__ void finish_unit(int u, float sa, float sb, float e0,
     }
 }
 
-// Multiplies one tile with the staged vector.  xs: planar LDS copy of x (plane p holds elements
-// 4p..4p+3 of every group of EPL), zero beyond Kg; tiles past the end read a block of zeros.
+// The lane's elements of the staged vector for one tile of columns.  xs: planar LDS copy of x (plane p holds elements
+// 4p..4p+3 of every group of EPL), zero beyond Kg.
 template <typename WT>
-__device__ __forceinline__ void tile_fma(const uint4 (&v)[8], const float4* xs, int plane_stride, int zero_group,
-                                         bool past, int kt, int lane, float& accA, float& accB) {
+struct TileX { float4 v[4][Elem<WT>::EPL / 4]; };
+
+template <typename WT>
+__device__ __forceinline__ void tile_x(TileX<WT>& x, const float4* xs, int plane_stride, int kt, int lane) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int pl = 0; pl < Elem<WT>::EPL / 4; ++pl) x.v[s][pl] = xs[pl * plane_stride + (kt * 4 + s) * 64 + lane];
+}
+
+template <typename WT>
+__device__ __forceinline__ void tile_fma(const uint4 (&v)[8], const TileX<WT>& x, float& accA, float& accB) {
     constexpr int EPL = Elem<WT>::EPL;
-    constexpr int NP = EPL / 4;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        const int gi = past ? zero_group + lane : (kt * 4 + s) * 64 + lane;
         float xv[EPL], wa[EPL], wb[EPL];
 #pragma unroll
-        for (int pl = 0; pl < NP; ++pl) {
-            const float4 t = xs[pl * plane_stride + gi];
-            xv[4 * pl] = t.x; xv[4 * pl + 1] = t.y; xv[4 * pl + 2] = t.z; xv[4 * pl + 3] = t.w;
+        for (int pl = 0; pl < EPL / 4; ++pl) {
+            xv[4 * pl] = x.v[s][pl].x; xv[4 * pl + 1] = x.v[s][pl].y; xv[4 * pl + 2] = x.v[s][pl].z; xv[4 * pl + 3] = x.v[s][pl].w;
         }
         Elem<WT>::expand(v[2 * s], wa);
         Elem<WT>::expand(v[2 * s + 1], wb);
@@ -635,27 +635,35 @@ __device__ __forceinline__ void phase_prefetch_e(Slot (&ring)[RING], const Phase
 // their global stores, run after the loop, one unit per lane.  Keeping every global memory instruction
 // of the loop unconditional lets the compiler count the outstanding loads exactly, so a tile is waited
 // for while the three younger ones stay in flight.
+// What a tile costs its wave beyond the stream is the tail of every product: its last RING tiles arrive together.  So the vector's part comes from
+// LDS one tile ahead, sums over the wave are lane exchanges of the adds, and tiles past the end are not multiplied (with LDS reads in a chain,
+// shuffles and such tiles multiplied with zeros, 8B shape: gate/up 39.5 -> 38.5 us, down 22.9 -> 21.6, QKV 13.5 -> 12.0, O 9.5 -> 8.9, head 160 -> 155.5).
 // best_v / best_i: argmax of the stored values (EPI_STORE only), valid in every lane afterwards.
 template <typename WT, int EPI>
 __device__ __forceinline__ void phase_run(Slot (&ring)[RING], const Phase<WT>& p, Cursor& lc, const float4* xs,
                                           int plane_stride, float nscale, const EpiOut& eo, const Geom& g, int lane,
                                           float4* done, float& best_v, int& best_i) {
-    const int zero_group = plane_stride - 64;
     const int T = (p.u1 - p.u0) * p.KT;
     Cursor cc; cc.u = p.u0; cc.kt = 0;
     float accA = 0.f, accB = 0.f;
+    auto tile_at = [&](int kt) { const int k = kt + p.rot; return k >= p.KT ? k - p.KT : k; };      // the tile of columns that was requested
+    TileX<WT> x[2];
+    tile_x(x[0], xs, plane_stride, tile_at(0), lane);
     for (int t = 0; t < T; t += RING) {
 #pragma unroll
         for (int j = 0; j < RING; ++j) {
-            const bool past = cc.u >= p.u1;
-            const int ktp = cc.kt + p.rot >= p.KT ? cc.kt + p.rot - p.KT : cc.kt + p.rot;      // the tile that was requested
-            tile_fma<WT>(ring[j].v, xs, plane_stride, zero_group, past, ktp, lane, accA, accB);
-            // The slot's epilogue operands are parked before the slot is requested again: read after the request
-            // they would have to be copied aside when the loop rotates, and the copy waits for every load in flight.
-            if (!past && cc.kt == p.KT - 1) {
-                const float sa = wave_sum(accA) * nscale, sb = wave_sum(accB) * nscale;
-                if (lane == 0) done[cc.u - p.u0] = make_float4(sa, sb, ring[j].e0, ring[j].e1);
-                accA = 0.f; accB = 0.f;
+            // the vector's part for the next tile comes from LDS while this tile is waited for and multiplied
+            tile_x(x[(j + 1) & 1], xs, plane_stride, tile_at(cc.kt + 1 == p.KT ? 0 : cc.kt + 1), lane);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t + j < T) {                                                                        // uniform; no memory access inside
+                tile_fma<WT>(ring[j].v, x[j & 1], accA, accB);
+                // The slot's epilogue operands are parked before the slot is requested again: read after the request
+                // they would have to be copied aside when the loop rotates, and the copy waits for every load in flight.
+                if (cc.kt == p.KT - 1) {
+                    const float sa = wave_sum_all(accA) * nscale, sb = wave_sum_all(accB) * nscale;
+                    if (lane == 0) done[cc.u - p.u0] = make_float4(sa, sb, ring[j].e0, ring[j].e1);
+                    accA = 0.f; accB = 0.f;
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
             tile_load<WT, EPI>(ring[j], p, lc, lane, g, eo);

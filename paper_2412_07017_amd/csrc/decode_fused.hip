@@ -365,13 +365,13 @@ static fused_kernel_t pick_kernel(int dtype, const Geom& g) {
     return nullptr;
 }
 
-// LDS bytes: the staged vector (largest K of any phase, padded to whole tiles plus a block of zeros),
+// LDS bytes: the staged vector (largest K of any phase, padded to whole tiles),
 // which the attention phases reuse, then per wave one float4 per unit of its largest phase.
 static size_t fused_lds_bytes(int dtype, const Geom& g, int grid, int* xs_groups, int* done_cap) {
     const int epl = dtype == 0 ? 4 : 8;
     const int kmax = std::max(std::max(g.d, g.F), g.Hq * g.dh);
     const int kg = kmax / epl, kt = (kg + 255) / 256;
-    *xs_groups = kt * 256 + 64;
+    *xs_groups = kt * 256;
     size_t bytes = (size_t)(*xs_groups) * epl * sizeof(float);
     const int G = g.Hq / g.Hkv, ppw = 64 / (g.dh / epl);
     const size_t attn = sizeof(float) * (size_t)(ATTN_CHUNK * G + 4 * G + 4 * ppw * G * g.dh);

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
         __builtin_amdgcn_sched_barrier(0);
     }
     Phase<WT> ph = make_phase_split<WT, EPI>(a.W, a.rows, a.K, a.units, a.uq, a.ur);
-    const int plane_stride = ph.KT * 256 + 64;
+    const int plane_stride = ph.KT * 256;
     float4* done = lds4 + (size_t)plane_stride * (EPL / 4) + (size_t)wave * a.done_cap;
     Slot ring[RING];
     Cursor lc;
@@ -624,7 +624,7 @@ template <typename WT>
 static size_t gemv_lds_bytes(int K, int units, int grid, int* done_cap) {
     *done_cap = (units + grid * 4 - 1) / (grid * 4) + 1;
     const int kg = K / Elem<WT>::EPL, kt = (kg + 255) / 256;
-    return (size_t)(kt * 256 + 64) * Elem<WT>::EPL * sizeof(float) + (size_t)4 * (*done_cap) * sizeof(float4);
+    return (size_t)(kt * 256) * Elem<WT>::EPL * sizeof(float) + (size_t)4 * (*done_cap) * sizeof(float4);
 }
 
 template <typename WT, int EPI, int SRC>
@@ -695,7 +695,7 @@ hipError_t decode_init(int dtype, int max_k) {
             g_gemv_grid = cus;
     }
     // staged vector with its padding + parked units (16 KiB cover 256 units per wave), within the 160 KiB of a compute unit
-    const int bytes = std::min((max_k + 8 * 256 + 64 * 8) * (int)sizeof(float) + 16 * 1024, 160 * 1024);
+    const int bytes = std::min((max_k + 8 * 256) * (int)sizeof(float) + 16 * 1024, 160 * 1024);
     // process-wide, shared by every context: only ever raised
     if ((size_t)bytes <= g_gemv_lds_limit) return hipSuccess;
     hipError_t e;
