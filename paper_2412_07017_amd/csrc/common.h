@@ -130,9 +130,9 @@ __device__ __forceinline__ uint4 load16(const void* p) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_run(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
+template <bool STREAM = true>                   // as load16_stream, else as load16
 __device__ __forceinline__ uint4 load16_run(__amdgpu_buffer_rsrc_t run, uint32_t offset, uint32_t base = 0) {
-    constexpr int STREAM = 2;                   // as load16_stream
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(run, offset, base, STREAM));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(run, offset, base, STREAM ? 2 : 0));
 }
 __device__ __forceinline__ float load_f32(const float* p) { return *(global_f32_ptr)(uintptr_t)p; }
 
