@@ -787,30 +787,29 @@ hipError_t forward_chunk(asynclm_ctx* c, PassBuilder& pb) {
         else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, sp.down.s, MT, c->attn_norm[l], rows, g, s); }))) return e;
         if (tail && l == c->cfg.n_layers - 1) {
             const char* wkv = (const char*)c->wqkv[l] + (size_t)qd * g.d * elem_bytes(c);
-            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(wkv, 2 * g.Hkv * g.dh, g.d, cb.nrm_hi, cb.nrm_lo, cb, kv_plan, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(wkv, 2 * g.Hkv * g.dh, g.d, cb.nrm_hi, cb.nrm_lo, cb, kv_plan, rows, s); }))) return e;
             if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, kv_plan.s, kvl, c->b, rows, MT, g, s, true); }))) return e;
             if (t.nhead > 0 && (e = last_row_layer(c, l, cb.x + (size_t)(rows - 1) * g.d, pb.max_keys))) return e;
             break;
         }
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.qkv, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.qkv, rows, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_rope_kv(cb, sp.qkv.s, kvl, c->b, rows, MT, g, s); }))) return e;
         if (wide_attn) { if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn_wide(cb, kvl, t.npieces > t.nblocks, t.ntasks, t.npieces, g, s); }))) return e; }
         else if ((e = run(c, KC_CHUNK_ATTN, [&] { return launch_chunk_attn(cb, kvl, asplit, t.ntasks, g, s); }))) return e;
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb, sp.o, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb, sp.o, rows, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, sp.o.s, MT, c->ffn_norm[l], rows, g, s); }))) return e;
         if (sp.gu.s == 1) {                 // no split-K: the SwiGLU is the product's epilogue
-            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, rows, s); }))) return e;
         } else {
-            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wgate_up[l], 2 * g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wgate_up[l], 2 * g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb, sp.gu, rows, s); }))) return e;
             if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_swiglu(cb, sp.gu.s, MT, rows, g, s); }))) return e;
         }
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb, sp.down, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_chunk_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb, sp.down, rows, s); }))) return e;
     }
     const bool head_on_mfma = t.nhead > 1 && g.V % 128 == 0 && (size_t)((t.nhead + 31) / 32) * 32 * g.V <= cb.part_capacity;
     if (head_on_mfma) {
-        const int MTh = (t.nhead + 31) / 32;
         if ((e = run(c, KC_CHUNK_MISC, [&] { return launch_chunk_head_rows(cb, sp.down.s, MT, c->final_norm, t.ngroups, g, s); }))) return e;
-        if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, GemmPlan{1, 4}, MTh, s); }))) return e;
+        if ((e = run(c, KC_LMHEAD, [&] { return launch_chunk_gemm(c->lm_head, g.V, g.d, cb.nrm_hi, cb.nrm_lo, cb, GemmPlan{1, 4}, t.nhead, s); }))) return e;
         if ((e = run(c, KC_ARGMAX, [&] { return launch_chunk_logits(cb, c->logits, c->b, t.ngroups, g, s); }))) return e;
     } else if (!tail) {
         for (int gi = 0; gi < t.ngroups; ++gi) {
@@ -893,18 +892,18 @@ hipError_t forward_wide_rows(asynclm_ctx* c, int seq, const int32_t* tokens, int
         else if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, s_down, MT, c->attn_norm[l], n, g, s, 3); }))) return e;
         if (l == c->cfg.n_layers - 1) {         // as in forward_chunk: keys and values of all rows, the rest for the last row only
             const char* wkv = (const char*)c->wqkv[l] + (size_t)qd * g.d * elem_bytes(c);
-            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(wkv, nkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_kv, MT, s); }))) return e;
+            if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(wkv, nkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_kv, n, s); }))) return e;
             if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_rows_rope_kv(cb, s_kv, MT, kvl, c->rb, c->b, p, g, s, true); }))) return e;
             if (with_head && (e = last_row_layer(c, l, cb.x + (size_t)(n - 1) * g.d, p.pos0 + n))) return e;
             break;
         }
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_qkv, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wqkv[l], nqkv, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, s_qkv, n, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_rows_rope_kv(cb, s_qkv, MT, kvl, c->rb, c->b, p, g, s, false); }))) return e;
         if ((e = run(c, KC_ATTN, [&] { return launch_rows_attn(dt, kvl, nsplit, c->rb, p, g, s, &cb); }))) return e;
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb.att_lo2, cb, s_o, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wo[l], g.d, qd, cb.att_hi, cb.att_lo, cb.att_lo2, cb, s_o, n, s); }))) return e;
         if ((e = run(c, KC_CHUNK_PREP, [&] { return launch_chunk_resid_norm(cb, s_o, MT, c->ffn_norm[l], n, g, s, 3); }))) return e;
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, MT, s); }))) return e;
-        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb.act_lo2, cb, s_down, MT, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm_swiglu(c->wgate_up[l], g.F, g.d, cb.nrm_hi, cb.nrm_lo, cb.nrm_lo2, cb, n, s); }))) return e;
+        if ((e = run(c, KC_CHUNK_GEMM, [&] { return launch_wide_gemm(c->wdown[l], g.d, g.F, cb.act_hi, cb.act_lo, cb.act_lo2, cb, s_down, n, s); }))) return e;
     }
     c->len[seq] += n;
     return hipSuccess;

@@ -439,8 +439,8 @@ __global__ __launch_bounds__(256) void k_chunk_rope_kv(const float* __restrict__
 //    operand order through a wave-private XOR-swizzled LDS tile and multiplied;
 //  * the activations of a k-block (32 rows, hi and lo planes: 16 KiB) are shared by the four waves
 //    through a double-buffered LDS tile that the workgroup fills one block ahead.
-// The loop body has no conditional code around loads or their uses: the prefetches past the end of a run
-// re-read its last block (cache hits).  The compiler sinks loads into conditional users
+// The loop body has no conditional code around loads or their uses: the requests past the end of a run fetch nothing (weight_run).
+// The compiler sinks loads into conditional users
 // and then waits for each load right before its product; the scheduling barriers keep the instruction
 // scheduler from doing the same within the straight-line body.
 
@@ -450,9 +450,10 @@ template <int PL> struct BStage { uint4 v[2 * PL]; };
 
 // Block `blk` of a wave's weight tile, row q of the lane = tile row 4 q + lane / 16: rows 0..15 start at w0, rows 16..31 at w1 (both the same
 // for the whole wave), off[q] is the lane's byte offset from there.  Not `live` (past the end of the run): zeros, nothing is fetched.
-struct WeightTile { const bf16_t *w0, *w1; uint32_t off[8]; };
+// Nor is anything fetched for rows from w0 + bytes (w1 + bytes) on.
+struct WeightTile { const bf16_t *w0, *w1; uint32_t bytes, off[8]; };
 __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const WeightTile& t, int blk, bool live) {
-    const uint32_t bytes = live ? 0xffffffffu : 0u, base = live ? (uint32_t)blk * 256 : 0u;
+    const uint32_t bytes = live ? t.bytes : 0u, base = live ? (uint32_t)blk * 256 : 0u;
     const __amdgpu_buffer_rsrc_t r0 = weight_run(t.w0, bytes), r1 = weight_run(t.w1, bytes);
 #pragma unroll
     for (int q = 0; q < 8; ++q) a[q] = load16_run(q < 4 ? r0 : r1, t.off[q], base);
@@ -460,28 +461,30 @@ __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const WeightTile& t, 
 // 32 consecutive rows of K columns from w on
 __device__ __forceinline__ WeightTile weight_tile(const bf16_t* w, int K, int lane) {
     WeightTile t;
-    t.w0 = t.w1 = w;
+    t.w0 = t.w1 = w; t.bytes = 64u * (uint32_t)K;
 #pragma unroll
     for (int q = 0; q < 8; ++q) t.off[q] = (uint32_t)(4 * q + (lane >> 4)) * (uint32_t)K * 2 + (lane & 15) * 16;
     return t;
 }
 
 // thread tid stages chunks tid and tid + 256 of the 512 16-byte chunks of each 8 KiB plane tile
+// off: the thread's byte offset in a tile, past every tile (DEAD_ROW) if its row is past the pass's last one: such rows cost no traffic.  Gate/up of the
+// 8B shape with 40 rows 47.4 -> 44.6 us, 48 rows 47.2 -> 45.9, the head with 16 rows 181 -> 178.8 (with blocks past the end of a run
+// neither requested nor multiplied: 24 rows 39.6 -> 39.2, the other products 16.0 -> 15.2 on average).
+constexpr uint32_t DEAD_ROW = 0x40000000u;
 template <int PL>
-__device__ __forceinline__ void gemm_b_load(BStage<PL>& st, const bf16_t* const (&x)[PL], int blk) {
-    const size_t base = (size_t)blk * 4096;
+__device__ __forceinline__ void gemm_b_load(BStage<PL>& st, const bf16_t* const (&x)[PL], int blk, bool live, uint32_t off) {
 #pragma unroll
-    for (int p = 0; p < PL; ++p) { st.v[2 * p] = load16(x[p] + base); st.v[2 * p + 1] = load16(x[p] + base + 2048); }
+    for (int p = 0; p < PL; ++p) {
+        const __amdgpu_buffer_rsrc_t run = weight_run(x[p] + (size_t)blk * 4096, live ? 8192 : 0);
+        st.v[2 * p] = load16_run<false>(run, off); st.v[2 * p + 1] = load16_run<false>(run, off + 4096);
+    }
 }
 
 template <int PL>
-__device__ __forceinline__ void gemm_b_store(const BStage<PL>& st, uint4* buf, int tid, bool live) {
+__device__ __forceinline__ void gemm_b_store(const BStage<PL>& st, uint4* buf, int tid) {
 #pragma unroll
-    for (int h = 0; h < 2 * PL; ++h) {
-        uint4 v = st.v[h];
-        v.x = live ? v.x : 0u; v.y = live ? v.y : 0u; v.z = live ? v.z : 0u; v.w = live ? v.w : 0u;
-        buf[(h >> 1) * 512 + (h & 1) * 256 + tid] = v;
-    }
+    for (int h = 0; h < 2 * PL; ++h) buf[(h >> 1) * 512 + (h & 1) * 256 + tid] = st.v[h];
 }
 
 // Transposes the weight tile into operand order through the wave's LDS tile (32 rows x 16 chunks of
@@ -542,13 +545,13 @@ __device__ __forceinline__ void gemm_tile_mma(const uint4 (&ta)[8], f32x16& acc,
 // takes `rp` <= 16 gate rows (columns t rp .. t rp + rp - 1 of the result) into tile rows 0..rp-1 and the matching up
 // rows into tile rows 16..16+rp-1: in the accumulator layout a gate product and its up product then sit in the same
 // lane (registers 4b + r and 4(b + 2) + r), and the wave writes silu(gate) * up as hi/lo planes in operand order
-// (act_hi, act_lo; N/2 columns) without any exchange.  The tile rows beyond rp repeat row rp - 1 (cache hits, results
+// (act_hi, act_lo; N/2 columns) without any exchange.  The tile rows beyond rp are not fetched (results
 // dropped): the launcher picks rp so that the tiles divide evenly among the waves of the device (14 rows for
 // F = 14336 on 256 compute units: 1024 tiles), which a fixed 16 or 32 rows per wave would not.
 template <bool SWIGLU, int PL>
 __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W, int N, int K,
                                                     const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo, const bf16_t* __restrict__ Xlo2,
-                                                    float* __restrict__ P, size_t s_stride, int n_stride, int S,
+                                                    float* __restrict__ P, size_t s_stride, int n_stride, int S, int rows,
                                                     bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2, int rp) {
     extern __shared__ uint4 gemm_lds[];             // [4 waves][512] weight tiles, then [2][PL][512] activation tiles
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -565,13 +568,14 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
     WeightTile wt = weight_tile(W + (SWIGLU ? 0 : (size_t)n0 * K), K, lane);
     if (SWIGLU) {
         const int g0 = min(n0, (N >> 1) - 1);
-        wt.w0 = W + (size_t)g0 * K; wt.w1 = W + (size_t)((N >> 1) + g0) * K;
+        wt.w0 = W + (size_t)g0 * K; wt.w1 = W + (size_t)((N >> 1) + g0) * K; wt.bytes = 2u * (uint32_t)nr * (uint32_t)K;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) wt.off[q] = (uint32_t)min(4 * (q & 3) + (lane >> 4), max(nr, 1) - 1) * (uint32_t)K * 2 + (lane & 15) * 16;
+        for (int q = 4; q < 8; ++q) wt.off[q] = wt.off[q - 4];
     }
     const bf16_t* x[PL];
-    x[0] = Xhi + tid * 8; x[1] = Xlo + tid * 8;
-    if (PL > 2) x[PL - 1] = Xlo2 + tid * 8;
+    x[0] = Xhi; x[1] = Xlo;
+    if (PL > 2) x[PL - 1] = Xlo2;
+    const uint32_t xoff = (tid & 31) < rows ? tid * 16 : DEAD_ROW;
 
     f32x16 acc;
 #pragma unroll
@@ -582,7 +586,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
         // read column block 0 of their own rows at the same time (rows are a multiple of 8 KiB apart) load few memory
         // channels at a time, and how badly depends on where the matrix lies (measured on the gate/up product, whose
         // workgroups all start together: 42 to 52 us for the same shape at different addresses).  Block i of the
-        // walk is b0 + (i + rot) mod nb; past the end the last block is read again (a cache hit).
+        // walk is b0 + (i + rot) mod nb.
         const int rot = (int)((blockIdx.x / 8 + (blockIdx.x & 7) * 4 + blockIdx.y * 3) % (unsigned)nb);
         auto blk = [&](int i) { const int x = min(i, nb - 1) + rot; return b0 + (x >= nb ? x - nb : x); };
         // Waits are in issue order, so the activation loads of block t+2 are issued before the weight loads of
@@ -591,25 +595,25 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
         constexpr int RING = GEMM_RING;
         uint4 ring[RING][8];
         BStage<PL> st[2];
-        gemm_b_load<PL>(st[0], x, blk(0));
-        gemm_b_load<PL>(st[1], x, blk(1));
+        gemm_b_load<PL>(st[0], x, blk(0), true, xoff);
+        gemm_b_load<PL>(st[1], x, blk(1), 1 < nb, xoff);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < RING - 1; ++u) gemm_a_load(ring[u], wt, blk(u), u < nb);
-        gemm_b_store<PL>(st[0], bt, tid, true);
+        gemm_b_store<PL>(st[0], bt, tid);
         __syncthreads();
         static_assert(RING % 2 == 0, "ring slot (u % RING) and activation buffer (u & 1) are static");
         for (int t = 0; t < nb; t += RING) {
 #pragma unroll
             for (int u = 0; u < RING; ++u) {
                 const int tt = t + u;                       // this block of the walk
-                gemm_b_load<PL>(st[u & 1], x, blk(tt + 2));
+                gemm_b_load<PL>(st[u & 1], x, blk(tt + 2), tt + 2 < nb, xoff);
                 __builtin_amdgcn_sched_barrier(0);
                 gemm_a_load(ring[(u + RING - 1) % RING], wt, blk(tt + RING - 1), tt + RING - 1 < nb);
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_tile_mma<PL>(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);
+                if (tt < nb) gemm_tile_mma<PL>(ring[u % RING], acc, at, bt + (u & 1) * BT, lane);        // uniform
                 __builtin_amdgcn_sched_barrier(0);
-                gemm_b_store<PL>(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid, tt + 1 < nb);
+                gemm_b_store<PL>(st[(u + 1) & 1], bt + ((u + 1) & 1) * BT, tid);
                 __syncthreads();
             }
         }
@@ -655,15 +659,16 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
 // activations of MW row tiles (one here, two in k_chunk_gemm_ks)
 template <int MW, int PL = 2> struct BUnit { uint4 v[MW][2][PL]; };      // [row tile][k-step of the unit][plane]
 
+// x: the row tiles' planes; off: the lane's byte offset in an operand of each, or DEAD_ROW
 template <int MW, int PL>
-__device__ __forceinline__ void wide_b_load(BUnit<MW, PL>& b, const bf16_t* (&x)[MW][PL], int blk, int unit) {
+__device__ __forceinline__ void wide_b_load(BUnit<MW, PL>& b, const bf16_t* const (&x)[MW][PL], const uint32_t (&off)[MW], int blk, int unit, bool live) {
 #pragma unroll
     for (int j = 0; j < MW; ++j)
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const size_t o = ((size_t)blk * 8 + unit * 2 + st) * 512;
+        for (int p = 0; p < PL; ++p) {
+            const __amdgpu_buffer_rsrc_t run = weight_run(x[j][p] + ((size_t)blk * 8 + unit * 2) * 512, live ? 2048 : 0);
 #pragma unroll
-            for (int p = 0; p < PL; ++p) b.v[j][st][p] = load16(x[j][p] + o);
+            for (int st = 0; st < 2; ++st) b.v[j][st][p] = load16_run<false>(run, off[j] + st * 1024);
         }
 }
 
@@ -706,12 +711,12 @@ __device__ __forceinline__ void wide_step3(const uint4 (&a)[4], const BUnit<1, 3
 template <bool SWIGLU, int PL>
 __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restrict__ W, int N, int K,
                                                              const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo, const bf16_t* __restrict__ Xlo2,
-                                                             float* __restrict__ P, size_t s_stride, int n_stride, int S, int MT,
+                                                             float* __restrict__ P, size_t s_stride, int n_stride, int S, int rows,
                                                              bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo, bf16_t* __restrict__ act_lo2) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]
     constexpr int QN = 8;                           // weight loads per thread and block: wave w stages rows 32 w ...
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles = N >> 7;
+    const int tiles = N >> 7, MT = (rows + 31) >> 5;
     int q0 = blockIdx.x, my = 0;
     if (PL == 3) {
         const int MY = (MT + 3) >> 2, total = gridDim.x / MY;       // weight tiles x splits
@@ -734,9 +739,10 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
         wslot[q] = wave * 512 + r * 16 + (c ^ (r & 15));
     }
     // activations: a row tile per wave; waves past the last tile repeat it and store nothing
-    const size_t xo = (size_t)min(mtile, MT - 1) * nblk * 4096 + lane * 8;
+    const size_t xo = (size_t)min(mtile, MT - 1) * nblk * 4096;
     const bf16_t* x[1][PL];
     x[0][0] = Xhi + xo; x[0][1] = Xlo + xo;
+    const uint32_t xoff[1] = {min(mtile, MT - 1) * 32 + (lane & 31) < rows ? lane * 16u : DEAD_ROW};
     if (PL > 2) x[0][PL - 1] = Xlo2 + xo;
 
     f32x16 acc[4][1];
@@ -762,7 +768,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
         w_load(b0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 3; ++u) wide_b_load<1, PL>(ring[u], x, b0, u);
+        for (int u = 0; u < 3; ++u) wide_b_load<1, PL>(ring[u], x, xoff, b0, u, true);
         __builtin_amdgcn_sched_barrier(0);
         w_store(gemm_lds);
         w_load(b0 + 1);
@@ -785,7 +791,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     // unit u + 3 of the stream: the last unit of this block, then the first three of the next
-                    wide_b_load<1, PL>(ring[(u + 3) & 3], x, u == 0 ? tt : min(tt + 1, last), (u + 3) & 3);
+                    wide_b_load<1, PL>(ring[(u + 3) & 3], x, xoff, u == 0 ? tt : tt + 1, (u + 3) & 3, u == 0 || tt < last);
                     __builtin_amdgcn_sched_barrier(0);
                     if (u == 1) {
                         // the next block's weights (requested one block ago) move to the other LDS buffer, whose
@@ -1102,7 +1108,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_big(const bf16_t* __restrict
 template <int MT, bool SWIGLU>
 __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict__ W, int N, int K,
                                                        const bf16_t* __restrict__ Xhi, const bf16_t* __restrict__ Xlo,
-                                                       float* __restrict__ P, size_t s_stride, int n_stride, int S,
+                                                       float* __restrict__ P, size_t s_stride, int n_stride, int S, int rows,
                                                        bf16_t* __restrict__ act_hi, bf16_t* __restrict__ act_lo) {
     extern __shared__ uint4 gemm_lds[];             // [2 buffers][4 weight-row tiles][512]; reused by the final sum
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1117,10 +1123,12 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
     const WeightTile wt = weight_tile(W + (size_t)wrow * K, K, lane);
     const int wr0 = lane >> 4, wc = lane & 15;
     const bf16_t* x[MT][2];
+    uint32_t xoff[MT];
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
-        const size_t o = (size_t)j * nblk * 4096 + lane * 8;
+        const size_t o = (size_t)j * nblk * 4096;
         x[j][0] = Xhi + o; x[j][1] = Xlo + o;
+        xoff[j] = j * 32 + (lane & 31) < rows ? lane * 16 : DEAD_ROW;
     }
 
     f32x16 acc[4][MT];
@@ -1133,13 +1141,15 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
 
     if (nb > 0) {
         // A block is short (32 products per wave with two row tiles), so the weights of block b0 + i travel in register
-        // set i % 2, requested two blocks ahead of their use, and the activations (from L2) in a ring of three blocks.
+        // set i % 2, requested two blocks ahead of their use, and the activations (from L2) one block ahead.  What bounds it is the
+        // memory with the activations beside the weights (gate/up of 40 rows 48.9 us when they were loaded whole: 42.4 without them, 45.8 without products);
+        // activations two or three blocks ahead 48.5 and 47.0 us, three or four weight sets 48.9 and 47.8, eight waves 48.5, this 46.1 (then less the dead rows).
         // (Three row tiles do not fit the register file this way; they take k_chunk_gemm_wide with an idle wave.)
         static_assert(MT == 2, "register budget");
         // rotated walk over the k-blocks, as in k_chunk_gemm: block i of the walk is b0 + (i + rot) mod nb
         const int rot = (int)((blockIdx.x / 8 + (blockIdx.x & 7) * 4 + blockIdx.y * 3) % (unsigned)nb);
         auto blk = [&](int i) { const int x = min(i, nb - 1) + rot; return b0 + (x >= nb ? x - nb : x); };
-        constexpr int NSET = 2, RING = 3, UNROLL = 6;   // LDS buffer u % 2 and ring slot u % RING are static
+        constexpr int NSET = 2, RING = 2, UNROLL = 2;   // LDS buffer u % 2 and ring slot u % RING are static
         uint4 wreg[NSET][8];
         BUnit<MT> ring[RING];
         auto w_load = [&](uint4 (&set)[8], int i) { gemm_a_load(set, wt, blk(i), i < nb); };      // block i of the walk
@@ -1154,7 +1164,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
         w_load(wreg[0], 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < RING - 1; ++i) wide_b_load<MT, 2>(ring[i], x, blk(i), wave);
+        for (int i = 0; i < RING - 1; ++i) wide_b_load<MT, 2>(ring[i], x, xoff, blk(i), wave, i < nb);
         __builtin_amdgcn_sched_barrier(0);
         w_store(wreg[0], gemm_lds);
         w_load(wreg[NSET - 1], 1);
@@ -1164,13 +1174,13 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
                 const int tt = t + u;                       // this block of the walk: LDS buffer u % 2, ring slot u % RING
-                if (tt >= nb) break;                        // uniform
                 const uint4* at = gemm_lds + (u & 1) * 2048;
                 uint4* other = gemm_lds + ((u & 1) ^ 1) * 2048;   // its readers passed the barrier that ended the previous block
-                wide_b_load<MT, 2>(ring[(u + RING - 1) % RING], x, blk(tt + RING - 1), wave);
+                wide_b_load<MT, 2>(ring[(u + RING - 1) % RING], x, xoff, blk(tt + RING - 1), wave, tt + RING - 1 < nb);
                 __builtin_amdgcn_sched_barrier(0);
                 w_load(wreg[u & 1], tt + 2);           // this set's previous block was stored one block ago
                 __builtin_amdgcn_sched_barrier(0);
+                if (tt < nb) {                              // uniform
                 uint4 a0[4], a1[4];
                 wide_a_read(a0, at, 2 * wave, lane);
                 wide_a_read(a1, at, 2 * wave + 1, lane);
@@ -1178,6 +1188,8 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                 wide_step<MT>(a0, ring[u % RING], 0, acc);
                 __builtin_amdgcn_sched_barrier(0);
                 wide_step<MT>(a1, ring[u % RING], 1, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 w_store(wreg[(u + 1) & 1], other);          // the next block's weights, requested two blocks ago
                 __syncthreads();
@@ -2040,8 +2052,8 @@ static hipError_t launch_big(const bf16_t* W, int N, int K, const bf16_t* xhi, c
 }
 
 hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                             GemmPlan pl, int MT, hipStream_t s) {
-    const int S = pl.s;
+                             GemmPlan pl, int rows, hipStream_t s) {
+    const int S = pl.s, MT = (rows + 31) / 32;
     const dim3 grid(N / 128, S), block(256);
     const size_t ps = (size_t)MT * 32 * N;
     if (S < 1 || S > CHUNK_GEMM_MAX_SPLIT || S > K / 128 || N % 128 || K % 128 || ps * S > c.part_capacity) return hipErrorInvalidValue;
@@ -2049,11 +2061,11 @@ hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, con
     // one row tile: weight-streaming kernel, a wave per 32 weight rows; two: the waves split the k-steps; three or four:
     // a wave per row tile (128-row workgroups); more: 256-row workgroups with pl.nt weight-row tiles
     if (MT == 1) {
-        hipLaunchKernelGGL((k_chunk_gemm<false, 2>), grid, block, gemm_lds_bytes(2), s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, nullptr, nullptr, nullptr, 0);
+        hipLaunchKernelGGL((k_chunk_gemm<false, 2>), grid, block, gemm_lds_bytes(2), s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, rows, nullptr, nullptr, nullptr, 0);
     } else if (MT == 2) {
-        hipLaunchKernelGGL((k_chunk_gemm_ks<2, false>), grid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, nullptr, nullptr);
+        hipLaunchKernelGGL((k_chunk_gemm_ks<2, false>), grid, block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, c.part, ps, N, S, rows, nullptr, nullptr);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<false, 2>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, MT, nullptr, nullptr, nullptr);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<false, 2>), dim3((unsigned)(N / 128) * S), block, GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, nullptr, c.part, ps, N, S, rows, nullptr, nullptr, nullptr);
     } else return launch_big<false>((const bf16_t*)W, N, K, xhi, xlo, c.part, S, pl.nt, MT, nullptr, nullptr, s);
     return hipGetLastError();
 }
@@ -2072,43 +2084,46 @@ static int gate_rows_per_wave(int F) {
 // Gate/up product with the SwiGLU in its epilogue (no split-K): W = [gate rows | up rows] (2F x K), result in
 // c.act_hi / c.act_lo.
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                                    GemmPlan pl, int MT, hipStream_t s) {
+                                    GemmPlan pl, int rows, hipStream_t s) {
+    const int MT = (rows + 31) / 32;
     if (MT < 1 || MT > CHUNK_MAX / 32 || F < 1 || K % 128 || (MT > 1 && F % 64)) return hipErrorInvalidValue;
     const bf16_t* Wb = (const bf16_t*)W;
     if (MT == 1) {
         const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
-        hipLaunchKernelGGL((k_chunk_gemm<true, 2>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(2), s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo, nullptr, rp);
+        hipLaunchKernelGGL((k_chunk_gemm<true, 2>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(2), s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo, nullptr, rp);
     } else if (MT == 2) {
-        hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, c.act_hi, c.act_lo);
+        hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo);
     } else if (MT <= 4) {
-        hipLaunchKernelGGL((k_chunk_gemm_wide<true, 2>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo, nullptr);
+        hipLaunchKernelGGL((k_chunk_gemm_wide<true, 2>), dim3((unsigned)(F / 64)), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo, nullptr);
     } else return launch_big<true>(Wb, 2 * F, K, xhi, xlo, nullptr, 1, pl.nt, MT, c.act_hi, c.act_lo, s);
     return hipGetLastError();
 }
 
 // Inputs of three planes: one row tile k_chunk_gemm, more k_chunk_gemm_wide.
 hipError_t launch_wide_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c, int S,
-                            int MT, hipStream_t s) {
+                            int rows, hipStream_t s) {
+    const int MT = (rows + 31) / 32;
     const size_t ps = (size_t)MT * 32 * N;
     if (S < 1 || S > CHUNK_GEMM_MAX_SPLIT || S > K / 128 || N % 128 || K % 128 || ps * S > c.part_capacity || MT < 1 || MT > WIDE_ROWS_MAX / 32) return hipErrorInvalidValue;
     if (MT == 1)
-        hipLaunchKernelGGL((k_chunk_gemm<false, 3>), dim3(N / 128, S), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, N, K, xhi, xlo, xlo2, c.part, ps, N, S, nullptr, nullptr, nullptr, 0);
+        hipLaunchKernelGGL((k_chunk_gemm<false, 3>), dim3(N / 128, S), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, N, K, xhi, xlo, xlo2, c.part, ps, N, S, rows, nullptr, nullptr, nullptr, 0);
     else
         hipLaunchKernelGGL((k_chunk_gemm_wide<false, 3>), dim3((unsigned)(N / 128) * S * ((MT + 3) / 4)), dim3(256), GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, N, K, xhi, xlo, xlo2,
-                           c.part, ps, N, S, MT, nullptr, nullptr, nullptr);
+                           c.part, ps, N, S, rows, nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c,
-                                   int MT, hipStream_t s) {
+                                   int rows, hipStream_t s) {
+    const int MT = (rows + 31) / 32;
     if (F < 1 || F % 64 || K % 128 || MT < 1 || MT > WIDE_ROWS_MAX / 32) return hipErrorInvalidValue;
     if (MT == 1) {
         const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
-        hipLaunchKernelGGL((k_chunk_gemm<true, 3>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2, nullptr, (size_t)0, 0, 1,
+        hipLaunchKernelGGL((k_chunk_gemm<true, 3>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2, nullptr, (size_t)0, 0, 1, rows,
                            c.act_hi, c.act_lo, c.act_lo2, rp);
     } else
         hipLaunchKernelGGL((k_chunk_gemm_wide<true, 3>), dim3((unsigned)(F / 64) * ((MT + 3) / 4)), dim3(256), GEMM_WIDE_LDS_BYTES, s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2,
-                           nullptr, (size_t)0, 0, 1, MT, c.act_hi, c.act_lo, c.act_lo2);
+                           nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo, c.act_lo2);
     return hipGetLastError();
 }
 

@@ -209,14 +209,14 @@ hipError_t launch_chunk_rope_kv(const ChunkBuffers& c, int S, void* kv_layer, co
 // per workgroup (passes of more than four row tiles only).
 struct GemmPlan { int s, nt; };
 hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                             GemmPlan pl, int MT, hipStream_t s);
+                             GemmPlan pl, int rows, hipStream_t s);
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
-                                    GemmPlan pl, int MT, hipStream_t s);
+                                    GemmPlan pl, int rows, hipStream_t s);
 // The same products with inputs of three planes (xlo2 / c.act_lo2 the third), any number of row tiles.
 hipError_t launch_wide_gemm(const void* W, int N, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c, int S,
-                            int MT, hipStream_t s);
+                            int rows, hipStream_t s);
 hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const bf16_t* xlo2, const ChunkBuffers& c,
-                                   int MT, hipStream_t s);
+                                   int rows, hipStream_t s);
 hipError_t launch_chunk_attn(const ChunkBuffers& c, const void* kv_layer, int nsplit, int ntasks, const Geom& g, hipStream_t s);
 // The key splits of every task are in the table; merge: some task has more than one.
 hipError_t launch_chunk_attn_wide(const ChunkBuffers& c, const void* kv_layer, bool merge, int ntasks, int npieces, const Geom& g, hipStream_t s);
