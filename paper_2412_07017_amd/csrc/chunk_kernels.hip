@@ -865,7 +865,8 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
 //  * weights and activations of a block of 32 columns go from global memory straight to LDS (16 bytes per lane and load,
 //    no registers): three buffers, the block after next is requested while a block is multiplied.  The weights are
 //    row-major in memory; the transposition into operand order is the choice of the 16-byte piece a lane loads (LDS row r,
-//    piece p holds piece p ^ ((r / 2) & 3) of the row: eight consecutive rows then cover all banks once).
+//    piece p holds piece p ^ ((r / 4) & 3) of the row: the 16 rows that a read takes at a time then cover all 64 banks once; with (r / 2) & 3,
+//    eight rows over half of them, 29 of 75 M LDS cycles were conflicts: gate/up of 2048 rows 704.6 -> 700.8 us, down 348.7 -> 347.7).
 //  * every load and every LDS read is issued between two products.  Issued together at the start of a block, the same
 //    loads kept the matrix cores idle for 40 % of the time (0.94-1.17 PFLOP/s); spread, the cores are busy 87-91 % of the
 //    cycles and the clock drops to the power limit instead (1.3-1.7 GHz with random operands, 2.4 with zeros).
@@ -1005,7 +1006,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_big(const bf16_t* __restrict
     for (int j = 0; j < LW; ++j) {
         // load q covers LDS rows 16 q .. 16 q + 15 of the tile, four lanes each; past the end the last one again
         const int q = min(wave * LW + j, 2 * NT - 1);
-        const int r = 16 * q + (lane >> 2), c = (lane & 3) ^ ((r >> 1) & 3);
+        const int r = 16 * q + (lane >> 2), c = (lane & 3) ^ ((r >> 2) & 3);
         int row;
         if (SWIGLU) {
             const int f = min((ntile * NT + (r >> 5)) * 16 + (r & 15), NR - 1);
@@ -1023,7 +1024,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_big(const bf16_t* __restrict
     }
     BigLane ln;
     {
-        const int i = lane & 31, gh = lane >> 5, z = (i >> 1) & 3;
+        const int i = lane & 31, gh = lane >> 5, z = (i >> 2) & 3;
         ln.a0 = i * 64 + ((gh ^ z) << 4); ln.a1 = i * 64 + (((2 + gh) ^ z) << 4);
         ln.b = BigShape<NT>::W_BYTES + wave * 8192 + lane * 16; ln.wave = wave;
     }
@@ -1670,6 +1671,9 @@ __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __res
         s = mma(kq[t % 3][0], ql[t], s);
         __builtin_amdgcn_sched_barrier(0);
     }
+    // A wave in its products goes before one in its softmax, so that the two waves of a SIMD do not keep step: 16k prompt, 2048 rows and layer 691 -> 673 us
+    // on average (the other way round, or one workgroup of a unit before the other: 688 and 708).
+    __builtin_amdgcn_s_setprio(0);
     u32x4 v0[4];                                                    // the first values are on their way during the softmax
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) v0[dt] = kt[vbase + dt * 128];
@@ -1708,6 +1712,7 @@ __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __res
     }
     st.mrun = mnew;
     __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
     // V^T chunk (plane, dt, t) is KiB plane * 8 + dt * 2 + t of the values; the next group of four is read while one is multiplied
     u32x4 v1[4];
 #pragma unroll
