@@ -22,6 +22,8 @@
 #include "common.h"
 #include "launch.h"
 
+#include <type_traits>
+
 namespace asynclm {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -1271,20 +1273,24 @@ struct ChunkAttnArgs {
 
 // K tile (32 keys x 128 channels, one plane) as loaded: instruction q covers rows 4q .. 4q+3, lane l holds
 // row 4q + l/16, 16-byte chunk l%16 (1 KiB contiguous per instruction).  Not `live`, here and for the values: past the wave's last tile,
-// nothing is fetched (weight_run).
+// nothing is fetched (weight_run).  STREAM: nobody else reads these keys and values: they leave no lines in the caches, which is the
+// faster way through them (decoding step at 16k keys 26.9 -> 24.7 us, and its merge 5.8 -> 4.7; 16 sequences in the shared-key kernel 73.0 -> 66.3; but where
+// two blocks of tasks read the same keys, 48 rows into 16k, 50.5 -> 52.6).
+template <bool STREAM>
 __device__ __forceinline__ void attn_k_load(uint4 (&kh)[8], uint4 (&kl)[8], const bf16_t* Kp, size_t lo, int tile, bool live, int lane) {
     const bf16_t* p = Kp + (size_t)tile * 32 * 128;
     const __amdgpu_buffer_rsrc_t hi_run = weight_run(p, live ? 8192 : 0), lo_run = weight_run(p + lo, live ? 8192 : 0);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) { kh[q] = load16_run<false>(hi_run, lane * 16 + q * 1024); kl[q] = load16_run<false>(lo_run, lane * 16 + q * 1024); }
+    for (int q = 0; q < 8; ++q) { kh[q] = load16_run<STREAM>(hi_run, lane * 16 + q * 1024); kl[q] = load16_run<STREAM>(lo_run, lane * 16 + q * 1024); }
 }
 
 // V^T tile (both planes) in operand order: instruction (dt, t) is one contiguous KiB in lane order.
+template <bool STREAM>
 __device__ __forceinline__ void attn_v_load(uint4 (&vh)[8], uint4 (&vl)[8], const bf16_t* Vt, size_t lo, int tile, bool live, int lane) {
     const bf16_t* p = Vt + (size_t)tile * 8 * 64 * 8;
     const __amdgpu_buffer_rsrc_t hi_run = weight_run(p, live ? 8192 : 0), lo_run = weight_run(p + lo, live ? 8192 : 0);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) { vh[k] = load16_run<false>(hi_run, lane * 16 + k * 1024); vl[k] = load16_run<false>(lo_run, lane * 16 + k * 1024); }
+    for (int k = 0; k < 8; ++k) { vh[k] = load16_run<STREAM>(hi_run, lane * 16 + k * 1024); vl[k] = load16_run<STREAM>(lo_run, lane * 16 + k * 1024); }
 }
 
 // chunk position of 16-byte chunk c of row r in the wave's LDS tile (conflict-free for the row-wise writes and
@@ -1426,19 +1432,19 @@ __global__ __launch_bounds__(256) void k_chunk_attn(ChunkAttnArgs a, Geom g) {
         // one tile at 1k: the decoding step's attention 28.5 -> 26.9 and 6.8 -> 6.7 us with its last tile not read again, 24 rows at 1.1k 8.8 -> 8.6).
         uint4 kh[8], kl[8], vh[8], vl[8];
         __builtin_amdgcn_sched_barrier(0);          // issue order q, K, V: the waits in the loop count on it
-        attn_k_load(kh, kl, Kp, lo, t0, true, lane);
+        attn_k_load<false>(kh, kl, Kp, lo, t0, true, lane);
         __builtin_amdgcn_sched_barrier(0);
-        attn_v_load(vh, vl, Vt, lo, t0, true, lane);
+        attn_v_load<false>(vh, vl, Vt, lo, t0, true, lane);
         __builtin_amdgcn_sched_barrier(0);
         for (int tile = t0; tile < t1; ++tile) {
             const bool more = tile + 1 < t1;
             attn_stage_k(kh, kl, kt, lane);
             __builtin_amdgcn_sched_barrier(0);
-            attn_k_load(kh, kl, Kp, lo, tile + 1, more, lane);
+            attn_k_load<false>(kh, kl, Kp, lo, tile + 1, more, lane);
             __builtin_amdgcn_sched_barrier(0);
             attn_tile(st, vh, vl, qh, ql, kt, tile * 32, qpos, lane);
             __builtin_amdgcn_sched_barrier(0);
-            attn_v_load(vh, vl, Vt, lo, tile + 1, more, lane);
+            attn_v_load<false>(vh, vl, Vt, lo, tile + 1, more, lane);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1507,9 +1513,9 @@ __global__ __launch_bounds__(256) void k_decode_attn_mfma(DecodeAttnArgs a, Geom
         st.mrun = -INFINITY; st.lrun = 0.f;
         uint4 kh[8], kl[8], vh[8], vl[8];
         __builtin_amdgcn_sched_barrier(0);          // issue order K, V, q: the waits in the loop count on it
-        attn_k_load(kh, kl, Kp, lo, t0, true, lane);
+        attn_k_load<true>(kh, kl, Kp, lo, t0, true, lane);
         __builtin_amdgcn_sched_barrier(0);
-        attn_v_load(vh, vl, Vt, lo, t0, true, lane);
+        attn_v_load<true>(vh, vl, Vt, lo, t0, true, lane);
         __builtin_amdgcn_sched_barrier(0);
         // B operand of S^T = K Q^T: lane (j, g) holds q[j][16 t + 8 g + e]; column j is q head j of the kv group
         uint4 qh[8], ql[8];
@@ -1528,11 +1534,11 @@ __global__ __launch_bounds__(256) void k_decode_attn_mfma(DecodeAttnArgs a, Geom
             const bool more = tile + 1 < t1;
             attn_stage_k(kh, kl, kt, lane);
             __builtin_amdgcn_sched_barrier(0);
-            attn_k_load(kh, kl, Kp, lo, tile + 1, more, lane);
+            attn_k_load<true>(kh, kl, Kp, lo, tile + 1, more, lane);
             __builtin_amdgcn_sched_barrier(0);
             attn_tile(st, vh, vl, qh, ql, kt, tile * 32, pos, lane);
             __builtin_amdgcn_sched_barrier(0);
-            attn_v_load(vh, vl, Vt, lo, tile + 1, more, lane);
+            attn_v_load<true>(vh, vl, Vt, lo, tile + 1, more, lane);
             __builtin_amdgcn_sched_barrier(0);
         }
         st.lrun += __shfl_xor(st.lrun, 32, 64);
@@ -1631,17 +1637,19 @@ struct WideSrc {
     uint32_t koff[4], voff;                 // the lane's elements within a tile
     int slot;                               // first LDS chunk of the wave's K loads
 };
+template <bool STREAM>                      // as for attn_k_load
 __device__ __forceinline__ void attn_wide_load(uint4* buf, const WideSrc& w, int tile, int j) {
     const bf16_t* src = j < 4 ? w.k + (size_t)tile * 4096 + w.koff[j & 3] : w.v + (size_t)tile * 4096 + w.voff + (j & 3) * 512;
-    __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)(buf + w.slot + (j < 4 ? 0 : 1024) + (j & 3) * 64), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)(buf + w.slot + (j < 4 ? 0 : 1024) + (j & 3) * 64), 16, 0, STREAM ? 2 : 0);
 }
 
 // One tile: multiplies the tile in `rd` (if `work`) and requests tile `next` into `wr`.  The buffers never meet, see big_block.
+template <bool STREAM>
 __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __restrict__ rd, uint4* __restrict__ wr, const WideSrc& w, int next,
                                                const u32x4 (&qh)[8], const u32x4 (&ql)[8], int key0, int qpos, bool work, int lane) {
     if (!work) {                                                    // uniform over the wave
 #pragma unroll
-        for (int j = 0; j < 8; ++j) attn_wide_load(wr, w, next, j);
+        for (int j = 0; j < 8; ++j) attn_wide_load<STREAM>(wr, w, next, j);
         return;
     }
     const int i = lane & 31, gh = lane >> 5;
@@ -1665,7 +1673,7 @@ __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __res
         if (t + 2 < 8) { kq[(t + 2) % 3][0] = kread(t + 2, 0); kq[(t + 2) % 3][1] = kread(t + 2, 1); }
         __builtin_amdgcn_sched_barrier(0);
         s = mma(kq[t % 3][0], qh[t], s);
-        attn_wide_load(wr, w, next, t);
+        attn_wide_load<STREAM>(wr, w, next, t);
         __builtin_amdgcn_sched_barrier(0);
         s = mma(kq[t % 3][1], qh[t], s);
         s = mma(kq[t % 3][0], ql[t], s);
@@ -1784,7 +1792,7 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
 
     if (t0 < t1) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) attn_wide_load(attn_lds, w, t0, j);
+        for (int j = 0; j < 8; ++j) attn_wide_load<false>(attn_lds, w, t0, j);
         u32x4 qh[8], ql[8];
         {
             const size_t qo = ((size_t)kvh * a.q_cols + (size_t)G * T.row0 + col) * DH + gh * 8;
@@ -1794,14 +1802,18 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
                 ql[t] = *(global_u32x4_ptr)(uintptr_t)(a.q_lo + qo + t * 16);
             }
         }
-        for (int tile = t0; tile < t1; ++tile) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's share of the tile has landed ...
-            __builtin_amdgcn_s_barrier();                           // ... and everybody's, and the other buffer has been read
-            __builtin_amdgcn_sched_barrier(0);
-            const int cur = (tile - t0) & 1;
-            attn_wide_tile(st, attn_lds + cur * 2048, attn_lds + (cur ^ 1) * 2048, w, min(tile + 1, t1 - 1), qh, ql, tile * 32, qpos,
-                           live && tile * 32 < Lw, lane);
-        }
+        auto walk = [&](auto stream) {
+            for (int tile = t0; tile < t1; ++tile) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's share of the tile has landed ...
+                __builtin_amdgcn_s_barrier();                           // ... and everybody's, and the other buffer has been read
+                __builtin_amdgcn_sched_barrier(0);
+                const int cur = (tile - t0) & 1;
+                attn_wide_tile<stream.value>(st, attn_lds + cur * 2048, attn_lds + (cur ^ 1) * 2048, w, min(tile + 1, t1 - 1), qh, ql, tile * 32, qpos,
+                                                  live && tile * 32 < Lw, lane);
+            }
+        };
+        if (G * T0.n <= 128) walk(std::true_type{});                // one block of tasks: uniform
+        else walk(std::false_type{});
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // no load may still be on its way to LDS when the workgroup ends
     }
     st.lrun += __shfl_xor(st.lrun, 32, 64);
