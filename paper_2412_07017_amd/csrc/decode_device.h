@@ -428,6 +428,80 @@ __device__ __forceinline__ float early_stage(const EarlyBatch<NB, GAIN>& b, floa
     return red[0] + red[1] + red[2] + red[3];
 }
 
+// The same for the merge of the attention's key splits (VecSource without x), at most EARLY_MERGE x 1024 elements: statistics, one (head, split)
+// per thread and pass, and partial results are requested before the first weight tiles and merged while those are on their way.  The weights
+// of the splits are formed once per head, in LDS.  Splits past the last and elements past the end are not fetched (weight_run).
+// Bound: every workgroup reads all partial results, 16 KB a split at 4096 columns, beside its 128 KB of weights.  O projection of the 8B shape
+// with 8 splits, requested behind the weights (stage_vector) / here: 12.9 / 10.5 us (8.9 without a merge).  More columns would need more than the
+// 286 registers that this takes: stage_vector.
+constexpr int EARLY_MERGE = 4;
+constexpr int EARLY_MERGE_HEADS = EARLY_MERGE * 1024 / 64;      // head_dim is 64 or 128
+struct EarlyMerge {
+    uint4 raw[EARLY_MERGE][MERGE_MAX_SPLIT];
+    float m[EARLY_MERGE_HEADS * MERGE_MAX_SPLIT / 256], l[EARLY_MERGE_HEADS * MERGE_MAX_SPLIT / 256];
+};
+
+__device__ __forceinline__ void merge_request(EarlyMerge& b, const VecSource& src) {
+    const int tid = threadIdx.x, ns = src.nsplit, hs = src.DH == 128 ? 5 : 4;       // float4s of a head: 1 << hs
+#pragma unroll
+    for (int i = 0; i < EARLY_MERGE_HEADS * MERGE_MAX_SPLIT / 256; ++i) {
+        const int h = min((i * 256 + tid) / MERGE_MAX_SPLIT, src.Hq - 1), s = min(tid % MERGE_MAX_SPLIT, ns - 1);
+        const float* pm = src.part_ml + ((size_t)h * ns + s) * 2;
+        b.m[i] = load_f32(pm); b.l[i] = load_f32(pm + 1);
+    }
+    const __amdgpu_buffer_rsrc_t run = weight_run(src.part_acc, (uint32_t)(src.Hq * ns * src.DH) * 4u);
+#pragma unroll
+    for (int j = 0; j < EARLY_MERGE; ++j) {
+        const int k4 = j * 256 + tid, h = k4 >> hs, d4 = k4 & ((1 << hs) - 1);
+#pragma unroll
+        for (int s = 0; s < MERGE_MAX_SPLIT; ++s)
+            b.raw[j][s] = load16_run<false>(run, s < ns ? (uint32_t)((((h * ns + s) << hs) + d4) * 16) : 0xfffffff0u);
+    }
+}
+
+template <typename WT>
+__device__ __forceinline__ void merge_stage(const EarlyMerge& b, const VecSource& src, float4* xs, int plane_stride, int K, int Kg, int KT) {
+    constexpr int NP = Elem<WT>::EPL / 4;
+    __shared__ float4 sw[EARLY_MERGE_HEADS][MERGE_MAX_SPLIT / 4];
+    __shared__ float sinv[EARLY_MERGE_HEADS];
+    const int tid = threadIdx.x, n4 = K >> 2, hs = src.DH == 128 ? 5 : 4;
+#pragma unroll
+    for (int i = 0; i < EARLY_MERGE_HEADS * MERGE_MAX_SPLIT / 256; ++i) {
+        const int h = (i * 256 + tid) / MERGE_MAX_SPLIT, s = tid % MERGE_MAX_SPLIT;
+        const float m = s < src.nsplit ? b.m[i] : -INFINITY;
+        float M = m;
+#pragma unroll
+        for (int o = MERGE_MAX_SPLIT / 2; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+        const float w = m > -INFINITY ? expf(m - M) : 0.f;
+        const float L = group_sum<MERGE_MAX_SPLIT>(b.l[i] * w);
+        reinterpret_cast<float*>(sw[h])[s] = w;
+        if (s == 0) sinv[h] = 1.f / L;
+    }
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (Kg + tid < KT * 256)
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl) xs[pl * plane_stride + Kg + tid] = zero;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < EARLY_MERGE; ++j) {
+        const int k4 = j * 256 + tid, h = min(k4 >> hs, EARLY_MERGE_HEADS - 1);
+        const float4 w0 = sw[h][0], w1 = sw[h][1];
+        const float w[MERGE_MAX_SPLIT] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+        const float inv = sinv[h];
+        float4 r = zero;
+#pragma unroll
+        for (int s = 0; s < MERGE_MAX_SPLIT; ++s) {
+            const float4 v = as_float4(b.raw[j][s]);
+            r.x = fmaf(v.x, w[s], r.x); r.y = fmaf(v.y, w[s], r.y); r.z = fmaf(v.z, w[s], r.z); r.w = fmaf(v.w, w[s], r.w);
+        }
+        if (k4 < n4) {
+            const int grp = k4 / NP, pl = k4 - grp * NP;
+            xs[pl * plane_stride + grp] = make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
+        }
+    }
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------------------------
 // matrix-vector product of one wave over its share of the rows, through a ring of register tiles
 // ---------------------------------------------------------------------------------------------

@@ -148,12 +148,19 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
     // NB > 0 (the vector is a plain one that fits one batch of NB x 16 bytes per thread; with a gain in the
     // normalising products, without in the residual ones): it is requested before the first weight tiles, so it is
     // back and staged long before them, and the first tile is multiplied as soon as it arrives.  NB = 0: the vector
-    // (any source) is staged after the requests.
+    // (any source) is staged after the requests.  NB = -EARLY_MERGE: the key splits of the attention, requested before the tiles too.
+    constexpr bool MERGE = NB < 0;
     constexpr int NB1 = NB > 0 ? NB : 1;
     constexpr bool GAIN = EPI != EPI_RESID;
     EarlyBatch<NB1, GAIN> vb;
     if (NB > 0 && !PIPE) {
         early_request(vb, a.x, a.gain, a.K);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    EarlyMerge mb;
+    const VecSource vs{a.x, a.gain, a.part_acc, a.part_ml, a.merge_nsplit, a.merge_dh, a.merge_hq};
+    if constexpr (MERGE) {
+        merge_request(mb, vs);
         __builtin_amdgcn_sched_barrier(0);
     }
     Phase<WT> ph = make_phase_split<WT, EPI>(a.W, a.rows, a.K, a.units, a.uq, a.ur);
@@ -180,10 +187,10 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_gemv(GemvArgs a, Geo
     }
     phase_prefetch_e<WT, EPI>(ring, ph, lc, g, eo);
 
-    float ssq;
-    if (NB > 0) ssq = early_stage<WT, NB1, GAIN>(vb, lds4, plane_stride, a.K, ph.Kg, ph.KT, red);
+    float ssq = 0.f;
+    if constexpr (MERGE) merge_stage<WT>(mb, vs, lds4, plane_stride, a.K, ph.Kg, ph.KT);
+    else if (NB > 0) ssq = early_stage<WT, NB1, GAIN>(vb, lds4, plane_stride, a.K, ph.Kg, ph.KT, red);
     else {
-        VecSource vs{a.x, a.gain, a.part_acc, a.part_ml, a.merge_nsplit, a.merge_dh, a.merge_hq};
         ssq = stage_vector<WT, (EPI == EPI_RESID ? 16 : 4)>(lds4, plane_stride, vs, a.K, ph.Kg, ph.KT, true, red);
     }
     const float nscale = a.gain ? rsqrtf(ssq / (float)a.K + g.eps) : 1.f;
@@ -614,6 +621,9 @@ static const void* gemv_func_n(int mode) {
 // The instantiation that serves a product with K columns (plain_x: the input is a plain vector, not split partials).
 template <typename WT, int EPI>
 static const void* gemv_func(int K, bool plain_x, int pipe /* mode: 0 default, 1 two-stream, 2 stamps */) {
+    if constexpr (EPI == EPI_RESID)
+        if (!plain_x && K <= 1024 * EARLY_MERGE && pipe != 1)
+            return pipe == 2 ? (const void*)(k_gemv<WT, EPI_RESID, -EARLY_MERGE, 2>) : (const void*)(k_gemv<WT, EPI_RESID, -EARLY_MERGE, 0>);
     if (plain_x && K <= 1024 * EarlyNB<EPI>::SMALL) return gemv_func_n<WT, EPI, EarlyNB<EPI>::SMALL>(pipe);
     if (plain_x && K <= 1024 * EarlyNB<EPI>::LARGE) return gemv_func_n<WT, EPI, EarlyNB<EPI>::LARGE>(pipe);
     if (EPI == EPI_RESID && plain_x && K <= 1024 * EarlyNB<EPI>::HUGE) return gemv_func_n<WT, EPI_RESID, EarlyNB<EPI_RESID>::HUGE>(pipe);
@@ -677,6 +687,9 @@ static hipError_t set_lds_p(int bytes) {
     if ((e = hipFuncSetAttribute((const void*)(k_gemv<WT, EPI, EarlyNB<EPI>::SMALL, PIPE>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes))) return e;
     if ((e = hipFuncSetAttribute((const void*)(k_gemv<WT, EPI, EarlyNB<EPI>::LARGE, PIPE>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes))) return e;
     if (EPI != EPI_RESID) return hipSuccess;
+    if constexpr (PIPE != 1)
+        if ((e = hipFuncSetAttribute((const void*)(k_gemv<WT, EPI_RESID, -EARLY_MERGE, PIPE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     std::min(bytes, 128 * 1024)))) return e;      // has LDS of its own, and at most 4096 columns
     return hipFuncSetAttribute((const void*)(k_gemv<WT, EPI_RESID, EarlyNB<EPI_RESID>::HUGE, PIPE>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 template <typename WT, int EPI>
