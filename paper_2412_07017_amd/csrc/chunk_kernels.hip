@@ -21,6 +21,7 @@
 // contiguous bytes of its own K / V^T row (k = 64 g + 8 t + e there).
 #include "common.h"
 #include "launch.h"
+#include "weight_tile.h"
 
 #include <type_traits>
 
@@ -450,23 +451,12 @@ constexpr int GEMM_RING = 4;        // weight tiles per wave in the register rin
 
 template <int PL> struct BStage { uint4 v[2 * PL]; };
 
-// Block `blk` of a wave's weight tile, row q of the lane = tile row 4 q + lane / 16: rows 0..15 start at w0, rows 16..31 at w1 (both the same
-// for the whole wave), off[q] is the lane's byte offset from there.  Not `live` (past the end of the run): zeros, nothing is fetched.
-// Nor is anything fetched for rows from w0 + bytes (w1 + bytes) on.
-struct WeightTile { const bf16_t *w0, *w1; uint32_t bytes, off[8]; };
+// Block `blk` of a wave's weight tile.  Not `live` (past the end of the run): zeros, nothing is fetched.
 __device__ __forceinline__ void gemm_a_load(uint4 (&a)[8], const WeightTile& t, int blk, bool live) {
-    const uint32_t bytes = live ? t.bytes : 0u, base = live ? (uint32_t)blk * 256 : 0u;
-    const __amdgpu_buffer_rsrc_t r0 = weight_run(t.w0, bytes), r1 = weight_run(t.w1, bytes);
+    const RunPart part = weight_part(t, blk, live);
+    const __amdgpu_buffer_rsrc_t r0 = weight_run(t.w0, part.bytes), r1 = weight_run(t.w1, part.bytes);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = load16_run(q < 4 ? r0 : r1, t.off[q], base);
-}
-// 32 consecutive rows of K columns from w on
-__device__ __forceinline__ WeightTile weight_tile(const bf16_t* w, int K, int lane) {
-    WeightTile t;
-    t.w0 = t.w1 = w; t.bytes = 64u * (uint32_t)K;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t.off[q] = (uint32_t)(4 * q + (lane >> 4)) * (uint32_t)K * 2 + (lane & 15) * 16;
-    return t;
+    for (int q = 0; q < 8; ++q) a[q] = load16_run(q < 4 ? r0 : r1, t.off[q], part.base);
 }
 
 // thread tid stages chunks tid and tid + 256 of the 512 16-byte chunks of each 8 KiB plane tile
@@ -561,19 +551,13 @@ __global__ __launch_bounds__(256) void k_chunk_gemm(const bf16_t* __restrict__ W
     uint4* bt = gemm_lds + 2048;
     constexpr int BT = PL * 512;                    // chunks in one activation buffer
     const int n0 = SWIGLU ? (blockIdx.x * 4 + wave) * rp : blockIdx.x * 128 + wave * 32;     // SWIGLU: first gate row
-    const int nr = SWIGLU ? max(0, min(rp, (N >> 1) - n0)) : 32;                              // SWIGLU: gate rows of this wave
+    const int nr = SWIGLU ? gate_rows(N >> 1, n0, rp) : 32;                                   // SWIGLU: gate rows of this wave
     const int sp = blockIdx.y;
     const int nblk = K >> 7;
     const int b0 = (int)((unsigned)(nblk * sp) / (unsigned)S), b1 = (int)((unsigned)(nblk * (sp + 1)) / (unsigned)S);   // (K / 128) * S < 2^31
     const int nb = b1 - b0;
 
-    WeightTile wt = weight_tile(W + (SWIGLU ? 0 : (size_t)n0 * K), K, lane);
-    if (SWIGLU) {
-        const int g0 = min(n0, (N >> 1) - 1);
-        wt.w0 = W + (size_t)g0 * K; wt.w1 = W + (size_t)((N >> 1) + g0) * K; wt.bytes = 2u * (uint32_t)nr * (uint32_t)K;
-#pragma unroll
-        for (int q = 4; q < 8; ++q) wt.off[q] = wt.off[q - 4];
-    }
+    const WeightTile wt = SWIGLU ? gate_up_tile(W, N >> 1, K, n0, nr, lane) : weight_tile(W + (size_t)n0 * K, K, lane);
     const bf16_t* x[PL];
     x[0] = Xhi; x[1] = Xlo;
     if (PL > 2) x[PL - 1] = Xlo2;
@@ -2088,17 +2072,6 @@ hipError_t launch_chunk_gemm(const void* W, int N, int K, const bf16_t* xhi, con
     return hipGetLastError();
 }
 
-// Gate rows per wave-tile of k_chunk_gemm: the fewest whole rounds of tiles over the device's waves that 16 rows per tile allow.
-static int gate_rows_per_wave(int F) {
-    const int waves = 4 * std::max(1, decode_gemv_grid());
-    int rp = 16;
-    for (int m = 1; m <= 64; ++m) {
-        rp = (F + waves * m - 1) / (waves * m);
-        if (rp <= 16) break;
-    }
-    return std::min(std::max(rp, 1), 16);
-}
-
 // Gate/up product with the SwiGLU in its epilogue (no split-K): W = [gate rows | up rows] (2F x K), result in
 // c.act_hi / c.act_lo.
 hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* xhi, const bf16_t* xlo, const ChunkBuffers& c,
@@ -2107,7 +2080,7 @@ hipError_t launch_chunk_gemm_swiglu(const void* W, int F, int K, const bf16_t* x
     if (MT < 1 || MT > CHUNK_MAX / 32 || F < 1 || K % 128 || (MT > 1 && F % 64)) return hipErrorInvalidValue;
     const bf16_t* Wb = (const bf16_t*)W;
     if (MT == 1) {
-        const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
+        const int rp = gate_rows_per_wave(F, 4 * std::max(1, decode_gemv_grid())), tiles = (F + rp - 1) / rp;
         hipLaunchKernelGGL((k_chunk_gemm<true, 2>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(2), s, Wb, 2 * F, K, xhi, xlo, nullptr, nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo, nullptr, rp);
     } else if (MT == 2) {
         hipLaunchKernelGGL((k_chunk_gemm_ks<2, true>), dim3(F / 64, 1), dim3(256), GEMM_WIDE_LDS_BYTES, s, Wb, 2 * F, K, xhi, xlo, nullptr, (size_t)0, 0, 1, rows, c.act_hi, c.act_lo);
@@ -2136,7 +2109,7 @@ hipError_t launch_wide_gemm_swiglu(const void* W, int F, int K, const bf16_t* xh
     const int MT = (rows + 31) / 32;
     if (F < 1 || F % 64 || K % 128 || MT < 1 || MT > WIDE_ROWS_MAX / 32) return hipErrorInvalidValue;
     if (MT == 1) {
-        const int rp = gate_rows_per_wave(F), tiles = (F + rp - 1) / rp;
+        const int rp = gate_rows_per_wave(F, 4 * std::max(1, decode_gemv_grid())), tiles = (F + rp - 1) / rp;
         hipLaunchKernelGGL((k_chunk_gemm<true, 3>), dim3((tiles + 3) / 4, 1), dim3(256), gemm_lds_bytes(3), s, (const bf16_t*)W, 2 * F, K, xhi, xlo, xlo2, nullptr, (size_t)0, 0, 1, rows,
                            c.act_hi, c.act_lo, c.act_lo2, rp);
     } else

@@ -120,3 +120,22 @@ def test_passes_that_end_inside_a_tile_of_rows(rows, kv):
         at += n
         assert np.abs(lm.logits(0) - dec.logits).max() <= (2.5e-3 if kv else 2e-4) * np.abs(dec.logits).max(), (n, at)
     lm.close()
+
+
+@pytest.mark.parametrize("ffn", [2176, 2432, 11008])
+@pytest.mark.parametrize("kv", [0, 1], ids=["paired cache", "single plane"])
+def test_gate_up_waves_without_rows(ffn, kv):
+    """Gate rows that do not fill the last workgroup's waves (3, 3 and 11 rows a wave on 256 compute units): the idle waves request nothing."""
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(2, 256, 2, 1, 128, ffn, 128, 1e-5, 10000.0, "bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    conv = lambda t: t.detach().to("cpu").to(torch.float32).numpy()
+    dec = orc.CachedDecoder(orc.Shape.of(model), {k: ([conv(t) for t in v] if isinstance(v, list) else conv(v)) for k, v in w.items()}, dtype=np.float32, kv_round=kv == 1)
+    toks = [int(t) for t in ai.uniform_tokens(ai.MASTER_SEED, 976, 56, model.vocab)]
+    lm = pkg.AsyncLM(model, w, max_positions=56, stream=torch.cuda.Stream(), kv_format=kv)
+    for a, b in ((0, 32), (32, 56)):
+        (lm.inject_interrupt if a else lm.prefill)(0, toks[a:b])
+        (dec.inject if a else dec.prefill)(toks[a:b])
+        assert np.abs(lm.logits(0) - dec.logits).max() <= (2.5e-3 if kv else 2e-4) * np.abs(dec.logits).max(), b    # as for passes that end inside a tile
+    lm.close()
