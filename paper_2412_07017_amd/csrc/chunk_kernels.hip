@@ -1627,13 +1627,14 @@ __device__ __forceinline__ void attn_wide_load(uint4* buf, const WideSrc& w, int
     __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)(buf + w.slot + (j < 4 ? 0 : 1024) + (j & 3) * 64), 16, 0, STREAM ? 2 : 0);
 }
 
-// One tile: multiplies the tile in `rd` (if `work`) and requests tile `next` into `wr`.  The buffers never meet, see big_block.
-template <bool STREAM>
+// One tile: multiplies the tile in `rd` (if `work`) and requests tile `next` into `wr` (MORE).  The buffers never meet, see big_block.
+template <bool STREAM, bool MORE>
 __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __restrict__ rd, uint4* __restrict__ wr, const WideSrc& w, int next,
                                                const u32x4 (&qh)[8], const u32x4 (&ql)[8], int key0, int qpos, bool work, int lane) {
     if (!work) {                                                    // uniform over the wave
 #pragma unroll
-        for (int j = 0; j < 8; ++j) attn_wide_load<STREAM>(wr, w, next, j);
+        for (int j = 0; j < 8; ++j)
+            if (MORE) attn_wide_load<STREAM>(wr, w, next, j);
         return;
     }
     const int i = lane & 31, gh = lane >> 5;
@@ -1657,7 +1658,7 @@ __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __res
         if (t + 2 < 8) { kq[(t + 2) % 3][0] = kread(t + 2, 0); kq[(t + 2) % 3][1] = kread(t + 2, 1); }
         __builtin_amdgcn_sched_barrier(0);
         s = mma(kq[t % 3][0], qh[t], s);
-        attn_wide_load<STREAM>(wr, w, next, t);
+        if (MORE) attn_wide_load<STREAM>(wr, w, next, t);
         __builtin_amdgcn_sched_barrier(0);
         s = mma(kq[t % 3][1], qh[t], s);
         s = mma(kq[t % 3][0], ql[t], s);
@@ -1775,8 +1776,12 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
     st.mrun = -INFINITY; st.lrun = 0.f;
 
     if (t0 < t1) {
+        const bool alone = G * T0.n <= 128;                         // one block of tasks: nobody else reads these keys
 #pragma unroll
-        for (int j = 0; j < 8; ++j) attn_wide_load<false>(attn_lds, w, t0, j);
+        for (int j = 0; j < 8; ++j) {
+            if (alone) attn_wide_load<true>(attn_lds, w, t0, j);
+            else attn_wide_load<false>(attn_lds, w, t0, j);
+        }
         u32x4 qh[8], ql[8];
         {
             const size_t qo = ((size_t)kvh * a.q_cols + (size_t)G * T.row0 + col) * DH + gh * 8;
@@ -1786,18 +1791,22 @@ __global__ __launch_bounds__(256, 2) void k_chunk_attn_wide(ChunkAttnArgs a, Geo
                 ql[t] = *(global_u32x4_ptr)(uintptr_t)(a.q_lo + qo + t * 16);
             }
         }
-        auto walk = [&](auto stream) {
-            for (int tile = t0; tile < t1; ++tile) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's share of the tile has landed ...
-                __builtin_amdgcn_s_barrier();                           // ... and everybody's, and the other buffer has been read
-                __builtin_amdgcn_sched_barrier(0);
-                const int cur = (tile - t0) & 1;
-                attn_wide_tile<stream.value>(st, attn_lds + cur * 2048, attn_lds + (cur ^ 1) * 2048, w, min(tile + 1, t1 - 1), qh, ql, tile * 32, qpos,
-                                                  live && tile * 32 < Lw, lane);
-            }
+        auto step = [&](auto stream, auto more, int tile) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's share of the tile has landed ...
+            __builtin_amdgcn_s_barrier();                           // ... and everybody's, and the other buffer has been read
+            __builtin_amdgcn_sched_barrier(0);
+            const int cur = (tile - t0) & 1;
+            attn_wide_tile<stream.value, more.value>(st, attn_lds + cur * 2048, attn_lds + (cur ^ 1) * 2048, w, min(tile + 1, t1 - 1), qh, ql, tile * 32, qpos,
+                                                     live && tile * 32 < Lw, lane);
         };
-        if (G * T0.n <= 128) walk(std::true_type{});                // one block of tasks: uniform
-        else walk(std::false_type{});
+        // Streamed tiles leave no lines behind, so the last one is not requested again in place of a next one that does not exist, which would come from memory:
+        // 24 rows into 4.2k (two tiles a workgroup) 679 -> 673 us, into 16k (eight) 741 -> 735, four layers; batches no difference beyond noise.  Where
+        // others read the tiles too the repeat is a cache hit and stays (without it 0.996x on a 16k prompt).
+        if (alone) {                                                // uniform
+            for (int tile = t0; tile < t1 - 1; ++tile) step(std::true_type{}, std::true_type{}, tile);
+            step(std::true_type{}, std::false_type{}, t1 - 1);
+        } else
+            for (int tile = t0; tile < t1; ++tile) step(std::false_type{}, std::true_type{}, tile);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // no load may still be on its way to LDS when the workgroup ends
     }
     st.lrun += __shfl_xor(st.lrun, 32, 64);

@@ -264,3 +264,29 @@ def test_weights_at_eight_bytes_past_an_alignment():
     (ka, va, la, ma), (kb, vb, lb, mb) = got
     assert _worst(ka, kb) <= TOL and _worst(va, vb) <= TOL
     assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL and np.linalg.norm(ma - mb) / np.linalg.norm(mb) <= TOL
+
+
+# Keys that one workgroup streams: pieces of one tile and of two, with one tile left over, all four waves at work (32 rows, the streamed kernel's most) and
+# three (25 rows: four tasks, the last of four columns).
+@pytest.mark.parametrize("ctx", [0, 1, 32, 33, 64, 130, 290])
+@pytest.mark.parametrize("rows", [25, 32])
+def test_streamed_keys_in_pieces_of_one_and_two_tiles(ctx, rows):
+    import paper_2412_07017_amd as pkg
+    model = ModelConfig(n_layers=2, d_model=512, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn=256, vocab=512, rms_eps=1e-5,
+                        rope_theta=10000.0, dtype="bf16")
+    w = ai.make_weights(model, device=torch.device("cuda:0"))
+    torch.cuda.synchronize()
+    toks = ai.uniform_tokens(ai.MASTER_SEED, 947, ctx + rows, model.vocab)
+    got = []
+    for chunk in (512, 1):                               # 1: token by token through the single-row kernels
+        lm = pkg.AsyncLM(model, w, max_positions=ctx + rows, stream=torch.cuda.Stream())
+        if ctx:
+            lm.prefill(0, toks[:ctx])
+        lm.set_option("chunk", chunk)
+        (lm.inject_interrupt if ctx else lm.prefill)(0, toks[ctx:])
+        got.append((*_planes(lm, model, ctx + rows), lm.logits(0)))
+        lm.close()
+    (ka, va, la), (kb, vb, lb) = got
+    assert _worst(ka, kb) <= TOL, _worst(ka, kb)
+    assert _worst(va, vb) <= TOL, _worst(va, vb)
+    assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL
