@@ -1148,7 +1148,7 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                 at[wave * 512 + r * 16 + (wc ^ (r & 15))] = set[q];
             }
         };
-        // issue order = completion order: weights of the first block, activations of the first two, weights of the second
+        // issue order = completion order: weights of the first block, activations of the first, weights of the second
         w_load(wreg[0], 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1169,14 +1169,14 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_ks(const bf16_t* __restrict_
                 w_load(wreg[u & 1], tt + 2);           // this set's previous block was stored one block ago
                 __builtin_amdgcn_sched_barrier(0);
                 if (tt < nb) {                              // uniform
-                uint4 a0[4], a1[4];
-                wide_a_read(a0, at, 2 * wave, lane);
-                wide_a_read(a1, at, 2 * wave + 1, lane);
-                __builtin_amdgcn_sched_barrier(0);
-                wide_step<MT>(a0, ring[u % RING], 0, acc);
-                __builtin_amdgcn_sched_barrier(0);
-                wide_step<MT>(a1, ring[u % RING], 1, acc);
-                __builtin_amdgcn_sched_barrier(0);
+                    uint4 a0[4], a1[4];
+                    wide_a_read(a0, at, 2 * wave, lane);
+                    wide_a_read(a1, at, 2 * wave + 1, lane);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wide_step<MT>(a0, ring[u % RING], 0, acc);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wide_step<MT>(a1, ring[u % RING], 1, acc);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 w_store(wreg[(u + 1) & 1], other);          // the next block's weights, requested two blocks ago
@@ -1409,7 +1409,7 @@ __global__ __launch_bounds__(256) void k_chunk_attn(ChunkAttnArgs a, Geom g) {
 #pragma unroll
             for (int t = 0; t < 8; ++t) { qh[t] = load16(a.q_hi + qo + t * 16); ql[t] = load16(a.q_lo + qo + t * 16); }
         }
-        // Once K of a tile is staged in LDS its registers take K of the next tile (clamped to the last one), and the V
+        // Once K of a tile is staged in LDS its registers take K of the next tile, and the V
         // registers take the next tile's V as soon as the P V product has used them, so the next tile's loads are in
         // flight while a tile is multiplied.  No conditional code around loads or their uses (the compiler would
         // sink the loads next to the uses); past the wave's last tile they fetch nothing (one tile of a wave's five or six at 16k keys, all of its

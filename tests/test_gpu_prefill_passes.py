@@ -266,8 +266,8 @@ def test_weights_at_eight_bytes_past_an_alignment():
     assert np.linalg.norm(la - lb) / np.linalg.norm(lb) <= TOL and np.linalg.norm(ma - mb) / np.linalg.norm(mb) <= TOL
 
 
-# Keys that one workgroup streams: pieces of one tile and of two, with one tile left over, all four waves at work (32 rows, the streamed kernel's most) and
-# three (25 rows: four tasks, the last of four columns).
+# Keys that one workgroup streams: pieces of one tile and of two, with one tile left over, four tasks (32 rows are the streamed
+# kernel's most; of 25 the last task has four columns).
 @pytest.mark.parametrize("ctx", [0, 1, 32, 33, 64, 130, 290])
 @pytest.mark.parametrize("rows", [25, 32])
 def test_streamed_keys_in_pieces_of_one_and_two_tiles(ctx, rows):
