@@ -747,15 +747,14 @@ hipError_t forward_chunk(asynclm_ctx* c, PassBuilder& pb) {
     const int asplit = pick_chunk_attn_split(c, pb.max_keys, t.ntasks);
     // Four waves on one tile of keys (k_chunk_attn_wide) or a wave of its own for every task and split (k_chunk_attn): the
     // first loads a tile once for up to four tasks and issues its loads from four waves, the second starts sooner and runs
-    // more waves of small work.  8B shape, 4 layers, whole pass: 24 rows (3 tasks) into 1.1k 668 (wide) against 664 us, 2.1k
-    // 685 / 679, 4.2k 707 / 723, 16.4k 786 / 810; 48 rows (6 tasks) into 1.1k 748 / 753, 2.1k 746 / 767, 16.4k 890 / 940.
-    // Key splits of the first: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
+    // more waves of small work.  8B shape, 4 layers, whole call, shared-key / other kernel, us: 24 rows (3 tasks) into 500 keys 627 / 621, 1.1k 632 / 627,
+    // 2.1k 653 / 643, 4.2k 668 / 685, 16.4k 733 / 773; 48 rows (6 tasks) into 500 697 / 695, 1.1k 697 / 700, 2.1k 713 / 728, 16.4k 827 / 873.
+    // Key splits of the first, one sequence: two workgroups per compute unit, at least two tiles each (one tile each: 1 % slower at 1.1k;
     // four workgroups per compute unit: 4 % slower at 16.4k, more partial results).  One split, which needs no merge, where
     // the blocks alone fill the units and the keys are few: 1019 tokens (4 layers) 2792 -> 2771 us, 2000 (2 layers) 1968 -> 1956,
     // 1300 tokens and 1024 rows after 1000 no difference; beyond, the second workgroup is worth more (1024 rows after
-    // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).  Several sequences, most
-    // tasks alone in their block: no more workgroups than fit at a time (12 sequences of up to 3.4k with one interrupt of 24,
-    // 4 layers: 5 splits 1054 us, 6 splits 1092; but 200 rows after up to 16k and three single rows, 2 layers: 6 splits 1190, 7 splits 1085).
+    // 4000 tokens 1588 against 1646 us, after 15000 2200 against 2331).  Several sequences are cut by plan_attention, each by its own length;
+    // of them wsplit only says how long the longest one's chain of tiles would be with one count for all (`even`).
     const long long wgs = (long long)t.nblocks * g.Hkv, slots = 2LL * c->n_cu;
     int wsplit = (int)std::max(1LL, std::min<long long>((slots + (t.ngroups > 1 && t.ntasks < 2 * t.nblocks ? 0 : wgs - 1)) / wgs, ((pb.max_keys + 31) / 32 + 1) / 2));
     if (wgs >= c->n_cu && pb.max_keys <= 2048) wsplit = 1;
@@ -765,9 +764,12 @@ hipError_t forward_chunk(asynclm_ctx* c, PassBuilder& pb) {
     // `even` dates from when the shared-key kernel had one count for all too, so that a sequence much longer than the others was a chain of
     // tiles that a quarter as many waves walked: at most 20 tiles over the average load of a workgroup slot.  plan_attention
     // cuts every sequence by its own length, which removes that reason: with the present cut the shared-key kernel is the faster one
-    // or as fast wherever the two were compared, also where `even` sends a batch to the other.  8B shape, 4 layers, shared-key / other kernel, us: one sequence of 16k
+    // or as fast wherever batches were compared, also where `even` sends one to the other kernel, and below 3072 keys, where the rule
+    // sends most there.  8B shape, 4 layers, shared-key / other kernel, us: 16 sequences of 512 to 4096 with an interrupt of 24 1034 / 1118; 8 of 128 to 4096 787 / 842; 12 of 128
+    // to 3400 with an interrupt 889 / 944; 16 of 500 to 900 774 / 810; 16 of 2000 to 2500 899 / 956, with an interrupt 994 / 1059; 4 of 1000 to 1500 695 / 692; 2 of 300 to
+    // 500 655 / 648.  Before single blocks' keys were streamed: one sequence of 16k
     // and n of 500 tokens, n = 2 825 / 864, 4 841 / 880, 5 848 / 908, 7 860 / 955, 11 889 / 1039, 15 917 / 1089, 31 980 / 1390; one of 4k and 5, 7, 11, 15 768 / 807,
-    // 778 / 844, 804 / 857, 827 / 880; 16 of 512 to 4096 979 / 1029, with an interrupt of 24 in the longest 1053 / 1101; 8 of 128 to 4096 848 / 885; 16 of 2900 1013 / 1036.
+    // 778 / 844, 804 / 857, 827 / 880; 16 of 2900 1013 / 1036.
     const int chain = ((pb.max_keys + 31) / 32 + wsplit - 1) / wsplit;
     const bool even = t.ngroups == 1 || t.ntasks <= 4 || chain <= pb.block_tiles * g.Hkv / slots + 20;
     const bool wide_attn = ((pb.max_keys >= 3072 || t.ntasks >= 4 * t.ngroups) && even) || (t.ntasks >= 16 && t.ntasks >= 3 * t.nblocks);

@@ -851,8 +851,9 @@ __global__ __launch_bounds__(256) void k_chunk_gemm_wide(const bf16_t* __restric
 //  * weights and activations of a block of 32 columns go from global memory straight to LDS (16 bytes per lane and load,
 //    no registers): three buffers, the block after next is requested while a block is multiplied.  The weights are
 //    row-major in memory; the transposition into operand order is the choice of the 16-byte piece a lane loads (LDS row r,
-//    piece p holds piece p ^ ((r / 4) & 3) of the row: the 16 rows that a read takes at a time then cover all 64 banks once; with (r / 2) & 3,
-//    eight rows over half of them, 29 of 75 M LDS cycles were conflicts: gate/up of 2048 rows 704.6 -> 700.8 us, down 348.7 -> 347.7).
+//    piece p holds piece p ^ ((r / 4) & 3) of the row: the 16 rows that a read takes at a time then cover all 64 banks once.  With (r / 2) & 3,
+//    eight rows over half of them, 29.4 of the 75.5 M LDS cycles of gate/up of 2048 rows were conflicts, now none of 46.1.  Time does not follow, the
+//    power limit binds: 781 and 787 us before, 781 and 784 after (two runs of the kernel trace), in a 16k prompt 727 / 725-726).
 //  * every load and every LDS read is issued between two products.  Issued together at the start of a block, the same
 //    loads kept the matrix cores idle for 40 % of the time (0.94-1.17 PFLOP/s); spread, the cores are busy 87-91 % of the
 //    cycles and the clock drops to the power limit instead (1.3-1.7 GHz with random operands, 2.4 with zeros).
@@ -1611,8 +1612,8 @@ __global__ __launch_bounds__(256) void k_decode_attn_merge(DecodeAttnArgs a, Geo
 // What bounds it: products and softmax alternate in a wave, so one wave per SIMD leaves the matrix cores idle during the
 // softmax and behind every LDS read.  The kernel is kept to 256 registers (values are read from LDS when they are used,
 // the next tile needs no registers), so that two workgroups share a compute unit and one multiplies while the other
-// does its softmax.  2048 rows over 8k keys on average (16k prompt of the 8B shape): 1190 -> 735 us a layer and pass =
-// 1.12 PFLOP/s counted with the three hi/lo products; 48 rows into 16.4k keys 66 -> 51 us against a wave per task.
+// does its softmax.  2048 rows over 8k keys on average (16k prompt of the 8B shape): 1190 -> 735 us a layer and pass
+// (698 now = 1.18 PFLOP/s counted with the three hi/lo products); 48 rows into 16.4k keys 66 -> 51 us (48.7 now) against a wave per task.
 
 // Where a wave's eight loads of a tile come from: four of the 16 KiB of K (4 rows each) and four of the 16 of V^T.  LDS in
 // 16-byte chunks: K hi [0, 512), K lo [512, 1024), V^T hi [1024, 1536), V^T lo [1536, 2048).
@@ -1664,8 +1665,10 @@ __device__ __forceinline__ void attn_wide_tile(AttnState& st, const uint4* __res
         s = mma(kq[t % 3][0], ql[t], s);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // A wave in its products goes before one in its softmax, so that the two waves of a SIMD do not keep step: 16k prompt, 2048 rows and layer 691 -> 673 us
-    // on average (the other way round, or one workgroup of a unit before the other: 688 and 708).
+    // A wave in its products goes before one in its softmax, so that the two waves of a SIMD do not keep step.  The more keys the more it gives; without / with it,
+    // us a layer: 2048 rows after 6k keys 603 / 588, after 14k 1270 / 1203; 70B shape, 2048 rows after none 201 / 184, after 2k 550 / 510; 24 rows into 8k 23.9 / 22.0; 48 into
+    // 16k 49.8 / 48.7; 16 sequences 66 / 66; 2048 rows after up to 4k and prompts of 300 to 1464 no difference but 1019 tokens 70.8 / 72.2.  (A 16k
+    // prompt with the softmax first is as without, with one workgroup of a unit before the other 2 % slower.)
     __builtin_amdgcn_s_setprio(0);
     u32x4 v0[4];                                                    // the first values are on their way during the softmax
 #pragma unroll
